@@ -132,15 +132,21 @@ sal_status sal_surface_set_check(const sal_surface_desc *surfaces, int32_t n_sur
 
 /* ----------------------------------------------------------------- labeling
  * Precision forms of the pair loop:
- *   SAL_PREC_FP64          every (point, triangle) solid angle in double, with
- *                          an exact sign of the triple product where double
- *                          cannot certify it ("plain FP64");
+ *   SAL_PREC_FP64          every solid angle in double, with an exact sign of
+ *                          the triple product where double cannot certify it
+ *                          ("plain FP64");
  *   SAL_PREC_FP32_RECHECK  solid angles in float32, summed per strip and
  *                          accumulated in double; a (point, surface) pair is
- *                          recomputed in the FP64 form when |w - T| <
- *                          recheck_band or when any of its triangles is
- *                          ill-conditioned in float32 (see kappa).  Labels are
- *                          those of the FP64 form. */
+ *                          recomputed, in double where float32 does not certify
+ *                          a term, when |w - T| < recheck_band or when any of
+ *                          its triangles is ill-conditioned in float32 (see
+ *                          kappa).  Labels are those of the FP64 form.
+ * In both, a patch of triangles seen from outside its bounding box is summed
+ * through a strip over its boundary (the two close to a surface that does not
+ * enclose the point), and points that share a box no triangle enters share one
+ * winding number.  Sums within 1e-3 of a whole number are that number: a closed
+ * surface has no other winding number off the surface.  Points exactly on a
+ * surface keep the sum of the triangles they do not lie on. */
 enum { SAL_PREC_FP64 = 0, SAL_PREC_FP32_RECHECK = 1 };
 enum { SAL_WINDING_NONE = 0, SAL_WINDING_F32 = 1, SAL_WINDING_F64 = 2 };
 /* Element rule of sal_refine_relabel (section 2.1.3):
@@ -157,16 +163,16 @@ typedef struct sal_label_options {
     double threshold;         /* T of section 2.1.3, in (0, 1); default 0.5 */
     double recheck_band;      /* default 1e-3 */
     double kappa;             /* float32 conditioning threshold; 0 = 2^-5 */
-    int32_t points_per_lane;  /* 0 = tuned; else 1, 2 or 4 */
-    int32_t block_waves;      /* 0 = tuned; else 1, 2, 4 or 8 wavefronts per block.
-                                 Tuned: the first call for a (device, precision,
-                                 log2 triangles, log2 points) times every candidate
-                                 on up to 2^19 of the points against the leading
-                                 strips of the set (about 32768 triangles, 8192 in
-                                 the FP64 form), synchronising the stream, and
-                                 caches the fastest for the process, and in the
-                                 file named by SAL_TUNE_CACHE if set; SAL_TUNE=0
-                                 disables tuning (1 point, 4 waves). */
+    int32_t points_per_lane;  /* 0, 1, 2 or 4: accepted; the kernels hold one point
+                                 per lane, whatever is asked */
+    int32_t block_waves;      /* 0 = tuned; else 1, 2, 4 or 8 wavefronts per block
+                                 (the results do not depend on it).  Tuned: the
+                                 first call for a (device, precision, log2
+                                 triangles, log2 points) times every size on up
+                                 to 2^19 of the points, synchronising the stream,
+                                 and caches the fastest for the process, and in
+                                 the file named by SAL_TUNE_CACHE if set;
+                                 SAL_TUNE=0 disables tuning (4 waves). */
     int32_t use_graph;        /* sal_label_batch: 1 = capture the launch sequence in a
                                  hipGraph and replay it while the same instances (same
                                  surface sets, pointers, sizes, options) come back;
@@ -207,7 +213,7 @@ typedef struct sal_label_stats {
     float ms_recheck;          /* device time of the FP64 recheck */
     float ms_total;            /* device time from the pair loop's start to the
                                   last kernel (launch-shape tuning excluded) */
-    int32_t points_per_lane;   /* launch shape used (chosen by the tuner when 0 was asked) */
+    int32_t points_per_lane;   /* launch shape used (block_waves: the tuner's when 0 was asked) */
     int32_t block_waves;
     int64_t n_pairs_culled;    /* pairs of n_pairs skipped by cull_bounds (w = 0 exactly) */
 } sal_label_stats;
@@ -230,12 +236,10 @@ sal_status sal_label_points(sal_context *ctx, const sal_surface_set *set, int64_
 
 /* sal_label_points for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments, kernels and results (labels; winding numbers
- * to the float32 form's tolerance, bit for bit with the same launch shape)
- * as sal_label_points, but the call allocates nothing: its scratch (counters,
- * flag list, recheck buffers, about 38 MB) is one static device array per
- * GPU, held until the process ends, and its counters are cleared by a fill
- * kernel on every call.  Limits and differences:
+ * hipMalloc.  Same arguments, kernels and results as sal_label_points, but the
+ * call allocates nothing: its scratch (counters, flag list, spatial order of
+ * the points, about 39 MB) is one static device array per
+ * GPU, held until the process ends.  Limits and differences:
  *   n_points  at most 1048576 per call (SAL_ERR_CAPACITY beyond; label larger
  *             sets in chunks);
  *   opt       cull_bounds must be 0 (SAL_ERR_INVALID_ARG); a launch shape left
@@ -488,14 +492,13 @@ sal_status sal_tet_mesh_inflate(sal_context *ctx, sal_tet_mesh *mesh, const sal_
                                 double zeta, sal_inflate_info *info);
 
 /* ------------------------------------------------------------ batched form
- * Many independent labeling problems in one persistent launch: the work is
- * cut into (instance, point block, surface, triangle range) items ordered by
- * cost, pulled by resident workgroups from a device counter; partial winding
- * sums are reduced per (point, surface) in a fixed order; one FP64 recheck
- * pass serves all instances.  With precision SAL_PREC_FP64 the items run the
- * plain FP64 walk (exact sign where double cannot certify it, points on a
- * surface enclosed) and there is no recheck.  Labels equal those of
- * sal_label_points on each instance.  Each instance's arrays follow the rules of sal_label_points.
+ * Many independent labeling problems in one launch sequence: the points of
+ * every instance are put in spatial order together, one grid labels 64
+ * neighbours per wavefront (small instances: one point), and one recheck pass
+ * serves all instances.  With precision SAL_PREC_FP64 every term is in double
+ * (exact sign where double cannot certify it, points on a surface enclosed).
+ * Labels equal those of sal_label_points on each instance.  Each instance's
+ * arrays follow the rules of sal_label_points.
  *   per_instance  NULL, or [n_inst] stats filled after synchronising */
 typedef struct sal_instance {
     const sal_surface_set *surfaces;

@@ -36,33 +36,49 @@ sal_status hip_error(hipError_t e, const char *what) {
     return e == hipErrorOutOfMemory ? SAL_ERR_OUT_OF_MEMORY : SAL_ERR_DEVICE;
 }
 
-// The flag list and the pair-major recheck scratch: a quarter of the flag
-// capacity in pairs (a point more often has one flagged surface than two; a
-// recheck with more pairs than that takes the per-point form).
-sal_status ensure_flag_capacity(sal_context *ctx, int64_t n) {
-    if (n <= ctx->flag_cap && ctx->rc_seg) return SAL_OK;
-    SAL_HIP(hipStreamSynchronize(ctx->stream));
-    auto release = [](void *&p) {
-        if (p) (void)hipFree(p);
-        p = nullptr;
-    };
-    release((void *&)ctx->flag_list);
-    release((void *&)ctx->rc_pairs);
-    release((void *&)ctx->rc_out);
-    release((void *&)ctx->rc_res);
-    ctx->batch_graph_key = 0;   // a captured batch graph points at the old list
-    ctx->flag_cap = 0;
-    ctx->rc_pair_cap = 0;
-    const int64_t cap = n < 4096 ? 4096 : n;
-    const int64_t pcap = cap / 4 + 64 * kMaxSurfaces;
-    SAL_HIP(dev_malloc((void **)&ctx->flag_list, (size_t)cap * sizeof(FlagEntry)));
-    SAL_HIP(dev_malloc((void **)&ctx->rc_res, (size_t)cap * sizeof(unsigned long long)));
-    SAL_HIP(dev_malloc((void **)&ctx->rc_pairs, (size_t)pcap * sizeof(RecheckPair)));
-    SAL_HIP(dev_malloc((void **)&ctx->rc_out, (size_t)pcap * sizeof(RecheckOut)));
-    if (!ctx->rc_seg) SAL_HIP(dev_malloc((void **)&ctx->rc_seg, sizeof(RecheckSeg)));
-    ctx->flag_cap = cap;
-    ctx->rc_pair_cap = pcap;
+namespace {
+
+// Replaces *p by a buffer of n entries; the old one must be out of use.
+template <typename T>
+sal_status renew(T **p, int64_t n) {
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
+    SAL_HIP(dev_malloc((void **)p, (size_t)n * sizeof(T)));
     return SAL_OK;
+}
+
+}  // namespace
+
+sal_status ensure_label_scratch(sal_context *ctx, int64_t points, int64_t tiles, int64_t insts) {
+    sal_status st;
+    if (points > ctx->point_cap || tiles > ctx->tile_cap || insts > ctx->inst_cap) {
+        SAL_HIP(hipStreamSynchronize(ctx->stream));
+        ctx->batch_graph_fields.clear();   // a captured batch graph points at the old buffers
+    }
+    if (points > ctx->point_cap) {
+        ctx->point_cap = 0;
+        if ((st = renew(&ctx->flag_list, points)) != SAL_OK || (st = renew(&ctx->ord_idx1, points)) != SAL_OK ||
+            (st = renew(&ctx->ord_key1, points)) != SAL_OK || (st = renew(&ctx->ord_perm, points)) != SAL_OK)
+            return st;
+        ctx->point_cap = points;
+    }
+    if (tiles > ctx->tile_cap) {
+        ctx->tile_cap = 0;
+        if ((st = renew(&ctx->ord_hist, tiles * kOrderBins)) != SAL_OK) return st;
+        ctx->tile_cap = tiles;
+    }
+    if (insts > ctx->inst_cap) {
+        ctx->inst_cap = 0;
+        if ((st = renew(&ctx->ord_tot, insts * kOrderBins)) != SAL_OK) return st;
+        ctx->inst_cap = insts;
+    }
+    return SAL_OK;
+}
+
+sal_status ensure_label_scratch(sal_context *ctx, int64_t n) {
+    if (n <= kPointFormMax) return SAL_OK;
+    const int64_t c = n < kChunkPoints ? n : kChunkPoints;
+    return ensure_label_scratch(ctx, c, order_tiles(c), 1);
 }
 
 sal_status resolve_options(const sal_label_options *in, sal_label_options *out) {
@@ -91,8 +107,35 @@ sal_status resolve_options(const sal_label_options *in, sal_label_options *out) 
 }
 
 LabelScratch context_scratch(const sal_context *ctx) {
-    return LabelScratch{ctx->counters, ctx->flag_list, ctx->rc_pairs, ctx->rc_out,
-                        ctx->rc_res,   ctx->rc_seg,    ctx->rc_pair_cap};
+    return LabelScratch{ctx->counters, ctx->flag_list, ctx->list_n,
+                        OrderScratch{ctx->ord_idx1, ctx->ord_key1, ctx->ord_perm, ctx->ord_hist, ctx->ord_tot}};
+}
+
+LabelInst make_inst(const sal_surface_set *set, int64_t n, const float *x, const float *y, const float *z,
+                    int32_t *labels, void *winding, int64_t wstride, unsigned long long *masks,
+                    unsigned long long *counters) {
+    LabelInst in{};
+    in.rec32 = set->rec32;
+    in.rec64 = set->rec64;
+    in.surf = set->surf;
+    in.ent = set->ent;
+    in.x = x;
+    in.y = y;
+    in.z = z;
+    in.labels = labels;
+    in.winding = winding;
+    in.masks = masks;
+    in.counters = counters;
+    in.n = n;
+    in.wstride = wstride;
+    in.n_surf = set->n_surf;
+    in.tile = order_tile(n);
+    in.n_tiles = (int32_t)order_tiles(n);
+    for (int c = 0; c < 3; ++c) {
+        in.lo[c] = set->lo[c];
+        in.scale[c] = 128.0f / (set->hi[c] - set->lo[c]);
+    }
+    return in;
 }
 
 sal_status enqueue_label_on(sal_context *ctx, const sal_surface_set *set, int64_t n,
@@ -108,60 +151,37 @@ sal_status enqueue_label_with(sal_context *ctx, const sal_surface_set *set, int6
                               const float *z, const sal_label_options &opt, int32_t *labels,
                               void *winding, hipEvent_t ev_mid, hipStream_t stream,
                               unsigned long long *masks, const LabelScratch &sc) {
-    PairloopArgs a{};
-    a.rec32 = set->rec32;
-    a.rec64 = set->rec64;
-    a.surf = set->surf;
-    a.n_surf = set->n_surf;
-    a.x = x;
-    a.y = y;
-    a.z = z;
-    a.n = n;
+    const bool fp64 = opt.precision == SAL_PREC_FP64;
+    LabelArgs a{};
+    a.winding_type = winding ? opt.winding_type : SAL_WINDING_NONE;
     a.n_dev = n_dev;
-    a.kappa = (float)opt.kappa;
     a.threshold = opt.threshold;
     a.band = opt.recheck_band;
-    a.labels = labels;
-    a.winding = winding;
-    a.winding_type = winding ? opt.winding_type : SAL_WINDING_NONE;
-    if (!winding) a.winding = nullptr;
-    a.masks = masks;
+    a.kappa = (float)opt.kappa;
     a.cull = opt.cull_bounds ? 1 : 0;
     a.flag_list = sc.flag_list;
-    a.counters = sc.counters;
-    if (opt.precision == SAL_PREC_FP64) {
-        SAL_HIP(launch_pairloop_f64(a, opt.block_waves, stream));
-        if (ev_mid) SAL_HIP(hipEventRecord(ev_mid, stream));
-        return SAL_OK;
+    a.list_n = sc.list_n;
+    a.ord = sc.ord;
+    const size_t wsize = opt.winding_type == SAL_WINDING_F64 ? sizeof(double) : sizeof(float);
+    for (int64_t at = 0; at < n; at += kChunkPoints) {
+        const int64_t m = n - at < kChunkPoints ? n - at : kChunkPoints;
+        a.n_dev_skip = at;
+        a.one = make_inst(set, m, x + at, y + at, z + at, labels + at,
+                          winding ? (char *)winding + (size_t)at * wsize : nullptr, n,
+                          masks ? masks + at : nullptr, sc.counters);
+        if (n <= kPointFormMax) {
+            // so few points that a wavefront each leaves the chip half empty:
+            // the surfaces are shared out too
+            const bool spread = set->n_surf > 1 && opt.block_waves > 1 && m <= (int64_t)ctx->n_cu * 8;
+            SAL_HIP(launch_label_point(a, fp64, spread, m, opt.block_waves, stream));
+            continue;
+        }
+        SAL_HIP(launch_order(a, a.one.n_tiles, stream));
+        SAL_HIP(launch_label_wave(a, fp64, (m + 63) / 64, opt.block_waves, stream));
+        if (ev_mid && at + m == n) SAL_HIP(hipEventRecord(ev_mid, stream));
+        SAL_HIP(launch_recheck(a, fp64, ctx->n_cu * 8, stream));
     }
-    SAL_HIP(launch_pairloop_f32(a, opt.points_per_lane, opt.block_waves, stream));
-    if (ev_mid) SAL_HIP(hipEventRecord(ev_mid, stream));
-    RecheckArgs r{};
-    r.rec32 = set->rec32;
-    r.rec64 = set->rec64;
-    r.surf = set->surf;
-    r.strip_off = set->strip_off;
-    r.x = x;
-    r.y = y;
-    r.z = z;
-    r.n = n;
-    r.threshold = opt.threshold;
-    r.kappa = (float)opt.kappa;
-    r.labels = labels;
-    r.winding = a.winding;
-    r.winding_type = a.winding_type;
-    r.masks = masks;
-    r.flag_list = sc.flag_list;
-    r.counters = sc.counters;
-    r.n_surf = set->n_surf;
-    r.pairs = sc.rc_pairs;
-    r.pair_out = sc.rc_out;
-    r.res = sc.rc_res;
-    r.seg = sc.rc_seg;
-    r.pair_cap = sc.rc_pair_cap;
-    r.target_waves = (int64_t)ctx->n_cu * 32;
-    const int64_t grid = n < (int64_t)ctx->n_cu * 8 ? n : (int64_t)ctx->n_cu * 8;
-    SAL_HIP(launch_recheck_f64(r, (int)grid, stream));
+    if (ev_mid && n <= kPointFormMax) SAL_HIP(hipEventRecord(ev_mid, stream));
     return SAL_OK;
 }
 
@@ -261,8 +281,8 @@ sal_status sal_context_create(int device, void *stream, sal_context **out) {
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(counters)"); }
     e = dev_malloc((void **)&ctx->tune_counters, kNumCounters * sizeof(unsigned long long));
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(counters)"); }
-    e = dev_malloc((void **)&ctx->batch_next, sizeof(unsigned int) * 4);
-    if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(batch counter)"); }
+    e = dev_malloc((void **)&ctx->list_n, sizeof(unsigned long long));
+    if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(list length)"); }
     e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipStreamCreate"); }
     *out = ctx;
@@ -282,20 +302,12 @@ void sal_context_destroy(sal_context *ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     for (auto &ev : ctx->ev)
         if (ev) (void)hipEventDestroy(ev);
-    if (ctx->flag_list) (void)hipFree(ctx->flag_list);
-    if (ctx->rc_pairs) (void)hipFree(ctx->rc_pairs);
-    if (ctx->rc_out) (void)hipFree(ctx->rc_out);
-    if (ctx->rc_res) (void)hipFree(ctx->rc_res);
-    if (ctx->rc_seg) (void)hipFree(ctx->rc_seg);
-    if (ctx->counters) (void)hipFree(ctx->counters);
-    if (ctx->tune_counters) (void)hipFree(ctx->tune_counters);
     if (ctx->batch_graph) (void)hipGraphExecDestroy(ctx->batch_graph);
-    if (ctx->batch_items) (void)hipFree(ctx->batch_items);
-    if (ctx->batch_insts) (void)hipFree(ctx->batch_insts);
-    if (ctx->batch_partial) (void)hipFree(ctx->batch_partial);
-    if (ctx->batch_mask) (void)hipFree(ctx->batch_mask);
-    if (ctx->batch_next) (void)hipFree(ctx->batch_next);
-    if (ctx->batch_counters) (void)hipFree(ctx->batch_counters);
+    void *bufs[] = {ctx->flag_list, ctx->ord_idx1, ctx->ord_key1,    ctx->ord_perm,      ctx->ord_hist,
+                    ctx->ord_tot,   ctx->list_n,   ctx->counters,    ctx->tune_counters, ctx->batch_insts,
+                    ctx->batch_counters};
+    for (void *p : bufs)
+        if (p) (void)hipFree(p);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
     delete ctx;
 }
@@ -343,11 +355,9 @@ sal_status sal_label_points(sal_context *ctx, const sal_surface_set *set, int64_
     SAL_HIP(hipSetDevice(ctx->device));
     // every argument is checked before anything is enqueued
     if (opt.cull_bounds && (st = ensure_surface_balls(ctx, set)) != SAL_OK) return st;
-    if (opt.precision == SAL_PREC_FP32_RECHECK) {
-        st = ensure_flag_capacity(ctx, n);
-        if (st != SAL_OK) return st;
-    }
-    SAL_HIP(launch_fill_u64(ctx->counters, 0ull, kNumCounters, ctx->stream));
+    if ((st = ensure_label_scratch(ctx, n)) != SAL_OK) return st;
+    // (without stats nothing reads the counters)
+    if (stats) SAL_HIP(launch_fill_u64(ctx->counters, 0ull, kNumCounters, ctx->stream));
     int shape[2] = {0, 0};
     st = enqueue_label(ctx, set, n, x, y, z, opt, labels, winding, stats ? ctx->ev[0] : nullptr,
                        stats ? ctx->ev[1] : nullptr, shape);

@@ -1,54 +1,37 @@
-// sal_label_batch: work list construction, persistent launch, optional
-// hipGraph capture / replay.
+// sal_label_batch: many independent (surface set, point set) instances in one
+// launch sequence, optionally captured in a hipGraph and replayed.
 #include <algorithm>
 #include <cstring>
-#include <numeric>
 #include <vector>
 
-#include "batch_internal.h"
 #include "runtime.h"
 
 namespace sal {
 namespace {
 
+// Instances up to this size are labeled one point per wavefront.  64 neighbours
+// of fewer points are so far apart that a common walk saves nothing, and a
+// small instance's few wavefronts would be the launch's tail.
+constexpr int64_t kBatchPointMax = 8192;
+
+constexpr int kBlockWaves = 4;
+
 template <typename T>
-sal_status ensure_dev(T **p, int64_t *have, int64_t need, hipStream_t s, sal_context *ctx) {
+sal_status ensure_dev(T **p, int64_t *have, int64_t need, sal_context *ctx) {
     if (need <= *have) return SAL_OK;
-    SAL_HIP(hipStreamSynchronize(s));
+    SAL_HIP(hipStreamSynchronize(ctx->stream));
     if (*p) SAL_HIP(hipFree(*p));
     *p = nullptr;
     *have = 0;
+    ctx->batch_graph_fields.clear();   // buffers moved: a captured graph is stale
     const int64_t cap = need + need / 4 + 64;
     SAL_HIP(dev_malloc((void **)p, (size_t)cap * sizeof(T)));
     *have = cap;
-    ctx->batch_graph_key = 0;   // buffers moved: a captured graph is stale
     return SAL_OK;
 }
 
-uint64_t mix(uint64_t h, uint64_t v) {
-    h ^= v + 0x9e3779b97f4a7c15ull + (h << 6) + (h >> 2);
-    return h;
-}
-
-// Splits strips [b, e) of one surface into `parts` ranges of nearly equal
-// triangle counts; returns record boundaries.
-std::vector<int64_t> strip_ranges(const sal_surface_set *set, const SurfaceDev &sd, int parts) {
-    std::vector<int64_t> out;
-    out.push_back(sd.rec_begin);
-    if (parts > 1) {
-        const int64_t tot = sd.n_tri;
-        int64_t acc = 0;
-        int done = 1;
-        for (int64_t s = sd.strip_begin; s < sd.strip_end && done < parts; ++s) {
-            acc += set->host_strip_tris[(size_t)s];
-            if (acc * parts >= tot * done && s + 1 < sd.strip_end) {
-                out.push_back(set->host_strip_off[(size_t)s + 1]);
-                ++done;
-            }
-        }
-    }
-    out.push_back(sd.rec_end);
-    return out;
+bool same_table(const std::vector<LabelInst> &a, const std::vector<LabelInst> &b) {
+    return a.size() == b.size() && std::memcmp(a.data(), b.data(), a.size() * sizeof(LabelInst)) == 0;
 }
 
 }  // namespace
@@ -66,7 +49,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
         if (st != SAL_OK) return st;
         if (opt.winding_type != SAL_WINDING_NONE)
             return set_error(SAL_ERR_INVALID_ARG, "the batched form has no winding output");
-        int64_t total = 0, total_pairs = 0;
+        int64_t total = 0;
         for (int i = 0; i < n_inst; ++i) {
             const sal_instance &in = inst[i];
             if (!in.surfaces) return set_error(SAL_ERR_INVALID_ARG, "instance without surfaces");
@@ -76,7 +59,6 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
             if (in.n_points > 0 && (!in.x || !in.y || !in.z || !in.labels))
                 return set_error(SAL_ERR_INVALID_ARG, "NULL point or label buffer");
             total += in.n_points;
-            total_pairs += in.n_points * in.surfaces->n_tri;
         }
         if (stats) std::memset(stats, 0, sizeof(sal_label_stats) * (size_t)n_inst);
         if (total == 0) return SAL_OK;
@@ -84,178 +66,98 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
         hipStream_t s = ctx->stream;
 
         const bool fp64 = opt.precision == SAL_PREC_FP64;
-
-        // cache key of this batch (work-list reuse, graph replay): the fields
-        // themselves, compared in full, and their hash as a quick first test
-        std::vector<uint64_t> fields;
-        fields.reserve((size_t)n_inst * 6 + 5);
-        for (int i = 0; i < n_inst; ++i) {
-            fields.push_back(inst[i].surfaces->uid);
-            fields.push_back((uint64_t)inst[i].n_points);
-            fields.push_back((uint64_t)(uintptr_t)inst[i].x);
-            fields.push_back((uint64_t)(uintptr_t)inst[i].y);
-            fields.push_back((uint64_t)(uintptr_t)inst[i].z);
-            fields.push_back((uint64_t)(uintptr_t)inst[i].labels);
-        }
-        const double kd = opt.kappa;
-        uint64_t kb;
-        std::memcpy(&kb, &kd, 8);
-        fields.push_back(kb);
-        std::memcpy(&kb, &opt.threshold, 8);
-        fields.push_back(kb);
-        std::memcpy(&kb, &opt.recheck_band, 8);
-        fields.push_back(kb);
-        fields.push_back((uint64_t)n_inst);
-        fields.push_back(fp64 ? 2u : 1u);
-        uint64_t key = 0x51ed270b2717ull;
-        for (const uint64_t f : fields) key = mix(key, f);
-        if (key == 0) key = 1;   // 0 marks "no batch"
-
-        st = ensure_flag_capacity(ctx, total);
-        if (st != SAL_OK) return st;
         if ((st = ensure_dev(&ctx->batch_counters, &ctx->batch_counters_n,
-                             (int64_t)n_inst * kNumCounters, s, ctx)) != SAL_OK)
+                             (int64_t)n_inst * kNumCounters, ctx)) != SAL_OK)
             return st;
 
-        const bool replay = opt.use_graph && ctx->batch_graph && ctx->batch_graph_key == key &&
-                            ctx->batch_graph_fields == fields;
-        // an eager call on the batch whose work list is already on the device
-        // skips the host-side build and upload
-        const bool reuse = !replay && !opt.use_graph && ctx->batch_items_key == key &&
-                           ctx->batch_items_fields == fields;
-        BatchArgs a{};
-        if (reuse) a.n_items = ctx->batch_n_items;
-        if (!replay && !reuse) {
-            // the item and instance buffers are about to be rewritten: a graph
-            // captured for another batch reads them, so it is stale from here
-            ctx->batch_graph_key = 0;
-            ctx->batch_items_key = 0;
-            // ---- work list: (instance, block, surface, strip range), largest first
-            const int64_t resident_waves = (int64_t)ctx->n_cu * 32;
-            int64_t cap = total_pairs / (8 * resident_waves);
-            if (cap < 64 * 4096) cap = 64 * 4096;
-            std::vector<BatchInst> hin((size_t)n_inst);
-            std::vector<BatchItem> items;
-            std::vector<int64_t> cost;
-            int64_t slot = 0, pbase = 0;
+        // The table: the instances of the 64-point form, cut into pieces of at
+        // most kChunkPoints, then those labeled point by point.
+        std::vector<LabelInst> table;
+        int64_t wave_points = 0, wave_groups = 0, tiles = 0, point_groups = 0;
+        size_t n_wave = 0;
+        for (const bool small : {false, true}) {
             for (int i = 0; i < n_inst; ++i) {
-                const sal_surface_set *set = inst[i].surfaces;
-                BatchInst &b = hin[(size_t)i];
-                std::memset(&b, 0, sizeof(b));
-                b.rec32 = set->rec32;
-                b.rec64 = set->rec64;
-                b.surf = set->surf;
-                b.strip_off = set->strip_off;
-                b.x = inst[i].x;
-                b.y = inst[i].y;
-                b.z = inst[i].z;
-                b.labels = inst[i].labels;
-                b.n = inst[i].n_points;
-                b.point_base = pbase;
-                b.slot_base = slot;
-                b.n_surf = set->n_surf;
-                std::vector<std::vector<int64_t>> ranges((size_t)set->n_surf);
-                int32_t so = 0;
-                for (int k = 0; k < set->n_surf; ++k) {
-                    const SurfaceDev &sd = set->host_table[(size_t)k];
-                    int64_t parts = (64 * sd.n_tri + cap - 1) / cap;
-                    const int64_t ns = sd.strip_end - sd.strip_begin;
-                    if (parts > ns) parts = ns;
-                    if (parts < 1) parts = 1;
-                    ranges[(size_t)k] = strip_ranges(set, sd, (int)parts);
-                    b.split_off[k] = so;
-                    so += (int32_t)(ranges[(size_t)k].size() - 1);
-                    b.surf_label[k] = sd.label;
-                }
-                b.split_off[set->n_surf] = so;
-                b.splits_total = so;
-                const int64_t nb = (b.n + 63) / 64;
-                for (int64_t blk = 0; blk < nb; ++blk) {
-                    for (int k = 0; k < set->n_surf; ++k) {
-                        const auto &rg = ranges[(size_t)k];
-                        for (size_t r = 0; r + 1 < rg.size(); ++r) {
-                            BatchItem it;
-                            it.inst = i;
-                            it.surf = k;
-                            it.block = blk;
-                            it.rec_begin = rg[r];
-                            it.rec_end = rg[r + 1];
-                            it.slot = slot + blk * so + b.split_off[k] + (int64_t)r;
-                            items.push_back(it);
-                            cost.push_back(it.rec_end - it.rec_begin);
-                        }
+                const sal_instance &in = inst[i];
+                if ((in.n_points <= kBatchPointMax) != small) continue;
+                for (int64_t at = 0; at < in.n_points; at += kChunkPoints) {
+                    const int64_t m = std::min(in.n_points - at, kChunkPoints);
+                    LabelInst q = make_inst(in.surfaces, m, in.x + at, in.y + at, in.z + at, in.labels + at,
+                                            nullptr, 0, nullptr, ctx->batch_counters + (int64_t)i * kNumCounters);
+                    if (small) {
+                        q.group_base = point_groups;
+                        point_groups += m;
+                    } else {
+                        q.group_base = wave_groups;
+                        q.order_base = wave_points;
+                        q.tile_base = tiles;
+                        wave_groups += (m + 63) / 64;
+                        wave_points += m;
+                        tiles += q.n_tiles;
                     }
+                    table.push_back(q);
                 }
-                slot += nb * so;
-                pbase += b.n;
             }
-            std::vector<int64_t> order(items.size());
-            std::iota(order.begin(), order.end(), 0);
-            std::stable_sort(order.begin(), order.end(),
-                             [&](int64_t p, int64_t q) { return cost[(size_t)p] > cost[(size_t)q]; });
-            std::vector<BatchItem> sorted(items.size());
-            for (size_t k = 0; k < order.size(); ++k) sorted[k] = items[(size_t)order[k]];
-
-            int64_t item_bytes_have = ctx->batch_items_bytes / (int64_t)sizeof(BatchItem);
-            if ((st = ensure_dev((BatchItem **)&ctx->batch_items, &item_bytes_have,
-                                 (int64_t)sorted.size(), s, ctx)) != SAL_OK)
-                return st;
-            ctx->batch_items_bytes = item_bytes_have * (int64_t)sizeof(BatchItem);
-            int64_t inst_have = ctx->batch_insts_bytes / (int64_t)sizeof(BatchInst);
-            if ((st = ensure_dev((BatchInst **)&ctx->batch_insts, &inst_have, (int64_t)n_inst, s,
-                                 ctx)) != SAL_OK)
-                return st;
-            ctx->batch_insts_bytes = inst_have * (int64_t)sizeof(BatchInst);
-            if (slot > ctx->batch_slots) {
-                SAL_HIP(hipStreamSynchronize(s));
-                if (ctx->batch_partial) SAL_HIP(hipFree(ctx->batch_partial));
-                if (ctx->batch_mask) SAL_HIP(hipFree(ctx->batch_mask));
-                ctx->batch_partial = nullptr;
-                ctx->batch_mask = nullptr;
-                ctx->batch_slots = 0;
-                ctx->batch_graph_key = 0;
-                const int64_t cap_slots = slot + slot / 4 + 64;
-                SAL_HIP(dev_malloc((void **)&ctx->batch_partial, (size_t)cap_slots * 64 * sizeof(double)));
-                SAL_HIP(dev_malloc((void **)&ctx->batch_mask, (size_t)cap_slots * sizeof(uint64_t)));
-                ctx->batch_slots = cap_slots;
-            }
-            // the previous call may still read these buffers
-            SAL_HIP(hipStreamSynchronize(s));
-            SAL_HIP(hipMemcpy(ctx->batch_items, sorted.data(), sorted.size() * sizeof(BatchItem),
-                              hipMemcpyHostToDevice));
-            SAL_HIP(hipMemcpy(ctx->batch_insts, hin.data(), hin.size() * sizeof(BatchInst),
-                              hipMemcpyHostToDevice));
-            a.n_items = (int64_t)sorted.size();
-            ctx->batch_items_key = key;
-            ctx->batch_items_fields = fields;
-            ctx->batch_n_items = a.n_items;
+            if (!small) n_wave = table.size();
         }
-        a.items = (const BatchItem *)ctx->batch_items;
-        a.insts = (const BatchInst *)ctx->batch_insts;
-        a.n_inst = n_inst;
-        a.total_points = total;
-        a.next_item = ctx->batch_next;
-        a.partial = ctx->batch_partial;
-        a.slot_mask = ctx->batch_mask;
-        a.kappa = (float)opt.kappa;
+        if ((st = ensure_label_scratch(ctx, wave_points, tiles, (int64_t)n_wave)) != SAL_OK) return st;
+        if ((int64_t)table.size() > ctx->batch_insts_cap) ctx->batch_table.clear();
+        if ((st = ensure_dev(&ctx->batch_insts, &ctx->batch_insts_cap, (int64_t)table.size(), ctx)) != SAL_OK)
+            return st;
+        if (!same_table(table, ctx->batch_table)) {
+            // a graph captured for another batch reads this table, and the
+            // previous call may still do so
+            ctx->batch_graph_fields.clear();
+            ctx->batch_table.clear();
+            SAL_HIP(hipStreamSynchronize(s));
+            SAL_HIP(hipMemcpy(ctx->batch_insts, table.data(), table.size() * sizeof(LabelInst),
+                              hipMemcpyHostToDevice));
+            ctx->batch_table = table;
+        }
+
+        const LabelScratch sc = context_scratch(ctx);
+        LabelArgs a{};
         a.threshold = opt.threshold;
         a.band = opt.recheck_band;
-        a.flag_list = ctx->flag_list;
-        a.counters = ctx->counters;
-        a.inst_counters = ctx->batch_counters;
-        a.fp64 = fp64 ? 1 : 0;
-        // workgroups of 4 wavefronts that fill the chip once: 8 wavefronts per
-        // SIMD for the float32 kernel, 4 for the FP64 one
-        const int pblocks = ctx->n_cu * (fp64 ? 4 : 8);
-        const int rblocks = (int)std::min<int64_t>(total, (int64_t)ctx->n_cu * 8);
-
+        a.kappa = (float)opt.kappa;
+        a.flag_list = sc.flag_list;
+        a.list_n = sc.list_n;
+        a.ord = sc.ord;
         auto enqueue = [&](hipStream_t q) -> sal_status {
-            SAL_HIP(launch_fill_u64((unsigned long long *)ctx->batch_next, 0ull, 1, q));
-            SAL_HIP(launch_fill_u64(ctx->counters, 0ull, kNumCounters, q));
             SAL_HIP(launch_fill_u64(ctx->batch_counters, 0ull, (int64_t)n_inst * kNumCounters, q));
-            SAL_HIP(launch_batch(a, pblocks, rblocks, q));
+            if (n_wave > 0) {
+                a.insts = ctx->batch_insts;
+                a.n_inst = (int32_t)n_wave;
+                SAL_HIP(launch_order(a, tiles, q));
+                SAL_HIP(launch_label_wave(a, fp64, wave_groups, kBlockWaves, q));
+            }
+            if (point_groups > 0) {
+                LabelArgs p = a;
+                p.insts = ctx->batch_insts + n_wave;
+                p.n_inst = (int32_t)(table.size() - n_wave);
+                SAL_HIP(launch_label_point(p, fp64, false, point_groups, kBlockWaves, q));
+            }
+            if (n_wave > 0) SAL_HIP(launch_recheck(a, fp64, ctx->n_cu * 8, q));
             return SAL_OK;
         };
+
+        // everything the captured launches read or are shaped by
+        std::vector<uint64_t> fields(table.size() * (sizeof(LabelInst) / 8));
+        static_assert(sizeof(LabelInst) % 8 == 0, "the table is compared as words");
+        std::memcpy(fields.data(), table.data(), table.size() * sizeof(LabelInst));
+        auto add = [&](const void *p, size_t bytes) {
+            uint64_t v = 0;
+            std::memcpy(&v, p, bytes);
+            fields.push_back(v);
+        };
+        add(&opt.kappa, 8);
+        add(&opt.threshold, 8);
+        add(&opt.recheck_band, 8);
+        add(&opt.precision, 4);
+        add(&n_inst, 4);
+        const void *ptrs[] = {ctx->batch_insts, ctx->batch_counters, sc.flag_list, sc.list_n, sc.ord.idx1,
+                              sc.ord.key1, sc.ord.perm, sc.ord.hist, sc.ord.tot};
+        for (const void *p : ptrs) add(&p, sizeof(p));
+        const bool replay = opt.use_graph && ctx->batch_graph && ctx->batch_graph_fields == fields;
 
         if (stats) SAL_HIP(hipEventRecord(ctx->ev[0], s));
         if (opt.use_graph) {
@@ -264,7 +166,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
                     SAL_HIP(hipGraphExecDestroy(ctx->batch_graph));
                     ctx->batch_graph = nullptr;
                 }
-                ctx->batch_graph_key = 0;
+                ctx->batch_graph_fields.clear();
                 hipGraph_t g = nullptr;
                 SAL_HIP(hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
                 sal_status cst = enqueue(ctx->capture_stream);
@@ -277,9 +179,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
                 ee = hipGraphInstantiate(&ctx->batch_graph, g, nullptr, nullptr, 0);
                 (void)hipGraphDestroy(g);
                 if (ee != hipSuccess) return hip_error(ee, "hipGraphInstantiate");
-                ctx->batch_graph_key = key;
                 ctx->batch_graph_fields = fields;
-                ctx->batch_graph_points = total;
             }
             SAL_HIP(hipGraphLaunch(ctx->batch_graph, s));
         } else {

@@ -188,11 +188,8 @@ sal_status label_scratch(sal_context *ctx, sal_tet_mesh *m, const sal_surface_se
                          const sal_label_options &opt, int32_t *labels, hipEvent_t ev_start,
                          hipEvent_t ev_mid, unsigned long long *masks = nullptr) {
     if (n <= 0) return SAL_OK;
-    if (opt.precision == SAL_PREC_FP32_RECHECK) {
-        sal_status st = ensure_flag_capacity(ctx, n);
-        if (st != SAL_OK) return st;
-    }
-    SAL_HIP(launch_fill_u64(ctx->counters + kCntFlagged, 0ull, 1, ctx->stream));
+    const sal_status st = ensure_label_scratch(ctx, n);
+    if (st != SAL_OK) return st;
     return enqueue_label(ctx, set, n, m->cen[0], m->cen[1], m->cen[2], opt, labels, nullptr,
                          ev_start, ev_mid, nullptr, masks);
 }
@@ -203,13 +200,10 @@ sal_status label_scratch_dev(sal_context *ctx, sal_tet_mesh *m, const sal_surfac
                              const sal_label_options &opt_in, int32_t *labels, hipEvent_t ev_start,
                              hipEvent_t ev_mid, unsigned long long *masks) {
     if (n_cap <= 0) return SAL_OK;
-    if (opt_in.precision == SAL_PREC_FP32_RECHECK) {
-        sal_status st = ensure_flag_capacity(ctx, n_cap);
-        if (st != SAL_OK) return st;
-    }
-    SAL_HIP(launch_fill_u64(ctx->counters + kCntFlagged, 0ull, 1, ctx->stream));
+    sal_status st = ensure_label_scratch(ctx, n_cap);
+    if (st != SAL_OK) return st;
     sal_label_options opt = opt_in;
-    sal_status st = tune_launch(ctx, set, n_cap, m->cen[0], m->cen[1], m->cen[2], labels, &opt);
+    st = tune_launch(ctx, set, n_cap, m->cen[0], m->cen[1], m->cen[2], labels, &opt);
     if (st != SAL_OK) return st;
     SAL_HIP(hipEventRecord(ev_start, ctx->stream));
     return enqueue_label_on(ctx, set, n_cap, (const int64_t *)n_dev, m->cen[0], m->cen[1],
@@ -299,9 +293,7 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
         }
         if (pts_max > 0) {
             if ((st = ensure_centroids(m, pts_max, s)) != SAL_OK) return st;
-            if (opt.precision == SAL_PREC_FP32_RECHECK &&
-                (st = ensure_flag_capacity(ctx, pts_max)) != SAL_OK)
-                return st;
+            if ((st = ensure_label_scratch(ctx, pts_max)) != SAL_OK) return st;
             if (nodes) {
                 int64_t c3 = m->mid_xyz_cap;
                 for (int a = 0; a < 3; ++a) {
@@ -500,11 +492,8 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
     if (m->lab_cap < budget &&
         (st = ensure_buf(&m->lab_scratch, &m->lab_cap, budget + budget / 2, s)) != SAL_OK)
         return st;
-    if (opt.precision == SAL_PREC_FP32_RECHECK && ctx->flag_cap < budget &&
-        (st = ensure_flag_capacity(ctx, budget + budget / 2)) != SAL_OK)
-        return st;
-    int64_t kid_cap = std::min(m->cen_cap, m->lab_cap);
-    if (opt.precision == SAL_PREC_FP32_RECHECK) kid_cap = std::min(kid_cap, ctx->flag_cap);
+    const int64_t kid_cap = std::min(m->cen_cap, m->lab_cap);
+    if ((st = ensure_label_scratch(ctx, kid_cap)) != SAL_OK) return st;
     int64_t list_need = 0, blocks_need = 1;
     for (int l = 0; l <= kMaxLevels; ++l) {
         list_need += m->cap[l];
@@ -539,12 +528,12 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
     add(set->uid);
     addp(ctx);
     addp(ctx->flag_list);
-    addp(ctx->rc_pairs);
-    addp(ctx->rc_out);
-    addp(ctx->rc_res);
-    addp(ctx->rc_seg);
-    add((uint64_t)ctx->flag_cap);
-    add((uint64_t)ctx->rc_pair_cap);
+    addp(ctx->list_n);
+    addp(ctx->ord_idx1);
+    addp(ctx->ord_key1);
+    addp(ctx->ord_perm);
+    addp(ctx->ord_hist);
+    addp(ctx->ord_tot);
     addp(ctx->counters);
     add((uint64_t)opt.precision);
     addd(opt.threshold);

@@ -1,7 +1,7 @@
 // sal_label_points_noalloc: point labeling for callers that cannot allocate
 // device memory (code under HIP graph capture, tight serving loops).  The
 // same kernels as sal_label_points; their scratch (counters, flag list,
-// recheck buffers) lives in one file-scope device array instead of the
+// spatial order) lives in one file-scope device array instead of the
 // context's growable buffers.
 #include <hip/hip_runtime.h>
 
@@ -14,20 +14,22 @@ namespace sal {
 namespace {
 
 constexpr int64_t kNoAllocMaxPoints = (int64_t)1 << 20;
-constexpr int64_t kNoAllocPairCap = kNoAllocMaxPoints / 4 + 64 * kMaxSurfaces;
 
 constexpr int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 
 // Byte offsets of the parts of the scratch array.
 constexpr int64_t kOffCounters = 0;
 constexpr int64_t kOffFlags = align256(kOffCounters + kNumCounters * 8);
-constexpr int64_t kOffRes = align256(kOffFlags + kNoAllocMaxPoints * (int64_t)sizeof(FlagEntry));
-constexpr int64_t kOffPairs = align256(kOffRes + kNoAllocMaxPoints * 8);
-constexpr int64_t kOffOut = align256(kOffPairs + kNoAllocPairCap * (int64_t)sizeof(RecheckPair));
-constexpr int64_t kOffSeg = align256(kOffOut + kNoAllocPairCap * (int64_t)sizeof(RecheckOut));
-constexpr int64_t kScratchBytes = align256(kOffSeg + (int64_t)sizeof(RecheckSeg));
+constexpr int64_t kOffListN = align256(kOffFlags + kNoAllocMaxPoints * (int64_t)sizeof(FlagEntry));
+constexpr int64_t kOffIdx1 = align256(kOffListN + 8);
+constexpr int64_t kOffKey1 = align256(kOffIdx1 + kNoAllocMaxPoints * 4);
+constexpr int64_t kOffPerm = align256(kOffKey1 + kNoAllocMaxPoints * 2);
+constexpr int64_t kOffHist = align256(kOffPerm + kNoAllocMaxPoints * 4);
+constexpr int64_t kOffTot = align256(kOffHist + kNoAllocMaxPoints / kMinTile * kOrderBins * 4);
+constexpr int64_t kScratchBytes = align256(kOffTot + kOrderBins * 4);
+static_assert(kNoAllocMaxPoints / kMinTile <= kMaxTiles, "every tile of a full call has the smallest size");
 
-// ~38 MB per device, held until the process ends.  Host code must never pass
+// ~39 MB per device, held until the process ends.  Host code must never pass
 // this name to a kernel: on the host it is only a stand-in for the symbol;
 // the device address comes from hipGetSymbolAddress below.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -88,20 +90,21 @@ extern "C" sal_status sal_label_points_noalloc(sal_context *ctx, const sal_surfa
         // no tuning (it times trial launches and synchronises): an unset
         // launch shape takes the tuner's usual choice, 1 point per lane and
         // 4 wavefronts per workgroup
-        if (opt.points_per_lane == 0 || opt.precision == SAL_PREC_FP64) opt.points_per_lane = 1;
+        opt.points_per_lane = 1;
         if (opt.block_waves == 0) opt.block_waves = 4;
         LabelScratch sc;
         sc.counters = (unsigned long long *)(base + kOffCounters);
         sc.flag_list = (FlagEntry *)(base + kOffFlags);
-        sc.rc_res = (unsigned long long *)(base + kOffRes);
-        sc.rc_pairs = (RecheckPair *)(base + kOffPairs);
-        sc.rc_out = (RecheckOut *)(base + kOffOut);
-        sc.rc_seg = (RecheckSeg *)(base + kOffSeg);
-        sc.rc_pair_cap = kNoAllocPairCap;
+        sc.list_n = (unsigned long long *)(base + kOffListN);
+        sc.ord.idx1 = (uint32_t *)(base + kOffIdx1);
+        sc.ord.key1 = (uint16_t *)(base + kOffKey1);
+        sc.ord.perm = (uint32_t *)(base + kOffPerm);
+        sc.ord.hist = (uint32_t *)(base + kOffHist);
+        sc.ord.tot = (uint32_t *)(base + kOffTot);
         hipStream_t s = ctx->stream;
-        // counters start at zero on every call (a fill kernel, not a memset
-        // node, so the call can be captured)
-        SAL_HIP(launch_fill_u64(sc.counters, 0ull, kNumCounters, s));
+        // counters start at zero where they are read (a fill kernel, not a
+        // memset node, so the call can be captured)
+        if (stats) SAL_HIP(launch_fill_u64(sc.counters, 0ull, kNumCounters, s));
         if (stats) SAL_HIP(hipEventRecord(ctx->ev[0], s));
         st = enqueue_label_with(ctx, set, n, nullptr, x, y, z, opt, labels, winding,
                                 stats ? ctx->ev[1] : nullptr, s, nullptr, sc);

@@ -1,0 +1,208 @@
+// Spatial order of the points to be labeled, so that the 64 points of a
+// wavefront lie close together: a stable counting sort by a 21-bit Morton code
+// of the point's cell in the surface set's box (128 cells per axis; points
+// outside it go to the border cells), 11 low bits, then 10 high bits.
+// Stable, so that the wavefronts, and with them every rounding, are the same
+// in every run.
+//
+// Per pass: a histogram per tile, a scan over the tiles of each bin, and a
+// scatter that ranks the keys of a tile in input order (wave by wave, 64 at a
+// time, equal digits found by one ballot per bit).  Bound by memory: 12 bytes a
+// point read twice, 6 written, 2 + 6 read, 4 written, against ~1000 terms of
+// labeling work.  All instances of a batch are sorted by the same three
+// launches (their tiles are separate).  No memsets, no allocations: the
+// launches can be captured.
+#include <hip/hip_runtime.h>
+
+#include "sal_internal.h"
+#include "strip_f32.h"
+
+namespace sal {
+namespace {
+
+constexpr int kThreads = 256, kWaves = kThreads / 64;
+
+using f32::ballot;
+using f32::lane_id;
+using f32::lanes_below;
+
+__device__ __forceinline__ int find_tile(const LabelInst *insts, int n_inst, int64_t t) {
+    int lo = 0, hi = n_inst - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (insts[mid].tile_base <= t) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Three bits apart: the low seven bits of v.
+__device__ __forceinline__ uint32_t spread3(uint32_t v) {
+    v = (v | (v << 8)) & 0x0000f00fu;
+    v = (v | (v << 4)) & 0x000c30c3u;
+    v = (v | (v << 2)) & 0x00249249u;
+    return v;
+}
+
+__device__ __forceinline__ uint32_t cell_code(const LabelInst &in, int64_t i) {
+    uint32_t q[3];
+    const float p[3] = {in.x[i], in.y[i], in.z[i]};
+    for (int c = 0; c < 3; ++c) {
+        // (a NaN becomes 0: fmaxf and fminf return the other operand)
+        const float f = fminf(fmaxf((p[c] - in.lo[c]) * in.scale[c], 0.0f), 127.0f);
+        q[c] = (uint32_t)f;
+    }
+    return spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
+}
+
+template <int PASS>
+__device__ __forceinline__ uint32_t digit(const LabelArgs &a, const LabelInst &in, int64_t i, uint32_t &code) {
+    if (PASS == 1) {
+        code = cell_code(in, i);
+        return code & (kOrderBins - 1);
+    }
+    code = a.ord.key1[in.order_base + i];
+    return code;
+}
+
+template <int PASS>
+constexpr int bins() { return PASS == 1 ? kOrderBins : 1 << kOrderBits2; }
+
+template <int PASS>
+__global__ __launch_bounds__(kThreads) void k_order_hist(LabelArgs a) {
+    __shared__ uint32_t h[bins<PASS>()];
+    const int ii = a.insts ? find_tile(a.insts, a.n_inst, blockIdx.x) : 0;
+    const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+    const int64_t n = label_count(a, in), t = (int64_t)blockIdx.x - in.tile_base;
+    if (PASS == 1 && blockIdx.x == 0 && threadIdx.x == 0) *a.list_n = 0ull;
+    for (int b = threadIdx.x; b < bins<PASS>(); b += kThreads) h[b] = 0u;
+    __syncthreads();
+    const int64_t i0 = t * in.tile, i1 = i0 + in.tile < n ? i0 + in.tile : n;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) {
+        uint32_t code;
+        atomicAdd(&h[digit<PASS>(a, in, i, code)], 1u);
+    }
+    __syncthreads();
+    uint32_t *out = a.ord.hist + kOrderBins * in.tile_base + t;
+    for (int b = threadIdx.x; b < bins<PASS>(); b += kThreads) out[(int64_t)b * in.n_tiles] = h[b];
+}
+
+// One wavefront per (bin, instance): exclusive scan over the tiles, in place.
+template <int PASS>
+__global__ __launch_bounds__(64) void k_order_scan(LabelArgs a) {
+    const int ii = (int)(blockIdx.x / bins<PASS>()), bin = (int)(blockIdx.x % bins<PASS>());
+    const int lane = lane_id();
+    const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+    uint32_t *h = a.ord.hist + kOrderBins * in.tile_base + (int64_t)bin * in.n_tiles;
+    uint32_t run = 0;
+    for (int b = 0; b < in.n_tiles; b += 64) {
+        const uint32_t v = b + lane < in.n_tiles ? h[b + lane] : 0u;
+        uint32_t s = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t u = (uint32_t)__shfl_up((int)s, d);
+            if (lane >= d) s += u;
+        }
+        if (b + lane < in.n_tiles) h[b + lane] = run + s - v;
+        run += (uint32_t)__shfl((int)s, 63);
+    }
+    if (lane == 0) a.ord.tot[(int64_t)ii * kOrderBins + bin] = run;
+}
+
+template <int PASS>
+__global__ __launch_bounds__(kThreads) void k_order_scatter(LabelArgs a) {
+    constexpr int B = bins<PASS>(), PER = B / kThreads, BITS = PASS == 1 ? kOrderBits1 : kOrderBits2;
+    __shared__ uint32_t cnt[kWaves][B];
+    __shared__ uint32_t base[B];
+    __shared__ uint32_t part[kThreads];
+    const int ii = a.insts ? find_tile(a.insts, a.n_inst, blockIdx.x) : 0;
+    const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+    const int64_t n = label_count(a, in), t = (int64_t)blockIdx.x - in.tile_base;
+    const int64_t i0 = t * in.tile, i1 = i0 + in.tile < n ? i0 + in.tile : n;
+    if (i0 >= i1) return;   // (the whole workgroup)
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    // where each bin of this tile starts: all smaller bins, then this bin's
+    // earlier tiles
+    const uint32_t *tot = a.ord.tot + (int64_t)ii * kOrderBins;
+    uint32_t sum = 0;
+    for (int q = 0; q < PER; ++q) sum += tot[tid * PER + q];
+    part[tid] = sum;
+    __syncthreads();
+    for (int d = 1; d < kThreads; d <<= 1) {
+        const uint32_t u = tid >= d ? part[tid - d] : 0u;
+        __syncthreads();
+        part[tid] += u;
+        __syncthreads();
+    }
+    uint32_t run = part[tid] - sum;
+    const uint32_t *h = a.ord.hist + kOrderBins * in.tile_base + t;
+    for (int q = 0; q < PER; ++q) {
+        const int b = tid * PER + q;
+        base[b] = run + h[(int64_t)b * in.n_tiles];
+        run += tot[b];
+    }
+    for (int w = 0; w < kWaves; ++w)
+        for (int b = tid; b < B; b += kThreads) cnt[w][b] = 0u;
+    __syncthreads();
+    // each wavefront owns a quarter of the tile, in order
+    const int64_t quarter = in.tile / kWaves;
+    const int64_t w0 = i0 + wave * quarter, w1 = w0 + quarter < i1 ? w0 + quarter : i1;
+    for (int64_t i = w0 + lane; i < w1; i += 64) {
+        uint32_t code;
+        atomicAdd(&cnt[wave][digit<PASS>(a, in, i, code)], 1u);
+    }
+    __syncthreads();
+    for (int b = tid; b < B; b += kThreads) {
+        uint32_t at = base[b];
+        for (int w = 0; w < kWaves; ++w) {
+            const uint32_t c = cnt[w][b];
+            cnt[w][b] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+    for (int64_t b = w0; b < w1; b += 64) {
+        const int64_t i = b + lane;
+        const bool have = i < w1;
+        uint32_t code = 0;
+        const uint32_t d = have ? digit<PASS>(a, in, i, code) : 0u;
+        uint64_t same = ballot(have);
+#pragma unroll
+        for (int q = 0; q < BITS; ++q) {
+            const uint64_t m = ballot((d >> q) & 1u);
+            same &= ((d >> q) & 1u) ? m : ~m;
+        }
+        const uint32_t at = cnt[wave][d] + (uint32_t)lanes_below(same);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (have) {
+            if (lanes_below(same) == 0) cnt[wave][d] = at + (uint32_t)__popcll(same);
+            if (PASS == 1) {
+                a.ord.idx1[in.order_base + at] = (uint32_t)i;
+                a.ord.key1[in.order_base + at] = (uint16_t)(code >> kOrderBits1);
+            } else {
+                a.ord.perm[in.order_base + at] = a.ord.idx1[in.order_base + i];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+}  // namespace
+
+hipError_t launch_order(const LabelArgs &a, int64_t tiles, hipStream_t s) {
+    if (tiles <= 0) return hipSuccess;
+    if (tiles > 0x7fffffff || (a.insts && a.n_inst > 0x7fffffff / kOrderBins)) return hipErrorInvalidValue;
+    const unsigned ni = (unsigned)(a.insts ? a.n_inst : 1);
+    const dim3 g((unsigned)tiles), b(kThreads);
+    k_order_hist<1><<<g, b, 0, s>>>(a);
+    k_order_scan<1><<<dim3(ni << kOrderBits1), dim3(64), 0, s>>>(a);
+    k_order_scatter<1><<<g, b, 0, s>>>(a);
+    k_order_hist<2><<<g, b, 0, s>>>(a);
+    k_order_scan<2><<<dim3(ni << kOrderBits2), dim3(64), 0, s>>>(a);
+    k_order_scatter<2><<<g, b, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace sal

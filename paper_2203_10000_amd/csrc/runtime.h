@@ -10,36 +10,30 @@ struct sal_context {
     int device = 0;
     hipStream_t stream = nullptr;
     hipEvent_t ev[8] = {};
+    // flag list and spatial order of the wavefront-per-64-points form
     sal::FlagEntry *flag_list = nullptr;
-    int64_t flag_cap = 0;
-    // pair-major recheck scratch (grows with the flag list)
-    sal::RecheckPair *rc_pairs = nullptr;
-    sal::RecheckOut *rc_out = nullptr;
-    unsigned long long *rc_res = nullptr;
-    sal::RecheckSeg *rc_seg = nullptr;
-    int64_t rc_pair_cap = 0;
+    uint32_t *ord_idx1 = nullptr;
+    uint16_t *ord_key1 = nullptr;
+    uint32_t *ord_perm = nullptr;
+    int64_t point_cap = 0;
+    uint32_t *ord_hist = nullptr;
+    int64_t tile_cap = 0;
+    uint32_t *ord_tot = nullptr;
+    int64_t inst_cap = 0;
+    unsigned long long *list_n = nullptr;
     unsigned long long *counters = nullptr;  // sal::kNumCounters
     unsigned long long *tune_counters = nullptr;
     int n_cu = 0;
-    // batched form
-    void *batch_items = nullptr;
-    int64_t batch_items_bytes = 0;
-    void *batch_insts = nullptr;
-    int64_t batch_insts_bytes = 0;
-    double *batch_partial = nullptr;
-    uint64_t *batch_mask = nullptr;
-    int64_t batch_slots = 0;
-    unsigned int *batch_next = nullptr;
+    // batched form: the instance table on the device and its host copy
+    sal::LabelInst *batch_insts = nullptr;
+    int64_t batch_insts_cap = 0;
+    std::vector<sal::LabelInst> batch_table;   // what batch_insts holds (empty: nothing)
     unsigned long long *batch_counters = nullptr;
     int64_t batch_counters_n = 0;
     hipStream_t capture_stream = nullptr;
     hipGraphExec_t batch_graph = nullptr;
-    uint64_t batch_graph_key = 0;
-    std::vector<uint64_t> batch_graph_fields;   // the fields hashed into batch_graph_key
-    int64_t batch_graph_points = 0;
-    uint64_t batch_items_key = 0;   // batch whose work list the item buffers hold (0: none)
-    std::vector<uint64_t> batch_items_fields;   // the fields hashed into batch_items_key
-    int64_t batch_n_items = 0;
+    std::vector<uint64_t> batch_graph_fields;   // everything the graph reads or is shaped by
+                                                // (empty: no valid graph)
 };
 
 struct sal_surface_set {
@@ -49,12 +43,11 @@ struct sal_surface_set {
     int64_t n_tri = 0, n_strips = 0, n_rec = 0, bytes = 0;
     sal::Rec32 *rec32 = nullptr;
     sal::Rec64 *rec64 = nullptr;
-    sal::SurfaceDev *surf = nullptr;        // n_surf entries, then the two tuner entries
-    sal::SurfaceDev *tune_surf = nullptr;   // surf + n_surf: [0] float32 trials, [1] FP64 trials,
-                                            // [2] float32 screening trials
+    sal::SurfaceDev *surf = nullptr;        // n_surf entries
+    sal::PatchEntry *ent = nullptr;         // patch trees of all surfaces
+    float lo[3] = {}, hi[3] = {};           // box of all surfaces
     int64_t *strip_off = nullptr;
     std::vector<sal::SurfaceDev> host_table;
-    std::vector<int64_t> host_strip_off;   // record index of every strip head
     std::vector<int32_t> host_strip_tris;  // triangles of every strip
     bool balls_ready = false;              // ball_w of every surface known
 };
@@ -70,14 +63,33 @@ void destroy_surface_set(sal_surface_set *set);
 // is asked for; until then no ball is used.
 sal_status ensure_surface_balls(sal_context *ctx, const sal_surface_set *set);
 
-// Grows the context scratch to hold a flag list of n entries.
-sal_status ensure_flag_capacity(sal_context *ctx, int64_t n);
+// Points of one launch sequence: larger calls run in pieces (their scratch is
+// some 34 bytes a point).
+constexpr int64_t kChunkPoints = (int64_t)1 << 27;
+
+// Up to this many points are labeled one per wavefront, in the order given.
+// The 64-point form pays six sorting launches first and needs enough
+// wavefronts to fill the chip.
+constexpr int64_t kPointFormMax = 65536;
+
+// Tile size and count of the spatial order for n points.
+inline int32_t order_tile(int64_t n) {
+    int64_t tile = kMinTile;
+    while ((n + tile - 1) / tile > kMaxTiles) tile *= 2;
+    return (int32_t)tile;
+}
+inline int64_t order_tiles(int64_t n) { return (n + order_tile(n) - 1) / order_tile(n); }
+
+// Grows the context's labeling scratch to hold `points` in `tiles` tiles of
+// `insts` instances at once.
+sal_status ensure_label_scratch(sal_context *ctx, int64_t points, int64_t tiles, int64_t insts);
+// The same for a call on n points (nothing for the point form).
+sal_status ensure_label_scratch(sal_context *ctx, int64_t n);
 
 // Validated options with defaults applied.
 sal_status resolve_options(const sal_label_options *in, sal_label_options *out);
 
-// Enqueues one labeling pass (pair loop, and recheck in the float32 form) of
-// n points; counters must be cleared by the caller.  The launch shape is
+// Enqueues one labeling pass (winding numbers, and the recheck) of n points; counters must be cleared by the caller.  The launch shape is
 // resolved first (tune_launch); then ev_start (before the pair loop) and
 // ev_after_pairloop are recorded when non-null, so that timings bracketed by
 // them leave out any tuning.
@@ -87,20 +99,21 @@ sal_status enqueue_label(sal_context *ctx, const sal_surface_set *set, int64_t n
                          hipEvent_t ev_after_pairloop, int *shape = nullptr,
                          unsigned long long *masks = nullptr);
 
-// The device scratch one labeling pass works in: the counters, the flag list
-// (one entry per point at most) and the pair-major recheck buffers.
+// The device scratch one labeling pass works in.
 struct LabelScratch {
     unsigned long long *counters;
     FlagEntry *flag_list;
-    RecheckPair *rc_pairs;
-    RecheckOut *rc_out;
-    unsigned long long *rc_res;
-    RecheckSeg *rc_seg;
-    int64_t rc_pair_cap;
+    unsigned long long *list_n;
+    OrderScratch ord;
 };
 
-// The context's own scratch (sized by ensure_flag_capacity).
+// The context's own scratch (sized by ensure_label_scratch).
 LabelScratch context_scratch(const sal_context *ctx);
+
+// The kernels' view of n points against a set; order, group and tile bases 0.
+LabelInst make_inst(const sal_surface_set *set, int64_t n, const float *x, const float *y, const float *z,
+                    int32_t *labels, void *winding, int64_t wstride, unsigned long long *masks,
+                    unsigned long long *counters);
 
 // The launches of one labeling pass with a resolved launch shape and the
 // given scratch, on `stream`; the counters must be cleared by the caller.
@@ -123,10 +136,9 @@ sal_status enqueue_label_on(sal_context *ctx, const sal_surface_set *set, int64_
                             hipEvent_t ev_mid, hipStream_t stream,
                             unsigned long long *masks = nullptr);
 
-// Resolves points_per_lane / block_waves left at 0 by timing the candidates
-// on a prefix of the points against a prefix of the strips (the tuner table
-// entries), so a trial costs a bounded number of pairs; the first use of a
-// size bucket synchronises the stream.  Cached per process.
+// Resolves points_per_lane (1) and block_waves left at 0: the workgroup sizes
+// are timed on a prefix of the points; the first use of a size bucket
+// synchronises the stream.  Cached per process.
 sal_status tune_launch(sal_context *ctx, const sal_surface_set *set, int64_t n, const float *x,
                        const float *y, const float *z, int32_t *labels, sal_label_options *opt);
 

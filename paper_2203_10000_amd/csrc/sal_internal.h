@@ -19,15 +19,15 @@ namespace sal {
 // per-vertex terms (v - p, |v - p|) and the dot product of the shared edge
 // are computed once per strip step instead of once per triangle.
 //
-// float32 stream, 32 bytes per record, read by every lane of a wavefront at
-// the same address (scalar loads, broadcast through SGPRs):
+// float32 stream, 32 bytes per record:
 //   head: { x0, y0, z0, x1, y1, z1, bits(m), 0 }
 //   tri : { x, y, z,  32 nx, 32 ny, 32 nz,  |n|,  KN_SMALL |n| }
 // where (x, y, z) is the strip's next vertex and n = (B - A) x (C - A) is the
 // outward (unnormalised) normal of the original triangle (A, B, C), computed in
 // double from the float32 vertices and rounded once.  The factor 32 is a power
 // of two (exact) that folds the small-angle bound |N/D| < 1/32 into one
-// comparison.
+// comparison.  The last word tells the two kinds apart: 0 in a head, > 0 in a
+// triangle (a degenerate cap triangle holds the smallest normal float).
 struct alignas(32) Rec32 {
     float v[8];
 };
@@ -49,20 +49,44 @@ constexpr float kNScale = 32.0f;     // normal pre-scale in the float32 stream (
 constexpr float kKnSmall = 5.0f;     // small-angle path needs D > 5 |n| r_Z + ...
 constexpr int kMaxSurfaces = 64;     // per-point masks are 64-bit
 
-// Per-surface table in device memory.
-// Triangles per tuner trial launch: float32 form, FP64 form, and the float32
-// screening launches (every shape once, before the closest two are timed on
-// the first prefix).
-constexpr int kTuneEntries = 3;
-constexpr int64_t kTuneTri[kTuneEntries] = {32768, 8192, 8192};
+// Patch tree.  The triangles of a surface are grouped into spatially compact
+// patches, four to a node, down to leaves of at most kLeafTri triangles.  A
+// patch with the opposite of any other surface over the same boundary loops (a
+// "cap") is closed, and a closed surface has winding number 0 at every point
+// outside its convex hull; so for a point outside the patch's box the cap's
+// solid angle equals the patch's.  A cap is a zigzag strip over each boundary
+// loop: about 3.2 sqrt(m) triangles for a patch of m.  Caps lie inside the
+// patch's hull, and the box is enlarged by kCapMargin of its extent, so a point
+// outside it sees no cap triangle from close by (float32 certifies the terms).
+// Entry e of node w is ent[4 w + e]; an unused entry has leaf_n = 0.
+struct alignas(16) PatchEntry {
+    float lo[3];
+    uint32_t cap_begin;    // cap strips: records [cap_begin, cap_begin + cap_n)
+    float hi[3];           // box of the patch's vertices, enlarged
+    uint32_t cap_n;
+    int32_t child;         // node of the patch's parts, -1 for a leaf
+    uint32_t leaf_begin;   // the patch's own triangles: records
+    uint32_t leaf_n;       // [leaf_begin, leaf_begin + leaf_n)
+    uint32_t pad;
+};
+// Record indices are relative to the surface's rec_begin, node indices to its
+// node_begin.
 
+// Leaf size: a leaf's records (triangles and strip heads) fit the 64 lanes of
+// one wavefront, and halving a mesh down to at most 56 leaves 28-56.
+constexpr int kLeafTri = 56;
+constexpr double kCapMargin = 0.02;
+
+// Per-surface table in device memory.
 struct SurfaceDev {
-    int64_t rec_begin, rec_end;      // [begin, end) in both record streams
+    int64_t rec_begin, rec_end;      // the surface's triangles: [begin, end) in both record
+                                     // streams (its caps follow)
     int64_t strip_begin, strip_end;  // [begin, end) in the strip table
+    int64_t node_begin;              // root node of the patch tree
     int64_t n_tri;
     int32_t label;
     int32_t pad;
-    float lo[3], hi[3];              // bounding box of the vertices (+-inf: never culled)
+    float lo[3], hi[3];              // bounding box of the vertices
     float ball[4];                   // centre and squared radius of a ball the surface does
                                      // not cross (radius shrunk for rounding)
     int32_t ball_w;                  // winding number inside that ball (0 or 1), -1: none
@@ -72,105 +96,94 @@ struct SurfaceDev {
 // A point with at least one (surface) winding number that the float32 pass
 // cannot certify.
 struct FlagEntry {
-    int64_t idx;     // point index
+    uint32_t idx;    // point index within its instance
+    int32_t inst;    // instance
     uint64_t enc;    // bit k: float32 pass found w_k >= T
-    uint64_t flg;    // bit k: surface k must be recomputed in FP64
+    uint64_t flg;    // bit k: surface k must be recomputed
 };
 
 // Device counters (uint64) of one labeling call.
 enum Counter {
-    kCntFlagged = 0,   // entries appended to the flag list
+    kCntFlagged = 0,   // points with a recomputed surface
     kCntBand = 1,      // (point, surface) pairs flagged by the band
     kCntCond = 2,      // pairs flagged by ill-conditioned triangles
     kCntExact = 3,     // exact-sign evaluations
-    kCntRecheck = 4,   // pairs recomputed in FP64
-    kCntRecheckF64 = 5,  // triangle terms of rechecked pairs evaluated in double
-    kCntCulled = 6,      // pairs skipped: every point of the wavefront outside the box
+    kCntRecheck = 4,   // pairs recomputed
+    kCntRecheckF64 = 5,  // triangle terms of recomputed pairs evaluated in double
+    kCntCulled = 6,      // pairs skipped by cull_bounds
     kNumCounters = 8
 };
 
-struct PairloopArgs {
-    const Rec32 *__restrict__ rec32;
-    const Rec64 *__restrict__ rec64;
-    const SurfaceDev *__restrict__ surf;
-    int n_surf;
-    const float *__restrict__ x;
-    const float *__restrict__ y;
-    const float *__restrict__ z;
-    int64_t n;
-    const int64_t *__restrict__ n_dev;   // when set, the point count is read here (n is the
-                                         // capacity the grid was sized for)
+// One set of points against one surface set, as the kernels see it.
+struct LabelInst {
+    const Rec32 *rec32;
+    const Rec64 *rec64;
+    const SurfaceDev *surf;
+    const PatchEntry *ent;
+    const float *x, *y, *z;
+    int32_t *labels;
+    void *winding;                // [n_surf][wstride] float or double, or null
+    unsigned long long *masks;    // [n] enclosure bits per point, or null
+    unsigned long long *counters; // kNumCounters
+    int64_t n, wstride;
+    int64_t order_base;           // first entry in the spatial order
+    int64_t group_base;           // first wavefront of the instance in its kernel's grid
+    int64_t tile_base;            // first tile of the spatial order
+    int32_t n_tiles, tile;        // tiles of `tile` points
+    int32_t n_surf;
+    int32_t pad;
+    float lo[3], scale[3];        // cells of the spatial order: (p - lo) * scale
+};
+
+// Spatial order of the points (order.hip): two stable counting passes over a
+// Morton code, kOrderBits1 low bits first.
+constexpr int kOrderBits1 = 11, kOrderBits2 = 10;   // 7 bits per axis
+constexpr int kOrderBins = 1 << kOrderBits1;
+constexpr int64_t kMinTile = 2048, kMaxTiles = 1024;   // per instance
+
+struct OrderScratch {
+    uint32_t *idx1;   // [points] order after the first pass
+    uint16_t *key1;   // [points] the second pass's digits in that order
+    uint32_t *perm;   // [points] the order
+    uint32_t *hist;   // [tiles][kOrderBins], bin-major within an instance
+    uint32_t *tot;    // [instances][kOrderBins]
+};
+
+struct LabelArgs {
+    LabelInst one;            // the instance when insts is null
+    const LabelInst *insts;
+    int32_t n_inst;
+    int32_t winding_type;
+    const int64_t *n_dev;     // when set, the one instance's point count is read here
+    int64_t n_dev_skip;       // (less this many, labeled before); one.n is the capacity
+                              // that the grids were sized for
+    double threshold, band;
     float kappa;
-    double threshold;
-    double band;
-    int32_t *__restrict__ labels;
-    void *__restrict__ winding;   // [n_surf][n] float or double, or null
-    int winding_type;
-    int cull;                     // skip a surface for a wavefront whose points all lie
-                                  // strictly outside its bounding box (w = 0 exactly)
-                                  // or inside its ball (w = ball_w exactly)
-    unsigned long long *__restrict__ masks;  // [n] enclosure bits per point, or null
-    FlagEntry *__restrict__ flag_list;  // capacity n
-    unsigned long long *__restrict__ counters;
+    int32_t cull;             // skip a surface for points strictly outside its box
+                              // (w = 0 exactly) or inside its ball (w = ball_w exactly)
+    FlagEntry *flag_list;     // capacity: the points
+    unsigned long long *list_n;   // its length
+    OrderScratch ord;
 };
 
-// Pair-major recheck: the flagged (point, surface) pairs grouped by surface,
-// each group padded to a multiple of 64 so that the 64 pairs of a wavefront
-// share one surface and its records can be scalar loads.
-struct RecheckPair {
-    int32_t entry;   // flag-list index; -1 = padding
-    int32_t surf;
-};
-struct RecheckOut {
-    double sum;      // sum of atan2(N, D) over the surface (half the solid angle)
-    int32_t on;      // the point lies on the surface
-    uint32_t pad;
-};
-struct RecheckSeg {
-    unsigned long long count[kMaxSurfaces];
-    unsigned long long cursor[kMaxSurfaces];
-    unsigned long long off[kMaxSurfaces];
-    unsigned long long total;     // padded pair count
-    unsigned long long overflow;  // more pairs than capacity: the per-point form runs instead
-    unsigned long long splits;    // strip ranges per surface (more wavefronts for few pairs)
-};
+__device__ __forceinline__ int64_t label_count(const LabelArgs &a, const LabelInst &in) {
+    if (!a.n_dev) return in.n;
+    const int64_t n = *a.n_dev - a.n_dev_skip;
+    return n < 0 ? 0 : (n < in.n ? n : in.n);
+}
 
-struct RecheckArgs {
-    const Rec32 *__restrict__ rec32;
-    const Rec64 *__restrict__ rec64;
-    const SurfaceDev *__restrict__ surf;
-    const int64_t *__restrict__ strip_off;  // record index of every strip head
-    const float *__restrict__ x;
-    const float *__restrict__ y;
-    const float *__restrict__ z;
-    int64_t n;
-    double threshold;
-    float kappa;
-    int32_t *__restrict__ labels;
-    void *__restrict__ winding;
-    int winding_type;
-    int cull;                     // skip a surface for a wavefront whose points all lie
-                                  // strictly outside its bounding box (w = 0 exactly)
-                                  // or inside its ball (w = ball_w exactly)
-    unsigned long long *__restrict__ masks;  // [n] enclosure bits per point, or null
-    const FlagEntry *__restrict__ flag_list;
-    unsigned long long *__restrict__ counters;
-    int n_surf;
-    RecheckPair *__restrict__ pairs;      // [pair_cap]
-    RecheckOut *__restrict__ pair_out;    // [pair_cap]
-    unsigned long long *__restrict__ res; // [flag capacity]: enclosed bits per flagged point
-    RecheckSeg *__restrict__ seg;
-    int64_t pair_cap;
-    int64_t target_waves;                  // wavefronts the pair-major form aims for
-};
-
-// Kernel launchers (pairloop.hip, recheck.hip).
-hipError_t launch_pairloop_f32(const PairloopArgs &a, int points_per_lane, int block_waves,
-                               hipStream_t s);
-hipError_t launch_pairloop_f64(const PairloopArgs &a, int block_waves, hipStream_t s);
-// The whole recheck: pair-major when the pairs fit, else one workgroup per
-// flagged point; grid_blocks sizes the grid-stride kernels.
-hipError_t launch_recheck_f64(const RecheckArgs &a, int grid_blocks, hipStream_t s);
+// Kernel launchers (label.hip, order.hip); `groups` and `tiles` are the
+// totals over the instances, block_waves the wavefronts of a workgroup.
+// Spatial order of every instance's points; also clears *list_n.
+hipError_t launch_order(const LabelArgs &a, int64_t tiles, hipStream_t s);
+// 64 points of the order per wavefront.
+hipError_t launch_label_wave(const LabelArgs &a, bool fp64, int64_t groups, int block_waves, hipStream_t s);
+// One point per wavefront, no order; results are final (nothing is flagged).
+// spread: the surfaces of a point are dealt to the workgroup's wavefronts.
+hipError_t launch_label_point(const LabelArgs &a, bool fp64, bool spread, int64_t groups, int block_waves,
+                              hipStream_t s);
+// Sums the flagged (point, surface) pairs again, one point per wavefront.
+hipError_t launch_recheck(const LabelArgs &a, bool fp64, int blocks, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t s);
 
 // ------------------------------------------------------------ host helpers

@@ -30,7 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include "exact_dev.h"
-#include "pairloop_f32.h"
+#include "strip_f32.h"
 #include "sal_internal.h"
 
 namespace sal {

@@ -4,7 +4,6 @@
 #include <cmath>
 #include <cstring>
 #include <atomic>
-#include <unordered_map>
 #include <vector>
 
 #include "runtime.h"
@@ -33,8 +32,15 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
     set->n_tri = total_tri;
     set->n_strips = (int64_t)strip_off.size();
     set->n_rec = (int64_t)r32.size();
-    set->host_table.assign(table.begin(), table.begin() + n);
-    set->host_strip_off = strip_off;
+    set->host_table = table;
+    for (int c = 0; c < 3; ++c) {
+        set->lo[c] = INFINITY;
+        set->hi[c] = -INFINITY;
+        for (const SurfaceDev &sd : table) {
+            set->lo[c] = std::min(set->lo[c], sd.lo[c]);
+            set->hi[c] = std::max(set->hi[c], sd.hi[c]);
+        }
+    }
     set->host_strip_tris = strip_tris;
     sal_status st = SAL_OK;
     auto up = [&](void **dst, const void *src, size_t bytes) -> sal_status {
@@ -48,12 +54,12 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
     if ((st = up((void **)&set->rec32, r32.data(), r32.size() * sizeof(Rec32))) != SAL_OK ||
         (st = up((void **)&set->rec64, r64.data(), r64.size() * sizeof(Rec64))) != SAL_OK ||
         (st = up((void **)&set->surf, table.data(), table.size() * sizeof(SurfaceDev))) != SAL_OK ||
+        (st = up((void **)&set->ent, rec.entries.data(), rec.entries.size() * sizeof(PatchEntry))) != SAL_OK ||
         (st = up((void **)&set->strip_off, strip_off.data(), strip_off.size() * sizeof(int64_t))) !=
             SAL_OK) {
         destroy_surface_set(set);
         return st;
     }
-    set->tune_surf = set->surf + n;
     *out = set;
     return SAL_OK;
 }
@@ -76,22 +82,14 @@ sal_status ensure_surface_balls(sal_context *ctx, const sal_surface_set *cset) {
     if (e == hipSuccess) e = hipMemcpy(dc, c.data(), c.size() * sizeof(float), hipMemcpyHostToDevice);
     // each centre against its own surface only: one FP64 launch per surface
     for (int i = 0; i < n && e == hipSuccess; ++i) {
-        PairloopArgs a{};
-        a.rec32 = set->rec32;
-        a.rec64 = set->rec64;
-        a.surf = set->surf + i;
-        a.n_surf = 1;
-        a.x = dc + i;
-        a.y = dc + n + i;
-        a.z = dc + 2 * n + i;
-        a.n = 1;
+        LabelArgs a{};
+        a.one = make_inst(set, 1, dc + i, dc + n + i, dc + 2 * n + i, dl + i, nullptr, 1, dm + i, ctx->counters);
+        a.one.surf = set->surf + i;
+        a.one.n_surf = 1;
         a.kappa = 0.03125f;
         a.threshold = 0.5;
         a.band = 0.0;
-        a.labels = dl + i;
-        a.masks = dm + i;
-        a.counters = ctx->counters;
-        e = launch_pairloop_f64(a, 1, ctx->stream);
+        e = launch_label_point(a, true, false, 1, 1, ctx->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = hipMemcpy(masks.data(), dm, (size_t)n * sizeof(unsigned long long), hipMemcpyDeviceToHost);
@@ -116,6 +114,7 @@ void destroy_surface_set(sal_surface_set *set) {
     if (set->rec32) (void)hipFree(set->rec32);
     if (set->rec64) (void)hipFree(set->rec64);
     if (set->surf) (void)hipFree(set->surf);
+    if (set->ent) (void)hipFree(set->ent);
     if (set->strip_off) (void)hipFree(set->strip_off);
     delete set;
 }

@@ -1,12 +1,13 @@
 // Host side of surface-set construction, with no device call: validation
-// of closed oriented manifolds, greedy triangle strips, the float32 /
-// float64 strip records and the per-surface table.  Kept apart from the
+// of closed oriented manifolds, the patch tree with its caps, greedy triangle
+// strips, the float32 / float64 strip records and the per-surface table.  Kept apart from the
 // upload so that validation runs (and is tested) without a GPU.
 #include <algorithm>
+#include <array>
+#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <new>
-#include <unordered_map>
 #include <vector>
 
 #include "surface_host.h"
@@ -15,20 +16,85 @@ namespace sal {
 
 namespace {
 
-inline uint64_t edge_key(uint32_t a, uint32_t b) { return ((uint64_t)a << 32) | b; }
-
 struct HostSurface {
     const float *xyz;
     int64_t nv, nt;
     std::vector<int32_t> tri;  // possibly reoriented copy
     int32_t label;
+    // Half-edge 3 t + c runs from corner c of triangle t to the next corner;
+    // twin[h] is the opposite half-edge.
+    std::vector<uint32_t> twin;
+
+    int32_t from(uint32_t h) const { return tri[h]; }
+    int32_t to(uint32_t h) const { return tri[h % 3 == 2 ? h - 2 : h + 1]; }
 };
 
-// One strip: the vertex sequence and, per triangle, its index in the surface.
+// One strip: the vertex sequence and, per triangle, its corners in the
+// outward order.
 struct Strip {
     std::vector<int32_t> verts;
-    std::vector<int32_t> tris;
+    std::vector<std::array<int32_t, 3>> tris;
 };
+
+// A directed edge used twice among the first n_tri triangles?
+bool repeated_edge(const HostSurface &s, int64_t n_tri) {
+    std::vector<uint64_t> e;
+    e.reserve((size_t)(3 * n_tri));
+    for (uint32_t h = 0; h < (uint32_t)(3 * n_tri); ++h)
+        e.push_back(((uint64_t)(uint32_t)s.from(h) << 32) | (uint32_t)s.to(h));
+    std::sort(e.begin(), e.end());
+    return std::adjacent_find(e.begin(), e.end()) != e.end();
+}
+
+enum class Pairing { ok, repeated, open };
+
+// Fills s.twin: the half-edges leaving each vertex, sorted by their other
+// end (a counting sort by vertex, then short sorts), hold each directed edge
+// once exactly when neighbours in a list differ.
+Pairing pair_half_edges(HostSurface &s) {
+    const uint32_t nh = (uint32_t)(3 * s.nt);
+    std::vector<uint32_t> start((size_t)s.nv + 1, 0);
+    for (uint32_t h = 0; h < nh; ++h) ++start[(size_t)s.from(h) + 1];
+    for (int64_t v = 0; v < s.nv; ++v) start[(size_t)v + 1] += start[(size_t)v];
+    struct Out {
+        int32_t to;
+        uint32_t h;
+    };
+    std::vector<Out> out((size_t)nh);
+    {
+        std::vector<uint32_t> at(start.begin(), start.end() - 1);
+        for (uint32_t h = 0; h < nh; ++h) out[at[(size_t)s.from(h)]++] = Out{s.to(h), h};
+    }
+    for (int64_t v = 0; v < s.nv; ++v) {
+        Out *b = out.data() + start[(size_t)v], *e = out.data() + start[(size_t)v + 1];
+        if (e - b <= 16) {
+            for (Out *i = b + 1; i < e; ++i) {
+                const Out x = *i;
+                Out *j = i;
+                for (; j > b && x.to < (j - 1)->to; --j) *j = *(j - 1);
+                *j = x;
+            }
+        } else {
+            std::sort(b, e, [](const Out &x, const Out &y) { return x.to < y.to; });
+        }
+        for (Out *i = b + 1; i < e; ++i)
+            if (i->to == (i - 1)->to) return Pairing::repeated;
+    }
+    s.twin.assign((size_t)nh, 0);
+    for (int64_t v = 0; v < s.nv; ++v)
+        for (uint32_t i = start[(size_t)v]; i < start[(size_t)v + 1]; ++i) {
+            const int32_t w = out[i].to;
+            const Out *b = out.data() + start[(size_t)w], *e = out.data() + start[(size_t)w + 1];
+            if (e - b > 16) {
+                b = std::lower_bound(b, e, (int32_t)v, [](const Out &x, int32_t t) { return x.to < t; });
+            } else {
+                while (b < e && b->to < v) ++b;
+            }
+            if (b == e || b->to != v) return Pairing::open;
+            s.twin[out[i].h] = b->h;
+        }
+    return Pairing::ok;
+}
 
 sal_status validate(HostSurface &s, int idx, bool auto_orient) {
     const std::string who = "surface " + std::to_string(idx) + ": ";
@@ -40,33 +106,30 @@ sal_status validate(HostSurface &s, int idx, bool auto_orient) {
     for (int64_t i = 0; i < 3 * s.nv; ++i)
         if (!std::isfinite(s.xyz[i]))
             return set_error(SAL_ERR_INVALID_ARG, who + "non-finite vertex coordinate");
-    std::unordered_map<uint64_t, int64_t> dir;
-    dir.reserve((size_t)(3 * s.nt * 2));
+    const std::string twice = who + "a directed edge is used twice";
     for (int64_t t = 0; t < s.nt; ++t) {
         const int32_t *f = &s.tri[3 * t];
-        for (int c = 0; c < 3; ++c)
-            if (f[c] < 0 || f[c] >= s.nv)
-                return set_error(SAL_ERR_INVALID_ARG, who + "vertex index out of range");
-        if (f[0] == f[1] || f[1] == f[2] || f[0] == f[2])
-            return set_error(SAL_ERR_INVALID_ARG, who + "triangle repeats a vertex");
-        const float *A = s.xyz + 3 * f[0], *B = s.xyz + 3 * f[1], *C = s.xyz + 3 * f[2];
-        const double e1[3] = {(double)B[0] - A[0], (double)B[1] - A[1], (double)B[2] - A[2]};
-        const double e2[3] = {(double)C[0] - A[0], (double)C[1] - A[1], (double)C[2] - A[2]};
-        const double n[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                             e1[0] * e2[1] - e1[1] * e2[0]};
-        if (n[0] == 0.0 && n[1] == 0.0 && n[2] == 0.0)
-            return set_error(SAL_ERR_INVALID_ARG, who + "zero-area triangle");
-        for (int c = 0; c < 3; ++c) {
-            const uint64_t k = edge_key((uint32_t)f[c], (uint32_t)f[(c + 1) % 3]);
-            if (!dir.emplace(k, t).second)
-                return set_error(SAL_ERR_NOT_CLOSED, who + "a directed edge is used twice");
+        const char *bad = nullptr;
+        for (int c = 0; c < 3 && !bad; ++c)
+            if (f[c] < 0 || f[c] >= s.nv) bad = "vertex index out of range";
+        if (!bad && (f[0] == f[1] || f[1] == f[2] || f[0] == f[2])) bad = "triangle repeats a vertex";
+        if (!bad) {
+            const float *A = s.xyz + 3 * f[0], *B = s.xyz + 3 * f[1], *C = s.xyz + 3 * f[2];
+            const double e1[3] = {(double)B[0] - A[0], (double)B[1] - A[1], (double)B[2] - A[2]};
+            const double e2[3] = {(double)C[0] - A[0], (double)C[1] - A[1], (double)C[2] - A[2]};
+            const double n[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
+                                 e1[0] * e2[1] - e1[1] * e2[0]};
+            if (n[0] == 0.0 && n[1] == 0.0 && n[2] == 0.0) bad = "zero-area triangle";
+        }
+        if (bad) {   // the first fault in triangle order is the one reported
+            if (repeated_edge(s, t)) return set_error(SAL_ERR_NOT_CLOSED, twice);
+            return set_error(SAL_ERR_INVALID_ARG, who + bad);
         }
     }
-    for (const auto &kv : dir) {
-        const uint32_t a = (uint32_t)(kv.first >> 32), b = (uint32_t)kv.first;
-        if (!dir.count(edge_key(b, a)))
-            return set_error(SAL_ERR_NOT_CLOSED, who + "boundary edge (surface is open)");
-    }
+    Pairing p = pair_half_edges(s);
+    if (p == Pairing::repeated) return set_error(SAL_ERR_NOT_CLOSED, twice);
+    if (p == Pairing::open)
+        return set_error(SAL_ERR_NOT_CLOSED, who + "boundary edge (surface is open)");
     // enclosed volume, about the vertex centroid for accuracy
     double c[3] = {0, 0, 0};
     for (int64_t i = 0; i < s.nv; ++i)
@@ -77,7 +140,7 @@ sal_status validate(HostSurface &s, int idx, bool auto_orient) {
         const int32_t *f = &s.tri[3 * t];
         double v[3][3];
         for (int r = 0; r < 3; ++r)
-            for (int d = 0; d < 3; ++d) v[r][d] = (double)s.xyz[3 * f[r] + d] - c[d];
+            for (int d = 0; d < 3; ++d) v[r][d] = (double)s.xyz[3 * (int64_t)f[r] + d] - c[d];
         vol += v[0][0] * (v[1][1] * v[2][2] - v[1][2] * v[2][1]) +
                v[0][1] * (v[1][2] * v[2][0] - v[1][0] * v[2][2]) +
                v[0][2] * (v[1][0] * v[2][1] - v[1][1] * v[2][0]);
@@ -88,86 +151,344 @@ sal_status validate(HostSurface &s, int idx, bool auto_orient) {
             return set_error(SAL_ERR_ORIENTATION,
                              who + "triangles are clockwise seen from outside (negative volume)");
         for (int64_t t = 0; t < s.nt; ++t) std::swap(s.tri[3 * t + 1], s.tri[3 * t + 2]);
+        (void)pair_half_edges(s);   // reversed edges pair as before
     }
     return SAL_OK;
 }
 
-// Greedy strips: from each unused seed triangle try the three rotations,
-// walk across the edge formed by the two newest vertices while the next
-// triangle is unused, and keep the longest walk.
-std::vector<Strip> make_strips(const HostSurface &s) {
-    const int64_t nt = s.nt;
-    std::unordered_map<uint64_t, int32_t> dir;
-    dir.reserve((size_t)(3 * nt * 2));
-    for (int64_t t = 0; t < nt; ++t)
-        for (int c = 0; c < 3; ++c)
-            dir[edge_key((uint32_t)s.tri[3 * t + c], (uint32_t)s.tri[3 * t + (c + 1) % 3])] =
-                (int32_t)t;
-    auto across = [&](int32_t cur, int32_t a, int32_t b) -> int32_t {
-        auto it = dir.find(edge_key((uint32_t)a, (uint32_t)b));
-        int32_t t1 = it == dir.end() ? -1 : it->second;
-        if (t1 != cur) return t1;
-        auto it2 = dir.find(edge_key((uint32_t)b, (uint32_t)a));
-        return it2 == dir.end() ? -1 : it2->second;
+// Builds one surface's patch tree, its strips and the caps' strips.
+class PatchBuilder {
+public:
+    explicit PatchBuilder(const HostSurface &s) : s_(s) {}
+
+    std::vector<Strip> strips;        // every leaf's strips, leaf by leaf
+    std::vector<Strip> caps;          // every cap's strips, patch by patch
+    std::vector<PatchEntry> entries;  // 4 per node; record ranges filled by place()
+
+    void build() {
+        const int64_t nt = s_.nt;
+        order_.resize((size_t)nt);
+        cen_.resize((size_t)(3 * nt));
+        for (int64_t t = 0; t < nt; ++t) {
+            order_[(size_t)t] = (int32_t)t;
+            for (int c = 0; c < 3; ++c) {
+                float sum = 0.0f;
+                for (int q = 0; q < 3; ++q) sum += s_.xyz[3 * (int64_t)s_.tri[(size_t)(3 * t + q)] + c] / 3.0f;
+                cen_[(size_t)(3 * t + c)] = sum;
+            }
+        }
+        pos_.assign((size_t)nt, 0);
+        used_.assign((size_t)nt, 0);
+        stamp_.assign((size_t)nt, -1);
+        first_out_.assign((size_t)s_.nv, -1);
+        on_path_.assign((size_t)s_.nv, -1);
+        new_node();
+        std::vector<uint32_t> none;
+        if (nt <= kLeafTri) leaf(0, 0, nt, &none);
+        else split(0, 0, nt, &none);
+    }
+
+    // The record ranges of the entries: strips in order from record 0, the
+    // caps from record n_rec.  A cap no shorter than its patch is not kept.
+    void place(uint32_t n_rec) {
+        std::vector<uint32_t> at((size_t)strips.size() + 1, 0), cap_at((size_t)caps.size() + 1, n_rec);
+        for (size_t i = 0; i < strips.size(); ++i) at[i + 1] = at[i] + 1 + (uint32_t)strips[i].tris.size();
+        for (size_t i = 0; i < caps.size(); ++i) cap_at[i + 1] = cap_at[i] + 1 + (uint32_t)caps[i].tris.size();
+        for (size_t e = 0; e < entries.size(); ++e) {
+            const Range &r = range_[e];
+            entries[e].leaf_begin = at[r.strip0];
+            entries[e].leaf_n = at[r.strip1] - at[r.strip0];
+            if (r.cap1 < r.cap0) {
+                entries[e].cap_begin = entries[e].leaf_begin;
+                entries[e].cap_n = entries[e].leaf_n;
+            } else {
+                entries[e].cap_begin = cap_at[r.cap0];
+                entries[e].cap_n = cap_at[r.cap1] - cap_at[r.cap0];
+            }
+        }
+    }
+
+private:
+    struct Range {
+        size_t strip0 = 0, strip1 = 0;
+        size_t cap0 = 0, cap1 = 0;   // cap1 < cap0: the patch itself
     };
-    auto third = [&](int32_t t, int32_t a, int32_t b) -> int32_t {
+    struct Box {
+        float lo[3], hi[3];
+    };
+
+    int32_t new_node() {
+        const int32_t w = (int32_t)(entries.size() / 4);
+        PatchEntry unused{};
         for (int c = 0; c < 3; ++c) {
-            const int32_t v = s.tri[3 * t + c];
+            unused.lo[c] = INFINITY;
+            unused.hi[c] = -INFINITY;
+        }
+        unused.child = -1;
+        entries.insert(entries.end(), 4, unused);
+        range_.insert(range_.end(), 4, Range{});
+        return w;
+    }
+
+    // Halves order_[b, e) at the median of the centroids' longest extent.
+    int64_t halve(int64_t b, int64_t e) {
+        float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+        for (int64_t i = b; i < e; ++i)
+            for (int c = 0; c < 3; ++c) {
+                const float x = cen_[3 * (size_t)order_[(size_t)i] + c];
+                lo[c] = std::min(lo[c], x);
+                hi[c] = std::max(hi[c], x);
+            }
+        int ax = 0;
+        for (int c = 1; c < 3; ++c)
+            if (hi[c] - lo[c] > hi[ax] - lo[ax]) ax = c;
+        const int64_t m = b + (e - b) / 2;
+        std::nth_element(order_.begin() + b, order_.begin() + m, order_.begin() + e,
+                         [&](int32_t p, int32_t q) {
+                             const float x = cen_[3 * (size_t)p + ax], y = cen_[3 * (size_t)q + ax];
+                             return x != y ? x < y : p < q;
+                         });
+        return m;
+    }
+
+    // Parts of order_[b, e) (more than a leaf): the entries of node w.  The
+    // patch's boundary half-edges go to *rim, its box is returned.
+    Box split(int32_t w, int64_t b, int64_t e, std::vector<uint32_t> *rim) {
+        int64_t cut[5] = {b, 0, 0, 0, 0};
+        int parts = 0;
+        const int64_t m = halve(b, e);
+        const int64_t half[2][2] = {{b, m}, {m, e}};
+        for (const auto &h : half) {
+            if (h[1] - h[0] > kLeafTri) cut[++parts] = halve(h[0], h[1]);
+            cut[++parts] = h[1];
+        }
+        std::vector<uint32_t> edges;
+        Box box = no_box();
+        for (int k = 0; k < parts; ++k) {
+            const size_t ent = 4 * (size_t)w + (size_t)k;
+            std::vector<uint32_t> part_rim;
+            Box pb;
+            if (cut[k + 1] - cut[k] <= kLeafTri) {
+                pb = leaf(ent, cut[k], cut[k + 1], &part_rim);
+            } else {
+                const int32_t child = new_node();
+                const size_t strip0 = strips.size();
+                pb = split(child, cut[k], cut[k + 1], &part_rim);
+                entries[ent].child = child;
+                range_[ent].strip0 = strip0;
+                range_[ent].strip1 = strips.size();
+                cap(ent, part_rim, cut[k + 1] - cut[k]);
+                set_box(ent, pb);
+            }
+            for (int c = 0; c < 3; ++c) {
+                box.lo[c] = std::min(box.lo[c], pb.lo[c]);
+                box.hi[c] = std::max(box.hi[c], pb.hi[c]);
+            }
+            edges.insert(edges.end(), part_rim.begin(), part_rim.end());
+        }
+        for (const uint32_t h : edges) {
+            const int64_t at = pos_[s_.twin[h] / 3];
+            // (a triangle not placed yet has position 0 and lies outside)
+            if (!placed(s_.twin[h] / 3) || at < b || at >= e) rim->push_back(h);
+        }
+        return box;
+    }
+
+    bool placed(uint32_t t) const { return used_[t] != 0; }
+
+    static Box no_box() {
+        return Box{{INFINITY, INFINITY, INFINITY}, {-INFINITY, -INFINITY, -INFINITY}};
+    }
+
+    Box leaf(size_t ent, int64_t b, int64_t e, std::vector<uint32_t> *rim) {
+        Box box = no_box();
+        std::sort(order_.begin() + b, order_.begin() + e);
+        for (int64_t i = b; i < e; ++i) {
+            const int32_t t = order_[(size_t)i];
+            pos_[(size_t)t] = (int32_t)i;
+            for (int q = 0; q < 3; ++q)
+                for (int c = 0; c < 3; ++c) {
+                    const float x = s_.xyz[3 * (int64_t)s_.tri[3 * (size_t)t + q] + c];
+                    box.lo[c] = std::min(box.lo[c], x);
+                    box.hi[c] = std::max(box.hi[c], x);
+                }
+        }
+        leaf_id_ = (int32_t)ent;
+        for (int64_t i = b; i < e; ++i) member_mark(order_[(size_t)i]);
+        range_[ent].strip0 = strips.size();
+        make_strips(b, e);
+        range_[ent].strip1 = strips.size();
+        for (int64_t i = b; i < e; ++i)
+            for (int c = 0; c < 3; ++c) {
+                const uint32_t h = 3 * (uint32_t)order_[(size_t)i] + (uint32_t)c;
+                if (!in_leaf((int32_t)(s_.twin[h] / 3))) rim->push_back(h);
+            }
+        cap(ent, *rim, e - b);
+        set_box(ent, box);
+        return box;
+    }
+
+    void set_box(size_t ent, const Box &box) {
+        double ext = 0.0;
+        for (int c = 0; c < 3; ++c) ext = std::max(ext, (double)box.hi[c] - box.lo[c]);
+        const double m = kCapMargin * ext;
+        for (int c = 0; c < 3; ++c) {
+            entries[ent].lo[c] = std::nextafterf((float)(box.lo[c] - m), -INFINITY);
+            entries[ent].hi[c] = std::nextafterf((float)(box.hi[c] + m), INFINITY);
+        }
+    }
+
+    // The leaf being built: its triangles carry its entry index.
+    void member_mark(int32_t t) {
+        if (member_.empty()) member_.assign((size_t)s_.nt, -1);
+        member_[(size_t)t] = leaf_id_;
+    }
+    bool in_leaf(int32_t t) const { return member_[(size_t)t] == leaf_id_; }
+
+    // The half-edge of triangle t between vertices a and b, in either direction.
+    uint32_t edge_of(int32_t t, int32_t a, int32_t b) const {
+        for (uint32_t c = 0; c < 3; ++c) {
+            const uint32_t h = 3 * (uint32_t)t + c;
+            const int32_t p = s_.from(h), q = s_.to(h);
+            if ((p == a && q == b) || (p == b && q == a)) return h;
+        }
+        return 3 * (uint32_t)t;
+    }
+    int32_t third(int32_t t, int32_t a, int32_t b) const {
+        for (int c = 0; c < 3; ++c) {
+            const int32_t v = s_.tri[3 * (size_t)t + c];
             if (v != a && v != b) return v;
         }
         return -1;
-    };
-    std::vector<uint8_t> used((size_t)nt, 0);
-    std::vector<int32_t> stamp((size_t)nt, -1);
-    std::vector<Strip> out;
-    int32_t attempt = 0;
-    for (int64_t seed = 0; seed < nt; ++seed) {
-        if (used[seed]) continue;
-        int best_rot = 0;
-        int64_t best_len = -1;
-        for (int rot = 0; rot < 3; ++rot) {
-            ++attempt;
-            int32_t y = s.tri[3 * seed + (rot + 1) % 3], z = s.tri[3 * seed + (rot + 2) % 3];
-            int32_t cur = (int32_t)seed;
-            stamp[cur] = attempt;
-            int64_t len = 1;
+    }
+
+    // Greedy strips over the leaf's triangles: from each unused seed triangle
+    // try the three rotations, walk across the edge formed by the two newest
+    // vertices while the next triangle is unused, and keep the longest walk.
+    void make_strips(int64_t b, int64_t e) {
+        for (int64_t i = b; i < e; ++i) {
+            const int32_t seed = order_[(size_t)i];
+            if (used_[(size_t)seed]) continue;
+            int best_rot = 0;
+            int64_t best_len = -1;
+            for (int rot = 0; rot < 3; ++rot) {
+                ++attempt_;
+                int32_t y = s_.tri[3 * (size_t)seed + (rot + 1) % 3], z = s_.tri[3 * (size_t)seed + (rot + 2) % 3];
+                int32_t cur = seed;
+                stamp_[(size_t)cur] = attempt_;
+                int64_t len = 1;
+                for (;;) {
+                    const int32_t nb = (int32_t)(s_.twin[edge_of(cur, y, z)] / 3);
+                    if (!in_leaf(nb) || used_[(size_t)nb] || stamp_[(size_t)nb] == attempt_) break;
+                    stamp_[(size_t)nb] = attempt_;
+                    const int32_t w = third(nb, y, z);
+                    y = z;
+                    z = w;
+                    cur = nb;
+                    ++len;
+                }
+                if (len > best_len) { best_len = len; best_rot = rot; }
+            }
+            Strip st;
+            int32_t y = s_.tri[3 * (size_t)seed + (best_rot + 1) % 3], z = s_.tri[3 * (size_t)seed + (best_rot + 2) % 3];
+            st.verts = {s_.tri[3 * (size_t)seed + best_rot], y, z};
+            st.tris.push_back(corners(seed));
+            used_[(size_t)seed] = 1;
+            int32_t cur = seed;
             for (;;) {
-                const int32_t nb = across(cur, y, z);
-                if (nb < 0 || used[nb] || stamp[nb] == attempt) break;
-                stamp[nb] = attempt;
+                const int32_t nb = (int32_t)(s_.twin[edge_of(cur, y, z)] / 3);
+                if (!in_leaf(nb) || used_[(size_t)nb]) break;
+                used_[(size_t)nb] = 1;
                 const int32_t w = third(nb, y, z);
+                st.verts.push_back(w);
+                st.tris.push_back(corners(nb));
                 y = z;
                 z = w;
                 cur = nb;
-                ++len;
             }
-            if (len > best_len) { best_len = len; best_rot = rot; }
+            strips.push_back(std::move(st));
         }
-        Strip st;
-        const int32_t x0 = s.tri[3 * seed + best_rot], y0 = s.tri[3 * seed + (best_rot + 1) % 3],
-                      z0 = s.tri[3 * seed + (best_rot + 2) % 3];
-        st.verts = {x0, y0, z0};
-        st.tris = {(int32_t)seed};
-        used[seed] = 1;
-        int32_t y = y0, z = z0, cur = (int32_t)seed;
-        for (;;) {
-            const int32_t nb = across(cur, y, z);
-            if (nb < 0 || used[nb]) break;
-            used[nb] = 1;
-            const int32_t w = third(nb, y, z);
-            st.verts.push_back(w);
-            st.tris.push_back(nb);
-            y = z;
-            z = w;
-            cur = nb;
-        }
-        out.push_back(std::move(st));
     }
-    return out;
-}
+    std::array<int32_t, 3> corners(int32_t t) const {
+        return {s_.tri[3 * (size_t)t], s_.tri[3 * (size_t)t + 1], s_.tri[3 * (size_t)t + 2]};
+    }
+
+    // The cap of a patch of n_tri triangles with boundary half-edges `rim`:
+    // the rim is cut into simple loops, each closed by a zigzag strip with the
+    // patch's own direction along the loop.
+    void cap(size_t ent, const std::vector<uint32_t> &rim, int64_t n_tri) {
+        range_[ent].cap0 = caps.size();
+        range_[ent].cap1 = caps.size();
+        if ((int64_t)rim.size() >= n_tri) {
+            range_[ent].cap0 = 1;   // no shorter than the patch
+            range_[ent].cap1 = 0;
+            return;
+        }
+        next_out_.assign(rim.size(), -1);
+        for (size_t i = 0; i < rim.size(); ++i) {
+            int32_t &head = first_out_[(size_t)s_.from(rim[i])];
+            next_out_[i] = head;
+            head = (int32_t)i;
+        }
+        std::vector<int32_t> path;
+        for (size_t i = 0; i < rim.size(); ++i) {
+            const int32_t v0 = s_.from(rim[i]);
+            if (first_out_[(size_t)v0] < 0) continue;
+            path.assign(1, v0);
+            on_path_[(size_t)v0] = 0;
+            for (;;) {
+                const int32_t v = path.back();
+                const int32_t e = first_out_[(size_t)v];
+                if (e < 0) break;   // only v0 can run out: every loop through it is closed
+                first_out_[(size_t)v] = next_out_[(size_t)e];
+                const int32_t w = s_.to(rim[(size_t)e]);
+                const int32_t k = on_path_[(size_t)w];
+                if (k < 0) {
+                    on_path_[(size_t)w] = (int32_t)path.size();
+                    path.push_back(w);
+                    continue;
+                }
+                zigzag(path.data() + k, (int64_t)path.size() - k);
+                while ((int32_t)path.size() > k + 1) {
+                    on_path_[(size_t)path.back()] = -1;
+                    path.pop_back();
+                }
+            }
+            for (const int32_t v : path) on_path_[(size_t)v] = -1;
+        }
+        range_[ent].cap1 = caps.size();
+    }
+
+    // Loop v_0 -> v_1 -> ... -> v_{L-1}: strip v_0, v_1, v_{L-1}, v_2, v_{L-2},
+    // ...; its even triangles are outward in strip order, its odd ones reversed.
+    void zigzag(const int32_t *v, int64_t L) {
+        if (L < 3) return;
+        Strip st;
+        int64_t i = 1, j = L - 1;
+        st.verts = {v[0], v[1]};
+        for (int64_t t = 0; t < L - 2; ++t) {
+            const int32_t z = (t & 1) == 0 ? v[j--] : v[++i];
+            const int32_t x = st.verts[(size_t)t], y = st.verts[(size_t)t + 1];
+            st.verts.push_back(z);
+            if ((t & 1) == 0) st.tris.push_back({x, y, z});
+            else st.tris.push_back({x, z, y});
+        }
+        caps.push_back(std::move(st));
+    }
+
+    const HostSurface &s_;
+    std::vector<int32_t> order_;      // triangles, patch by patch
+    std::vector<float> cen_;
+    std::vector<int32_t> pos_;        // position of a placed triangle in order_
+    std::vector<uint8_t> used_;       // triangles already in a strip
+    std::vector<int32_t> stamp_, member_;
+    std::vector<Range> range_;
+    std::vector<int32_t> first_out_, next_out_, on_path_;
+    int32_t attempt_ = 0, leaf_id_ = -1;
+};
 
 // +1 when (p, q, r) is a rotation of the triangle's stored order, else -1.
-double parity(const int32_t *f, int32_t p, int32_t q, int32_t r) {
+double parity(const std::array<int32_t, 3> &f, int32_t p, int32_t q, int32_t r) {
     for (int c = 0; c < 3; ++c)
         if (f[c] == p && f[(c + 1) % 3] == q && f[(c + 2) % 3] == r) return 1.0;
     return -1.0;
@@ -230,6 +551,53 @@ double dist2_point_triangle(const double p[3], const double a[3], const double b
     return dot(d, d);
 }
 
+// The records of one strip, appended to both streams.
+void append_strip(const float *V, const Strip &s, std::vector<Rec32> &r32, std::vector<Rec64> &r64) {
+    const int m = (int)s.tris.size();
+    Rec32 h32{};
+    Rec64 h64{};
+    for (int c = 0; c < 3; ++c) {
+        h32.v[c] = V[3 * (int64_t)s.verts[0] + c];
+        h32.v[3 + c] = V[3 * (int64_t)s.verts[1] + c];
+        h64.v[c] = h32.v[c];
+        h64.v[3 + c] = h32.v[3 + c];
+    }
+    int32_t mi = m;
+    std::memcpy(&h32.v[6], &mi, 4);
+    int64_t ml = m;
+    std::memcpy(&h64.v[6], &ml, 8);
+    r32.push_back(h32);
+    r64.push_back(h64);
+    for (int t = 0; t < m; ++t) {
+        const std::array<int32_t, 3> &f = s.tris[(size_t)t];
+        const float *A = V + 3 * (int64_t)f[0], *B = V + 3 * (int64_t)f[1], *C = V + 3 * (int64_t)f[2];
+        const double e1[3] = {(double)B[0] - A[0], (double)B[1] - A[1], (double)B[2] - A[2]};
+        const double e2[3] = {(double)C[0] - A[0], (double)C[1] - A[1], (double)C[2] - A[2]};
+        const double nn[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
+                              e1[0] * e2[1] - e1[1] * e2[0]};
+        const double nlen = std::sqrt(nn[0] * nn[0] + nn[1] * nn[1] + nn[2] * nn[2]);
+        const double nb = std::sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]) *
+                          std::sqrt(e2[0] * e2[0] + e2[1] * e2[1] + e2[2] * e2[2]);
+        const int64_t z = s.verts[(size_t)t + 2];
+        Rec32 q32{};
+        Rec64 q64{};
+        for (int c = 0; c < 3; ++c) {
+            q32.v[c] = V[3 * z + c];
+            q32.v[3 + c] = (float)(kNScale * nn[c]);
+            q64.v[c] = V[3 * z + c];
+            q64.v[3 + c] = nn[c];
+        }
+        q32.v[6] = (float)nlen;
+        q32.v[7] = std::max((float)(kKnSmall * nlen), FLT_MIN);   // > 0 marks a triangle
+        // the exact-sign guard's bound factor: 32 eps |B - A||C - A| (a
+        // power-of-two scaling, so exact), slightly enlarged
+        q64.v[6] = kGuardEps * (nb * (1.0 + 1e-12));
+        q64.v[7] = parity(f, s.verts[(size_t)t], s.verts[(size_t)t + 1], s.verts[(size_t)t + 2]);
+        r32.push_back(q32);
+        r64.push_back(q64);
+    }
+}
+
 }  // namespace
 
 
@@ -243,6 +611,8 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
     std::vector<int64_t> &strip_off = rec->strip_off;
     std::vector<int32_t> &strip_tris = rec->strip_tris;
     std::vector<SurfaceDev> &table = rec->table;
+    std::vector<PatchEntry> &entries = rec->entries;
+    entries.clear();
     r32.clear();
     r64.clear();
     strip_off.clear();
@@ -262,7 +632,8 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
         hs.tri.assign(desc[i].tri, desc[i].tri + 3 * hs.nt);
         sal_status st = validate(hs, i, (flags & SAL_SURF_AUTO_ORIENT) != 0);
         if (st != SAL_OK) return st;
-        const std::vector<Strip> strips = make_strips(hs);
+        PatchBuilder patches(hs);
+        patches.build();
         SurfaceDev &sd = table[(size_t)i];
         sd.rec_begin = (int64_t)r32.size();
         sd.strip_begin = (int64_t)strip_off.size();
@@ -304,77 +675,17 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
             sd.pad2 = 0;
         }
         total_tri += hs.nt;
-        const float *V = hs.xyz;
-        for (const Strip &s : strips) {
+        for (const Strip &strip : patches.strips) {
             strip_off.push_back((int64_t)r32.size());
-            const int m = (int)s.tris.size();
-            strip_tris.push_back(m);
-            Rec32 h32{};
-            Rec64 h64{};
-            for (int c = 0; c < 3; ++c) {
-                h32.v[c] = V[3 * s.verts[0] + c];
-                h32.v[3 + c] = V[3 * s.verts[1] + c];
-                h64.v[c] = V[3 * s.verts[0] + c];
-                h64.v[3 + c] = V[3 * s.verts[1] + c];
-            }
-            int32_t mi = m;
-            std::memcpy(&h32.v[6], &mi, 4);
-            int64_t ml = m;
-            std::memcpy(&h64.v[6], &ml, 8);
-            r32.push_back(h32);
-            r64.push_back(h64);
-            for (int t = 0; t < m; ++t) {
-                const int32_t *f = &hs.tri[3 * (size_t)s.tris[t]];
-                const float *A = V + 3 * f[0], *B = V + 3 * f[1], *C = V + 3 * f[2];
-                const double e1[3] = {(double)B[0] - A[0], (double)B[1] - A[1], (double)B[2] - A[2]};
-                const double e2[3] = {(double)C[0] - A[0], (double)C[1] - A[1], (double)C[2] - A[2]};
-                const double nn[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                                      e1[0] * e2[1] - e1[1] * e2[0]};
-                const double nlen = std::sqrt(nn[0] * nn[0] + nn[1] * nn[1] + nn[2] * nn[2]);
-                const double nb = std::sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]) *
-                                  std::sqrt(e2[0] * e2[0] + e2[1] * e2[1] + e2[2] * e2[2]);
-                const int32_t z = s.verts[t + 2];
-                Rec32 q32{};
-                Rec64 q64{};
-                for (int c = 0; c < 3; ++c) {
-                    q32.v[c] = V[3 * z + c];
-                    q32.v[3 + c] = (float)(kNScale * nn[c]);
-                    q64.v[c] = V[3 * z + c];
-                    q64.v[3 + c] = nn[c];
-                }
-                q32.v[6] = (float)nlen;
-                q32.v[7] = (float)(kKnSmall * nlen);
-                // the exact-sign guard's bound factor: 32 eps |B - A||C - A| (a
-                // power-of-two scaling, so exact), slightly enlarged
-                q64.v[6] = kGuardEps * (nb * (1.0 + 1e-12));
-                q64.v[7] = parity(f, s.verts[t], s.verts[t + 1], s.verts[t + 2]);
-                r32.push_back(q32);
-                r64.push_back(q64);
-            }
+            strip_tris.push_back((int32_t)strip.tris.size());
+            append_strip(hs.xyz, strip, r32, r64);
         }
         sd.rec_end = (int64_t)r32.size();
         sd.strip_end = (int64_t)strip_off.size();
-    }
-
-    // Extra table entries for the launch-shape tuner: the leading whole
-    // strips of the record stream up to about kTuneTri[i] triangles, so that
-    // a trial launch costs a bounded number of pairs on any mesh.
-    for (int i = 0; i < kTuneEntries; ++i) {
-        SurfaceDev t{};
-        int64_t s = 0, tris = 0;
-        while (s < (int64_t)strip_off.size() && tris < kTuneTri[i]) tris += strip_tris[(size_t)s++];
-        t.rec_begin = 0;
-        t.rec_end = s < (int64_t)strip_off.size() ? strip_off[(size_t)s] : (int64_t)r32.size();
-        t.strip_begin = 0;
-        t.strip_end = s;
-        t.n_tri = tris;
-        t.label = 1;
-        for (int c = 0; c < 3; ++c) {
-            t.lo[c] = -INFINITY;
-            t.hi[c] = INFINITY;
-        }
-        t.ball_w = -1;
-        table.push_back(t);
+        patches.place((uint32_t)(sd.rec_end - sd.rec_begin));
+        for (const Strip &strip : patches.caps) append_strip(hs.xyz, strip, r32, r64);
+        sd.node_begin = (int64_t)(entries.size() / 4);
+        entries.insert(entries.end(), patches.entries.begin(), patches.entries.end());
     }
     return SAL_OK;
 }
@@ -394,6 +705,7 @@ extern "C" sal_status sal_surface_set_check(const sal_surface_desc *surfaces, in
             info->device_bytes = (int64_t)(rec.r32.size() * sizeof(sal::Rec32) +
                                            rec.r64.size() * sizeof(sal::Rec64) +
                                            rec.table.size() * sizeof(sal::SurfaceDev) +
+                                           rec.entries.size() * sizeof(sal::PatchEntry) +
                                            rec.strip_off.size() * sizeof(int64_t));
         }
         return SAL_OK;

@@ -8,15 +8,16 @@
 
 namespace sal {
 
-// Everything a surface set uploads: strip records in both precisions, the
-// record index and triangle count of every strip, and the per-surface table
-// (n entries, then the tuner's two entries).
+// Everything a surface set uploads: strip records in both precisions (each
+// surface's triangles, then its caps), the patch tree, the record index and
+// triangle count of every strip of triangles, and the per-surface table.
 struct SurfaceRecords {
     std::vector<Rec32> r32;
     std::vector<Rec64> r64;
     std::vector<int64_t> strip_off;
     std::vector<int32_t> strip_tris;
     std::vector<SurfaceDev> table;
+    std::vector<PatchEntry> entries;   // four per node
     int64_t total_tri = 0;
 };
 

@@ -1,0 +1,127 @@
+"""The patch tree on surfaces that are not star-shaped or smooth (a torus, two
+separate balls, a box of coplanar triangles, the smallest mesh), on both sides
+of the point count where the 64-point form takes over, and on points too far
+apart for a common walk: labels and winding numbers against the oracle, and
+against one another's form."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+import paper_2203_10000_amd as sal  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+POINT_FORM_MAX = 65536
+TOL = {"fp32": 1e-5, "fp64": 1e-12}   # the forms' stated bounds on winding numbers
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return sal.Context(0)
+
+
+def _torus(n, m, big, small):
+    a, b = np.meshgrid(2 * np.pi * np.arange(n) / n, 2 * np.pi * np.arange(m) / m, indexing="ij")
+    r = big + small * np.cos(b)
+    v = np.stack([r * np.cos(a), r * np.sin(a), small * np.sin(b)], -1).reshape(-1, 3)
+    i, j = (x.reshape(-1) for x in np.meshgrid(np.arange(n), np.arange(m), indexing="ij"))
+    p = lambda x, y: (x % n) * m + y % m  # noqa: E731
+    f = np.concatenate([np.stack([p(i, j), p(i + 1, j), p(i + 1, j + 1)], 1),
+                        np.stack([p(i, j), p(i + 1, j + 1), p(i, j + 1)], 1)])
+    return v, f
+
+
+def _box(n, half):
+    ids, v, f = {}, [], []
+
+    def vid(p):
+        if p not in ids:
+            ids[p] = len(v)
+            v.append([half * (2.0 * c / n - 1.0) for c in p])
+        return ids[p]
+
+    for ax in range(3):
+        for side in (0, n):
+            for i in range(n):
+                for j in range(n):
+                    q = []
+                    for a, b in ((i, j), (i + 1, j), (i + 1, j + 1), (i, j + 1)):
+                        p = [0, 0, 0]
+                        p[ax], p[(ax + 1) % 3], p[(ax + 2) % 3] = side, a, b
+                        q.append(vid(tuple(p)))
+                    t = [(q[0], q[1], q[2]), (q[0], q[2], q[3])]
+                    f += t if side else [(a, c, b) for a, b, c in t]
+    return np.array(v), np.array(f)
+
+
+def _two_balls():
+    v, f = synth.icosphere(2)
+    return np.concatenate([v * 20 + (30, 0, 0), v * 25 - (35, 5, 0)]), np.concatenate([f, f + len(v)])
+
+
+class _Surf:
+    def __init__(self, v, f, label):
+        self.v, self.f, self.label = v.astype(np.float32), f.astype(np.int32), label
+
+
+SHAPES = {"torus": lambda: _torus(48, 24, 50.0, 16.0), "two balls": _two_balls,
+          "box": lambda: _box(9, 45.0), "icosahedron": lambda: tuple(x * (60.0 if k == 0 else 1) for k, x in
+                                                                     enumerate(synth.icosphere(0)))}
+
+
+def _points(surf, n, seed):
+    rng = np.random.default_rng(seed)
+    v, f = surf.v.astype(np.float64), surf.f
+    t = f[rng.integers(0, len(f), n // 4)]
+    w = rng.dirichlet((1.0, 1.0, 1.0), n // 4)
+    near = (w[:, :, None] * v[t]).sum(1) + rng.normal(0.0, 0.3, (n // 4, 3))
+    free = rng.uniform(-80.0, 80.0, (n - n // 4, 3))
+    return np.concatenate([near, free]).T.astype(np.float32).copy()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+def test_both_forms_match_the_oracle(ctx, shape, precision):
+    surf = _Surf(*SHAPES[shape](), label=3)
+    ss = sal.SurfaceSet(ctx, [surf])
+    pts = _points(surf, POINT_FORM_MAX + 1, 17)
+    # a vertex, an edge midpoint, points far outside and without a place
+    pts[:, 5] = surf.v[0]
+    pts[:, 6:9] = [[np.nan, 3e30, 0.0], [0.0, 0.0, np.inf], [0.0, 0.0, 0.0]]
+    fin = np.isfinite(pts).all(0)
+    want, w_ref = oracle.label(np.where(fin, pts, 0).astype(np.float32), [surf], want_w=True)
+    want = np.where(fin, want, -1)
+    for n in (POINT_FORM_MAX + 1, POINT_FORM_MAX):
+        d = torch.from_numpy(pts[:, :n].copy()).cuda()
+        lab, w, _ = sal.label_points(ctx, ss, d, precision=precision, winding="f64")
+        w = w.cpu().numpy()
+        assert np.array_equal(lab.cpu().numpy(), want[:n]), n
+        assert np.abs(w - w_ref[:, :n])[:, fin[:n]].max() < TOL[precision], n
+        assert np.isnan(w[:, ~fin[:n]]).all()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_points_too_far_apart_for_a_common_walk(ctx, precision):
+    """An instance just above the size of the single-point form: 64 neighbours
+    of its points span boxes that hundreds of the surface's leaves enter."""
+    v, f = synth.icosphere(6)
+    surf = _Surf(v * 70.0, f, 2)
+    ss = sal.SurfaceSet(ctx, [surf])
+    rng = np.random.default_rng(4)
+    outs = []
+    for n in (8192, 8193):
+        pts = rng.uniform(-80.0, 80.0, (3, n)).astype(np.float32)
+        lab = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        outs.append((pts, lab))
+    inst = [(ss, torch.from_numpy(p).cuda(), lab) for p, lab in outs]
+    sal.label_batch(ctx, inst, precision=precision)
+    for (p, lab), (_, d, _) in zip(outs, inst):
+        one, _, _ = sal.label_points(ctx, ss, d, precision=precision)   # single-point form
+        assert torch.equal(lab, one)
+        idx = rng.integers(0, p.shape[1], 400)
+        assert np.array_equal(lab.cpu().numpy()[idx], oracle.label(p[:, idx].copy(), [surf]))
