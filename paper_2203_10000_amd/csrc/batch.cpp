@@ -9,11 +9,6 @@
 namespace sal {
 namespace {
 
-// Instances up to this size are labeled one point per wavefront.  64 neighbours
-// of fewer points are so far apart that a common walk saves nothing, and a
-// small instance's few wavefronts would be the launch's tail.
-constexpr int64_t kBatchPointMax = 8192;
-
 constexpr int kBlockWaves = 4;
 
 template <typename T>
@@ -78,7 +73,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
         for (const bool small : {false, true}) {
             for (int i = 0; i < n_inst; ++i) {
                 const sal_instance &in = inst[i];
-                if ((in.n_points <= kBatchPointMax) != small) continue;
+                if ((in.n_points <= kPointFormMax) != small) continue;
                 for (int64_t at = 0; at < in.n_points; at += kChunkPoints) {
                     const int64_t m = std::min(in.n_points - at, kChunkPoints);
                     LabelInst q = make_inst(in.surfaces, m, in.x + at, in.y + at, in.z + at, in.labels + at,

@@ -7,33 +7,27 @@
 // PatchEntry), so a point needs about 8 sqrt(T) terms instead of T.  And the
 // winding number is constant where the surface does not pass: a wavefront whose
 // 64 points lie in a box that meets no triangle needs it at one of them.
-//   k_label_wave   64 neighbouring points (order.hip) per wavefront: surfaces
-//                  that do not enter the points' box are summed for one point,
-//                  a lane per term; the others lane by lane, every lane its own
-//                  point, over the same strips with scalar record loads.
+//   k_label_wave   64 neighbouring points (order.hip) per wavefront: the
+//                  surface is summed at one point of their box, a lane per
+//                  term, and the others differ from it by the signed number of
+//                  near triangles that the segment between them crosses.
 //   k_label_point  one point per wavefront, a lane per term: few points.
 //   k_recheck      the same for flagged (point, surface) pairs.
 // No MFMA: a term has K = 3 products, square roots and a sign-sensitive sum.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "patch.h"
 #include "sal_internal.h"
-#include "strip_f32.h"
-#include "strip_f64.h"
+#include "wave.h"
 
 namespace sal {
 namespace {
 
-using namespace f32;
 using patch::Lists;
 using patch::Mode;
 using patch::PointSum;
-
-// A walk evaluates every listed record for all 64 points.  64 single-point sums
-// cost about 64 x 8 sqrt(T) / 64 lane steps, each some three walk steps: above
-// this many records (well past 24 sqrt(T) of 300,000 triangles) the points are
-// too far apart for a common walk and are summed one by one.
-constexpr int kWalkRecs = 16384;
 
 // Instance of wavefront g, by its place in the grid.
 __device__ __forceinline__ int find_group(const LabelInst *insts, int n_inst, int64_t g) {
@@ -44,10 +38,6 @@ __device__ __forceinline__ int find_group(const LabelInst *insts, int n_inst, in
         else hi = mid - 1;
     }
     return lo;
-}
-
-__device__ __forceinline__ float readlane_f(float v, int src) {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), src));
 }
 
 // A closed surface's winding number is a whole number at every point off it:
@@ -82,18 +72,18 @@ __device__ __forceinline__ PointSum point_surface(const LabelInst &in, const Sur
     if (x < sd.lo[0] || x > sd.hi[0] || y < sd.lo[1] || y > sd.hi[1] || z < sd.lo[2] || z > sd.hi[2])
         return PointSum{0.0, false, false, 0u, 0u};
     const float p[3] = {x, y, z};
-    int n_near, n_far, nr, fr;
-    if (!patch::sort_patches(in.ent + 4 * sd.node_begin, p, p, L, n_near, n_far, nr, fr)) {
+    int n_near, n_far;
+    if (!patch::sort_patches(in.ent + 4 * sd.node_begin, p, p, L, n_near, n_far)) {
         // (a list is full only where hundreds of patches share the point)
         n_near = 1;
         n_far = 0;
-        patch::wave_sync();
+        wave_sync();
         if (lane_id() == 0) L.near[0] = make_uint2(0u, (uint32_t)(sd.rec_end - sd.rec_begin));
-        patch::wave_sync();
+        wave_sync();
     }
     const PointSum s = patch::point_sum<MODE>(in.rec32 + sd.rec_begin, in.rec64 + sd.rec_begin, L, n_near,
                                               n_far, x, y, z, kap);
-    patch::wave_sync();   // the lists are free again
+    wave_sync();   // the lists are free again
     return s;
 }
 
@@ -203,10 +193,11 @@ __global__ __launch_bounds__(512) void k_label_point(LabelArgs a) {
 }
 
 // ------------------------------------------------------------- 64 per wavefront
-// What bounds it: the lane-by-lane walks of surfaces that enter a wavefront's
-// box are bound by vector issue (29 instructions per term, as the strip walk);
-// the single-point sums and the tree by load latency, hidden by the other
-// wavefronts.
+// What bounds it: load latency in the sum at the box's point (a few dozen
+// dependent rounds) and in the tree; the crossings are some 45 instructions a
+// triangle that meets the box.  A lane-by-lane walk over the same patches instead
+// of the crossings took 5.4 of 8.0 ms for 6M lattice points x 81,920 triangles
+// (1400 terms a point); with the crossings the whole kernel takes 3.4.
 template <bool F64>
 __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
     extern __shared__ __align__(16) unsigned char shared[];
@@ -235,18 +226,33 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
             lo[c] = fminf(lo[c], __shfl_xor(lo[c], d));
             hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], d));
         }
-        lo[c] = readlane_f(lo[c], 0);
-        hi[c] = readlane_f(hi[c], 0);
+        lo[c] = readlane_v(lo[c], 0);
+        hi[c] = readlane_v(hi[c], 0);
     }
-    const float kap = a.kappa, branch_cut = kPiF - 0.25f * kap;
     uint64_t enc = 0, flg = 0;
     int32_t lab = 0;
     Tally t;
-    unsigned n_exact = 0;   // walks: this lane's
+    // the sums' point q: inside the box, off its planes of symmetry so that
+    // segments to lattice points seldom pass through edges of a regular mesh
+    typedef typename std::conditional<F64, double, float>::type T;
+    float q[3];
+    T d[3], D;
+    auto place = [&](const float (&f)[3]) {
+        T d2 = 0;
+        for (int c = 0; c < 3; ++c) {
+            q[c] = fminf(fmaxf(fmaf(hi[c] - lo[c], f[c], lo[c]), lo[c]), hi[c]);
+            const T r = fmax((T)hi[c] - (T)q[c], (T)q[c] - (T)lo[c]);
+            d2 += r * r;
+        }
+        d[0] = (T)px - (T)q[0];
+        d[1] = (T)py - (T)q[1];
+        d[2] = (T)pz - (T)q[2];
+        D = sqrt(d2) * (T)1.00001;
+    };
     for (int k = 0; k < in.n_surf; ++k) {
         const SurfaceDev &sd = in.surf[k];
         double w = 0.0;
-        bool cond = false, on = false, apart = false;
+        bool cond = false, apart = false;
         bool outside = good_mask == 0 || lo[0] > sd.hi[0] || hi[0] < sd.lo[0] || lo[1] > sd.hi[1] ||
                        hi[1] < sd.lo[1] || lo[2] > sd.hi[2] || hi[2] < sd.lo[2];
         if (a.cull && good_mask) {
@@ -263,52 +269,40 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
         if (!outside) {
             const Rec32 *rec32 = in.rec32 + sd.rec_begin;
             const Rec64 *rec64 = in.rec64 + sd.rec_begin;
-            int n_near, n_far, near_recs = 0, far_recs = 0;
-            const bool fits = patch::sort_patches(in.ent + 4 * sd.node_begin, lo, hi, L, n_near, n_far,
-                                                  near_recs, far_recs);
-            bool done = false;
-            if (fits && (n_near == 0 || !patch::near_triangle_meets(rec32, L, n_near, lo, hi))) {
-                // the surface does not enter the box: one winding number
-                const int l0 = __builtin_ctzll(good_mask);
-                const PointSum s = patch::point_sum<F64 ? patch::kDouble : patch::kFloat>(
-                    rec32, rec64, L, n_near, n_far, readlane_f(px, l0), readlane_f(py, l0), readlane_f(pz, l0),
-                    kap);
-                const double v = s.half * kInv2Pi, r = rint(v);
-                done = !s.uncertain && !s.on && fabs(v - r) < 1e-3;
-                w = r;
-                t.exact += s.exact;
-            }
-            if (!done && fits && near_recs + far_recs <= kWalkRecs) {
-                double S = 0.0;
-                uint64_t cmask = 0;
-                int hit = 0;
-                for (int i = 0; i < n_near + n_far; ++i) {
-                    const uint2 q = i < n_near ? L.near[i] : L.far[i - n_near];
-                    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.x);
-                    const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.y);
-                    if (F64)
-                        S += f64::surface_sum((const CRec64 *)rec64, b, (int64_t)b + m, px, py, pz, px, py, pz,
-                                              hit, n_exact);
-                    else
-                        strips_sum((const CRec32 *)rec32, b, (int64_t)b + m, px, py, pz, good_mask, kap,
-                                   branch_cut, S, cmask);
+            int n_near, n_far;
+            bool known = false;
+            if (patch::sort_patches(in.ent + 4 * sd.node_begin, lo, hi, L, n_near, n_far)) {
+                // q's own sum; where float32 does not certify it, another point's
+                const float at[3][3] = {{0.4871f, 0.5237f, 0.5113f}, {0.3137f, 0.6719f, 0.4481f},
+                                        {0.6863f, 0.3571f, 0.6229f}};
+                for (int i = 0; i < 3 && !known; ++i) {
+                    place(at[i]);
+                    const PointSum s = patch::point_sum<F64 ? patch::kDouble : patch::kFloat>(
+                        rec32, rec64, L, n_near, n_far, q[0], q[1], q[2], a.kappa);
+                    const double v = s.half * kInv2Pi;
+                    w = rint(v);
+                    known = !s.uncertain && !s.on && fabs(v - w) < 1e-3;
+                    t.exact += s.exact;
                 }
-                on = hit != 0;
-                cond = (cmask >> lane) & 1ull;
-                w = S * kInv2Pi;
-                if (!on && !cond) w = whole(w);
-            } else if (!done) {
+            }
+            if (known) {
+                int delta = 0;
+                bool uncertain = false;
+                patch::near_crossings<T>(rec32, rec64, L, n_near, lo, hi, q, d, D, delta, uncertain);
+                w += (double)delta;
+                cond = uncertain;
+            } else {
                 apart = true;   // left to k_recheck
             }
-            patch::wave_sync();   // the lists are free again
+            wave_sync();   // the lists are free again
         }
-        const bool inside = on || w >= a.threshold;
-        if (apart) flg |= 1ull << k;
+        const bool inside = w >= a.threshold;
+        if (apart || cond) flg |= 1ull << k;
         if (!F64 && !apart) {
             const bool band = fabs(w - a.threshold) < a.band;
             t.band += __popcll(ballot(band) & good_mask);
             t.cond += __popcll(ballot(cond) & good_mask);
-            if (band || cond) flg |= 1ull << k;
+            if (band) flg |= 1ull << k;
         }
         if (inside) { enc |= 1ull << k; lab = sd.label; }
         if (valid) store_winding(in, a.winding_type, k, idx, good ? w : __builtin_nan(""));
@@ -317,14 +311,13 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
         in.labels[idx] = good ? lab : -1;
         if (in.masks) in.masks[idx] = good ? enc : 0ull;
     }
-    if (good) t.exact += n_exact;
     const bool want = good && flg != 0;
     const uint64_t m = ballot(want);
     if (m) {
         const int leader = __builtin_ctzll(m);
         int64_t base = 0;
         if (lane == leader) base = (int64_t)atomicAdd(a.list_n, (unsigned long long)__popcll(m));
-        base = bcast_i64(base, leader);
+        base = readlane_v(base, leader);
         if (want) {
             FlagEntry e;
             e.idx = (uint32_t)idx;

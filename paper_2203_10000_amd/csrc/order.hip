@@ -15,16 +15,12 @@
 #include <hip/hip_runtime.h>
 
 #include "sal_internal.h"
-#include "strip_f32.h"
+#include "wave.h"
 
 namespace sal {
 namespace {
 
 constexpr int kThreads = 256, kWaves = kThreads / 64;
-
-using f32::ballot;
-using f32::lane_id;
-using f32::lanes_below;
 
 __device__ __forceinline__ int find_tile(const LabelInst *insts, int n_inst, int64_t t) {
     int lo = 0, hi = n_inst - 1;
@@ -173,8 +169,7 @@ __global__ __launch_bounds__(kThreads) void k_order_scatter(LabelArgs a) {
             same &= ((d >> q) & 1u) ? m : ~m;
         }
         const uint32_t at = cnt[wave][d] + (uint32_t)lanes_below(same);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         if (have) {
             if (lanes_below(same) == 0) cnt[wave][d] = at + (uint32_t)__popcll(same);
             if (PASS == 1) {
@@ -184,8 +179,7 @@ __global__ __launch_bounds__(kThreads) void k_order_scatter(LabelArgs a) {
                 a.ord.perm[in.order_base + at] = a.ord.idx1[in.order_base + i];
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
 }
 

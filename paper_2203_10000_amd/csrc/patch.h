@@ -6,14 +6,10 @@
 
 #include "mixed_term.h"
 #include "sal_internal.h"
-#include "strip_f32.h"
+#include "wave.h"
 
 namespace sal {
 namespace patch {
-
-using f32::ballot;
-using f32::lane_id;
-using f32::lanes_below;
 
 constexpr int kNearCap = 96;    // near leaves of one box (96 x ~45 triangles)
 constexpr int kFarCap = 384;    // far patches: 3 siblings per level and near node
@@ -27,24 +23,16 @@ struct Lists {
     uint32_t front[2][kFrontCap];
 };
 
-// Orders LDS accesses between the lanes of one wavefront.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Sorts the surface's patches by the box [lo, hi] (the same in every lane):
 // patches whose box it misses go to the far list as their caps, leaves it
 // meets to the near list.  Sixteen nodes are opened at a time, one lane per
 // entry.  False when a list is full.
 __device__ __forceinline__ bool sort_patches(const PatchEntry *__restrict__ ent, const float (&lo)[3],
-                                             const float (&hi)[3], Lists &L, int &n_near, int &n_far,
-                                             int &near_recs, int &far_recs) {
+                                             const float (&hi)[3], Lists &L, int &n_near, int &n_far) {
     const int lane = lane_id();
     int nf = 1, side = 0;
     n_near = 0;
     n_far = 0;
-    int nr = 0, fr = 0;   // per-lane counts
     if (lane == 0) L.front[0][0] = 0u;
     wave_sync();
     while (nf > 0) {
@@ -67,14 +55,8 @@ __device__ __forceinline__ bool sort_patches(const PatchEntry *__restrict__ ent,
             if (n_far + __popcll(mf) > kFarCap || n_near + __popcll(mn) > kNearCap ||
                 nf2 + __popcll(mo) > kFrontCap)
                 return false;
-            if (to_far) {
-                L.far[n_far + lanes_below(mf)] = make_uint2(e0.w, e1.w);
-                fr += (int)e1.w;
-            }
-            if (to_near) {
-                L.near[n_near + lanes_below(mn)] = make_uint2(e2.y, e2.z);
-                nr += (int)e2.z;
-            }
+            if (to_far) L.far[n_far + lanes_below(mf)] = make_uint2(e0.w, e1.w);
+            if (to_near) L.near[n_near + lanes_below(mn)] = make_uint2(e2.y, e2.z);
             if (open) L.front[side ^ 1][nf2 + lanes_below(mo)] = e2.x;
             n_far += __popcll(mf);
             n_near += __popcll(mn);
@@ -84,13 +66,6 @@ __device__ __forceinline__ bool sort_patches(const PatchEntry *__restrict__ ent,
         nf = nf2;
         side ^= 1;
     }
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        nr += __shfl_xor(nr, d);
-        fr += __shfl_xor(fr, d);
-    }
-    near_recs = __builtin_amdgcn_readfirstlane(nr);
-    far_recs = __builtin_amdgcn_readfirstlane(fr);
     return true;
 }
 
@@ -124,41 +99,6 @@ __device__ __forceinline__ bool load_tri(const Rec32 *__restrict__ rec, uint32_t
     return true;
 }
 
-// Whether any triangle of the near list may meet the box [lo, hi]: its own
-// box does (exact comparisons) and its plane passes within the box's radius
-// (with a margin some thirty times the rounding of the products).  "No" is a
-// proof that the surface does not enter the box.
-__device__ __forceinline__ bool near_triangle_meets(const Rec32 *__restrict__ rec, const Lists &L, int n_near,
-                                                    const float (&lo)[3], const float (&hi)[3]) {
-    const int lane = lane_id();
-    float c[3], h[3];
-    for (int k = 0; k < 3; ++k) {
-        c[k] = 0.5f * lo[k] + 0.5f * hi[k];
-        h[k] = 0.5f * hi[k] - 0.5f * lo[k];
-    }
-    const float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + h[0] + h[1] + h[2];
-    for (int i = 0; i < n_near; ++i) {
-        const uint2 g = L.near[i];
-        for (uint32_t o = 0; o < g.y; o += 64) {
-            bool meets = false;
-            Tri t;
-            if (o + lane < g.y && load_tri(rec, g.x, g.x + o + lane, t)) {
-                meets = true;
-                for (int k = 0; k < 3; ++k)
-                    meets = meets && fminf(fminf(t.X[k], t.Y[k]), t.Z[k]) <= hi[k] &&
-                            fmaxf(fmaxf(t.X[k], t.Y[k]), t.Z[k]) >= lo[k];
-                const float s = fmaf(c[0] - t.Z[0], t.n[0], fmaf(c[1] - t.Z[1], t.n[1], (c[2] - t.Z[2]) * t.n[2]));
-                const float reach = fmaf(h[0], fabsf(t.n[0]), fmaf(h[1], fabsf(t.n[1]), h[2] * fabsf(t.n[2])));
-                const float size = scale + fabsf(t.Z[0]) + fabsf(t.Z[1]) + fabsf(t.Z[2]);
-                const float margin = 4e-6f * size * (fabsf(t.n[0]) + fabsf(t.n[1]) + fabsf(t.n[2]));
-                if (fabsf(s) > reach + margin) meets = false;
-            }
-            if (ballot(meets) != 0) return true;
-        }
-    }
-    return false;
-}
-
 struct PointSum {
     double half;       // sum of atan2(N, D): half the solid angle
     bool on;           // the point lies on a triangle
@@ -182,7 +122,7 @@ __device__ __forceinline__ PointSum point_sum(const Rec32 *__restrict__ rec32, c
                                               const Lists &L, int n_near, int n_far, float px, float py,
                                               float pz, float kap) {
     const int lane = lane_id(), sub = lane & 7;
-    const float branch_cut = f32::kPiF - 0.25f * kap;
+    const float branch_cut = mixed::kPiF - 0.25f * kap;
     const int items = n_near + n_far;
     const uint64_t leaders = 0x0101010101010101ull;
     PointSum out{0.0, false, false, 0u, 0u};
@@ -265,6 +205,159 @@ __device__ __forceinline__ PointSum point_sum(const Rec32 *__restrict__ rec32, c
     out.on = ballot(on != 0) != 0;
     out.uncertain = ballot(out.uncertain) != 0;
     return out;
+}
+
+// ----------------------------------------------------------------- crossings
+// Winding numbers of 64 points p in a box from that of one point q in it: the
+// segment q p stays in the box, and only triangles that meet the box can cross
+// it.  A triangle is crossed when p and q lie on different sides of its plane and
+// the line passes it on one side of all three edges.  The signs come from
+// products relative to q, with bounds on their rounding (u the unit roundoff, L
+// the largest distance of a vertex from q, D that of a point): edge products
+// err by less than 12 u L^2 D, plane products by less than 10 u |n| (D + L) plus
+// the double rounding of n; twice that is taken.  A lane whose sign is within a
+// bound, and not settled by the others, is uncertain.
+template <typename T>
+struct Bounds;
+template <>
+struct Bounds<float> {
+    static constexpr float edge = 24.0f * 5.9604645e-8f, plane = 20.0f * 5.9604645e-8f;
+    static constexpr float normal = 1.5e-13f;   // 32 (scaled normals) x 4.7e-15, per L^2
+    static constexpr float huge = 1e37f;
+};
+template <>
+struct Bounds<double> {
+    static constexpr double edge = 24.0 * 1.1102230246251565e-16, plane = 20.0 * 1.1102230246251565e-16;
+    static constexpr double normal = 5e-15;
+    static constexpr double huge = 1e300;
+};
+
+// What 64 points need of one triangle, relative to q.
+template <typename T>
+struct Crossing {
+    T e[3][3];   // edge products (X - q) x (Y - q) and on
+    T n[3], s;   // side * normal, side * n . (Z - q)
+    T tol_e, tol_s;
+    int side;    // +1: q outside (n . (q - Z) > 0), -1: inside, 0: not certain
+
+    __device__ __forceinline__ Crossing from(int lane) const {
+        Crossing o;
+        for (int i = 0; i < 3; ++i) {
+            for (int c = 0; c < 3; ++c) o.e[i][c] = readlane_v(e[i][c], lane);
+            o.n[i] = readlane_v(n[i], lane);
+        }
+        o.s = readlane_v(s, lane);
+        o.tol_e = readlane_v(tol_e, lane);
+        o.tol_s = readlane_v(tol_s, lane);
+        o.side = readlane_i(side, lane);
+        return o;
+    }
+};
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+template <typename T>
+__device__ __forceinline__ T dot_t(const T (&a)[3], const T (&b)[3]) {
+    return fma_t(a[0], b[0], fma_t(a[1], b[1], a[2] * b[2]));
+}
+
+template <typename T>
+__device__ __forceinline__ Crossing<T> make_crossing(const Tri &t, const T (&n)[3], const float (&q)[3], T D) {
+    typedef Bounds<T> B;
+    Crossing<T> o;
+    T v[3][3], l2 = 0;
+    for (int c = 0; c < 3; ++c) {
+        v[0][c] = (T)t.X[c] - (T)q[c];
+        v[1][c] = (T)t.Y[c] - (T)q[c];
+        v[2][c] = (T)t.Z[c] - (T)q[c];
+    }
+    for (int i = 0; i < 3; ++i) {
+        const T d2 = dot_t(v[i], v[i]);
+        l2 = d2 > l2 ? d2 : l2;
+        const T(&a)[3] = v[i], (&b)[3] = v[(i + 1) % 3];
+        o.e[i][0] = fma_t(a[1], b[2], -(a[2] * b[1]));
+        o.e[i][1] = fma_t(a[2], b[0], -(a[0] * b[2]));
+        o.e[i][2] = fma_t(a[0], b[1], -(a[1] * b[0]));
+    }
+    const T len = fabs(n[0]) + fabs(n[1]) + fabs(n[2]), reach = D + sqrt(l2);
+    const T s = dot_t(n, v[2]);
+    o.tol_e = B::edge * l2 * D;
+    o.tol_s = reach * (B::plane * len + B::normal * l2);
+    // far out of range: nothing is certain (also catches NaN)
+    if (!(l2 * reach < B::huge) || !(len * reach < B::huge)) o.tol_e = o.tol_s = B::huge;
+    o.side = s < -o.tol_s ? 1 : (s > o.tol_s ? -1 : 0);
+    for (int c = 0; c < 3; ++c) o.n[c] = (T)o.side * n[c];
+    o.s = (T)o.side * s;
+    return o;
+}
+
+// Adds the change of the winding number from q to q + d where the triangle is
+// crossed (entering: +1).
+template <typename T>
+__device__ __forceinline__ void cross(const Crossing<T> &t, const T (&d)[3], int &delta, bool &uncertain) {
+    const T a = fma_t(t.n[0], d[0], fma_t(t.n[1], d[1], fma_t(t.n[2], d[2], -t.s)));   // > 0: q's side
+    const T u = dot_t(t.e[0], d), v = dot_t(t.e[1], d), w = dot_t(t.e[2], d);
+    const bool pos = u > t.tol_e && v > t.tol_e && w > t.tol_e, neg = u < -t.tol_e && v < -t.tol_e && w < -t.tol_e;
+    const bool beside = (u > t.tol_e || v > t.tol_e || w > t.tol_e) && (u < -t.tol_e || v < -t.tol_e || w < -t.tol_e);
+    const bool same = a > t.tol_s, through = a < -t.tol_s;
+    if (same || beside) return;
+    if (through && (pos || neg)) delta += t.side;
+    else uncertain = true;
+}
+
+// Whether triangle t may meet the box of centre c and half extents h (scale: |c|
+// + h): its own box does (exact comparisons) and its plane passes within the
+// box's radius, with a margin some thirty times the products' rounding.
+__device__ __forceinline__ bool may_meet(const Tri &t, const float (&lo)[3], const float (&hi)[3],
+                                         const float (&c)[3], const float (&h)[3], float scale) {
+    bool meets = true;
+    float ext = 0.0f;
+    for (int k = 0; k < 3; ++k) {
+        const float a = fminf(fminf(t.X[k], t.Y[k]), t.Z[k]), b = fmaxf(fmaxf(t.X[k], t.Y[k]), t.Z[k]);
+        meets = meets && a <= hi[k] && b >= lo[k];
+        ext = fmaxf(ext, b - a);
+    }
+    const float s = fmaf(c[0] - t.Z[0], t.n[0], fmaf(c[1] - t.Z[1], t.n[1], (c[2] - t.Z[2]) * t.n[2]));
+    const float reach = fmaf(h[0], fabsf(t.n[0]), fmaf(h[1], fabsf(t.n[1]), h[2] * fabsf(t.n[2])));
+    const float size = scale + fabsf(t.Z[0]) + fabsf(t.Z[1]) + fabsf(t.Z[2]);
+    const float margin = size * (4e-6f * (fabsf(t.n[0]) + fabsf(t.n[1]) + fabsf(t.n[2])) + 1.5e-12f * ext * ext);
+    return meets && !(fabsf(s) > reach + margin);
+}
+
+// Change of the winding number from q to each lane's point q + d (d as
+// computed; D bounds its length) through the near list's triangles.
+template <typename T>
+__device__ __forceinline__ void near_crossings(const Rec32 *__restrict__ rec32, const Rec64 *__restrict__ rec64,
+                                               const Lists &L, int n_near, const float (&lo)[3],
+                                               const float (&hi)[3], const float (&q)[3], const T (&d)[3], T D,
+                                               int &delta, bool &uncertain) {
+    const int lane = lane_id();
+    float c[3], h[3];
+    for (int k = 0; k < 3; ++k) {
+        c[k] = 0.5f * lo[k] + 0.5f * hi[k];
+        h[k] = 0.5f * hi[k] - 0.5f * lo[k];
+    }
+    const float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + h[0] + h[1] + h[2];
+    for (int i = 0; i < n_near; ++i) {
+        const uint2 g = L.near[i];
+        const uint32_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.x);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.y);
+        for (uint32_t o = 0; o < n; o += 64) {
+            const uint32_t r = begin + o + (uint32_t)lane;
+            Tri t;
+            bool meets = false;
+            if (o + lane < n && load_tri(rec32, begin, r, t)) meets = may_meet(t, lo, hi, c, h, scale);
+            uint64_t m = ballot(meets);
+            if (m == 0) continue;
+            Crossing<T> own;
+            if (meets) {
+                T nn[3];
+                for (int k = 0; k < 3; ++k) nn[k] = sizeof(T) == 8 ? (T)rec64[r].v[3 + k] : (T)t.n[k];
+                own = make_crossing<T>(t, nn, q, D);
+            }
+            for (; m; m &= m - 1) cross(own.from(__builtin_ctzll(m)), d, delta, uncertain);
+        }
+    }
 }
 
 }  // namespace patch

@@ -67,10 +67,10 @@ sal_status ensure_surface_balls(sal_context *ctx, const sal_surface_set *set);
 // some 34 bytes a point).
 constexpr int64_t kChunkPoints = (int64_t)1 << 27;
 
-// Up to this many points are labeled one per wavefront, in the order given.
-// The 64-point form pays six sorting launches first and needs enough
-// wavefronts to fill the chip.
-constexpr int64_t kPointFormMax = 65536;
+// Up to this many points (of a call, of a batch's instance) are labeled one per
+// wavefront, in the order given.  The 64-point form pays six sorting launches
+// first and needs enough wavefronts to fill the chip.
+constexpr int64_t kPointFormMax = 8192;
 
 // Tile size and count of the spatial order for n points.
 inline int32_t order_tile(int64_t n) {

@@ -14,7 +14,7 @@ import paper_2203_10000_amd as sal  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-POINT_FORM_MAX = 65536
+POINT_FORM_MAX = 8192
 TOL = {"fp32": 1e-5, "fp64": 1e-12}   # the forms' stated bounds on winding numbers
 
 
@@ -89,14 +89,14 @@ def _points(surf, n, seed):
 def test_both_forms_match_the_oracle(ctx, shape, precision):
     surf = _Surf(*SHAPES[shape](), label=3)
     ss = sal.SurfaceSet(ctx, [surf])
-    pts = _points(surf, POINT_FORM_MAX + 1, 17)
+    pts = _points(surf, 70001, 17)
     # a vertex, an edge midpoint, points far outside and without a place
     pts[:, 5] = surf.v[0]
     pts[:, 6:9] = [[np.nan, 3e30, 0.0], [0.0, 0.0, np.inf], [0.0, 0.0, 0.0]]
     fin = np.isfinite(pts).all(0)
     want, w_ref = oracle.label(np.where(fin, pts, 0).astype(np.float32), [surf], want_w=True)
     want = np.where(fin, want, -1)
-    for n in (POINT_FORM_MAX + 1, POINT_FORM_MAX):
+    for n in (70001, POINT_FORM_MAX + 1, POINT_FORM_MAX):
         d = torch.from_numpy(pts[:, :n].copy()).cuda()
         lab, w, _ = sal.label_points(ctx, ss, d, precision=precision, winding="f64")
         w = w.cpu().numpy()
@@ -114,7 +114,7 @@ def test_points_too_far_apart_for_a_common_walk(ctx, precision):
     ss = sal.SurfaceSet(ctx, [surf])
     rng = np.random.default_rng(4)
     outs = []
-    for n in (8192, 8193):
+    for n in (POINT_FORM_MAX, POINT_FORM_MAX + 1):
         pts = rng.uniform(-80.0, 80.0, (3, n)).astype(np.float32)
         lab = torch.full((n,), -7, dtype=torch.int32, device="cuda")
         outs.append((pts, lab))
