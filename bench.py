@@ -96,9 +96,9 @@ def calibrate_copy():
 
 
 def source_digest():
-    """Hash of the float32 labeling sources (kernels, patch tree, strip walk)."""
+    """Hash of the float32 labeling sources (kernels, order, patch tree)."""
     h = hashlib.sha256()
-    for name in ("label.hip", "patch.h", "strip_f32.h"):
+    for name in ("label.hip", "order.hip", "patch.h", "tri_f64.h"):
         h.update(open(os.path.join(ROOT, "paper_2203_10000_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]
 

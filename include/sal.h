@@ -37,7 +37,7 @@
  *     sal_last_error_message() returns a thread-local description of the
  *     last error on the calling thread.
  *   - Nothing in this library runs on the CPU except argument checking,
- *     surface preprocessing (validation, triangle strips) and launch logic.
+ *     surface preprocessing (validation, patch trees) and launch logic.
  */
 #ifndef SAL_H
 #define SAL_H
@@ -89,9 +89,9 @@ void sal_context_destroy(sal_context *ctx); /* NULL-safe; waits for the stream *
 
 /* ------------------------------------------------------------- surface set
  * The closed segmentation surfaces of section 2.1 in hierarchy order
- * (outermost first).  Creation validates every surface, builds triangle
- * strips and copies the geometry to the device (float32 strip records plus a
- * float64 copy for the recheck and plain-FP64 forms).  The set owns its
+ * (outermost first).  Creation validates every surface, cuts it
+ * into a tree of patches and copies the triangles, the patches' caps and the
+ * tree to the device (float32; double precision is formed from it exactly).  The set owns its
  * device memory and does not reference the descriptors after the call.
  *
  * Errors: SAL_ERR_INVALID_ARG (NULL, n_surfaces outside 1..64, an index out
@@ -117,12 +117,12 @@ void sal_surface_set_destroy(sal_surface_set *set); /* NULL-safe */
 typedef struct sal_surface_set_info {
     int32_t n_surfaces;
     int64_t n_triangles;   /* total over all surfaces */
-    int64_t n_strips;      /* triangle strips built at creation */
+    int64_t n_strips;      /* triangle runs (leaf patches) built at creation */
     int64_t device_bytes;  /* device memory held by the set */
 } sal_surface_set_info;
 sal_status sal_surface_set_get_info(const sal_surface_set *set, sal_surface_set_info *info);
 
-/* The validation and strip building of sal_surface_set_create (section
+/* The validation and patch building of sal_surface_set_create (section
  * 2.1.3: closed, consistently oriented segmentation boundaries) on the host
  * alone, with no context and no device: the same checks and error statuses,
  * and with SAL_OK `info` (if not NULL) gets what the set would hold

@@ -115,8 +115,7 @@ LabelInst make_inst(const sal_surface_set *set, int64_t n, const float *x, const
                     int32_t *labels, void *winding, int64_t wstride, unsigned long long *masks,
                     unsigned long long *counters) {
     LabelInst in{};
-    in.rec32 = set->rec32;
-    in.rec64 = set->rec64;
+    in.rec = set->rec;
     in.surf = set->surf;
     in.ent = set->ent;
     in.x = x;

@@ -73,7 +73,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
         for (const bool small : {false, true}) {
             for (int i = 0; i < n_inst; ++i) {
                 const sal_instance &in = inst[i];
-                if ((in.n_points <= kPointFormMax) != small) continue;
+                if ((in.n_points <= kBatchPointMax) != small) continue;
                 for (int64_t at = 0; at < in.n_points; at += kChunkPoints) {
                     const int64_t m = std::min(in.n_points - at, kChunkPoints);
                     LabelInst q = make_inst(in.surfaces, m, in.x + at, in.y + at, in.z + at, in.labels + at,

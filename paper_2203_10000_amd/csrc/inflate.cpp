@@ -1,5 +1,5 @@
 // Inflation of the compartment boundaries (paper section 2.2.2): host side.
-// Per call the surface set's strips are unrolled into float32 triangles and
+// Per call the surface set's triangles are copied with sorted vertices and
 // binned on the level-0 lattice; the interface nodes of the conforming mesh
 // then move in one launch that reads the positions from before the call.
 #include <algorithm>
@@ -56,19 +56,14 @@ sal_status sal_tet_mesh_inflate(sal_context *ctx, sal_tet_mesh *m, const sal_sur
         if ((st = ensure_smooth_graph(v, s)) != SAL_OK) return st;
         SmoothCache *c = *v.cache;
         Buffers b;
-        // triangles, first index of each strip's
-        std::vector<int64_t> base(set->host_strip_tris.size());
-        int64_t n_tri = 0;
-        for (size_t k = 0; k < base.size(); ++k) {
-            base[k] = n_tri;
-            n_tri += set->host_strip_tris[k];
-        }
-        int64_t *tri_base = nullptr;
+        const int64_t n_tri = set->n_tri;
         float *tri = nullptr;
-        if ((st = b.get(&tri_base, (int64_t)base.size())) != SAL_OK || (st = b.get(&tri, 9 * n_tri)) != SAL_OK)
-            return st;
-        SAL_HIP(hipMemcpyAsync(tri_base, base.data(), base.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
-        SAL_HIP(launch_strip_triangles(set->rec64, set->strip_off, tri_base, (int64_t)base.size(), tri, s));
+        if ((st = b.get(&tri, 9 * n_tri)) != SAL_OK) return st;
+        int64_t base = 0;
+        for (const SurfaceDev &sd : set->host_table) {
+            SAL_HIP(launch_sorted_triangles(set->rec, sd.rec_begin, sd.n_tri, base, tri, s));
+            base += sd.n_tri;
+        }
         // bins: count, scan, place
         int32_t *count = nullptr, *items = nullptr;
         int64_t *start = nullptr;

@@ -26,38 +26,24 @@ __device__ __forceinline__ bool lex_less(const double *a, const double *b) {
     return a[2] < b[2];
 }
 
-// Triangles of strip s: (v_k, v_k+1, v_k+2) with v_0, v_1 in the head record
-// and v_k+2 the vertex of the k-th record after it; stored with sorted
+// The records [first, first + n) as triangles [base, base + n) with sorted
 // vertices, in float32 (the surface vertices are float32 values, so this
 // loses nothing and halves the bytes each test reads).
-__global__ void k_strip_triangles(const Rec64 *__restrict__ rec, const int64_t *__restrict__ strip_off,
-                                  const int64_t *__restrict__ tri_base, int64_t n_strips,
-                                  float *__restrict__ tri) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n_strips) return;
-    const int64_t h = strip_off[s];
-    int64_t m;
-    memcpy(&m, &rec[h].v[6], 8);
+__global__ void k_sorted_triangles(const TriRec *__restrict__ rec, int64_t first, int64_t n, int64_t base,
+                                   float *__restrict__ tri) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
     double w[3][3];
-    for (int c = 0; c < 3; ++c) {
-        w[0][c] = rec[h].v[c];
-        w[1][c] = rec[h].v[3 + c];
-    }
-    for (int64_t k = 0; k < m; ++k) {
-        for (int c = 0; c < 3; ++c) w[2][c] = rec[h + 1 + k].v[c];
-        const double *p[3] = {w[0], w[1], w[2]};
-        // sort three
-        if (lex_less(p[1], p[0])) { const double *x = p[0]; p[0] = p[1]; p[1] = x; }
-        if (lex_less(p[2], p[1])) { const double *x = p[1]; p[1] = p[2]; p[2] = x; }
-        if (lex_less(p[1], p[0])) { const double *x = p[0]; p[0] = p[1]; p[1] = x; }
-        float *o = tri + 9 * (tri_base[s] + k);
-        for (int v = 0; v < 3; ++v)
-            for (int c = 0; c < 3; ++c) o[3 * v + c] = (float)p[v][c];
-        for (int c = 0; c < 3; ++c) {
-            w[0][c] = w[1][c];
-            w[1][c] = w[2][c];
-        }
-    }
+    for (int v = 0; v < 3; ++v)
+        for (int c = 0; c < 3; ++c) w[v][c] = rec[first + t].v[4 * v + c];
+    const double *p[3] = {w[0], w[1], w[2]};
+    // sort three
+    if (lex_less(p[1], p[0])) { const double *x = p[0]; p[0] = p[1]; p[1] = x; }
+    if (lex_less(p[2], p[1])) { const double *x = p[1]; p[1] = p[2]; p[2] = x; }
+    if (lex_less(p[1], p[0])) { const double *x = p[0]; p[0] = p[1]; p[1] = x; }
+    float *o = tri + 9 * (base + t);
+    for (int v = 0; v < 3; ++v)
+        for (int c = 0; c < 3; ++c) o[3 * v + c] = (float)p[v][c];
 }
 
 __device__ __forceinline__ int bin_of(double x, double o, double h, int n) {
@@ -273,10 +259,10 @@ __global__ __launch_bounds__(1024) void k_sum_pairs(const double *__restrict__ p
 
 int64_t inflate_blocks(int64_t n) { return (n * kInflateGroup + kSmoothThreads - 1) / kSmoothThreads; }
 
-hipError_t launch_strip_triangles(const Rec64 *rec, const int64_t *strip_off, const int64_t *tri_base,
-                                  int64_t n_strips, float *tri, hipStream_t s) {
-    if (n_strips <= 0) return hipSuccess;
-    k_strip_triangles<<<grid_of(n_strips), kSmoothThreads, 0, s>>>(rec, strip_off, tri_base, n_strips, tri);
+hipError_t launch_sorted_triangles(const TriRec *rec, int64_t first, int64_t n, int64_t base, float *tri,
+                                   hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    k_sorted_triangles<<<grid_of(n), kSmoothThreads, 0, s>>>(rec, first, n, base, tri);
     return hipGetLastError();
 }
 

@@ -9,7 +9,7 @@
 // 64 points lie in a box that meets no triangle needs it at one of them.
 //   k_label_wave   64 neighbouring points (order.hip) per wavefront: the
 //                  surface is summed at one point of their box, a lane per
-//                  term, and the others differ from it by the signed number of
+//                  triangle, and the others differ from it by the signed number of
 //                  near triangles that the segment between them crosses.
 //   k_label_point  one point per wavefront, a lane per term: few points.
 //   k_recheck      the same for flagged (point, surface) pairs.
@@ -28,6 +28,11 @@ namespace {
 using patch::Lists;
 using patch::Mode;
 using patch::PointSum;
+
+// A run of lanes is halved while its box meets more leaves than this (each costs
+// a load, a test of 64 triangles, and ~80 instructions for every triangle that
+// meets the box; a halved run sums one point more), down to kSplitMin lanes.
+constexpr int kSplitLeaves = 32, kSplitMin = 4;
 
 // Instance of wavefront g, by its place in the grid.
 __device__ __forceinline__ int find_group(const LabelInst *insts, int n_inst, int64_t g) {
@@ -81,10 +86,26 @@ __device__ __forceinline__ PointSum point_surface(const LabelInst &in, const Sur
         if (lane_id() == 0) L.near[0] = make_uint2(0u, (uint32_t)(sd.rec_end - sd.rec_begin));
         wave_sync();
     }
-    const PointSum s = patch::point_sum<MODE>(in.rec32 + sd.rec_begin, in.rec64 + sd.rec_begin, L, n_near,
-                                              n_far, x, y, z, kap);
+    const PointSum s = patch::point_sum<MODE>(in.rec + sd.rec_begin, L, n_near, n_far, x, y, z, kap);
     wave_sync();   // the lists are free again
     return s;
+}
+
+// Box of the points of the lanes with `mine`, in every lane.
+__device__ __forceinline__ void box_of(bool mine, float x, float y, float z, float (&lo)[3], float (&hi)[3]) {
+    const float inf = __builtin_inff();
+    const float p[3] = {x, y, z};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        float a = mine ? p[c] : inf, b = mine ? p[c] : -inf;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            a = fminf(a, __shfl_xor(a, d));
+            b = fmaxf(b, __shfl_xor(b, d));
+        }
+        lo[c] = readlane_v(a, 0);
+        hi[c] = readlane_v(b, 0);
+    }
 }
 
 __device__ __forceinline__ unsigned wave_add(unsigned v) {
@@ -193,11 +214,12 @@ __global__ __launch_bounds__(512) void k_label_point(LabelArgs a) {
 }
 
 // ------------------------------------------------------------- 64 per wavefront
-// What bounds it: load latency in the sum at the box's point (a few dozen
-// dependent rounds) and in the tree; the crossings are some 45 instructions a
-// triangle that meets the box.  A lane-by-lane walk over the same patches instead
-// of the crossings took 5.4 of 8.0 ms for 6M lattice points x 81,920 triangles
-// (1400 terms a point); with the crossings the whole kernel takes 3.4.
+// What bounds it: load latency in the sum at the box's point and in the tree; the
+// crossings are some 80 instructions a triangle that meets the box.  6M lattice
+// points x 81,920 triangles, this kernel: 8.0 ms with a lane-by-lane walk over
+// the patches where the surface enters the box (1400 terms a point), 3.4 with the
+// crossings, 1.9 with one 48-byte record a triangle instead of strips (one
+// round of loads a term instead of three), 1.4 in Hilbert instead of Morton order.
 template <bool F64>
 __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
     extern __shared__ __align__(16) unsigned char shared[];
@@ -216,39 +238,12 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
     const bool good = valid && finite3(px, py, pz);
     if (!good) { px = 0.0f; py = 0.0f; pz = 0.0f; }
     const uint64_t good_mask = ballot(good);
-    const float inf = __builtin_inff();
-    float lo[3] = {good ? px : inf, good ? py : inf, good ? pz : inf};
-    float hi[3] = {good ? px : -inf, good ? py : -inf, good ? pz : -inf};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            lo[c] = fminf(lo[c], __shfl_xor(lo[c], d));
-            hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], d));
-        }
-        lo[c] = readlane_v(lo[c], 0);
-        hi[c] = readlane_v(hi[c], 0);
-    }
+    float lo[3], hi[3];
+    box_of(good, px, py, pz, lo, hi);
     uint64_t enc = 0, flg = 0;
     int32_t lab = 0;
     Tally t;
-    // the sums' point q: inside the box, off its planes of symmetry so that
-    // segments to lattice points seldom pass through edges of a regular mesh
     typedef typename std::conditional<F64, double, float>::type T;
-    float q[3];
-    T d[3], D;
-    auto place = [&](const float (&f)[3]) {
-        T d2 = 0;
-        for (int c = 0; c < 3; ++c) {
-            q[c] = fminf(fmaxf(fmaf(hi[c] - lo[c], f[c], lo[c]), lo[c]), hi[c]);
-            const T r = fmax((T)hi[c] - (T)q[c], (T)q[c] - (T)lo[c]);
-            d2 += r * r;
-        }
-        d[0] = (T)px - (T)q[0];
-        d[1] = (T)py - (T)q[1];
-        d[2] = (T)pz - (T)q[2];
-        D = sqrt(d2) * (T)1.00001;
-    };
     for (int k = 0; k < in.n_surf; ++k) {
         const SurfaceDev &sd = in.surf[k];
         double w = 0.0;
@@ -267,34 +262,65 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
             }
         }
         if (!outside) {
-            const Rec32 *rec32 = in.rec32 + sd.rec_begin;
-            const Rec64 *rec64 = in.rec64 + sd.rec_begin;
-            int n_near, n_far;
-            bool known = false;
-            if (patch::sort_patches(in.ent + 4 * sd.node_begin, lo, hi, L, n_near, n_far)) {
-                // q's own sum; where float32 does not certify it, another point's
+            const TriRec *rec = in.rec + sd.rec_begin;
+            // the whole wavefront, or aligned runs of lanes, halved while their box
+            // meets too many leaves
+            for (int pos = 0, len = 64; pos < 64;) {
+                const uint64_t run = (len == 64 ? ~0ull : ((1ull << len) - 1ull) << pos) & good_mask;
+                float blo[3], bhi[3];
+                int n_near = 0, n_far = 0;
+                bool fits = true;
+                if (run) {
+                    if (len == 64) {
+                        for (int c = 0; c < 3; ++c) { blo[c] = lo[c]; bhi[c] = hi[c]; }
+                    } else {
+                        const bool mine = (run >> lane) & 1ull;
+                        box_of(mine, px, py, pz, blo, bhi);
+                    }
+                    fits = patch::sort_patches(in.ent + 4 * sd.node_begin, blo, bhi, L, n_near, n_far);
+                    if ((!fits || n_near > kSplitLeaves) && len > kSplitMin) {
+                        len >>= 1;
+                        wave_sync();
+                        continue;
+                    }
+                }
+                double v = 0.0;
+                int delta = 0;
+                bool known = false, uncertain = false;
+                // The sum's point: inside the box, off its planes of symmetry, so
+                // that segments to lattice points seldom pass through edges of a
+                // regular mesh; where float32 does not certify its sum, another.
                 const float at[3][3] = {{0.4871f, 0.5237f, 0.5113f}, {0.3137f, 0.6719f, 0.4481f},
                                         {0.6863f, 0.3571f, 0.6229f}};
-                for (int i = 0; i < 3 && !known; ++i) {
-                    place(at[i]);
+                for (int i = 0; i < 3 && run && fits && !known; ++i) {
+                    float q[3];
+                    for (int c = 0; c < 3; ++c)
+                        q[c] = fminf(fmaxf(fmaf(bhi[c] - blo[c], at[i][c], blo[c]), blo[c]), bhi[c]);
                     const PointSum s = patch::point_sum<F64 ? patch::kDouble : patch::kFloat>(
-                        rec32, rec64, L, n_near, n_far, q[0], q[1], q[2], a.kappa);
-                    const double v = s.half * kInv2Pi;
-                    w = rint(v);
-                    known = !s.uncertain && !s.on && fabs(v - w) < 1e-3;
+                        rec, L, n_near, n_far, q[0], q[1], q[2], a.kappa);
+                    v = rint(s.half * kInv2Pi);
+                    known = !s.uncertain && !s.on && fabs(s.half * kInv2Pi - v) < 1e-3;
                     t.exact += s.exact;
+                    if (known && n_near > 0) {
+                        const T d[3] = {(T)px - (T)q[0], (T)py - (T)q[1], (T)pz - (T)q[2]};
+                        T d2 = 0;
+                        for (int c = 0; c < 3; ++c) {
+                            const T r = fmax((T)bhi[c] - (T)q[c], (T)q[c] - (T)blo[c]);
+                            d2 += r * r;
+                        }
+                        patch::near_crossings<T>(rec, L, n_near, blo, bhi, q, d, sqrt(d2) * (T)1.00001, delta,
+                                                 uncertain);
+                    }
                 }
+                if ((run >> lane) & 1ull) {
+                    w = v + (double)delta;
+                    cond = known && uncertain;
+                    apart = !known;   // left to k_recheck
+                }
+                wave_sync();   // the lists are free again
+                pos += len;
+                len = pos & -pos;   // the largest run aligned here
             }
-            if (known) {
-                int delta = 0;
-                bool uncertain = false;
-                patch::near_crossings<T>(rec32, rec64, L, n_near, lo, hi, q, d, D, delta, uncertain);
-                w += (double)delta;
-                cond = uncertain;
-            } else {
-                apart = true;   // left to k_recheck
-            }
-            wave_sync();   // the lists are free again
         }
         const bool inside = w >= a.threshold;
         if (apart || cond) flg |= 1ull << k;

@@ -1,7 +1,12 @@
 // Spatial order of the points to be labeled, so that the 64 points of a
-// wavefront lie close together: a stable counting sort by a 21-bit Morton code
-// of the point's cell in the surface set's box (128 cells per axis; points
-// outside it go to the border cells), 11 low bits, then 10 high bits.
+// wavefront lie close together: a stable counting sort by the place of the
+// point's cell (128 per axis of the surface set's box; points outside it go to
+// the border cells) on a Hilbert curve, 11 low bits, then 10 high bits.  Along a
+// Hilbert curve consecutive cells are neighbours.  In Morton order one run of 64
+// in a hundred jumps across a quarter of the box (on 1.3M lattice points: extent
+// 13.6 mm on average, 46.7 mm at the 99th percentile, 198 mm at most, against
+// 11.2, 17.5 and 20.0 mm), its surfaces meet far more boxes (0.69 of them
+// against 0.52 over four shells), and such wavefronts are the launch's tail.
 // Stable, so that the wavefronts, and with them every rounding, are the same
 // in every run.
 //
@@ -21,6 +26,8 @@ namespace sal {
 namespace {
 
 constexpr int kThreads = 256, kWaves = kThreads / 64;
+constexpr int kAxisBits = 7;
+static_assert(3 * kAxisBits == kOrderBits1 + kOrderBits2, "two digits hold a place on the curve");
 
 __device__ __forceinline__ int find_tile(const LabelInst *insts, int n_inst, int64_t t) {
     int lo = 0, hi = n_inst - 1;
@@ -40,6 +47,30 @@ __device__ __forceinline__ uint32_t spread3(uint32_t v) {
     return v;
 }
 
+// Place of cell q (kAxisBits bits an axis) on the Hilbert curve: J. Skilling,
+// "Programming the Hilbert curve", AIP Conf. Proc. 707 (2004) -- from the top bit
+// down, each axis' bit either reflects the lower bits of axis 0 or exchanges them
+// with its own; a Gray decode across the axes follows.
+__device__ __forceinline__ uint32_t hilbert(uint32_t (&q)[3]) {
+#pragma unroll
+    for (int b = kAxisBits - 1; b > 0; --b) {
+        const uint32_t low = (1u << b) - 1u;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const uint32_t set = 0u - ((q[c] >> b) & 1u);           // all ones where the bit is set
+            const uint32_t flip = low & set, swap = (q[0] ^ q[c]) & low & ~set;
+            q[0] ^= flip | swap;
+            q[c] ^= swap;                                           // (axis 0 exchanges with itself: 0)
+        }
+    }
+    q[1] ^= q[0];
+    q[2] ^= q[1];
+    uint32_t t = 0;
+#pragma unroll
+    for (int b = kAxisBits - 1; b > 0; --b) t ^= ((1u << b) - 1u) & (0u - ((q[2] >> b) & 1u));
+    return (spread3(q[0] ^ t) << 2) | (spread3(q[1] ^ t) << 1) | spread3(q[2] ^ t);
+}
+
 __device__ __forceinline__ uint32_t cell_code(const LabelInst &in, int64_t i) {
     uint32_t q[3];
     const float p[3] = {in.x[i], in.y[i], in.z[i]};
@@ -48,7 +79,7 @@ __device__ __forceinline__ uint32_t cell_code(const LabelInst &in, int64_t i) {
         const float f = fminf(fmaxf((p[c] - in.lo[c]) * in.scale[c], 0.0f), 127.0f);
         q[c] = (uint32_t)f;
     }
-    return spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
+    return hilbert(q);
 }
 
 template <int PASS>

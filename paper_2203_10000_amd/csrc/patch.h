@@ -4,8 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
-#include "mixed_term.h"
 #include "sal_internal.h"
+#include "tri_f64.h"
 #include "wave.h"
 
 namespace sal {
@@ -69,34 +69,10 @@ __device__ __forceinline__ bool sort_patches(const PatchEntry *__restrict__ ent,
     return true;
 }
 
-// The triangle that ends at record r of a strip range starting at `begin`
-// (its vertices are that of r and the two before it); false for a head.
-struct Tri {
-    float X[3], Y[3], Z[3], n[3], len, lim;
-};
-__device__ __forceinline__ bool load_tri(const Rec32 *__restrict__ rec, uint32_t begin, uint32_t r, Tri &t) {
+__device__ __forceinline__ Tri load_tri(const TriRec *__restrict__ rec, uint32_t r) {
     const float4 *q = (const float4 *)(rec + r);
-    const float4 a = q[0], b = q[1];
-    if (b.w == 0.0f) return false;
-    const float4 *p1 = (const float4 *)(rec + (r - 1));
-    const float4 c = p1[0], d = p1[1];
-    t.Z[0] = a.x; t.Z[1] = a.y; t.Z[2] = a.z;
-    t.n[0] = a.w; t.n[1] = b.x; t.n[2] = b.y;
-    t.len = b.z;
-    t.lim = b.w;
-    if (d.w == 0.0f) {   // first triangle of a strip: both vertices in the head
-        t.X[0] = c.x; t.X[1] = c.y; t.X[2] = c.z;
-        t.Y[0] = c.w; t.Y[1] = d.x; t.Y[2] = d.y;
-    } else {
-        t.Y[0] = c.x; t.Y[1] = c.y; t.Y[2] = c.z;
-        const float4 *p2 = (const float4 *)(rec + (r - 2 > begin ? r - 2 : begin));
-        const float4 e = p2[0], f = p2[1];
-        const bool head = f.w == 0.0f;
-        t.X[0] = head ? e.w : e.x;
-        t.X[1] = head ? f.x : e.y;
-        t.X[2] = head ? f.y : e.z;
-    }
-    return true;
+    const float4 a = q[0], b = q[1], c = q[2];
+    return Tri{{a.x, a.y, a.z}, {b.x, b.y, b.z}, {c.x, c.y, c.z}, {a.w, b.w, c.w}};
 }
 
 struct PointSum {
@@ -114,89 +90,99 @@ enum Mode { kFloat, kMixed, kDouble };
 // Half the solid angle of the listed ranges at one point (the same in every
 // lane).  Eight groups of eight lanes take ranges in turn, a group the next one
 // as it becomes free (all lanes run in step, so the assignment, and with it
-// the result, depends on the lists alone); a lane evaluates the triangle that
-// ends at its record.  Caps average 25-30 triangles, so wider groups would
-// leave more lanes idle at a range's end.
+// the result, depends on the lists alone); a lane evaluates one triangle.  Most
+// caps have 20-60 triangles, so wider groups would leave more lanes idle at a
+// range's end.  The next triangles are loaded before the present ones are
+// evaluated: a round waits for memory only as far as the arithmetic of the
+// rounds and of the other wavefronts does not cover it.
 template <Mode MODE>
-__device__ __forceinline__ PointSum point_sum(const Rec32 *__restrict__ rec32, const Rec64 *__restrict__ rec64,
-                                              const Lists &L, int n_near, int n_far, float px, float py,
-                                              float pz, float kap) {
+__device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, const Lists &L, int n_near,
+                                              int n_far, float px, float py, float pz, float kap) {
     const int lane = lane_id(), sub = lane & 7;
-    const float branch_cut = mixed::kPiF - 0.25f * kap;
+    const float branch_cut = kPiF - 0.25f * kap;
     const int items = n_near + n_far;
     const uint64_t leaders = 0x0101010101010101ull;
     PointSum out{0.0, false, false, 0u, 0u};
     float accf = 0.0f;
     double acc = 0.0;
     int next = 0, on = 0;
-    uint32_t begin = 0, cur = 0, end = 0;
-    bool more = true;
-    for (;;) {
+    uint32_t cur = 0, end = 0;   // this group's range
+    bool more = true, cap = false;
+    // the lane's triangle of the coming round
+    Tri t;
+    bool have, t_cap;
+    auto fetch = [&]() {
         // groups whose range is finished take the next ones in group order
-        bool need = more && cur >= end;
-        uint64_t m = ballot(need);
+        const bool need = more && cur >= end;
+        const uint64_t m = ballot(need);
         if (m != 0) {
             const int it = next + __popcll(m & leaders & ((1ull << (lane & ~7)) - 1ull));
             if (need) {
                 more = it < items;
+                cap = it >= n_near;
                 if (more) {
-                    const uint2 g = it < n_near ? L.near[it] : L.far[it - n_near];
-                    begin = g.x;
+                    const uint2 g = cap ? L.far[it - n_near] : L.near[it];
                     cur = g.x;
                     end = g.x + g.y;
                 }
             }
             next += __popcll(m & leaders);
         }
-        if (ballot(more) == 0) break;
         const uint32_t r = cur + (uint32_t)sub;
-        Tri t;
-        if (more && r < end && load_tri(rec32, begin, r, t)) {
-            if (MODE == kDouble) {
-                const mixed::F64Term d = mixed::f64_triangle(t.X[0], t.X[1], t.X[2], t.Y[0], t.Y[1], t.Y[2],
-                                                             rec64[r].v, px, py, pz);
+        have = more && r < end;
+        t_cap = cap;
+        t = load_tri(rec, have ? r : 0u);   // (record 0 exists: the loads are unconditional)
+        cur += 8;
+    };
+    fetch();
+    while (ballot(have) != 0) {
+        const Tri q = t;
+        const bool live = have, q_cap = t_cap;
+        fetch();
+        if (MODE == kDouble) {
+            if (live) {
+                const F64Term d = f64_term(q, px, py, pz, q_cap);
                 acc += d.half;
                 on |= d.on;
                 out.exact += d.exact;
+            }
+            continue;
+        }
+        const float ax = q.A[0] - px, ay = q.A[1] - py, az = q.A[2] - pz;
+        const float bx = q.B[0] - px, by = q.B[1] - py, bz = q.B[2] - pz;
+        const float cx = q.C[0] - px, cy = q.C[1] - py, cz = q.C[2] - pz;
+        const float ar = __builtin_amdgcn_sqrtf(fmaf(ax, ax, fmaf(ay, ay, az * az)));
+        const float br = __builtin_amdgcn_sqrtf(fmaf(bx, bx, fmaf(by, by, bz * bz)));
+        const float cr = __builtin_amdgcn_sqrtf(fmaf(cx, cx, fmaf(cy, cy, cz * cz)));
+        const float len = __builtin_amdgcn_sqrtf(fmaf(q.n[0], q.n[0], fmaf(q.n[1], q.n[1], q.n[2] * q.n[2])));
+        const float e01 = fmaf(ax, bx, fmaf(ay, by, az * bz));
+        const float e02 = fmaf(ax, cx, fmaf(ay, cy, az * cz));
+        const float e12 = fmaf(bx, cx, fmaf(by, cy, bz * cz));
+        const float nn = fmaf(cx, q.n[0], fmaf(cy, q.n[1], cz * q.n[2]));   // 32 N
+        const float mm = ar * br * cr;
+        const float dd = fmaf(e12, ar, fmaf(e02, br, fmaf(e01, cr, mm)));
+        const float lim = fmaf(len * (kKnSmall / kNScale), cr, fmaf(kap, mm, fabsf(nn)));
+        if (__builtin_expect(live && dd > lim, 1)) {   // |N / D| < 1/32: the series
+            const float u = nn * __builtin_amdgcn_rcpf(dd);
+            const float s2 = u * u;
+            accf = fmaf(u, fmaf(fmaf(kA2, s2, kA1), s2, kA0), accf);
+        } else if (live) {
+            const float n1 = nn * (1.0f / kNScale);
+            const float ang = atan2f(n1, dd);
+            const float thr = fmaf(cr, kap * (1.0f / kNScale) * len, kap * mm);
+            const bool ill = !(fmaxf(fabsf(n1), fabsf(dd)) > thr) || fabsf(ang) > branch_cut;   // (NaN is ill)
+            if (!ill) {
+                accf += ang;
+            } else if (MODE == kFloat) {
+                out.uncertain = true;
             } else {
-                const float ax = t.X[0] - px, ay = t.X[1] - py, az = t.X[2] - pz;
-                const float bx = t.Y[0] - px, by = t.Y[1] - py, bz = t.Y[2] - pz;
-                const float cx = t.Z[0] - px, cy = t.Z[1] - py, cz = t.Z[2] - pz;
-                const float ar = __builtin_amdgcn_sqrtf(fmaf(ax, ax, fmaf(ay, ay, az * az)));
-                const float br = __builtin_amdgcn_sqrtf(fmaf(bx, bx, fmaf(by, by, bz * bz)));
-                const float cr = __builtin_amdgcn_sqrtf(fmaf(cx, cx, fmaf(cy, cy, cz * cz)));
-                const float e01 = fmaf(ax, bx, fmaf(ay, by, az * bz));
-                const float e02 = fmaf(ax, cx, fmaf(ay, cy, az * cz));
-                const float e12 = fmaf(bx, cx, fmaf(by, cy, bz * cz));
-                const float nn = fmaf(cx, t.n[0], fmaf(cy, t.n[1], cz * t.n[2]));   // 32 N
-                const float mm = ar * br * cr;
-                const float dd = fmaf(e12, ar, fmaf(e02, br, fmaf(e01, cr, mm)));
-                const float lim = fmaf(t.lim, cr, fmaf(kap, mm, fabsf(nn)));
-                if (__builtin_expect(dd > lim, 1)) {   // |N / D| < 1/32: the series
-                    const float u = nn * __builtin_amdgcn_rcpf(dd);
-                    const float s2 = u * u;
-                    accf = fmaf(u, fmaf(fmaf(mixed::kA2, s2, mixed::kA1), s2, mixed::kA0), accf);
-                } else {
-                    const float n1 = nn * (1.0f / kNScale);
-                    const float ang = atan2f(n1, dd);
-                    const float thr = fmaf(cr, kap * t.len, kap * mm);
-                    const bool ill = !(fmaxf(fabsf(n1), fabsf(dd)) > thr) || fabsf(ang) > branch_cut;
-                    if (!ill) {
-                        accf += ang;
-                    } else if (MODE == kFloat) {
-                        out.uncertain = true;
-                    } else {
-                        const mixed::F64Term d = mixed::f64_triangle(t.X[0], t.X[1], t.X[2], t.Y[0], t.Y[1],
-                                                                     t.Y[2], rec64[r].v, px, py, pz);
-                        acc += d.half;
-                        on |= d.on;
-                        out.exact += d.exact;
-                        out.n_f64 += 1u;
-                    }
-                }
+                const F64Term d = f64_term(q, px, py, pz, q_cap);
+                acc += d.half;
+                on |= d.on;
+                out.exact += d.exact;
+                out.n_f64 += 1u;
             }
         }
-        cur += 8;
     }
     acc += (double)accf;
 #pragma unroll
@@ -235,10 +221,10 @@ struct Bounds<double> {
 // What 64 points need of one triangle, relative to q.
 template <typename T>
 struct Crossing {
-    T e[3][3];   // edge products (X - q) x (Y - q) and on
-    T n[3], s;   // side * normal, side * n . (Z - q)
+    T e[3][3];   // edge products (A - q) x (B - q) and on
+    T n[3], s;   // side * normal, side * n . (C - q)
     T tol_e, tol_s;
-    int side;    // +1: q outside (n . (q - Z) > 0), -1: inside, 0: not certain
+    int side;    // +1: q outside (n . (q - C) > 0), -1: inside, 0: not certain
 
     __device__ __forceinline__ Crossing from(int lane) const {
         Crossing o;
@@ -262,14 +248,24 @@ __device__ __forceinline__ T dot_t(const T (&a)[3], const T (&b)[3]) {
 }
 
 template <typename T>
-__device__ __forceinline__ Crossing<T> make_crossing(const Tri &t, const T (&n)[3], const float (&q)[3], T D) {
+__device__ __forceinline__ Crossing<T> make_crossing(const Tri &t, const float (&q)[3], T D) {
     typedef Bounds<T> B;
     Crossing<T> o;
-    T v[3][3], l2 = 0;
+    T v[3][3], l2 = 0, n[3];
+    if (sizeof(T) == 8) {
+        const T e1[3] = {(T)t.B[0] - (T)t.A[0], (T)t.B[1] - (T)t.A[1], (T)t.B[2] - (T)t.A[2]};
+        const T e2[3] = {(T)t.C[0] - (T)t.A[0], (T)t.C[1] - (T)t.A[1], (T)t.C[2] - (T)t.A[2]};
+        for (int c = 0; c < 3; ++c) {
+            const int u = (c + 1) % 3, w = (c + 2) % 3;
+            n[c] = e1[u] * e2[w] - e1[w] * e2[u];
+        }
+    } else {
+        for (int c = 0; c < 3; ++c) n[c] = (T)t.n[c];
+    }
     for (int c = 0; c < 3; ++c) {
-        v[0][c] = (T)t.X[c] - (T)q[c];
-        v[1][c] = (T)t.Y[c] - (T)q[c];
-        v[2][c] = (T)t.Z[c] - (T)q[c];
+        v[0][c] = (T)t.A[c] - (T)q[c];
+        v[1][c] = (T)t.B[c] - (T)q[c];
+        v[2][c] = (T)t.C[c] - (T)q[c];
     }
     for (int i = 0; i < 3; ++i) {
         const T d2 = dot_t(v[i], v[i]);
@@ -313,13 +309,13 @@ __device__ __forceinline__ bool may_meet(const Tri &t, const float (&lo)[3], con
     bool meets = true;
     float ext = 0.0f;
     for (int k = 0; k < 3; ++k) {
-        const float a = fminf(fminf(t.X[k], t.Y[k]), t.Z[k]), b = fmaxf(fmaxf(t.X[k], t.Y[k]), t.Z[k]);
+        const float a = fminf(fminf(t.A[k], t.B[k]), t.C[k]), b = fmaxf(fmaxf(t.A[k], t.B[k]), t.C[k]);
         meets = meets && a <= hi[k] && b >= lo[k];
         ext = fmaxf(ext, b - a);
     }
-    const float s = fmaf(c[0] - t.Z[0], t.n[0], fmaf(c[1] - t.Z[1], t.n[1], (c[2] - t.Z[2]) * t.n[2]));
+    const float s = fmaf(c[0] - t.C[0], t.n[0], fmaf(c[1] - t.C[1], t.n[1], (c[2] - t.C[2]) * t.n[2]));
     const float reach = fmaf(h[0], fabsf(t.n[0]), fmaf(h[1], fabsf(t.n[1]), h[2] * fabsf(t.n[2])));
-    const float size = scale + fabsf(t.Z[0]) + fabsf(t.Z[1]) + fabsf(t.Z[2]);
+    const float size = scale + fabsf(t.C[0]) + fabsf(t.C[1]) + fabsf(t.C[2]);
     const float margin = size * (4e-6f * (fabsf(t.n[0]) + fabsf(t.n[1]) + fabsf(t.n[2])) + 1.5e-12f * ext * ext);
     return meets && !(fabsf(s) > reach + margin);
 }
@@ -327,10 +323,10 @@ __device__ __forceinline__ bool may_meet(const Tri &t, const float (&lo)[3], con
 // Change of the winding number from q to each lane's point q + d (d as
 // computed; D bounds its length) through the near list's triangles.
 template <typename T>
-__device__ __forceinline__ void near_crossings(const Rec32 *__restrict__ rec32, const Rec64 *__restrict__ rec64,
-                                               const Lists &L, int n_near, const float (&lo)[3],
-                                               const float (&hi)[3], const float (&q)[3], const T (&d)[3], T D,
-                                               int &delta, bool &uncertain) {
+__device__ __forceinline__ void near_crossings(const TriRec *__restrict__ rec, const Lists &L, int n_near,
+                                               const float (&lo)[3], const float (&hi)[3],
+                                               const float (&q)[3], const T (&d)[3], T D, int &delta,
+                                               bool &uncertain) {
     const int lane = lane_id();
     float c[3], h[3];
     for (int k = 0; k < 3; ++k) {
@@ -338,25 +334,25 @@ __device__ __forceinline__ void near_crossings(const Rec32 *__restrict__ rec32, 
         h[k] = 0.5f * hi[k] - 0.5f * lo[k];
     }
     const float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + h[0] + h[1] + h[2];
+    // a leaf a round (a leaf has at most 64 triangles), the next one's loaded ahead
+    Tri t;
+    bool have = false;
+    auto fetch = [&](int i) {
+        const uint2 g = L.near[i < n_near ? i : 0];
+        have = i < n_near && (uint32_t)lane < g.y;
+        t = load_tri(rec, have ? g.x + (uint32_t)lane : 0u);
+    };
+    if (n_near > 0) fetch(0);
     for (int i = 0; i < n_near; ++i) {
-        const uint2 g = L.near[i];
-        const uint32_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.x);
-        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.y);
-        for (uint32_t o = 0; o < n; o += 64) {
-            const uint32_t r = begin + o + (uint32_t)lane;
-            Tri t;
-            bool meets = false;
-            if (o + lane < n && load_tri(rec32, begin, r, t)) meets = may_meet(t, lo, hi, c, h, scale);
-            uint64_t m = ballot(meets);
-            if (m == 0) continue;
-            Crossing<T> own;
-            if (meets) {
-                T nn[3];
-                for (int k = 0; k < 3; ++k) nn[k] = sizeof(T) == 8 ? (T)rec64[r].v[3 + k] : (T)t.n[k];
-                own = make_crossing<T>(t, nn, q, D);
-            }
-            for (; m; m &= m - 1) cross(own.from(__builtin_ctzll(m)), d, delta, uncertain);
-        }
+        const Tri now = t;
+        const bool live = have;
+        fetch(i + 1);
+        const bool meets = live && may_meet(now, lo, hi, c, h, scale);
+        uint64_t m = ballot(meets);
+        if (m == 0) continue;
+        Crossing<T> own;
+        if (meets) own = make_crossing<T>(now, q, D);
+        for (; m; m &= m - 1) cross(own.from(__builtin_ctzll(m)), d, delta, uncertain);
     }
 }
 

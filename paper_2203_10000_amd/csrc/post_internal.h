@@ -118,8 +118,8 @@ hipError_t launch_row_heads(const int64_t *rowptr, const uint32_t *cols, const i
                             int64_t n, uint32_t *head, hipStream_t s);
 // Inflation (inflate.hip): triangles of the surface set (9 floats, sorted
 // vertices), binned on the level-0 lattice.
-hipError_t launch_strip_triangles(const Rec64 *rec, const int64_t *strip_off, const int64_t *tri_base,
-                                  int64_t n_strips, float *tri, hipStream_t s);
+hipError_t launch_sorted_triangles(const TriRec *rec, int64_t first, int64_t n, int64_t base, float *tri,
+                                   hipStream_t s);
 // pass 0 counts the triangles of each bin into count; pass 1 (count zeroed,
 // start its exclusive sum) places them into items.
 hipError_t launch_bin_triangles(const float *tri, int64_t n_tri, const LatticeGeom &g, int pass,

@@ -40,15 +40,12 @@ struct sal_surface_set {
     uint64_t uid = 0;      // unique per creation (graph cache keys)
     int device = 0;
     int n_surf = 0;
-    int64_t n_tri = 0, n_strips = 0, n_rec = 0, bytes = 0;
-    sal::Rec32 *rec32 = nullptr;
-    sal::Rec64 *rec64 = nullptr;
+    int64_t n_tri = 0, n_strips = 0, bytes = 0;   // (n_strips: leaf patches)
+    sal::TriRec *rec = nullptr;
     sal::SurfaceDev *surf = nullptr;        // n_surf entries
     sal::PatchEntry *ent = nullptr;         // patch trees of all surfaces
     float lo[3] = {}, hi[3] = {};           // box of all surfaces
-    int64_t *strip_off = nullptr;
     std::vector<sal::SurfaceDev> host_table;
-    std::vector<int32_t> host_strip_tris;  // triangles of every strip
     bool balls_ready = false;              // ball_w of every surface known
 };
 
@@ -67,10 +64,16 @@ sal_status ensure_surface_balls(sal_context *ctx, const sal_surface_set *set);
 // some 34 bytes a point).
 constexpr int64_t kChunkPoints = (int64_t)1 << 27;
 
-// Up to this many points (of a call, of a batch's instance) are labeled one per
-// wavefront, in the order given.  The 64-point form pays six sorting launches
-// first and needs enough wavefronts to fill the chip.
-constexpr int64_t kPointFormMax = 8192;
+// Up to this many points are labeled one per wavefront, in the order given.  The
+// 64-point form pays six sorting launches first, and its wavefronts work through
+// their surfaces one after the other; with few of them on the chip that chain is
+// the time.  Measured (us, point form / 64-point form; box points): four shells
+// of 5,120 triangles, 8,192 points 118 / 300, 16,384 203 / 235, 32,768 359 / 203;
+// four of 20,480: 16,384 328 / 648, 65,536 1094 / 343.
+constexpr int64_t kPointFormMax = 16384;
+
+// The same for an instance of a batch, whose other instances fill the chip.
+constexpr int64_t kBatchPointMax = 8192;
 
 // Tile size and count of the spatial order for n points.
 inline int32_t order_tile(int64_t n) {

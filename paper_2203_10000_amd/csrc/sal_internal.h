@@ -13,40 +13,23 @@
 namespace sal {
 
 // ---------------------------------------------------------------- records
-// A surface is stored as triangle strips.  A strip with vertices
-// v0, v1, ..., v_{m+1} holds the m triangles (v_i, v_{i+1}, v_{i+2}); the two
-// last vertices of one triangle are the two first of the next, so the
-// per-vertex terms (v - p, |v - p|) and the dot product of the shared edge
-// are computed once per strip step instead of once per triangle.
-//
-// float32 stream, 32 bytes per record:
-//   head: { x0, y0, z0, x1, y1, z1, bits(m), 0 }
-//   tri : { x, y, z,  32 nx, 32 ny, 32 nz,  |n|,  KN_SMALL |n| }
-// where (x, y, z) is the strip's next vertex and n = (B - A) x (C - A) is the
-// outward (unnormalised) normal of the original triangle (A, B, C), computed in
-// double from the float32 vertices and rounded once.  The factor 32 is a power
-// of two (exact) that folds the small-angle bound |N/D| < 1/32 into one
-// comparison.  The last word tells the two kinds apart: 0 in a head, > 0 in a
-// triangle (a degenerate cap triangle holds the smallest normal float).
-struct alignas(32) Rec32 {
-    float v[8];
-};
-
-// float64 stream, same record order, 64 bytes per record:
-//   head: { x0, y0, z0, x1, y1, z1, bits(m), 0 }
-//   tri : { x, y, z,  nx, ny, nz,  32 eps |B - A| |C - A| (enlarged),  sigma }
-// sigma = +1 when the strip order (v_i, v_{i+1}, v_{i+2}) is an even
-// permutation of (A, B, C), -1 otherwise; it orients the exact predicate.
-struct alignas(64) Rec64 {
-    double v[8];
+// A surface is stored as separate triangles (A, B, C), counter-clockwise seen
+// from outside, 48 bytes each, so that a lane reads one with three 16-byte loads
+// and needs no neighbour:
+//   { A, 32 nx, B, 32 ny, C, 32 nz }
+// n = (B - A) x (C - A), computed in double from the float32 vertices and
+// rounded once.  The factor 32 is a power of two (exact) that folds the
+// small-angle bound |N/D| < 1/32 into one comparison.
+struct alignas(16) TriRec {
+    float v[12];
 };
 
 // |N - N_exact| <= ~10 eps |c| |B - A||C - A| for the double triple product
-// N = (Z - p) . n; the FP64 records store 32 eps |B - A||C - A| (32 eps =
-// 2^-48, margin included) so the guard is one product: |N| <= |c| v[6].
+// N = (C - p) . n; a sign is taken as certain above 32 eps |c| |B - A||C - A|
+// (32 eps = 2^-48, margin included).
 constexpr double kGuardEps = 32.0 * 1.1102230246251565e-16;
-constexpr float kNScale = 32.0f;     // normal pre-scale in the float32 stream (a power of two)
-constexpr float kKnSmall = 5.0f;     // small-angle path needs D > 5 |n| r_Z + ...
+constexpr float kNScale = 32.0f;     // normal pre-scale of the records (a power of two)
+constexpr float kKnSmall = 5.0f;     // small-angle path needs D > 5 |n| r_C + ...
 constexpr int kMaxSurfaces = 64;     // per-point masks are 64-bit
 
 // Patch tree.  The triangles of a surface are grouped into spatially compact
@@ -54,14 +37,14 @@ constexpr int kMaxSurfaces = 64;     // per-point masks are 64-bit
 // patch with the opposite of any other surface over the same boundary loops (a
 // "cap") is closed, and a closed surface has winding number 0 at every point
 // outside its convex hull; so for a point outside the patch's box the cap's
-// solid angle equals the patch's.  A cap is a zigzag strip over each boundary
-// loop: about 3.2 sqrt(m) triangles for a patch of m.  Caps lie inside the
+// solid angle equals the patch's.  A cap zigzags over each boundary loop: about
+// 3.2 sqrt(m) triangles for a patch of m.  Caps lie inside the
 // patch's hull, and the box is enlarged by kCapMargin of its extent, so a point
 // outside it sees no cap triangle from close by (float32 certifies the terms).
 // Entry e of node w is ent[4 w + e]; an unused entry has leaf_n = 0.
 struct alignas(16) PatchEntry {
     float lo[3];
-    uint32_t cap_begin;    // cap strips: records [cap_begin, cap_begin + cap_n)
+    uint32_t cap_begin;    // the cap: records [cap_begin, cap_begin + cap_n)
     float hi[3];           // box of the patch's vertices, enlarged
     uint32_t cap_n;
     int32_t child;         // node of the patch's parts, -1 for a leaf
@@ -72,16 +55,14 @@ struct alignas(16) PatchEntry {
 // Record indices are relative to the surface's rec_begin, node indices to its
 // node_begin.
 
-// Leaf size: a leaf's records (triangles and strip heads) fit the 64 lanes of
-// one wavefront, and halving a mesh down to at most 56 leaves 28-56.
-constexpr int kLeafTri = 56;
+// Leaf size: the lanes of one wavefront.
+constexpr int kLeafTri = 64;
 constexpr double kCapMargin = 0.02;
 
 // Per-surface table in device memory.
 struct SurfaceDev {
-    int64_t rec_begin, rec_end;      // the surface's triangles: [begin, end) in both record
-                                     // streams (its caps follow)
-    int64_t strip_begin, strip_end;  // [begin, end) in the strip table
+    int64_t rec_begin, rec_end;      // the surface's triangles: records [begin, end)
+                                     // (its caps follow)
     int64_t node_begin;              // root node of the patch tree
     int64_t n_tri;
     int32_t label;
@@ -116,8 +97,7 @@ enum Counter {
 
 // One set of points against one surface set, as the kernels see it.
 struct LabelInst {
-    const Rec32 *rec32;
-    const Rec64 *rec64;
+    const TriRec *rec;
     const SurfaceDev *surf;
     const PatchEntry *ent;
     const float *x, *y, *z;
@@ -135,8 +115,8 @@ struct LabelInst {
     float lo[3], scale[3];        // cells of the spatial order: (p - lo) * scale
 };
 
-// Spatial order of the points (order.hip): two stable counting passes over a
-// Morton code, kOrderBits1 low bits first.
+// Spatial order of the points (order.hip): two stable counting passes over the
+// place on a Hilbert curve, kOrderBits1 low bits first.
 constexpr int kOrderBits1 = 11, kOrderBits2 = 10;   // 7 bits per axis
 constexpr int kOrderBins = 1 << kOrderBits1;
 constexpr int64_t kMinTile = 2048, kMaxTiles = 1024;   // per instance

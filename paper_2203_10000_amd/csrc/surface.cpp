@@ -1,5 +1,5 @@
 // Surface-set construction: validation of closed oriented manifolds, greedy
-// triangle strips, float32 / float64 strip records on the device.
+// patch trees and triangle records on the device.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -17,10 +17,6 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
     SurfaceRecords rec;
     sal_status st0 = build_surface_records(desc, n, flags, &rec);
     if (st0 != SAL_OK) return st0;
-    const std::vector<Rec32> &r32 = rec.r32;
-    const std::vector<Rec64> &r64 = rec.r64;
-    const std::vector<int64_t> &strip_off = rec.strip_off;
-    const std::vector<int32_t> &strip_tris = rec.strip_tris;
     const std::vector<SurfaceDev> &table = rec.table;
     const int64_t total_tri = rec.total_tri;
     SAL_HIP(hipSetDevice(ctx->device));
@@ -30,8 +26,7 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
     set->device = ctx->device;
     set->n_surf = n;
     set->n_tri = total_tri;
-    set->n_strips = (int64_t)strip_off.size();
-    set->n_rec = (int64_t)r32.size();
+    set->n_strips = rec.n_leaves;
     set->host_table = table;
     for (int c = 0; c < 3; ++c) {
         set->lo[c] = INFINITY;
@@ -41,7 +36,6 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
             set->hi[c] = std::max(set->hi[c], sd.hi[c]);
         }
     }
-    set->host_strip_tris = strip_tris;
     sal_status st = SAL_OK;
     auto up = [&](void **dst, const void *src, size_t bytes) -> sal_status {
         hipError_t e = dev_malloc(dst, bytes);
@@ -51,12 +45,9 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
         set->bytes += bytes;
         return SAL_OK;
     };
-    if ((st = up((void **)&set->rec32, r32.data(), r32.size() * sizeof(Rec32))) != SAL_OK ||
-        (st = up((void **)&set->rec64, r64.data(), r64.size() * sizeof(Rec64))) != SAL_OK ||
+    if ((st = up((void **)&set->rec, rec.recs.data(), rec.recs.size() * sizeof(TriRec))) != SAL_OK ||
         (st = up((void **)&set->surf, table.data(), table.size() * sizeof(SurfaceDev))) != SAL_OK ||
-        (st = up((void **)&set->ent, rec.entries.data(), rec.entries.size() * sizeof(PatchEntry))) != SAL_OK ||
-        (st = up((void **)&set->strip_off, strip_off.data(), strip_off.size() * sizeof(int64_t))) !=
-            SAL_OK) {
+        (st = up((void **)&set->ent, rec.entries.data(), rec.entries.size() * sizeof(PatchEntry))) != SAL_OK) {
         destroy_surface_set(set);
         return st;
     }
@@ -111,11 +102,9 @@ sal_status ensure_surface_balls(sal_context *ctx, const sal_surface_set *cset) {
 void destroy_surface_set(sal_surface_set *set) {
     if (!set) return;
     (void)hipSetDevice(set->device);
-    if (set->rec32) (void)hipFree(set->rec32);
-    if (set->rec64) (void)hipFree(set->rec64);
+    if (set->rec) (void)hipFree(set->rec);
     if (set->surf) (void)hipFree(set->surf);
     if (set->ent) (void)hipFree(set->ent);
-    if (set->strip_off) (void)hipFree(set->strip_off);
     delete set;
 }
 

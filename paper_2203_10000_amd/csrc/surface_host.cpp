@@ -1,10 +1,9 @@
 // Host side of surface-set construction, with no device call: validation
-// of closed oriented manifolds, the patch tree with its caps, greedy triangle
-// strips, the float32 / float64 strip records and the per-surface table.  Kept apart from the
+// of closed oriented manifolds, the patch tree with its caps, the triangle
+// records and the per-surface table.  Kept apart from the
 // upload so that validation runs (and is tested) without a GPU.
 #include <algorithm>
 #include <array>
-#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -27,13 +26,6 @@ struct HostSurface {
 
     int32_t from(uint32_t h) const { return tri[h]; }
     int32_t to(uint32_t h) const { return tri[h % 3 == 2 ? h - 2 : h + 1]; }
-};
-
-// One strip: the vertex sequence and, per triangle, its corners in the
-// outward order.
-struct Strip {
-    std::vector<int32_t> verts;
-    std::vector<std::array<int32_t, 3>> tris;
 };
 
 // A directed edge used twice among the first n_tri triangles?
@@ -156,30 +148,31 @@ sal_status validate(HostSurface &s, int idx, bool auto_orient) {
     return SAL_OK;
 }
 
-// Builds one surface's patch tree, its strips and the caps' strips.
+// Builds one surface's patch tree: the order of its triangles and the caps.
 class PatchBuilder {
 public:
     explicit PatchBuilder(const HostSurface &s) : s_(s) {}
 
-    std::vector<Strip> strips;        // every leaf's strips, leaf by leaf
-    std::vector<Strip> caps;          // every cap's strips, patch by patch
-    std::vector<PatchEntry> entries;  // 4 per node; record ranges filled by place()
+    typedef std::array<int32_t, 3> Corners;
+
+    std::vector<int32_t> order;       // triangles, leaf by leaf: their records
+    std::vector<Corners> caps;        // the caps' triangles, patch by patch: the records after
+    std::vector<PatchEntry> entries;  // 4 per node
+    int64_t n_leaves = 0;
 
     void build() {
         const int64_t nt = s_.nt;
-        order_.resize((size_t)nt);
+        order.resize((size_t)nt);
         cen_.resize((size_t)(3 * nt));
         for (int64_t t = 0; t < nt; ++t) {
-            order_[(size_t)t] = (int32_t)t;
+            order[(size_t)t] = (int32_t)t;
             for (int c = 0; c < 3; ++c) {
                 float sum = 0.0f;
                 for (int q = 0; q < 3; ++q) sum += s_.xyz[3 * (int64_t)s_.tri[(size_t)(3 * t + q)] + c] / 3.0f;
                 cen_[(size_t)(3 * t + c)] = sum;
             }
         }
-        pos_.assign((size_t)nt, 0);
-        used_.assign((size_t)nt, 0);
-        stamp_.assign((size_t)nt, -1);
+        pos_.assign((size_t)nt, -1);
         first_out_.assign((size_t)s_.nv, -1);
         on_path_.assign((size_t)s_.nv, -1);
         new_node();
@@ -188,31 +181,7 @@ public:
         else split(0, 0, nt, &none);
     }
 
-    // The record ranges of the entries: strips in order from record 0, the
-    // caps from record n_rec.  A cap no shorter than its patch is not kept.
-    void place(uint32_t n_rec) {
-        std::vector<uint32_t> at((size_t)strips.size() + 1, 0), cap_at((size_t)caps.size() + 1, n_rec);
-        for (size_t i = 0; i < strips.size(); ++i) at[i + 1] = at[i] + 1 + (uint32_t)strips[i].tris.size();
-        for (size_t i = 0; i < caps.size(); ++i) cap_at[i + 1] = cap_at[i] + 1 + (uint32_t)caps[i].tris.size();
-        for (size_t e = 0; e < entries.size(); ++e) {
-            const Range &r = range_[e];
-            entries[e].leaf_begin = at[r.strip0];
-            entries[e].leaf_n = at[r.strip1] - at[r.strip0];
-            if (r.cap1 < r.cap0) {
-                entries[e].cap_begin = entries[e].leaf_begin;
-                entries[e].cap_n = entries[e].leaf_n;
-            } else {
-                entries[e].cap_begin = cap_at[r.cap0];
-                entries[e].cap_n = cap_at[r.cap1] - cap_at[r.cap0];
-            }
-        }
-    }
-
 private:
-    struct Range {
-        size_t strip0 = 0, strip1 = 0;
-        size_t cap0 = 0, cap1 = 0;   // cap1 < cap0: the patch itself
-    };
     struct Box {
         float lo[3], hi[3];
     };
@@ -226,16 +195,15 @@ private:
         }
         unused.child = -1;
         entries.insert(entries.end(), 4, unused);
-        range_.insert(range_.end(), 4, Range{});
         return w;
     }
 
-    // Halves order_[b, e) at the median of the centroids' longest extent.
+    // Halves order[b, e) at the median of the centroids' longest extent.
     int64_t halve(int64_t b, int64_t e) {
         float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
         for (int64_t i = b; i < e; ++i)
             for (int c = 0; c < 3; ++c) {
-                const float x = cen_[3 * (size_t)order_[(size_t)i] + c];
+                const float x = cen_[3 * (size_t)order[(size_t)i] + c];
                 lo[c] = std::min(lo[c], x);
                 hi[c] = std::max(hi[c], x);
             }
@@ -243,7 +211,7 @@ private:
         for (int c = 1; c < 3; ++c)
             if (hi[c] - lo[c] > hi[ax] - lo[ax]) ax = c;
         const int64_t m = b + (e - b) / 2;
-        std::nth_element(order_.begin() + b, order_.begin() + m, order_.begin() + e,
+        std::nth_element(order.begin() + b, order.begin() + m, order.begin() + e,
                          [&](int32_t p, int32_t q) {
                              const float x = cen_[3 * (size_t)p + ax], y = cen_[3 * (size_t)q + ax];
                              return x != y ? x < y : p < q;
@@ -251,7 +219,7 @@ private:
         return m;
     }
 
-    // Parts of order_[b, e) (more than a leaf): the entries of node w.  The
+    // Parts of order[b, e) (more than a leaf): the entries of node w.  The
     // patch's boundary half-edges go to *rim, its box is returned.
     Box split(int32_t w, int64_t b, int64_t e, std::vector<uint32_t> *rim) {
         int64_t cut[5] = {b, 0, 0, 0, 0};
@@ -272,12 +240,9 @@ private:
                 pb = leaf(ent, cut[k], cut[k + 1], &part_rim);
             } else {
                 const int32_t child = new_node();
-                const size_t strip0 = strips.size();
                 pb = split(child, cut[k], cut[k + 1], &part_rim);
                 entries[ent].child = child;
-                range_[ent].strip0 = strip0;
-                range_[ent].strip1 = strips.size();
-                cap(ent, part_rim, cut[k + 1] - cut[k]);
+                cap(ent, part_rim, cut[k], cut[k + 1] - cut[k]);
                 set_box(ent, pb);
             }
             for (int c = 0; c < 3; ++c) {
@@ -287,14 +252,11 @@ private:
             edges.insert(edges.end(), part_rim.begin(), part_rim.end());
         }
         for (const uint32_t h : edges) {
-            const int64_t at = pos_[s_.twin[h] / 3];
-            // (a triangle not placed yet has position 0 and lies outside)
-            if (!placed(s_.twin[h] / 3) || at < b || at >= e) rim->push_back(h);
+            const int64_t at = pos_[s_.twin[h] / 3];   // (-1: in a patch still to come)
+            if (at < b || at >= e) rim->push_back(h);
         }
         return box;
     }
-
-    bool placed(uint32_t t) const { return used_[t] != 0; }
 
     static Box no_box() {
         return Box{{INFINITY, INFINITY, INFINITY}, {-INFINITY, -INFINITY, -INFINITY}};
@@ -302,9 +264,9 @@ private:
 
     Box leaf(size_t ent, int64_t b, int64_t e, std::vector<uint32_t> *rim) {
         Box box = no_box();
-        std::sort(order_.begin() + b, order_.begin() + e);
+        std::sort(order.begin() + b, order.begin() + e);
         for (int64_t i = b; i < e; ++i) {
-            const int32_t t = order_[(size_t)i];
+            const int32_t t = order[(size_t)i];
             pos_[(size_t)t] = (int32_t)i;
             for (int q = 0; q < 3; ++q)
                 for (int c = 0; c < 3; ++c) {
@@ -313,17 +275,14 @@ private:
                     box.hi[c] = std::max(box.hi[c], x);
                 }
         }
-        leaf_id_ = (int32_t)ent;
-        for (int64_t i = b; i < e; ++i) member_mark(order_[(size_t)i]);
-        range_[ent].strip0 = strips.size();
-        make_strips(b, e);
-        range_[ent].strip1 = strips.size();
         for (int64_t i = b; i < e; ++i)
             for (int c = 0; c < 3; ++c) {
-                const uint32_t h = 3 * (uint32_t)order_[(size_t)i] + (uint32_t)c;
-                if (!in_leaf((int32_t)(s_.twin[h] / 3))) rim->push_back(h);
+                const uint32_t h = 3 * (uint32_t)order[(size_t)i] + (uint32_t)c;
+                const int64_t at = pos_[s_.twin[h] / 3];
+                if (at < b || at >= e) rim->push_back(h);
             }
-        cap(ent, *rim, e - b);
+        ++n_leaves;
+        cap(ent, *rim, b, e - b);
         set_box(ent, box);
         return box;
     }
@@ -338,92 +297,18 @@ private:
         }
     }
 
-    // The leaf being built: its triangles carry its entry index.
-    void member_mark(int32_t t) {
-        if (member_.empty()) member_.assign((size_t)s_.nt, -1);
-        member_[(size_t)t] = leaf_id_;
-    }
-    bool in_leaf(int32_t t) const { return member_[(size_t)t] == leaf_id_; }
-
-    // The half-edge of triangle t between vertices a and b, in either direction.
-    uint32_t edge_of(int32_t t, int32_t a, int32_t b) const {
-        for (uint32_t c = 0; c < 3; ++c) {
-            const uint32_t h = 3 * (uint32_t)t + c;
-            const int32_t p = s_.from(h), q = s_.to(h);
-            if ((p == a && q == b) || (p == b && q == a)) return h;
-        }
-        return 3 * (uint32_t)t;
-    }
-    int32_t third(int32_t t, int32_t a, int32_t b) const {
-        for (int c = 0; c < 3; ++c) {
-            const int32_t v = s_.tri[3 * (size_t)t + c];
-            if (v != a && v != b) return v;
-        }
-        return -1;
-    }
-
-    // Greedy strips over the leaf's triangles: from each unused seed triangle
-    // try the three rotations, walk across the edge formed by the two newest
-    // vertices while the next triangle is unused, and keep the longest walk.
-    void make_strips(int64_t b, int64_t e) {
-        for (int64_t i = b; i < e; ++i) {
-            const int32_t seed = order_[(size_t)i];
-            if (used_[(size_t)seed]) continue;
-            int best_rot = 0;
-            int64_t best_len = -1;
-            for (int rot = 0; rot < 3; ++rot) {
-                ++attempt_;
-                int32_t y = s_.tri[3 * (size_t)seed + (rot + 1) % 3], z = s_.tri[3 * (size_t)seed + (rot + 2) % 3];
-                int32_t cur = seed;
-                stamp_[(size_t)cur] = attempt_;
-                int64_t len = 1;
-                for (;;) {
-                    const int32_t nb = (int32_t)(s_.twin[edge_of(cur, y, z)] / 3);
-                    if (!in_leaf(nb) || used_[(size_t)nb] || stamp_[(size_t)nb] == attempt_) break;
-                    stamp_[(size_t)nb] = attempt_;
-                    const int32_t w = third(nb, y, z);
-                    y = z;
-                    z = w;
-                    cur = nb;
-                    ++len;
-                }
-                if (len > best_len) { best_len = len; best_rot = rot; }
-            }
-            Strip st;
-            int32_t y = s_.tri[3 * (size_t)seed + (best_rot + 1) % 3], z = s_.tri[3 * (size_t)seed + (best_rot + 2) % 3];
-            st.verts = {s_.tri[3 * (size_t)seed + best_rot], y, z};
-            st.tris.push_back(corners(seed));
-            used_[(size_t)seed] = 1;
-            int32_t cur = seed;
-            for (;;) {
-                const int32_t nb = (int32_t)(s_.twin[edge_of(cur, y, z)] / 3);
-                if (!in_leaf(nb) || used_[(size_t)nb]) break;
-                used_[(size_t)nb] = 1;
-                const int32_t w = third(nb, y, z);
-                st.verts.push_back(w);
-                st.tris.push_back(corners(nb));
-                y = z;
-                z = w;
-                cur = nb;
-            }
-            strips.push_back(std::move(st));
-        }
-    }
-    std::array<int32_t, 3> corners(int32_t t) const {
-        return {s_.tri[3 * (size_t)t], s_.tri[3 * (size_t)t + 1], s_.tri[3 * (size_t)t + 2]};
-    }
-
-    // The cap of a patch of n_tri triangles with boundary half-edges `rim`:
-    // the rim is cut into simple loops, each closed by a zigzag strip with the
-    // patch's own direction along the loop.
-    void cap(size_t ent, const std::vector<uint32_t> &rim, int64_t n_tri) {
-        range_[ent].cap0 = caps.size();
-        range_[ent].cap1 = caps.size();
-        if ((int64_t)rim.size() >= n_tri) {
-            range_[ent].cap0 = 1;   // no shorter than the patch
-            range_[ent].cap1 = 0;
-            return;
-        }
+    // The record ranges of a patch, triangles [begin, begin + n_tri), and its cap:
+    // the boundary half-edges `rim` are cut into simple loops, each closed by a
+    // zigzag with the patch's own direction along the loop.  A cap no shorter
+    // than the patch is not kept.
+    void cap(size_t ent, const std::vector<uint32_t> &rim, int64_t begin, int64_t n_tri) {
+        PatchEntry &pe = entries[ent];
+        pe.leaf_begin = (uint32_t)begin;
+        pe.leaf_n = (uint32_t)n_tri;
+        pe.cap_begin = pe.leaf_begin;
+        pe.cap_n = pe.leaf_n;
+        if ((int64_t)rim.size() >= n_tri) return;
+        const size_t cap0 = caps.size();
         next_out_.assign(rim.size(), -1);
         for (size_t i = 0; i < rim.size(); ++i) {
             int32_t &head = first_out_[(size_t)s_.from(rim[i])];
@@ -456,43 +341,29 @@ private:
             }
             for (const int32_t v : path) on_path_[(size_t)v] = -1;
         }
-        range_[ent].cap1 = caps.size();
+        pe.cap_begin = (uint32_t)(s_.nt + (int64_t)cap0);
+        pe.cap_n = (uint32_t)(caps.size() - cap0);
     }
 
-    // Loop v_0 -> v_1 -> ... -> v_{L-1}: strip v_0, v_1, v_{L-1}, v_2, v_{L-2},
+    // Loop v_0 -> v_1 -> ... -> v_{L-1}: the strip v_0, v_1, v_{L-1}, v_2, v_{L-2},
     // ...; its even triangles are outward in strip order, its odd ones reversed.
     void zigzag(const int32_t *v, int64_t L) {
-        if (L < 3) return;
-        Strip st;
         int64_t i = 1, j = L - 1;
-        st.verts = {v[0], v[1]};
+        int32_t x = v[0], y = v[1];
         for (int64_t t = 0; t < L - 2; ++t) {
             const int32_t z = (t & 1) == 0 ? v[j--] : v[++i];
-            const int32_t x = st.verts[(size_t)t], y = st.verts[(size_t)t + 1];
-            st.verts.push_back(z);
-            if ((t & 1) == 0) st.tris.push_back({x, y, z});
-            else st.tris.push_back({x, z, y});
+            if ((t & 1) == 0) caps.push_back({x, y, z});
+            else caps.push_back({x, z, y});
+            x = y;
+            y = z;
         }
-        caps.push_back(std::move(st));
     }
 
     const HostSurface &s_;
-    std::vector<int32_t> order_;      // triangles, patch by patch
     std::vector<float> cen_;
-    std::vector<int32_t> pos_;        // position of a placed triangle in order_
-    std::vector<uint8_t> used_;       // triangles already in a strip
-    std::vector<int32_t> stamp_, member_;
-    std::vector<Range> range_;
+    std::vector<int32_t> pos_;        // a triangle's place in `order` once its leaf is built
     std::vector<int32_t> first_out_, next_out_, on_path_;
-    int32_t attempt_ = 0, leaf_id_ = -1;
 };
-
-// +1 when (p, q, r) is a rotation of the triangle's stored order, else -1.
-double parity(const std::array<int32_t, 3> &f, int32_t p, int32_t q, int32_t r) {
-    for (int c = 0; c < 3; ++c)
-        if (f[c] == p && f[(c + 1) % 3] == q && f[(c + 2) % 3] == r) return 1.0;
-    return -1.0;
-}
 
 // Squared distance from p to triangle (a, b, c), in double: the closest
 // point found by the Voronoi-region walk over vertices, edges and face
@@ -551,51 +422,20 @@ double dist2_point_triangle(const double p[3], const double a[3], const double b
     return dot(d, d);
 }
 
-// The records of one strip, appended to both streams.
-void append_strip(const float *V, const Strip &s, std::vector<Rec32> &r32, std::vector<Rec64> &r64) {
-    const int m = (int)s.tris.size();
-    Rec32 h32{};
-    Rec64 h64{};
-    for (int c = 0; c < 3; ++c) {
-        h32.v[c] = V[3 * (int64_t)s.verts[0] + c];
-        h32.v[3 + c] = V[3 * (int64_t)s.verts[1] + c];
-        h64.v[c] = h32.v[c];
-        h64.v[3 + c] = h32.v[3 + c];
+TriRec record(const float *V, int32_t a, int32_t b, int32_t c) {
+    const float *A = V + 3 * (int64_t)a, *B = V + 3 * (int64_t)b, *C = V + 3 * (int64_t)c;
+    const double e1[3] = {(double)B[0] - A[0], (double)B[1] - A[1], (double)B[2] - A[2]};
+    const double e2[3] = {(double)C[0] - A[0], (double)C[1] - A[1], (double)C[2] - A[2]};
+    const double n[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
+                         e1[0] * e2[1] - e1[1] * e2[0]};
+    TriRec r;
+    for (int k = 0; k < 3; ++k) {
+        r.v[k] = A[k];
+        r.v[4 + k] = B[k];
+        r.v[8 + k] = C[k];
+        r.v[4 * k + 3] = (float)(kNScale * n[k]);
     }
-    int32_t mi = m;
-    std::memcpy(&h32.v[6], &mi, 4);
-    int64_t ml = m;
-    std::memcpy(&h64.v[6], &ml, 8);
-    r32.push_back(h32);
-    r64.push_back(h64);
-    for (int t = 0; t < m; ++t) {
-        const std::array<int32_t, 3> &f = s.tris[(size_t)t];
-        const float *A = V + 3 * (int64_t)f[0], *B = V + 3 * (int64_t)f[1], *C = V + 3 * (int64_t)f[2];
-        const double e1[3] = {(double)B[0] - A[0], (double)B[1] - A[1], (double)B[2] - A[2]};
-        const double e2[3] = {(double)C[0] - A[0], (double)C[1] - A[1], (double)C[2] - A[2]};
-        const double nn[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                              e1[0] * e2[1] - e1[1] * e2[0]};
-        const double nlen = std::sqrt(nn[0] * nn[0] + nn[1] * nn[1] + nn[2] * nn[2]);
-        const double nb = std::sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]) *
-                          std::sqrt(e2[0] * e2[0] + e2[1] * e2[1] + e2[2] * e2[2]);
-        const int64_t z = s.verts[(size_t)t + 2];
-        Rec32 q32{};
-        Rec64 q64{};
-        for (int c = 0; c < 3; ++c) {
-            q32.v[c] = V[3 * z + c];
-            q32.v[3 + c] = (float)(kNScale * nn[c]);
-            q64.v[c] = V[3 * z + c];
-            q64.v[3 + c] = nn[c];
-        }
-        q32.v[6] = (float)nlen;
-        q32.v[7] = std::max((float)(kKnSmall * nlen), FLT_MIN);   // > 0 marks a triangle
-        // the exact-sign guard's bound factor: 32 eps |B - A||C - A| (a
-        // power-of-two scaling, so exact), slightly enlarged
-        q64.v[6] = kGuardEps * (nb * (1.0 + 1e-12));
-        q64.v[7] = parity(f, s.verts[(size_t)t], s.verts[(size_t)t + 1], s.verts[(size_t)t + 2]);
-        r32.push_back(q32);
-        r64.push_back(q64);
-    }
+    return r;
 }
 
 }  // namespace
@@ -606,17 +446,12 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
     if (!desc || !rec) return set_error(SAL_ERR_INVALID_ARG, "NULL argument");
     if (n < 1 || n > kMaxSurfaces)
         return set_error(SAL_ERR_INVALID_ARG, "n_surfaces must be in 1..64");
-    std::vector<Rec32> &r32 = rec->r32;
-    std::vector<Rec64> &r64 = rec->r64;
-    std::vector<int64_t> &strip_off = rec->strip_off;
-    std::vector<int32_t> &strip_tris = rec->strip_tris;
+    std::vector<TriRec> &recs = rec->recs;
     std::vector<SurfaceDev> &table = rec->table;
     std::vector<PatchEntry> &entries = rec->entries;
+    recs.clear();
     entries.clear();
-    r32.clear();
-    r64.clear();
-    strip_off.clear();
-    strip_tris.clear();
+    rec->n_leaves = 0;
     table.assign((size_t)n, SurfaceDev{});
     int64_t &total_tri = rec->total_tri;
     total_tri = 0;
@@ -635,8 +470,7 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
         PatchBuilder patches(hs);
         patches.build();
         SurfaceDev &sd = table[(size_t)i];
-        sd.rec_begin = (int64_t)r32.size();
-        sd.strip_begin = (int64_t)strip_off.size();
+        sd.rec_begin = (int64_t)recs.size();
         sd.n_tri = hs.nt;
         sd.label = hs.label;
         sd.pad = 0;
@@ -675,15 +509,12 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
             sd.pad2 = 0;
         }
         total_tri += hs.nt;
-        for (const Strip &strip : patches.strips) {
-            strip_off.push_back((int64_t)r32.size());
-            strip_tris.push_back((int32_t)strip.tris.size());
-            append_strip(hs.xyz, strip, r32, r64);
-        }
-        sd.rec_end = (int64_t)r32.size();
-        sd.strip_end = (int64_t)strip_off.size();
-        patches.place((uint32_t)(sd.rec_end - sd.rec_begin));
-        for (const Strip &strip : patches.caps) append_strip(hs.xyz, strip, r32, r64);
+        recs.reserve(recs.size() + patches.order.size() + patches.caps.size());
+        for (const int32_t t : patches.order)
+            recs.push_back(record(hs.xyz, hs.tri[3 * (size_t)t], hs.tri[3 * (size_t)t + 1], hs.tri[3 * (size_t)t + 2]));
+        sd.rec_end = (int64_t)recs.size();
+        for (const auto &c : patches.caps) recs.push_back(record(hs.xyz, c[0], c[1], c[2]));
+        rec->n_leaves += patches.n_leaves;
         sd.node_begin = (int64_t)(entries.size() / 4);
         entries.insert(entries.end(), patches.entries.begin(), patches.entries.end());
     }
@@ -701,12 +532,10 @@ extern "C" sal_status sal_surface_set_check(const sal_surface_desc *surfaces, in
         if (info) {
             info->n_surfaces = n_surfaces;
             info->n_triangles = rec.total_tri;
-            info->n_strips = (int64_t)rec.strip_off.size();
-            info->device_bytes = (int64_t)(rec.r32.size() * sizeof(sal::Rec32) +
-                                           rec.r64.size() * sizeof(sal::Rec64) +
+            info->n_strips = rec.n_leaves;
+            info->device_bytes = (int64_t)(rec.recs.size() * sizeof(sal::TriRec) +
                                            rec.table.size() * sizeof(sal::SurfaceDev) +
-                                           rec.entries.size() * sizeof(sal::PatchEntry) +
-                                           rec.strip_off.size() * sizeof(int64_t));
+                                           rec.entries.size() * sizeof(sal::PatchEntry));
         }
         return SAL_OK;
     } catch (const std::bad_alloc &) {

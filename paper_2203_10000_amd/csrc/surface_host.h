@@ -8,17 +8,13 @@
 
 namespace sal {
 
-// Everything a surface set uploads: strip records in both precisions (each
-// surface's triangles, then its caps), the patch tree, the record index and
-// triangle count of every strip of triangles, and the per-surface table.
+// Everything a surface set uploads: triangle records (each surface's
+// triangles, then its caps), the patch trees and the per-surface table.
 struct SurfaceRecords {
-    std::vector<Rec32> r32;
-    std::vector<Rec64> r64;
-    std::vector<int64_t> strip_off;
-    std::vector<int32_t> strip_tris;
+    std::vector<TriRec> recs;
     std::vector<SurfaceDev> table;
     std::vector<PatchEntry> entries;   // four per node
-    int64_t total_tri = 0;
+    int64_t total_tri = 0, n_leaves = 0;
 };
 
 // Validates the surfaces (section 2.1.3: closed, consistently oriented

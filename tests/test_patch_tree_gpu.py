@@ -14,7 +14,8 @@ import paper_2203_10000_amd as sal  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-POINT_FORM_MAX = 8192
+POINT_FORM_MAX = 16384         # of label_points
+BATCH_POINT_MAX = 8192         # of a batch's instance
 TOL = {"fp32": 1e-5, "fp64": 1e-12}   # the forms' stated bounds on winding numbers
 
 
@@ -114,7 +115,7 @@ def test_points_too_far_apart_for_a_common_walk(ctx, precision):
     ss = sal.SurfaceSet(ctx, [surf])
     rng = np.random.default_rng(4)
     outs = []
-    for n in (POINT_FORM_MAX, POINT_FORM_MAX + 1):
+    for n in (BATCH_POINT_MAX, BATCH_POINT_MAX + 1):
         pts = rng.uniform(-80.0, 80.0, (3, n)).astype(np.float32)
         lab = torch.full((n,), -7, dtype=torch.int32, device="cuda")
         outs.append((pts, lab))
