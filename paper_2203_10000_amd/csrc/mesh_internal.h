@@ -160,6 +160,30 @@ hipError_t launch_node_ids(const int64_t *tet_keys, int64_t n, const int64_t *no
 hipError_t launch_node_xyz(const LatticeGeom &g, const int64_t *nodes, int64_t n, float *xyz,
                            hipStream_t s);
 
+// Checkpoint import (import.hip).
+struct ImportTables {
+    unsigned long long *leaf;    // [leaf_cap] keys of the leaves (open addressing, ~0 empty)
+    int32_t *label;              // [leaf_cap]
+    int64_t leaf_cap;
+    unsigned long long *inner;   // [inner_cap] keys of the refined tetrahedra
+    int64_t inner_cap;
+};
+// What is wrong with a leaf set.  first: (index << 2) | reason of the first leaf
+// that is no leaf of the lattice (0: level or permutation, 1: outside, 2: no
+// label), ~0 when there is none; bits: faults of the set as a whole.
+struct ImportFaults {
+    unsigned long long first;
+    unsigned int bits, pad;
+};
+enum { kFaultTwice = 0, kFaultChildren = 1, kFaultBoth = 2, kFaultCover = 3 };
+hipError_t launch_import_insert(const uint64_t *keys, const int32_t *labels, int64_t n, const LatticeGeom &g,
+                                const ChildTables &T, const ImportTables &t, ImportFaults *f, hipStream_t s);
+hipError_t launch_import_lattice(const LevelPtrs &L, const LatticeGeom &g, int64_t n0, const ImportTables &t,
+                                 ImportFaults *f, hipStream_t s);
+hipError_t launch_import_children(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
+                                  const int32_t *list, int64_t count, const ImportTables &t, ImportFaults *f,
+                                  hipStream_t s);
+
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s);
 
