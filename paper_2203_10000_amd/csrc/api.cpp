@@ -1,5 +1,4 @@
 // C-ABI entry points: contexts, surface sets, point labeling.
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -14,21 +13,6 @@ static thread_local std::string g_last_error;
 sal_status set_error(sal_status s, const std::string &msg) {
     g_last_error = msg;
     return s;
-}
-
-// Allocation fault injection (sal_debug_fail_allocation): the countdown is
-// the number of allocations left before the one that fails; 0 = off.
-static std::atomic<int64_t> g_fail_countdown{0};
-
-hipError_t dev_malloc(void **ptr, size_t bytes) {
-    int64_t c = g_fail_countdown.load();
-    while (c > 0 && !g_fail_countdown.compare_exchange_weak(c, c - 1)) {
-    }
-    if (c == 1) {
-        if (ptr) *ptr = nullptr;
-        return hipErrorOutOfMemory;
-    }
-    return hipMalloc(ptr, bytes);
 }
 
 sal_status hip_error(hipError_t e, const char *what) {
@@ -237,7 +221,7 @@ const char *sal_last_error_message(void) { return g_last_error.c_str(); }
 
 int sal_abi_version(void) { return SAL_ABI_VERSION; }
 
-void sal_debug_fail_allocation(int64_t n) { g_fail_countdown.store(n > 0 ? n : 0); }
+void sal_debug_fail_allocation(int64_t n) { sal::fail_allocation(n); }
 
 void sal_label_options_default(sal_label_options *o) {
     if (!o) return;
@@ -265,6 +249,7 @@ sal_status sal_context_create(int device, void *stream, sal_context **out) {
     SAL_HIP(hipSetDevice(device));
     auto *ctx = new sal_context();
     ctx->device = device;
+    pool_add_context();
     ctx->stream = (hipStream_t)stream;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->n_cu = prop.multiProcessorCount;
@@ -292,6 +277,7 @@ sal_status sal_context_create(int device, void *stream, sal_context **out) {
 sal_status sal_context_set_stream(sal_context *ctx, void *stream) {
     if (!ctx) return set_error(SAL_ERR_INVALID_ARG, "ctx is NULL");
     ctx->stream = (hipStream_t)stream;
+    ctx->stream_token = new_stream_token();
     return SAL_OK;
 }
 
@@ -308,6 +294,7 @@ void sal_context_destroy(sal_context *ctx) {
     for (void *p : bufs)
         if (p) (void)hipFree(p);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
+    pool_remove_context();
     delete ctx;
 }
 

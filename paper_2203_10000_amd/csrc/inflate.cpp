@@ -13,13 +13,16 @@ namespace sal {
 namespace {
 
 struct Buffers {
+    uint64_t token;
     std::vector<void *> p;
+    explicit Buffers(uint64_t t) : token(t) {}
+    Buffers(const Buffers &) = delete;
     ~Buffers() {
-        for (void *q : p) (void)hipFree(q);
+        for (void *q : p) pool_free(q, token);
     }
     template <typename T>
     sal_status get(T **out, int64_t n) {
-        if (dev_malloc((void **)out, (size_t)std::max<int64_t>(n, 1) * sizeof(T)) != hipSuccess)
+        if (pool_malloc((void **)out, (size_t)std::max<int64_t>(n, 1) * sizeof(T), token) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(inflation)");
         p.push_back(*out);
         return SAL_OK;
@@ -46,7 +49,7 @@ sal_status sal_tet_mesh_inflate(sal_context *ctx, sal_tet_mesh *m, const sal_sur
             return set_error(SAL_ERR_INVALID_ARG, "mesh or surfaces live on another device");
         if (!(zeta >= 0.0 && zeta < 1.0)) return set_error(SAL_ERR_INVALID_ARG, "zeta must lie in [0, 1)");
         ConformView v{};
-        if (!conform_view(m, &v)) return set_error(SAL_ERR_INVALID_ARG, "call sal_tet_mesh_conform first");
+        if (!conform_view(ctx, m, &v)) return set_error(SAL_ERR_INVALID_ARG, "call sal_tet_mesh_conform first");
         const int64_t n_bins = (int64_t)v.g.cells[0] * v.g.cells[1] * v.g.cells[2];
         if (n_bins + 1 > INT32_MAX) return set_error(SAL_ERR_CAPACITY, "inflation: too many lattice cells");
         SAL_HIP(hipSetDevice(ctx->device));
@@ -55,7 +58,7 @@ sal_status sal_tet_mesh_inflate(sal_context *ctx, sal_tet_mesh *m, const sal_sur
         SAL_HIP(hipEventRecord(ctx->ev[0], s));
         if ((st = ensure_smooth_graph(v, s)) != SAL_OK) return st;
         SmoothCache *c = *v.cache;
-        Buffers b;
+        Buffers b(v.token);
         const int64_t n_tri = set->n_tri;
         float *tri = nullptr;
         if ((st = b.get(&tri, 9 * n_tri)) != SAL_OK) return st;

@@ -48,6 +48,7 @@ static ChildTables make_child_tables() {
 
 struct sal_tet_mesh {
     int device = 0;
+    uint64_t token = 0;   // the stream order of the call at work on the mesh
     sal::LatticeGeom g{};
     sal::ChildTables T{};
     int64_t n[sal::kMaxLevels + 1] = {};
@@ -122,15 +123,22 @@ sal::LevelPtrs ptrs(const sal_tet_mesh *m) {
 }
 
 template <typename T>
-sal_status grow(T **p, int64_t old_n, int64_t new_cap, hipStream_t s) {
+hipError_t mesh_malloc(const sal_tet_mesh *m, T **p, int64_t n) {
+    return pool_malloc((void **)p, (size_t)n * sizeof(T), m->token);
+}
+
+template <typename T>
+sal_status grow(const sal_tet_mesh *m, T **p, int64_t old_n, int64_t new_cap, hipStream_t s) {
     T *q = nullptr;
-    SAL_HIP(dev_malloc((void **)&q, (size_t)new_cap * sizeof(T)));
-    if (*p && old_n > 0)
-        SAL_HIP(hipMemcpyAsync(q, *p, (size_t)old_n * sizeof(T), hipMemcpyDeviceToDevice, s));
-    if (*p) {
-        SAL_HIP(hipStreamSynchronize(s));
-        SAL_HIP(hipFree(*p));
+    SAL_HIP(mesh_malloc(m, &q, new_cap));
+    if (*p && old_n > 0) {
+        const hipError_t e = hipMemcpyAsync(q, *p, (size_t)old_n * sizeof(T), hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) {
+            pool_free(q, m->token);
+            return hip_error(e, "copy of a grown buffer");
+        }
     }
+    pool_free(*p, m->token);   // (what reads it is ahead in the stream)
     *p = q;
     return SAL_OK;
 }
@@ -140,22 +148,22 @@ sal_status ensure_level(sal_tet_mesh *m, int l, int64_t need, hipStream_t s) {
     int64_t cap = m->cap[l] + m->cap[l] / 2;
     if (cap < need) cap = need;
     sal_status st;
-    if (l > 0 && (st = grow(&m->key[l], m->n[l], cap, s)) != SAL_OK) return st;
-    if ((st = grow(&m->label[l], m->n[l], cap, s)) != SAL_OK) return st;
-    if ((st = grow(&m->child[l], m->n[l], cap, s)) != SAL_OK) return st;
-    if ((st = grow(&m->flag[l], m->n[l], cap, s)) != SAL_OK) return st;
+    if (l > 0 && (st = grow(m, &m->key[l], m->n[l], cap, s)) != SAL_OK) return st;
+    if ((st = grow(m, &m->label[l], m->n[l], cap, s)) != SAL_OK) return st;
+    if ((st = grow(m, &m->child[l], m->n[l], cap, s)) != SAL_OK) return st;
+    if ((st = grow(m, &m->flag[l], m->n[l], cap, s)) != SAL_OK) return st;
     if (l > 0 && m->rule == SAL_RULE_FOUR_NODES &&
-        (st = grow(&m->vmask[l], 4 * m->n[l], 4 * cap, s)) != SAL_OK)
+        (st = grow(m, &m->vmask[l], 4 * m->n[l], 4 * cap, s)) != SAL_OK)
         return st;
     m->cap[l] = cap;
     return SAL_OK;
 }
 
 template <typename T>
-sal_status ensure_buf(T **p, int64_t *cap, int64_t need, hipStream_t s) {
+sal_status ensure_buf(const sal_tet_mesh *m, T **p, int64_t *cap, int64_t need, hipStream_t s) {
     if (need <= *cap) return SAL_OK;
     const int64_t c = need + need / 4 + 1024;
-    sal_status st = grow(p, 0, c, s);
+    sal_status st = grow(m, p, 0, c, s);
     if (st == SAL_OK) *cap = c;
     return st;
 }
@@ -165,7 +173,7 @@ sal_status ensure_centroids(sal_tet_mesh *m, int64_t need, hipStream_t s) {
     const int64_t c = need + need / 4 + 1024;
     for (int a = 0; a < 3; ++a) {
         int64_t dummy = 0;
-        sal_status st = grow(&m->cen[a], 0, c, s);
+        sal_status st = grow(m, &m->cen[a], 0, c, s);
         (void)dummy;
         if (st != SAL_OK) return st;
     }
@@ -175,7 +183,7 @@ sal_status ensure_centroids(sal_tet_mesh *m, int64_t need, hipStream_t s) {
 
 sal_status compact(sal_tet_mesh *m, const CompactSrc &src, int64_t n, int32_t *out, int64_t *total,
                    hipStream_t s) {
-    sal_status st = ensure_buf(&m->blocks, &m->blocks_cap, compact_blocks(n) + 1, s);
+    sal_status st = ensure_buf(m, &m->blocks, &m->blocks_cap, compact_blocks(n) + 1, s);
     if (st != SAL_OK) return st;
     SAL_HIP(launch_compact(src, n, m->blocks, total, out, s));
     return SAL_OK;
@@ -218,18 +226,17 @@ sal_status ensure_node_table(sal_tet_mesh *m, int64_t more, hipStream_t s) {
     int64_t cap = 1 << 16;
     while (cap < need) cap <<= 1;
     unsigned long long *k = nullptr, *v = nullptr;
-    SAL_HIP(dev_malloc((void **)&k, (size_t)cap * sizeof(unsigned long long)));
-    const hipError_t ev = dev_malloc((void **)&v, (size_t)cap * sizeof(unsigned long long));
+    SAL_HIP(mesh_malloc(m, &k, cap));
+    const hipError_t ev = mesh_malloc(m, &v, cap);
     if (ev != hipSuccess) {
-        (void)hipFree(k);
+        pool_free(k, m->token);
         return hip_error(ev, "hipMalloc(node table)");
     }
     SAL_HIP(launch_fill_u64(k, ~0ull, cap, s));
     if (m->tkeys) {
         SAL_HIP(launch_node_rehash(m->tkeys, m->tmasks, m->tcap, k, v, cap, s));
-        SAL_HIP(hipStreamSynchronize(s));
-        SAL_HIP(hipFree(m->tkeys));
-        SAL_HIP(hipFree(m->tmasks));
+        pool_free(m->tkeys, m->token);
+        pool_free(m->tmasks, m->token);
     }
     m->tkeys = k;
     m->tmasks = v;
@@ -256,7 +263,7 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
     const int top = m->max_level;
     int64_t total_entries = 0;
     for (int l = 0; l <= top; ++l) total_entries += m->n[l];
-    if ((st = ensure_buf(&m->list, &m->list_cap, total_entries, s)) != SAL_OK) return st;
+    if ((st = ensure_buf(m, &m->list, &m->list_cap, total_entries, s)) != SAL_OK) return st;
     SAL_HIP(launch_fill_u64(ctx->counters, 0ull, kNumCounters, s));
     SAL_HIP(hipEventRecord(m->ev[2], s));
     for (int l = 0; l <= top; ++l) SAL_HIP(launch_fill_u8(m->flag[l], 0, m->n[l], s));
@@ -298,18 +305,18 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
                 int64_t c3 = m->mid_xyz_cap;
                 for (int a = 0; a < 3; ++a) {
                     c3 = m->mid_xyz_cap;
-                    if ((st = ensure_buf(&m->mid_xyz[a], &c3, pts_max, s)) != SAL_OK) return st;
+                    if ((st = ensure_buf(m, &m->mid_xyz[a], &c3, pts_max, s)) != SAL_OK) return st;
                 }
                 m->mid_xyz_cap = c3;
-                if ((st = ensure_buf(&m->lab_scratch, &m->lab_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(&m->mid_masks, &m->mid_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(&m->mid_key, &m->mid_key_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(&m->mid_slot, &m->mid_slot_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(&m->new_list, &m->new_list_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(&m->new_masks, &m->new_masks_cap, pts_max, s)) != SAL_OK ||
+                if ((st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, pts_max, s)) != SAL_OK ||
+                    (st = ensure_buf(m, &m->mid_masks, &m->mid_cap, pts_max, s)) != SAL_OK ||
+                    (st = ensure_buf(m, &m->mid_key, &m->mid_key_cap, pts_max, s)) != SAL_OK ||
+                    (st = ensure_buf(m, &m->mid_slot, &m->mid_slot_cap, pts_max, s)) != SAL_OK ||
+                    (st = ensure_buf(m, &m->new_list, &m->new_list_cap, pts_max, s)) != SAL_OK ||
+                    (st = ensure_buf(m, &m->new_masks, &m->new_masks_cap, pts_max, s)) != SAL_OK ||
                     (st = ensure_node_table(m, pts_sum, s)) != SAL_OK)
                     return st;
-                if (!m->n_new && dev_malloc((void **)&m->n_new, sizeof(unsigned long long)) != hipSuccess)
+                if (!m->n_new && mesh_malloc(m, &m->n_new, 1) != hipSuccess)
                     return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(node counter)");
             }
         }
@@ -327,18 +334,18 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
             int64_t c3 = m->mid_xyz_cap;
             for (int a = 0; a < 3; ++a) {
                 c3 = m->mid_xyz_cap;
-                if ((st = ensure_buf(&m->mid_xyz[a], &c3, n_pts, s)) != SAL_OK) return st;
+                if ((st = ensure_buf(m, &m->mid_xyz[a], &c3, n_pts, s)) != SAL_OK) return st;
             }
             m->mid_xyz_cap = c3;
-            if ((st = ensure_buf(&m->lab_scratch, &m->lab_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(&m->mid_masks, &m->mid_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(&m->mid_key, &m->mid_key_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(&m->mid_slot, &m->mid_slot_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(&m->new_list, &m->new_list_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(&m->new_masks, &m->new_masks_cap, n_pts, s)) != SAL_OK ||
+            if ((st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, n_pts, s)) != SAL_OK ||
+                (st = ensure_buf(m, &m->mid_masks, &m->mid_cap, n_pts, s)) != SAL_OK ||
+                (st = ensure_buf(m, &m->mid_key, &m->mid_key_cap, n_pts, s)) != SAL_OK ||
+                (st = ensure_buf(m, &m->mid_slot, &m->mid_slot_cap, n_pts, s)) != SAL_OK ||
+                (st = ensure_buf(m, &m->new_list, &m->new_list_cap, n_pts, s)) != SAL_OK ||
+                (st = ensure_buf(m, &m->new_masks, &m->new_masks_cap, n_pts, s)) != SAL_OK ||
                 (st = ensure_node_table(m, n_pts, s)) != SAL_OK)
                 return st;
-            if (!m->n_new && dev_malloc((void **)&m->n_new, sizeof(unsigned long long)) != hipSuccess)
+            if (!m->n_new && mesh_malloc(m, &m->n_new, 1) != hipSuccess)
                 return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(node counter)");
         }
         const int64_t base_block = m->n[l + 1] / 8;
@@ -490,7 +497,7 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
         if ((st = reserve_level(m, l, budget, s)) != SAL_OK) return st;
     if (m->cen_cap < budget && (st = ensure_centroids(m, budget + budget / 2, s)) != SAL_OK) return st;
     if (m->lab_cap < budget &&
-        (st = ensure_buf(&m->lab_scratch, &m->lab_cap, budget + budget / 2, s)) != SAL_OK)
+        (st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, budget + budget / 2, s)) != SAL_OK)
         return st;
     const int64_t kid_cap = std::min(m->cen_cap, m->lab_cap);
     if ((st = ensure_label_scratch(ctx, kid_cap)) != SAL_OK) return st;
@@ -499,9 +506,9 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
         list_need += m->cap[l];
         blocks_need = std::max<int64_t>(blocks_need, compact_blocks(m->cap[l]) + 1);
     }
-    if ((st = ensure_buf(&m->list, &m->list_cap, list_need, s)) != SAL_OK) return st;
-    if ((st = ensure_buf(&m->blocks, &m->blocks_cap, blocks_need, s)) != SAL_OK) return st;
-    if (!m->rs && dev_malloc((void **)&m->rs, sizeof(RoundState)) != hipSuccess)
+    if ((st = ensure_buf(m, &m->list, &m->list_cap, list_need, s)) != SAL_OK) return st;
+    if ((st = ensure_buf(m, &m->blocks, &m->blocks_cap, blocks_need, s)) != SAL_OK) return st;
+    if (!m->rs && mesh_malloc(m, &m->rs, 1) != hipSuccess)
         return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(round state)");
 
     // The launch shape is fixed in the graph: resolve it now (tuning
@@ -630,9 +637,11 @@ namespace sal {
 
 // The conforming mesh for the post-processing passes; null before
 // sal_tet_mesh_conform.
-bool conform_view(sal_tet_mesh *m, ConformView *v) {
+bool conform_view(const sal_context *ctx, sal_tet_mesh *m, ConformView *v) {
     if (!m || !m->conformed) return false;
+    m->token = ctx->stream_token;
     v->g = m->g;
+    v->token = m->token;
     v->n_tets = m->conf_tets;
     v->n_nodes = m->conf_nodes;
     v->ids = m->conf_ids;
@@ -648,17 +657,21 @@ namespace {
 
 // Device scratch freed when the call ends.
 struct DevScratch {
+    uint64_t token;
     std::vector<void *> bufs;
+    explicit DevScratch(uint64_t t) : token(t) {}
+    DevScratch(const DevScratch &) = delete;
     ~DevScratch() { clear(); }
     void clear() {
-        for (void *p : bufs) (void)hipFree(p);
+        for (void *p : bufs) pool_free(p, token);
         bufs.clear();
     }
     template <typename T>
     sal_status get(T **p, int64_t n) {
         void *q = nullptr;
         const size_t bytes = (size_t)std::max<int64_t>(n, 1) * sizeof(T);
-        if (dev_malloc(&q, bytes) != hipSuccess) return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(conform)");
+        if (pool_malloc(&q, bytes, token) != hipSuccess)
+            return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(mesh scratch)");
         bufs.push_back(q);
         *p = (T *)q;
         return SAL_OK;
@@ -669,18 +682,19 @@ struct DevScratch {
 // quarter to spare) only when a round needs more than it holds.
 template <typename T>
 struct GrowBuf {
+    uint64_t token;
     T *p = nullptr;
     int64_t cap = 0;
-    ~GrowBuf() {
-        if (p) (void)hipFree(p);
-    }
+    explicit GrowBuf(uint64_t t) : token(t) {}
+    GrowBuf(const GrowBuf &) = delete;
+    ~GrowBuf() { pool_free(p, token); }
     sal_status need(int64_t n) {
         if (n <= cap) return SAL_OK;
-        if (p) (void)hipFree(p);
+        pool_free(p, token);
         p = nullptr;
         cap = 0;
         const int64_t c = n + n / 4 + 1024;
-        if (dev_malloc((void **)&p, (size_t)c * sizeof(T)) != hipSuccess)
+        if (pool_malloc((void **)&p, (size_t)c * sizeof(T), token) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(conform)");
         cap = c;
         return SAL_OK;
@@ -696,33 +710,22 @@ void sal_tet_mesh_destroy(sal_tet_mesh *m) {
     if (!m) return;
     (void)hipSetDevice(m->device);
     (void)hipDeviceSynchronize();
+    // (the device is idle: whoever takes a block next need not wait)
+    auto drop = [](void *p) { pool_free(p, 0); };
     for (int l = 0; l <= kMaxLevels; ++l) {
-        if (m->key[l]) (void)hipFree(m->key[l]);
-        if (m->label[l]) (void)hipFree(m->label[l]);
-        if (m->child[l]) (void)hipFree(m->child[l]);
-        if (m->flag[l]) (void)hipFree(m->flag[l]);
+        drop(m->key[l]);
+        drop(m->label[l]);
+        drop(m->child[l]);
+        drop(m->flag[l]);
+        drop(m->vmask[l]);
     }
-    for (auto &c : m->cen)
-        if (c) (void)hipFree(c);
-    if (m->list) (void)hipFree(m->list);
-    if (m->blocks) (void)hipFree(m->blocks);
-    if (m->totals) (void)hipFree(m->totals);
-    if (m->lab_scratch) (void)hipFree(m->lab_scratch);
-    sal::smooth_cache_free(m->smooth);
-    void *conf[] = {m->conf_ids, m->conf_labels, m->conf_keys, m->conf_xyz};
-    for (void *p : conf)
-        if (p) (void)hipFree(p);
-    if (m->node0) (void)hipFree(m->node0);
-    for (auto *v : m->vmask)
-        if (v) (void)hipFree(v);
-    if (m->mid_masks) (void)hipFree(m->mid_masks);
-    for (auto *p : m->mid_xyz)
-        if (p) (void)hipFree(p);
-    void *more[] = {m->mid_key, m->mid_slot, m->new_list, m->new_masks, m->n_new, m->tkeys,
-                    m->tmasks};
-    for (void *p : more)
-        if (p) (void)hipFree(p);
-    if (m->rs) (void)hipFree(m->rs);
+    for (auto *c : m->cen) drop(c);
+    for (auto *p : m->mid_xyz) drop(p);
+    sal::smooth_cache_free(m->smooth, 0);
+    void *more[] = {m->list,      m->blocks,    m->totals,    m->lab_scratch, m->conf_ids, m->conf_labels,
+                    m->conf_keys, m->conf_xyz,  m->node0,     m->mid_masks,   m->mid_key,  m->mid_slot,
+                    m->new_list,  m->new_masks, m->n_new,     m->tkeys,       m->tmasks,   m->rs};
+    for (void *p : more) drop(p);
     if (m->round_graph) (void)hipGraphExecDestroy(m->round_graph);
     for (auto &e : m->ev)
         if (e) (void)hipEventDestroy(e);
@@ -746,6 +749,7 @@ sal_status sal_tet_mesh_create_lattice(sal_context *ctx, const double origin[3],
         SAL_HIP(hipSetDevice(ctx->device));
         auto *m = new sal_tet_mesh();
         m->device = ctx->device;
+        m->token = ctx->stream_token;
         for (int a = 0; a < 3; ++a) {
             m->g.origin[a] = origin[a];
             m->g.cells[a] = cells[a];
@@ -758,7 +762,7 @@ sal_status sal_tet_mesh_create_lattice(sal_context *ctx, const double origin[3],
             if (hipEventCreate(&e) != hipSuccess) return fail(set_error(SAL_ERR_DEVICE, "hipEventCreate"));
         if ((st = ensure_level(m, 0, n0, ctx->stream)) != SAL_OK) return fail(st);
         m->n[0] = n0;
-        if (dev_malloc((void **)&m->totals, (kMaxLevels + 1) * sizeof(int64_t)) != hipSuccess)
+        if (mesh_malloc(m, &m->totals, kMaxLevels + 1) != hipSuccess)
             return fail(set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(totals)"));
         if (hipError_t e = launch_fill_i32(m->child[0], -1, n0, ctx->stream); e != hipSuccess)
             return fail(hip_error(e, "fill child"));
@@ -791,6 +795,7 @@ sal_status check_refine_args(sal_context *ctx, sal_tet_mesh *m, const sal_surfac
     sal_status st = resolve_options(opt_in, opt);
     if (st != SAL_OK) return st;
     opt->winding_type = SAL_WINDING_NONE;
+    m->token = ctx->stream_token;
     if (m->conformed)
         return set_error(SAL_ERR_INVALID_ARG, "the mesh was made conforming; it cannot be refined");
     if (m->labeled0 && m->rule != opt->element_rule)
@@ -816,9 +821,8 @@ sal_status label_lattice(sal_context *ctx, sal_tet_mesh *m, const sal_surface_se
         const int64_t n_nodes = (int64_t)(m->g.cells[0] + 1) * (m->g.cells[1] + 1) *
                                 (int64_t)(m->g.cells[2] + 1);
         if ((st = ensure_centroids(m, n_nodes, s)) != SAL_OK) return st;
-        if ((st = ensure_buf(&m->lab_scratch, &m->lab_cap, n_nodes, s)) != SAL_OK) return st;
-        if (!m->node0 && dev_malloc((void **)&m->node0, (size_t)n_nodes * sizeof(uint64_t)) !=
-                             hipSuccess)
+        if ((st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, n_nodes, s)) != SAL_OK) return st;
+        if (!m->node0 && mesh_malloc(m, &m->node0, n_nodes) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(node masks)");
         SAL_HIP(launch_lattice_nodes(m->g, n_nodes, m->cen[0], m->cen[1], m->cen[2], s));
         if ((st = label_scratch(ctx, m, set, n_nodes, opt, m->lab_scratch, m->ev[10], m->ev[9],
@@ -937,20 +941,21 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
             if (done) return;
             int32_t **i32[] = {&m->conf_ids, &m->conf_labels};
             for (int32_t **p : i32)
-                if (*p) (void)hipFree(*p), *p = nullptr;
-            if (m->conf_keys) (void)hipFree(m->conf_keys), m->conf_keys = nullptr;
-            if (m->conf_xyz) (void)hipFree(m->conf_xyz), m->conf_xyz = nullptr;
+                pool_free(*p, m->token), *p = nullptr;
+            pool_free(m->conf_keys, m->token), m->conf_keys = nullptr;
+            pool_free(m->conf_xyz, m->token), m->conf_xyz = nullptr;
         }
     };
     try {
         if (!ctx || !m) return set_error(SAL_ERR_INVALID_ARG, "NULL argument");
         if (m->device != ctx->device) return set_error(SAL_ERR_INVALID_ARG, "mesh lives on another device");
         if (m->conformed) return set_error(SAL_ERR_INVALID_ARG, "the mesh is already conforming");
+        m->token = ctx->stream_token;
         DropUnlessDone guard{m};
         SAL_HIP(hipSetDevice(ctx->device));
         hipStream_t s = ctx->stream;
         sal_status st;
-        DevScratch keep;                 // lives to the end of the call
+        DevScratch keep(m->token);                 // lives to the end of the call
         unsigned long long *counters = nullptr;   // [0] keys added, [1] overflow
         if ((st = keep.get(&counters, 2)) != SAL_OK) return st;
         // closure state: flags per entry (hanging bits, quarter point, red)
@@ -959,7 +964,7 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         for (int l = 0; l <= m->max_level; ++l) entries += m->n[l];
         int64_t cap = 1 << 16, used = 0;
         while (cap < 2 * entries) cap <<= 1;
-        DevScratch set_mem;
+        DevScratch set_mem(m->token);
         unsigned long long *set = nullptr;
         // (re)builds the set from every entry and the full patterns
         auto rebuild = [&]() -> sal_status {
@@ -987,9 +992,9 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         };
         if ((st = rebuild()) != SAL_OK) return st;
         int rounds = 0;
-        GrowBuf<int32_t> red_buf;              // red leaves of a round
-        GrowBuf<unsigned long long> fresh_buf; // vertices new in a round
-        GrowBuf<uint32_t> cells_buf;           // level-0 cells those vertices touch, one bit each
+        GrowBuf<int32_t> red_buf(m->token);   // red leaves of a round
+        GrowBuf<unsigned long long> fresh_buf(m->token);   // vertices new in a round
+        GrowBuf<uint32_t> cells_buf(m->token);   // level-0 cells those vertices touch, one bit each
         const int64_t cell_words =
             ((int64_t)m->g.cells[0] * m->g.cells[1] * m->g.cells[2] + 31) / 32;
         for (;;) {
@@ -1066,7 +1071,7 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         // the leaves in index order per level
         int64_t count[kMaxLevels + 1] = {0}, off[kMaxLevels + 2] = {0}, n_all = 0;
         for (int l = 0; l <= m->max_level; ++l) off[l + 1] = off[l] + m->n[l];
-        if ((st = ensure_buf(&m->list, &m->list_cap, off[m->max_level + 1], s)) != SAL_OK) return st;
+        if ((st = ensure_buf(m, &m->list, &m->list_cap, off[m->max_level + 1], s)) != SAL_OK) return st;
         for (int l = 0; l <= m->max_level; ++l) {
             CompactSrc src{nullptr, m->child[l]};
             if ((st = compact(m, src, m->n[l], m->list + off[l], m->totals + l, s)) != SAL_OK) return st;
@@ -1110,10 +1115,8 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
             (st = keep.get(&pos, n_corner)) != SAL_OK || (st = keep.get(&head, n_corner)) != SAL_OK ||
             (st = keep.get(&nodes, n_corner)) != SAL_OK)
             return st;
-        if (dev_malloc((void **)&m->conf_labels, (size_t)std::max<int64_t>(n_tets, 1) * sizeof(int32_t)) !=
-                hipSuccess ||
-            dev_malloc((void **)&m->conf_ids, (size_t)std::max<int64_t>(n_corner, 1) * sizeof(int32_t)) !=
-                hipSuccess)
+        if (mesh_malloc(m, &m->conf_labels, std::max<int64_t>(n_tets, 1)) != hipSuccess ||
+            mesh_malloc(m, &m->conf_ids, std::max<int64_t>(n_corner, 1)) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(conforming mesh)");
         LevelPtrs L = ptrs(m);
         int64_t boff = 0;
@@ -1134,10 +1137,8 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         SAL_HIP(hipMemcpyAsync(&last_head, head + n_corner - 1, sizeof(last_head), hipMemcpyDeviceToHost, s));
         SAL_HIP(hipStreamSynchronize(s));
         const int64_t n_nodes = last_pos + last_head;
-        if (dev_malloc((void **)&m->conf_keys, (size_t)std::max<int64_t>(n_nodes, 1) * sizeof(int64_t)) !=
-                hipSuccess ||
-            dev_malloc((void **)&m->conf_xyz, (size_t)std::max<int64_t>(3 * n_nodes, 1) * sizeof(float)) !=
-                hipSuccess)
+        if (mesh_malloc(m, &m->conf_keys, std::max<int64_t>(n_nodes, 1)) != hipSuccess ||
+            mesh_malloc(m, &m->conf_xyz, std::max<int64_t>(3 * n_nodes, 1)) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(conforming nodes)");
         SAL_HIP(hipMemcpyAsync(m->conf_keys, nodes, (size_t)n_nodes * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
         SAL_HIP(launch_node_ids(tkeys, n_corner, m->conf_keys, n_nodes, m->conf_ids, s));
@@ -1191,12 +1192,13 @@ sal_status sal_tet_mesh_import(sal_context *ctx, sal_tet_mesh *m, int64_t n, con
         if (m->device != ctx->device) return set_error(SAL_ERR_INVALID_ARG, "mesh lives on another device");
         if (m->labeled0 || m->max_level != 0 || m->conformed)
             return set_error(SAL_ERR_INVALID_ARG, "import needs a mesh fresh from sal_tet_mesh_create_lattice");
+        m->token = ctx->stream_token;
         if (n <= 0 || !keys || !labels) return set_error(SAL_ERR_INVALID_ARG, "no leaves to import");
         SAL_HIP(hipSetDevice(ctx->device));
         hipStream_t s = ctx->stream;
         const int64_t n0 = m->n[0];
         sal_status st;
-        DevScratch keep;
+        DevScratch keep(m->token);
         ImportTables t{};
         t.leaf_cap = t.inner_cap = 4096;
         while (t.leaf_cap < 4 * n) t.leaf_cap <<= 1;
@@ -1228,7 +1230,7 @@ sal_status sal_tet_mesh_import(sal_context *ctx, sal_tet_mesh *m, int64_t n, con
             int64_t refined = 0;
             if (l < kMaxLevels) {
                 CompactSrc src{m->flag[l], nullptr, 0};
-                if ((st = ensure_buf(&m->list, &m->list_cap, count[l], s)) != SAL_OK ||
+                if ((st = ensure_buf(m, &m->list, &m->list_cap, count[l], s)) != SAL_OK ||
                     (st = compact(m, src, count[l], m->list, m->totals + l, s)) != SAL_OK)
                     return undo(st);
                 SAL_HIP(hipMemcpyAsync(&refined, m->totals + l, sizeof(refined), hipMemcpyDeviceToHost, s));
@@ -1278,11 +1280,12 @@ sal_status sal_tet_mesh_export(sal_context *ctx, const sal_tet_mesh *mc, uint64_
     try {
         if (!ctx || !mc) return set_error(SAL_ERR_INVALID_ARG, "NULL argument");
         auto *m = const_cast<sal_tet_mesh *>(mc);
+        m->token = ctx->stream_token;
         SAL_HIP(hipSetDevice(ctx->device));
         hipStream_t s = ctx->stream;
         int64_t total_entries = 0;
         for (int l = 0; l <= m->max_level; ++l) total_entries += m->n[l];
-        sal_status st = ensure_buf(&m->list, &m->list_cap, total_entries, s);
+        sal_status st = ensure_buf(m, &m->list, &m->list_cap, total_entries, s);
         if (st != SAL_OK) return st;
         int64_t off[kMaxLevels + 2] = {0};
         for (int l = 0; l <= m->max_level; ++l) {

@@ -15,6 +15,7 @@ namespace sal {
 struct SmoothCache;
 struct ConformView {
     LatticeGeom g;
+    uint64_t token;          // stream order of the call (its allocations)
     int64_t n_tets, n_nodes;
     const int32_t *ids;      // [n_tets][4]
     const int32_t *labels;   // [n_tets]
@@ -45,10 +46,10 @@ struct SmoothCache {
     int64_t partials_cap = 0;
     double *sum = nullptr;       // [1]
 };
-void smooth_cache_free(SmoothCache *c);
+void smooth_cache_free(SmoothCache *c, uint64_t token);
 
 // Defined with the mesh: false when the mesh is not conforming yet.
-bool conform_view(sal_tet_mesh *m, ConformView *v);
+bool conform_view(const sal_context *ctx, sal_tet_mesh *m, ConformView *v);
 int mesh_device(const sal_tet_mesh *m);
 
 constexpr int kSmoothThreads = 256;

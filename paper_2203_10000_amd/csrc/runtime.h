@@ -9,6 +9,7 @@
 struct sal_context {
     int device = 0;
     hipStream_t stream = nullptr;
+    uint64_t stream_token = sal::new_stream_token();   // another with each set_stream
     hipEvent_t ev[8] = {};
     // flag list and spatial order of the wavefront-per-64-points form
     sal::FlagEntry *flag_list = nullptr;

@@ -172,7 +172,18 @@ sal_status set_error(sal_status s, const std::string &msg);
 // Every device allocation of the library goes through here: hipMalloc, or a
 // simulated out-of-memory when sal_debug_fail_allocation armed this call.
 hipError_t dev_malloc(void **ptr, size_t bytes);
+void fail_allocation(int64_t n);
 sal_status hip_error(hipError_t e, const char *what);
+
+// Allocations of meshes and of single calls, from blocks kept on the current
+// device (devmem.cpp).  `token` names the stream order that the block is used in
+// (sal_context::stream_token); a freed block may still be in use there.  Token 0:
+// no work on it is pending.
+hipError_t pool_malloc(void **ptr, size_t bytes, uint64_t token);
+void pool_free(void *ptr, uint64_t token);
+uint64_t new_stream_token();
+void pool_add_context();
+void pool_remove_context();
 
 }  // namespace sal
 

@@ -14,13 +14,12 @@
 
 namespace sal {
 
-void smooth_cache_free(SmoothCache *c) {
+void smooth_cache_free(SmoothCache *c, uint64_t token) {
     if (!c) return;
     void *p[] = {c->rowptr, c->cols, c->cls, c->order, c->list[0], c->list[1], c->seg[0], c->seg[1],
                  c->head[0], c->head[1],
                  c->pos[0], c->pos[1], c->partials, c->sum};
-    for (void *q : p)
-        if (q) (void)hipFree(q);
+    for (void *q : p) pool_free(q, token);
     delete c;
 }
 
@@ -33,21 +32,24 @@ int bits_for(int64_t n) {
 }
 
 template <typename T>
-sal_status dev_alloc(T **p, int64_t n) {
-    if (dev_malloc((void **)p, (size_t)std::max<int64_t>(n, 1) * sizeof(T)) != hipSuccess)
+sal_status dev_alloc(T **p, int64_t n, uint64_t token) {
+    if (pool_malloc((void **)p, (size_t)std::max<int64_t>(n, 1) * sizeof(T), token) != hipSuccess)
         return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(smoothing)");
     return SAL_OK;
 }
 
 // Frees its buffers when the graph construction ends.
 struct Temp {
+    uint64_t token;
     std::vector<void *> p;
+    explicit Temp(uint64_t t) : token(t) {}
+    Temp(const Temp &) = delete;
     ~Temp() {
-        for (void *q : p) (void)hipFree(q);
+        for (void *q : p) pool_free(q, token);
     }
     template <typename T>
     sal_status get(T **out, int64_t n) {
-        sal_status st = dev_alloc(out, n);
+        sal_status st = dev_alloc(out, n, token);
         if (st == SAL_OK) p.push_back(*out);
         return st;
     }
@@ -57,7 +59,7 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
     if (v.n_nodes >= (int64_t(1) << 28)) return set_error(SAL_ERR_CAPACITY, "smoothing: 2^28 nodes or more");
     if (6 * v.n_tets > INT32_MAX) return set_error(SAL_ERR_CAPACITY, "smoothing: too many tetrahedra");
     sal_status st;
-    Temp t;
+    Temp t(v.token);
     const int64_t n_occ = 6 * v.n_tets;
     uint64_t *occ = nullptr, *occ_sorted = nullptr;
     int32_t *head = nullptr;
@@ -100,7 +102,7 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
     int32_t *ids = nullptr, *rank = nullptr;
     if ((st = t.get(&code, v.n_nodes)) != SAL_OK || (st = t.get(&code_sorted, v.n_nodes)) != SAL_OK ||
         (st = t.get(&ids, v.n_nodes)) != SAL_OK || (st = t.get(&rank, v.n_nodes)) != SAL_OK ||
-        (st = dev_alloc(&c->order, v.n_nodes)) != SAL_OK)
+        (st = dev_alloc(&c->order, v.n_nodes, v.token)) != SAL_OK)
         return st;
     size_t bm = 0;
     SAL_HIP(launch_morton_order(v.keys, v.n_nodes, code, code_sorted, ids, c->order, rank, nullptr, &bm, s));
@@ -113,8 +115,8 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
     char *tmp3 = nullptr;
     if ((st = t.get(&tmp3, (int64_t)b3)) != SAL_OK) return st;
     SAL_HIP(sort_keys_u64(dkeys, dsorted, n2, 32 + nb, tmp3, &b3, s));
-    if ((st = dev_alloc(&c->rowptr, v.n_nodes + 1)) != SAL_OK || (st = dev_alloc(&c->cols, n2)) != SAL_OK ||
-        (st = dev_alloc(&c->cls, v.n_nodes)) != SAL_OK)
+    if ((st = dev_alloc(&c->rowptr, v.n_nodes + 1, v.token)) != SAL_OK || (st = dev_alloc(&c->cols, n2, v.token)) != SAL_OK ||
+        (st = dev_alloc(&c->cls, v.n_nodes, v.token)) != SAL_OK)
         return st;
     SAL_HIP(launch_csr(dsorted, n2, v.n_nodes, c->rowptr, c->cols, s));
     SAL_HIP(launch_node_class(c->rowptr, c->cols, v.keys, c->order, v.n_nodes, v.g, c->cls, s));
@@ -123,7 +125,7 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
     if ((st = t.get(&blocks, compact_blocks(v.n_nodes) + 1)) != SAL_OK || (st = t.get(&totals, 2)) != SAL_OK)
         return st;
     for (int ph = 0; ph < 2; ++ph) {
-        if ((st = dev_alloc(&c->list[ph], v.n_nodes)) != SAL_OK) return st;
+        if ((st = dev_alloc(&c->list[ph], v.n_nodes, v.token)) != SAL_OK) return st;
         CompactSrc src{c->cls, nullptr, (uint8_t)(ph == 0 ? 1 : 2)};
         SAL_HIP(launch_compact(src, v.n_nodes, blocks, totals + ph, c->list[ph], s));
     }
@@ -135,14 +137,14 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
     c->n_nodes = v.n_nodes;
     c->n_edges = n_edges;
     c->partials_cap = taubin_blocks(std::max(c->n_list[0], c->n_list[1]));
-    if ((st = dev_alloc(&c->partials, c->partials_cap)) != SAL_OK || (st = dev_alloc(&c->sum, 1)) != SAL_OK ||
-        (st = dev_alloc(&c->pos[0], v.n_nodes)) != SAL_OK || (st = dev_alloc(&c->pos[1], v.n_nodes)) != SAL_OK)
+    if ((st = dev_alloc(&c->partials, c->partials_cap, v.token)) != SAL_OK || (st = dev_alloc(&c->sum, 1, v.token)) != SAL_OK ||
+        (st = dev_alloc(&c->pos[0], v.n_nodes, v.token)) != SAL_OK || (st = dev_alloc(&c->pos[1], v.n_nodes, v.token)) != SAL_OK)
         return st;
     if (n2 >= (int64_t(1) << 32)) return set_error(SAL_ERR_CAPACITY, "smoothing: 2^32 row entries or more");
     for (int ph = 0; ph < 2; ++ph) {
-        if ((st = dev_alloc(&c->seg[ph], c->n_list[ph])) != SAL_OK) return st;
+        if ((st = dev_alloc(&c->seg[ph], c->n_list[ph], v.token)) != SAL_OK) return st;
         SAL_HIP(launch_row_segments(c->rowptr, c->list[ph], c->n_list[ph], c->seg[ph], s));
-        if ((st = dev_alloc(&c->head[ph], c->n_list[ph] * kTaubinGroup * kTaubinUnroll)) != SAL_OK)
+        if ((st = dev_alloc(&c->head[ph], c->n_list[ph] * kTaubinGroup * kTaubinUnroll, v.token)) != SAL_OK)
             return st;
         SAL_HIP(launch_row_heads(c->rowptr, c->cols, c->list[ph], c->n_list[ph], c->head[ph], s));
         double e = 0.0;
@@ -197,7 +199,7 @@ sal_status ensure_smooth_graph(const ConformView &v, hipStream_t s) {
     auto *c = new SmoothCache();
     const sal_status st = build_graph(v, c, s);
     if (st != SAL_OK) {
-        smooth_cache_free(c);
+        smooth_cache_free(c, v.token);
         return st;
     }
     *v.cache = c;
@@ -234,7 +236,7 @@ sal_status sal_tet_mesh_smooth(sal_context *ctx, sal_tet_mesh *m, const sal_smoo
         if (!ctx || !m) return set_error(SAL_ERR_INVALID_ARG, "NULL argument");
         if (mesh_device(m) != ctx->device) return set_error(SAL_ERR_INVALID_ARG, "mesh lives on another device");
         ConformView v{};
-        if (!conform_view(m, &v)) return set_error(SAL_ERR_INVALID_ARG, "call sal_tet_mesh_conform first");
+        if (!conform_view(ctx, m, &v)) return set_error(SAL_ERR_INVALID_ARG, "call sal_tet_mesh_conform first");
         sal_smooth_params p;
         sal_smooth_params_default(&p);
         if (params) p = *params;
