@@ -1,4 +1,5 @@
 // C-ABI entry points: contexts, surface sets, point labeling.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -33,36 +34,56 @@ sal_status renew(T **p, int64_t n) {
 
 }  // namespace
 
-sal_status ensure_label_scratch(sal_context *ctx, int64_t points, int64_t tiles, int64_t insts) {
+sal_status ensure_label_scratch(sal_context *ctx, const ScratchSize &need) {
     sal_status st;
-    if (points > ctx->point_cap || tiles > ctx->tile_cap || insts > ctx->inst_cap) {
+    if (need.points > ctx->point_cap || need.tiles > ctx->tile_cap || need.insts > ctx->inst_cap ||
+        need.spans > ctx->span_cap || need.pairs > ctx->pair_cap) {
         SAL_HIP(hipStreamSynchronize(ctx->stream));
         ctx->batch_graph_fields.clear();   // a captured batch graph points at the old buffers
     }
-    if (points > ctx->point_cap) {
+    if (need.points > ctx->point_cap) {
         ctx->point_cap = 0;
-        if ((st = renew(&ctx->flag_list, points)) != SAL_OK || (st = renew(&ctx->ord_idx1, points)) != SAL_OK ||
-            (st = renew(&ctx->ord_key1, points)) != SAL_OK || (st = renew(&ctx->ord_perm, points)) != SAL_OK)
+        if ((st = renew(&ctx->flag_list, need.points)) != SAL_OK ||
+            (st = renew(&ctx->ord_idx1, need.points)) != SAL_OK ||
+            (st = renew(&ctx->ord_key1, need.points)) != SAL_OK ||
+            (st = renew(&ctx->ord_perm, need.points)) != SAL_OK)
             return st;
-        ctx->point_cap = points;
+        ctx->point_cap = need.points;
     }
-    if (tiles > ctx->tile_cap) {
+    if (need.tiles > ctx->tile_cap) {
         ctx->tile_cap = 0;
-        if ((st = renew(&ctx->ord_hist, tiles * kOrderBins)) != SAL_OK) return st;
-        ctx->tile_cap = tiles;
+        if ((st = renew(&ctx->ord_hist, need.tiles * kOrderBins)) != SAL_OK) return st;
+        ctx->tile_cap = need.tiles;
     }
-    if (insts > ctx->inst_cap) {
+    if (need.insts > ctx->inst_cap) {
         ctx->inst_cap = 0;
-        if ((st = renew(&ctx->ord_tot, insts * kOrderBins)) != SAL_OK) return st;
-        ctx->inst_cap = insts;
+        if ((st = renew(&ctx->ord_tot, need.insts * kOrderBins)) != SAL_OK) return st;
+        ctx->inst_cap = need.insts;
+    }
+    if (need.spans > ctx->span_cap) {
+        ctx->span_cap = 0;
+        if ((st = renew(&ctx->span_w, need.spans)) != SAL_OK || (st = renew(&ctx->open_spans, need.spans)) != SAL_OK)
+            return st;
+        ctx->span_cap = need.spans;
+    }
+    if (need.pairs > ctx->pair_cap) {
+        ctx->pair_cap = 0;
+        if ((st = renew(&ctx->pairs, need.pairs)) != SAL_OK) return st;
+        ctx->pair_cap = need.pairs;
     }
     return SAL_OK;
 }
 
-sal_status ensure_label_scratch(sal_context *ctx, int64_t n) {
+sal_status ensure_label_scratch(sal_context *ctx, const sal_surface_set *set, int64_t n) {
     if (n <= kPointFormMax) return SAL_OK;
     const int64_t c = n < kChunkPoints ? n : kChunkPoints;
-    return ensure_label_scratch(ctx, c, order_tiles(c), 1);
+    ScratchSize z;
+    z.points = c;
+    z.tiles = order_tiles(c);
+    z.insts = 1;
+    z.spans = span_count(c) * set->n_surf;
+    z.pairs = group_count(c) * set->n_surf;
+    return ensure_label_scratch(ctx, z);
 }
 
 sal_status resolve_options(const sal_label_options *in, sal_label_options *out) {
@@ -91,7 +112,7 @@ sal_status resolve_options(const sal_label_options *in, sal_label_options *out) 
 }
 
 LabelScratch context_scratch(const sal_context *ctx) {
-    return LabelScratch{ctx->counters, ctx->flag_list, ctx->list_n,
+    return LabelScratch{ctx->counters, ctx->flag_list, ctx->work, ctx->span_w, ctx->open_spans, ctx->pairs,
                         OrderScratch{ctx->ord_idx1, ctx->ord_key1, ctx->ord_perm, ctx->ord_hist, ctx->ord_tot}};
 }
 
@@ -143,7 +164,9 @@ sal_status enqueue_label_with(sal_context *ctx, const sal_surface_set *set, int6
     a.kappa = (float)opt.kappa;
     a.cull = opt.cull_bounds ? 1 : 0;
     a.flag_list = sc.flag_list;
-    a.list_n = sc.list_n;
+    a.work = sc.work;
+    a.open_spans = sc.open_spans;
+    a.pairs = sc.pairs;
     a.ord = sc.ord;
     const size_t wsize = opt.winding_type == SAL_WINDING_F64 ? sizeof(double) : sizeof(float);
     for (int64_t at = 0; at < n; at += kChunkPoints) {
@@ -160,7 +183,12 @@ sal_status enqueue_label_with(sal_context *ctx, const sal_surface_set *set, int6
             continue;
         }
         SAL_HIP(launch_order(a, a.one.n_tiles, stream));
-        SAL_HIP(launch_label_wave(a, fp64, (m + 63) / 64, opt.block_waves, stream));
+        a.span_w = m * set->n_surf >= kSpanPairs ? sc.span_w : nullptr;
+        a.n_pairs = group_count(m) * set->n_surf;
+        if (a.span_w) SAL_HIP(launch_label_span(a, span_count(m) * set->n_surf, stream));
+        SAL_HIP(launch_label_pair(a, fp64, std::min<int64_t>(a.n_pairs, (int64_t)ctx->n_cu * kPairWaves),
+                                  opt.block_waves, stream));
+        SAL_HIP(launch_label_final(a, fp64, group_count(m), stream));
         if (ev_mid && at + m == n) SAL_HIP(hipEventRecord(ev_mid, stream));
         SAL_HIP(launch_recheck(a, fp64, ctx->n_cu * 8, stream));
     }
@@ -265,8 +293,8 @@ sal_status sal_context_create(int device, void *stream, sal_context **out) {
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(counters)"); }
     e = dev_malloc((void **)&ctx->tune_counters, kNumCounters * sizeof(unsigned long long));
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(counters)"); }
-    e = dev_malloc((void **)&ctx->list_n, sizeof(unsigned long long));
-    if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(list length)"); }
+    e = dev_malloc((void **)&ctx->work, kNumWork * sizeof(unsigned long long));
+    if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(work counters)"); }
     e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipStreamCreate"); }
     *out = ctx;
@@ -289,7 +317,8 @@ void sal_context_destroy(sal_context *ctx) {
         if (ev) (void)hipEventDestroy(ev);
     if (ctx->batch_graph) (void)hipGraphExecDestroy(ctx->batch_graph);
     void *bufs[] = {ctx->flag_list, ctx->ord_idx1, ctx->ord_key1,    ctx->ord_perm,      ctx->ord_hist,
-                    ctx->ord_tot,   ctx->list_n,   ctx->counters,    ctx->tune_counters, ctx->batch_insts,
+                    ctx->ord_tot,   ctx->work,     ctx->span_w,      ctx->open_spans, ctx->pairs,
+                    ctx->counters,    ctx->tune_counters, ctx->batch_insts,
                     ctx->batch_counters};
     for (void *p : bufs)
         if (p) (void)hipFree(p);
@@ -341,7 +370,7 @@ sal_status sal_label_points(sal_context *ctx, const sal_surface_set *set, int64_
     SAL_HIP(hipSetDevice(ctx->device));
     // every argument is checked before anything is enqueued
     if (opt.cull_bounds && (st = ensure_surface_balls(ctx, set)) != SAL_OK) return st;
-    if ((st = ensure_label_scratch(ctx, n)) != SAL_OK) return st;
+    if ((st = ensure_label_scratch(ctx, set, n)) != SAL_OK) return st;
     // (without stats nothing reads the counters)
     if (stats) SAL_HIP(launch_fill_u64(ctx->counters, 0ull, kNumCounters, ctx->stream));
     int shape[2] = {0, 0};

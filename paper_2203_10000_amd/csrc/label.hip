@@ -7,10 +7,14 @@
 // PatchEntry), so a point needs about 8 sqrt(T) terms instead of T.  And the
 // winding number is constant where the surface does not pass: a wavefront whose
 // 64 points lie in a box that meets no triangle needs it at one of them.
-//   k_label_wave   64 neighbouring points (order.hip) per wavefront: the
-//                  surface is summed at one point of their box, a lane per
-//                  triangle, and the others differ from it by the signed number of
-//                  near triangles that the segment between them crosses.
+//   k_label_span   512 neighbouring points (order.hip) and one surface per
+//                  wavefront: the winding number they share, if the surface does
+//                  not enter their box.
+//   k_label_pair   64 neighbouring points and one surface that their span left
+//                  open: a ray gives one point of their box its winding number, and
+//                  the others differ from it by the signed number of near triangles
+//                  that the segment between them crosses.
+//   k_label_final  the labels from both.
 //   k_label_point  one point per wavefront, a lane per term: few points.
 //   k_recheck      the same for flagged (point, surface) pairs.
 // No MFMA: a term has K = 3 products, square roots and a sign-sensitive sum.
@@ -29,28 +33,29 @@ using patch::Lists;
 using patch::Mode;
 using patch::PointSum;
 
-// A run of lanes is halved while its box meets more leaves than this (each costs
-// a load, a test of 64 triangles, and ~80 instructions for every triangle that
-// meets the box; a halved run sums one point more), down to kSplitMin lanes.
-constexpr int kSplitLeaves = 32, kSplitMin = 4;
+// A run of lanes is halved while its box meets too many triangles for the lists,
+// down to kSplitMin lanes; below it a ray per point (k_recheck) is cheaper.
+// 60,001 points within 1 mm of two surfaces of 81,000 triangles, two shells of
+// points of 2,048: 4 lanes 340 and 447 us, 16 lanes 295 and 128, 32 lanes 454 and
+// 137.
+constexpr int kSplitMin = 16;
 
-// Instance of wavefront g, by its place in the grid.
-__device__ __forceinline__ int find_group(const LabelInst *insts, int n_inst, int64_t g) {
+// Below this many (group, surface) pairs a wavefront takes a quarter of a group:
+// its chain is shorter, and the chip has places for all of them.  8,192 pairs or
+// fewer (us, whole groups / quarters): 60,001 points by two surfaces 398 / 295;
+// 3,072 pairs of 196,608 lattice points 90 / 120.
+constexpr int64_t kQuarterPairs = 2048;
+
+// Instance of place g in a grid whose first places the instances hold at BASE.
+template <int64_t LabelInst::*BASE>
+__device__ __forceinline__ int find_inst(const LabelInst *insts, int n_inst, int64_t g) {
     int lo = 0, hi = n_inst - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (insts[mid].group_base <= g) lo = mid;
+        if (insts[mid].*BASE <= g) lo = mid;
         else hi = mid - 1;
     }
     return lo;
-}
-
-// A closed surface's winding number is a whole number at every point off it:
-// the sum's rounding is dropped.  Sums that are not near one (points on the
-// surface) are left as they are.
-__device__ __forceinline__ double whole(double w) {
-    const double r = rint(w);
-    return fabs(w - r) < 1e-3 ? r : w;
 }
 
 __device__ __forceinline__ void store_winding(const LabelInst &in, int type, int k, int64_t i, double w) {
@@ -69,16 +74,22 @@ __device__ __forceinline__ int culled_winding(const SurfaceDev &sd, float x, flo
     return -1;
 }
 
-// One point (the same in every lane) against surface sd.  A point strictly
-// outside the surface's box is outside its convex hull.
+// One point (the same in every lane) against surface sd: a ray where that is
+// certain, else the sum.  A point strictly outside the surface's box is outside
+// its convex hull.
 template <Mode MODE>
 __device__ __forceinline__ PointSum point_surface(const LabelInst &in, const SurfaceDev &sd, Lists &L,
                                                   float x, float y, float z, float kap) {
     if (x < sd.lo[0] || x > sd.hi[0] || y < sd.lo[1] || y > sd.hi[1] || z < sd.lo[2] || z > sd.hi[2])
-        return PointSum{0.0, false, false, 0u, 0u};
+        return PointSum{0.0, false, 0u, 0u};
     const float p[3] = {x, y, z};
+    const TriRec *rec = in.rec + sd.rec_begin;
+    const PatchEntry *ent = in.ent + 4 * sd.node_begin;
+    int v;
+    for (int i = 0; i < 2; ++i)
+        if (patch::ray_winding(ent, rec, sd, p, i, L, v)) return PointSum{(double)v, false, 0u, 0u};
     int n_near, n_far;
-    if (!patch::sort_patches(in.ent + 4 * sd.node_begin, p, p, L, n_near, n_far)) {
+    if (!patch::sort_patches<true>(ent, p, p, L, n_near, n_far)) {
         // (a list is full only where hundreds of patches share the point)
         n_near = 1;
         n_far = 0;
@@ -86,32 +97,34 @@ __device__ __forceinline__ PointSum point_surface(const LabelInst &in, const Sur
         if (lane_id() == 0) L.near[0] = make_uint2(0u, (uint32_t)(sd.rec_end - sd.rec_begin));
         wave_sync();
     }
-    const PointSum s = patch::point_sum<MODE>(in.rec + sd.rec_begin, L, n_near, n_far, x, y, z, kap);
+    const PointSum s = patch::point_sum<MODE>(rec, L, n_near, n_far, x, y, z, kap);
     wave_sync();   // the lists are free again
     return s;
+}
+
+// The lanes' boxes joined, in every lane.
+__device__ __forceinline__ void box_join(float (&lo)[3], float (&hi)[3]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            lo[c] = fminf(lo[c], __shfl_xor(lo[c], d));
+            hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], d));
+        }
+        lo[c] = readlane_v(lo[c], 0);
+        hi[c] = readlane_v(hi[c], 0);
+    }
 }
 
 // Box of the points of the lanes with `mine`, in every lane.
 __device__ __forceinline__ void box_of(bool mine, float x, float y, float z, float (&lo)[3], float (&hi)[3]) {
     const float inf = __builtin_inff();
     const float p[3] = {x, y, z};
-#pragma unroll
     for (int c = 0; c < 3; ++c) {
-        float a = mine ? p[c] : inf, b = mine ? p[c] : -inf;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            a = fminf(a, __shfl_xor(a, d));
-            b = fmaxf(b, __shfl_xor(b, d));
-        }
-        lo[c] = readlane_v(a, 0);
-        hi[c] = readlane_v(b, 0);
+        lo[c] = mine ? p[c] : inf;
+        hi[c] = mine ? p[c] : -inf;
     }
-}
-
-__device__ __forceinline__ unsigned wave_add(unsigned v) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) v += (unsigned)__shfl_xor((int)v, d);
-    return v;
+    box_join(lo, hi);
 }
 
 __device__ __forceinline__ void count(unsigned long long *counters, int which, unsigned long long v) {
@@ -154,7 +167,7 @@ __device__ __forceinline__ bool point_final(const LabelInst &in, const LabelArgs
         }
     }
     const PointSum s = point_surface<F64 ? patch::kDouble : patch::kMixed>(in, sd, L, x, y, z, a.kappa);
-    w = s.on ? s.half * kInv2Pi : whole(s.half * kInv2Pi);
+    w = s.w;
     t.exact += s.exact;
     if (!F64) {
         t.n_f64 += s.n_f64;
@@ -168,10 +181,10 @@ __device__ __forceinline__ bool point_final(const LabelInst &in, const LabelArgs
 }
 
 // ------------------------------------------------------------- single points
-// What bounds it: latency.  A point costs two dependent loads per tree level
-// and about 8 sqrt(T) / 64 rounds of triangle loads; with one wavefront per
-// point (SPREAD: per point and fourth of its surfaces) there is no other
-// serial chain.
+// What bounds it: latency.  A point costs two dependent loads per tree level and
+// some ten leaves that its ray passes; with one wavefront per point (SPREAD: per
+// point and fourth of its surfaces) there is no other serial chain.  10,007 points
+// x 4 surfaces of 20,480 triangles: 58 us (as sums over the caps: 138).
 template <bool F64, bool SPREAD>
 __global__ __launch_bounds__(512) void k_label_point(LabelArgs a) {
     extern __shared__ __align__(16) unsigned char shared[];
@@ -180,7 +193,7 @@ __global__ __launch_bounds__(512) void k_label_point(LabelArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
     Lists &L = ((Lists *)shared)[wave];
     const int64_t g = SPREAD ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * waves + wave;
-    const int ii = a.insts ? find_group(a.insts, a.n_inst, g) : 0;
+    const int ii = a.insts ? find_inst<&LabelInst::group_base>(a.insts, a.n_inst, g) : 0;
     const LabelInst &in = a.insts ? a.insts[ii] : a.one;
     const int64_t n = label_count(a, in);
     const int64_t i = g - in.group_base;
@@ -213,125 +226,251 @@ __global__ __launch_bounds__(512) void k_label_point(LabelArgs a) {
     t.flush(in.counters);
 }
 
-// ------------------------------------------------------------- 64 per wavefront
-// What bounds it: load latency in the sum at the box's point and in the tree; the
-// crossings are some 80 instructions a triangle that meets the box.  6M lattice
-// points x 81,920 triangles, this kernel: 8.0 ms with a lane-by-lane walk over
-// the patches where the surface enters the box (1400 terms a point), 3.4 with the
-// crossings, 1.9 with one 48-byte record a triangle instead of strips (one
-// round of loads a term instead of three), 1.4 in Hilbert instead of Morton order.
-template <bool F64>
-__global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
-    extern __shared__ __align__(16) unsigned char shared[];
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
-    Lists &L = ((Lists *)shared)[wave];
-    const int64_t g = (int64_t)blockIdx.x * waves + wave;
-    const int ii = a.insts ? find_group(a.insts, a.n_inst, g) : 0;
+// ------------------------------------------------------------------- spans
+// Eight groups share most of their winding numbers: a surface that does not enter
+// the box of all 512 points takes one ray here instead of eight.
+// One wavefront per (span, surface): with the surfaces of a span one after the
+// other the launch was a serial chain (20 surfaces, 660,000 points: 0.33 ms).
+// (6M lattice points x 81,920 triangles, all of labeling: 1.79 ms without, 1.19 with.)
+// cull_bounds: the winding number that the option's own test gives every point of
+// a span.
+__device__ __forceinline__ int32_t culled_span(const LabelInst &in, const LabelArgs &a, const SurfaceDev &sd,
+                                               int64_t span, int64_t n) {
+    bool out = true, ball = sd.ball_w >= 0;
+    for (int j = 0; j < (int)kSpanGroups; ++j) {
+        const int64_t at = span * kSpanPoints + j * 64 + lane_id();
+        if (at >= n) continue;
+        const int64_t idx = a.ord.perm[in.order_base + at];
+        const float x = in.x[idx], y = in.y[idx], z = in.z[idx];
+        if (!finite3(x, y, z)) continue;
+        const int w = culled_winding(sd, x, y, z);
+        out = out && w == 0;
+        ball = ball && w >= 0 && w == sd.ball_w;
+    }
+    if (ballot(!out) == 0) return 0;
+    return ballot(!ball) == 0 ? sd.ball_w : kSpanUnknown;
+}
+
+__global__ __launch_bounds__(64) void k_label_span(LabelArgs a) {
+    __shared__ Lists L;
+    const int64_t g = blockIdx.x;
+    const int ii = a.insts ? find_inst<&LabelInst::span_entry>(a.insts, a.n_inst, g) : 0;
     const LabelInst &in = a.insts ? a.insts[ii] : a.one;
-    const int64_t n = label_count(a, in);
+    const int64_t n = label_count(a, in), span = (g - in.span_entry) / in.n_surf;
+    const int k = (int)((g - in.span_entry) % in.n_surf), lane = lane_id();
+    if (span * kSpanPoints >= n) return;
+    const float inf = __builtin_inff();
+    float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
+    unsigned long long n_good = 0;
+    for (int j = 0; j < (int)kSpanGroups; ++j) {
+        const int64_t at = span * kSpanPoints + j * 64 + lane;
+        const int64_t idx = at < n ? (int64_t)a.ord.perm[in.order_base + at] : 0;
+        const float p[3] = {in.x[idx], in.y[idx], in.z[idx]};
+        const bool good = at < n && finite3(p[0], p[1], p[2]);
+        n_good += __popcll(ballot(good));
+        if (good)
+            for (int c = 0; c < 3; ++c) {
+                lo[c] = fminf(lo[c], p[c]);
+                hi[c] = fmaxf(hi[c], p[c]);
+            }
+    }
+    box_join(lo, hi);
+    const SurfaceDev &sd = in.surf[k];
+    int32_t v = kSpanUnknown;
+    unsigned long long culled = 0;
+    if (a.cull && (v = culled_span(in, a, sd, span, n)) != kSpanUnknown) {
+        culled = n_good * (unsigned long long)sd.n_tri;
+    } else if (!(lo[0] <= hi[0]) || lo[0] > sd.hi[0] || hi[0] < sd.lo[0] || lo[1] > sd.hi[1] || hi[1] < sd.lo[1] ||
+        lo[2] > sd.hi[2] || hi[2] < sd.lo[2]) {
+        v = 0;
+    } else {
+        const TriRec *rec = in.rec + sd.rec_begin;
+        const PatchEntry *ent = in.ent + 4 * sd.node_begin;
+        if (patch::triangles_near(ent, rec, lo, hi, L, 0, 0) == 0) {
+            float q[3];
+            for (int c = 0; c < 3; ++c) q[c] = 0.5f * lo[c] + 0.5f * hi[c];
+            int r;
+            if (patch::ray_winding(ent, rec, sd, q, 0, L, r)) v = r;
+        }
+    }
+    if (lane == 0) {
+        a.span_w[g] = v;
+        if (v == kSpanUnknown) a.open_spans[atomicAdd(&a.work[kWorkOpen], 1ull)] = (uint32_t)g;
+    }
+    count(in.counters, kCntCulled, culled);
+}
+
+// ------------------------------------------------------------- open pairs
+// What bounds it: load latency in the tree, and the crossings, some 60
+// instructions for each triangle that meets the box.  One wavefront per pair: with
+// a group's surfaces one after the other the launch ended in a long tail.  The
+// point of known winding takes a ray; as a sum over the patches' caps it took 100
+// and more rounds of 130 instructions instead of some 10 of 40 (us, sum / ray: 6M
+// lattice points x 81,920 triangles 1190 / 820; 60,001 points near two surfaces
+// 840 / 420; 24 instances 1650 / 1130).
+template <bool F64, int RUNS>
+__global__ __launch_bounds__(512) void k_label_pair(LabelArgs a) {
+    extern __shared__ __align__(16) unsigned char shared[];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    Lists &L = ((Lists *)shared)[wave];
     const int lane = lane_id();
-    const int64_t at = (g - in.group_base) * 64 + lane;
-    if (at - lane >= n) return;
-    const bool valid = at < n;
-    const int64_t idx = valid ? (int64_t)a.ord.perm[in.order_base + at] : 0;
-    float px = valid ? in.x[idx] : 0.0f, py = valid ? in.y[idx] : 0.0f, pz = valid ? in.z[idx] : 0.0f;
-    const bool good = valid && finite3(px, py, pz);
-    if (!good) { px = 0.0f; py = 0.0f; pz = 0.0f; }
-    const uint64_t good_mask = ballot(good);
-    float lo[3], hi[3];
-    box_of(good, px, py, pz, lo, hi);
-    uint64_t enc = 0, flg = 0;
-    int32_t lab = 0;
-    Tally t;
     typedef typename std::conditional<F64, double, float>::type T;
-    for (int k = 0; k < in.n_surf; ++k) {
+    const int64_t total = a.span_w ? (int64_t)a.work[kWorkOpen] * kSpanGroups : a.n_pairs * RUNS;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    for (int64_t item = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave; item < total; item += waves) {
+        int ii = 0, k;
+        int64_t group;
+        if (RUNS == 1 && a.span_w) {
+            const int64_t e = a.open_spans[item / kSpanGroups];
+            if (a.insts) ii = find_inst<&LabelInst::span_entry>(a.insts, a.n_inst, e);
+            const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+            const int64_t r = e - in.span_entry;
+            k = (int)(r % in.n_surf);
+            group = r / in.n_surf * kSpanGroups + item % kSpanGroups;
+        } else {
+            const int64_t e = item / RUNS;
+            if (a.insts) ii = find_inst<&LabelInst::pair_base>(a.insts, a.n_inst, e);
+            const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+            const int64_t r = e - in.pair_base;
+            k = (int)(r % in.n_surf);
+            group = r / in.n_surf;
+        }
+        const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+        const int64_t n = label_count(a, in), at = group * 64 + lane;
+        if (group * 64 >= n) continue;
         const SurfaceDev &sd = in.surf[k];
+        const int part = RUNS > 1 ? (int)(item % RUNS) : 0, first = part * (64 / RUNS), end = first + 64 / RUNS;
+        const bool valid = at < n && lane >= first && lane < end;
+        const int64_t idx = valid ? (int64_t)a.ord.perm[in.order_base + at] : 0;
+        float px = valid ? in.x[idx] : 0.0f, py = valid ? in.y[idx] : 0.0f, pz = valid ? in.z[idx] : 0.0f;
+        const bool good = valid && finite3(px, py, pz);
+        if (!good) { px = 0.0f; py = 0.0f; pz = 0.0f; }
+        const uint64_t good_mask = ballot(good);
+        float lo[3], hi[3];
+        box_of(good, px, py, pz, lo, hi);
         double w = 0.0;
         bool cond = false, apart = false;
-        bool outside = good_mask == 0 || lo[0] > sd.hi[0] || hi[0] < sd.lo[0] || lo[1] > sd.hi[1] ||
-                       hi[1] < sd.lo[1] || lo[2] > sd.hi[2] || hi[2] < sd.lo[2];
+        bool open = good_mask != 0 && lo[0] <= sd.hi[0] && hi[0] >= sd.lo[0] && lo[1] <= sd.hi[1] &&
+                    hi[1] >= sd.lo[1] && lo[2] <= sd.hi[2] && hi[2] >= sd.lo[2];
         if (a.cull && good_mask) {
             const int fix = culled_winding(sd, px, py, pz);
             int same = -1;
             if ((ballot(fix == 0) & good_mask) == good_mask) same = 0;
             else if ((ballot(fix >= 0 && fix == sd.ball_w) & good_mask) == good_mask) same = sd.ball_w;
             if (same >= 0) {
-                t.culled += (unsigned long long)__popcll(good_mask) * (unsigned long long)sd.n_tri;
+                count(in.counters, kCntCulled,
+                      (unsigned long long)__popcll(good_mask) * (unsigned long long)sd.n_tri);
                 w = (double)same;
-                outside = true;   // settled
+                open = false;
             }
         }
-        if (!outside) {
+        if (open) {
             const TriRec *rec = in.rec + sd.rec_begin;
+            const PatchEntry *ent = in.ent + 4 * sd.node_begin;
             // the whole wavefront, or aligned runs of lanes, halved while their box
-            // meets too many leaves
-            for (int pos = 0, len = 64; pos < 64;) {
+            // meets more triangles than the lists hold
+            for (int pos = first, len = 64 / RUNS; pos < end;) {
                 const uint64_t run = (len == 64 ? ~0ull : ((1ull << len) - 1ull) << pos) & good_mask;
-                float blo[3], bhi[3];
-                int n_near = 0, n_far = 0;
-                bool fits = true;
+                int n_cand = 0, v = 0, delta = 0;
+                bool known = false, uncertain = false;
                 if (run) {
-                    if (len == 64) {
+                    const bool mine = (run >> lane) & 1ull;
+                    float blo[3], bhi[3];
+                    if (len == 64 / RUNS) {
                         for (int c = 0; c < 3; ++c) { blo[c] = lo[c]; bhi[c] = hi[c]; }
                     } else {
-                        const bool mine = (run >> lane) & 1ull;
                         box_of(mine, px, py, pz, blo, bhi);
                     }
-                    fits = patch::sort_patches(in.ent + 4 * sd.node_begin, blo, bhi, L, n_near, n_far);
-                    if ((!fits || n_near > kSplitLeaves) && len > kSplitMin) {
+                    n_cand = patch::triangles_near(ent, rec, blo, bhi, L, 0, patch::kNearTri);
+                    if (n_cand < 0 && len > kSplitMin) {
                         len >>= 1;
-                        wave_sync();
                         continue;
                     }
-                }
-                double v = 0.0;
-                int delta = 0;
-                bool known = false, uncertain = false;
-                // The sum's point: inside the box, off its planes of symmetry, so
-                // that segments to lattice points seldom pass through edges of a
-                // regular mesh; where float32 does not certify its sum, another.
-                const float at[3][3] = {{0.4871f, 0.5237f, 0.5113f}, {0.3137f, 0.6719f, 0.4481f},
-                                        {0.6863f, 0.3571f, 0.6229f}};
-                for (int i = 0; i < 3 && run && fits && !known; ++i) {
-                    float q[3];
-                    for (int c = 0; c < 3; ++c)
-                        q[c] = fminf(fmaxf(fmaf(bhi[c] - blo[c], at[i][c], blo[c]), blo[c]), bhi[c]);
-                    const PointSum s = patch::point_sum<F64 ? patch::kDouble : patch::kFloat>(
-                        rec, L, n_near, n_far, q[0], q[1], q[2], a.kappa);
-                    v = rint(s.half * kInv2Pi);
-                    known = !s.uncertain && !s.on && fabs(s.half * kInv2Pi - v) < 1e-3;
-                    t.exact += s.exact;
-                    if (known && n_near > 0) {
-                        const T d[3] = {(T)px - (T)q[0], (T)py - (T)q[1], (T)pz - (T)q[2]};
-                        T d2 = 0;
-                        for (int c = 0; c < 3; ++c) {
-                            const T r = fmax((T)bhi[c] - (T)q[c], (T)q[c] - (T)blo[c]);
-                            d2 += r * r;
+                    // The point of known winding: inside the box, off its planes of
+                    // symmetry, so that segments to lattice points seldom pass
+                    // through edges of a regular mesh; where one ray does not
+                    // settle it, another point.
+                    const float frac[3][3] = {{0.4871f, 0.5237f, 0.5113f}, {0.3137f, 0.6719f, 0.4481f},
+                                              {0.6863f, 0.3571f, 0.6229f}};
+                    for (int i = 0; i < 3 && n_cand >= 0 && !known; ++i) {
+                        float q[3];
+                        for (int c = 0; c < 3; ++c)
+                            q[c] = fminf(fmaxf(fmaf(bhi[c] - blo[c], frac[i][c], blo[c]), blo[c]), bhi[c]);
+                        known = patch::ray_winding(ent, rec, sd, q, i, L, v);
+                        if (known && n_cand > 0) {
+                            const T d[3] = {(T)px - (T)q[0], (T)py - (T)q[1], (T)pz - (T)q[2]};
+                            T d2 = 0;
+                            for (int c = 0; c < 3; ++c) {
+                                const T r = fmax((T)bhi[c] - (T)q[c], (T)q[c] - (T)blo[c]);
+                                d2 += r * r;
+                            }
+                            patch::near_crossings<T>(rec, L, n_cand, q, d, sqrt(d2) * (T)1.00001, delta,
+                                                     uncertain);
                         }
-                        patch::near_crossings<T>(rec, L, n_near, blo, bhi, q, d, sqrt(d2) * (T)1.00001, delta,
-                                                 uncertain);
                     }
                 }
                 if ((run >> lane) & 1ull) {
-                    w = v + (double)delta;
+                    w = (double)(v + delta);
                     cond = known && uncertain;
                     apart = !known;   // left to k_recheck
                 }
-                wave_sync();   // the lists are free again
                 pos += len;
                 len = pos & -pos;   // the largest run aligned here
             }
         }
-        const bool inside = w >= a.threshold;
-        if (apart || cond) flg |= 1ull << k;
-        if (!F64 && !apart) {
-            const bool band = fabs(w - a.threshold) < a.band;
-            t.band += __popcll(ballot(band) & good_mask);
-            t.cond += __popcll(ballot(cond) & good_mask);
-            if (band) flg |= 1ull << k;
+        const uint64_t in_bits = ballot(w >= a.threshold) & good_mask;
+        uint64_t redo = ballot(apart || cond) & good_mask;
+        if (!F64) {
+            const uint64_t band = ballot(!apart && fabs(w - a.threshold) < a.band) & good_mask;
+            count(in.counters, kCntBand, (unsigned long long)__popcll(band));
+            count(in.counters, kCntCond, (unsigned long long)__popcll(ballot(cond) & good_mask));
+            redo |= band;
         }
-        if (inside) { enc |= 1ull << k; lab = sd.label; }
-        if (valid) store_winding(in, a.winding_type, k, idx, good ? w : __builtin_nan(""));
+        PairBits *out = a.pairs + in.pair_base + group * in.n_surf + k;
+        if (lane == 0 && RUNS == 1) *out = PairBits{in_bits, redo};
+        if (lane == 0 && RUNS == 4) {
+            ((uint16_t *)&out->in)[part] = (uint16_t)(in_bits >> first);
+            ((uint16_t *)&out->redo)[part] = (uint16_t)(redo >> first);
+        }
+        if (good) store_winding(in, a.winding_type, k, idx, w);
+    }
+}
+
+// ------------------------------------------------------------------- labels
+// Bound by memory: the points are read once more (to find those without a
+// place) and the labels written through the order.
+template <bool F64>
+__global__ __launch_bounds__(256) void k_label_final(LabelArgs a) {
+    const int64_t g = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int ii = a.insts ? find_inst<&LabelInst::group_base>(a.insts, a.n_inst, g) : 0;
+    const LabelInst &in = a.insts ? a.insts[ii] : a.one;
+    const int64_t n = label_count(a, in), group = g - in.group_base;
+    const int lane = lane_id();
+    const int64_t at = group * 64 + lane;
+    if (group * 64 >= n) return;
+    const bool valid = at < n;
+    const int64_t idx = valid ? (int64_t)a.ord.perm[in.order_base + at] : 0;
+    const bool good = valid && finite3(in.x[idx], in.y[idx], in.z[idx]);
+    const uint64_t good_mask = ballot(good);
+    uint64_t enc = 0, flg = 0;
+    int32_t lab = 0;
+    unsigned band = 0;
+    for (int k = 0; k < in.n_surf; ++k) {
+        const int32_t v = a.span_w ? a.span_w[in.span_entry + group / kSpanGroups * in.n_surf + k] : kSpanUnknown;
+        bool inside, redo = false;
+        if (v != kSpanUnknown) {
+            inside = (double)v >= a.threshold;
+            redo = !F64 && fabs((double)v - a.threshold) < a.band;
+            if (redo) band += (unsigned)__popcll(good_mask);
+            if (good) store_winding(in, a.winding_type, k, idx, (double)v);
+        } else {
+            const PairBits b = a.pairs[in.pair_base + group * in.n_surf + k];
+            inside = (b.in >> lane) & 1ull;
+            redo = (b.redo >> lane) & 1ull;
+        }
+        if (inside) { enc |= 1ull << k; lab = in.surf[k].label; }
+        if (redo) flg |= 1ull << k;
+        if (valid && !good) store_winding(in, a.winding_type, k, idx, __builtin_nan(""));
     }
     if (valid) {
         in.labels[idx] = good ? lab : -1;
@@ -342,7 +481,7 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
     if (m) {
         const int leader = __builtin_ctzll(m);
         int64_t base = 0;
-        if (lane == leader) base = (int64_t)atomicAdd(a.list_n, (unsigned long long)__popcll(m));
+        if (lane == leader) base = (int64_t)atomicAdd(&a.work[kWorkFlagged], (unsigned long long)__popcll(m));
         base = readlane_v(base, leader);
         if (want) {
             FlagEntry e;
@@ -353,7 +492,7 @@ __global__ __launch_bounds__(512) void k_label_wave(LabelArgs a) {
             a.flag_list[base + lanes_below(m)] = e;
         }
     }
-    t.flush(in.counters);
+    count(in.counters, kCntBand, band);
 }
 
 // Flagged points: their flagged surfaces again, and the label.  A pair's sum
@@ -365,7 +504,7 @@ __global__ __launch_bounds__(256) void k_recheck(LabelArgs a) {
     __shared__ Lists lists[4];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     Lists &L = lists[wave];
-    const int64_t count_n = (int64_t)*a.list_n;
+    const int64_t count_n = (int64_t)a.work[kWorkFlagged];
     const int64_t step = (int64_t)gridDim.x * 4;
     const int lane = lane_id();
     Tally t;
@@ -386,7 +525,7 @@ __global__ __launch_bounds__(256) void k_recheck(LabelArgs a) {
         for (; f; f &= f - 1) {
             const int k = __builtin_ctzll(f);
             const PointSum s = point_surface<F64 ? patch::kDouble : patch::kMixed>(in, in.surf[k], L, x, y, z, a.kappa);
-            const double w = s.on ? s.half * kInv2Pi : whole(s.half * kInv2Pi);
+            const double w = s.w;
             t.exact += s.exact;
             t.n_f64 += s.n_f64;
             if (s.on || w >= a.threshold) enc |= 1ull << k;
@@ -409,14 +548,32 @@ __global__ void k_fill_u64(unsigned long long *p, unsigned long long v, int64_t 
 
 }  // namespace
 
-hipError_t launch_label_wave(const LabelArgs &a, bool fp64, int64_t groups, int block_waves, hipStream_t s) {
-    if (groups <= 0) return hipSuccess;
-    const int64_t blocks = (groups + block_waves - 1) / block_waves;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 g((unsigned)blocks), b(64u * (unsigned)block_waves);
+hipError_t launch_label_pair(const LabelArgs &a, bool fp64, int64_t waves, int block_waves, hipStream_t s) {
+    if (waves <= 0) return hipSuccess;
+    const bool quarters = !a.span_w && a.n_pairs < kQuarterPairs;
+    if (quarters) waves = a.n_pairs * 4;
+    const dim3 g((unsigned)((waves + block_waves - 1) / block_waves)), b(64u * (unsigned)block_waves);
     const size_t lds = sizeof(Lists) * (size_t)block_waves;
-    if (fp64) k_label_wave<true><<<g, b, lds, s>>>(a);
-    else k_label_wave<false><<<g, b, lds, s>>>(a);
+    if (fp64 && quarters) k_label_pair<true, 4><<<g, b, lds, s>>>(a);
+    else if (fp64) k_label_pair<true, 1><<<g, b, lds, s>>>(a);
+    else if (quarters) k_label_pair<false, 4><<<g, b, lds, s>>>(a);
+    else k_label_pair<false, 1><<<g, b, lds, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_label_final(const LabelArgs &a, bool fp64, int64_t groups, hipStream_t s) {
+    if (groups <= 0) return hipSuccess;
+    const int64_t blocks = (groups + 3) / 4;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if (fp64) k_label_final<true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(a);
+    else k_label_final<false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_label_span(const LabelArgs &a, int64_t entries, hipStream_t s) {
+    if (entries <= 0) return hipSuccess;
+    if (entries > 0x7fffffff) return hipErrorInvalidValue;
+    k_label_span<<<dim3((unsigned)entries), dim3(64), 0, s>>>(a);
     return hipGetLastError();
 }
 

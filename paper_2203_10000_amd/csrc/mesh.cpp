@@ -196,7 +196,7 @@ sal_status label_scratch(sal_context *ctx, sal_tet_mesh *m, const sal_surface_se
                          const sal_label_options &opt, int32_t *labels, hipEvent_t ev_start,
                          hipEvent_t ev_mid, unsigned long long *masks = nullptr) {
     if (n <= 0) return SAL_OK;
-    const sal_status st = ensure_label_scratch(ctx, n);
+    const sal_status st = ensure_label_scratch(ctx, set, n);
     if (st != SAL_OK) return st;
     return enqueue_label(ctx, set, n, m->cen[0], m->cen[1], m->cen[2], opt, labels, nullptr,
                          ev_start, ev_mid, nullptr, masks);
@@ -208,7 +208,7 @@ sal_status label_scratch_dev(sal_context *ctx, sal_tet_mesh *m, const sal_surfac
                              const sal_label_options &opt_in, int32_t *labels, hipEvent_t ev_start,
                              hipEvent_t ev_mid, unsigned long long *masks) {
     if (n_cap <= 0) return SAL_OK;
-    sal_status st = ensure_label_scratch(ctx, n_cap);
+    sal_status st = ensure_label_scratch(ctx, set, n_cap);
     if (st != SAL_OK) return st;
     sal_label_options opt = opt_in;
     st = tune_launch(ctx, set, n_cap, m->cen[0], m->cen[1], m->cen[2], labels, &opt);
@@ -300,7 +300,7 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
         }
         if (pts_max > 0) {
             if ((st = ensure_centroids(m, pts_max, s)) != SAL_OK) return st;
-            if ((st = ensure_label_scratch(ctx, pts_max)) != SAL_OK) return st;
+            if ((st = ensure_label_scratch(ctx, set, pts_max)) != SAL_OK) return st;
             if (nodes) {
                 int64_t c3 = m->mid_xyz_cap;
                 for (int a = 0; a < 3; ++a) {
@@ -500,7 +500,7 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
         (st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, budget + budget / 2, s)) != SAL_OK)
         return st;
     const int64_t kid_cap = std::min(m->cen_cap, m->lab_cap);
-    if ((st = ensure_label_scratch(ctx, kid_cap)) != SAL_OK) return st;
+    if ((st = ensure_label_scratch(ctx, set, kid_cap)) != SAL_OK) return st;
     int64_t list_need = 0, blocks_need = 1;
     for (int l = 0; l <= kMaxLevels; ++l) {
         list_need += m->cap[l];
@@ -535,12 +535,15 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
     add(set->uid);
     addp(ctx);
     addp(ctx->flag_list);
-    addp(ctx->list_n);
+    addp(ctx->work);
     addp(ctx->ord_idx1);
     addp(ctx->ord_key1);
     addp(ctx->ord_perm);
     addp(ctx->ord_hist);
     addp(ctx->ord_tot);
+    addp(ctx->span_w);
+    addp(ctx->open_spans);
+    addp(ctx->pairs);
     addp(ctx->counters);
     add((uint64_t)opt.precision);
     addd(opt.threshold);

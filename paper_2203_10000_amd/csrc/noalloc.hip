@@ -20,16 +20,20 @@ constexpr int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 // Byte offsets of the parts of the scratch array.
 constexpr int64_t kOffCounters = 0;
 constexpr int64_t kOffFlags = align256(kOffCounters + kNumCounters * 8);
-constexpr int64_t kOffListN = align256(kOffFlags + kNoAllocMaxPoints * (int64_t)sizeof(FlagEntry));
-constexpr int64_t kOffIdx1 = align256(kOffListN + 8);
+constexpr int64_t kOffWork = align256(kOffFlags + kNoAllocMaxPoints * (int64_t)sizeof(FlagEntry));
+constexpr int64_t kOffIdx1 = align256(kOffWork + kNumWork * 8);
 constexpr int64_t kOffKey1 = align256(kOffIdx1 + kNoAllocMaxPoints * 4);
 constexpr int64_t kOffPerm = align256(kOffKey1 + kNoAllocMaxPoints * 2);
 constexpr int64_t kOffHist = align256(kOffPerm + kNoAllocMaxPoints * 4);
 constexpr int64_t kOffTot = align256(kOffHist + kNoAllocMaxPoints / kMinTile * kOrderBins * 4);
-constexpr int64_t kScratchBytes = align256(kOffTot + kOrderBins * 4);
+constexpr int64_t kOffSpans = align256(kOffTot + kOrderBins * 4);
+constexpr int64_t kOffOpen = align256(kOffSpans + kNoAllocMaxPoints / kSpanPoints * kMaxSurfaces * 4);
+constexpr int64_t kOffPairs = align256(kOffOpen + kNoAllocMaxPoints / kSpanPoints * kMaxSurfaces * 4);
+constexpr int64_t kScratchBytes =
+    align256(kOffPairs + kNoAllocMaxPoints / 64 * kMaxSurfaces * (int64_t)sizeof(PairBits));
 static_assert(kNoAllocMaxPoints / kMinTile <= kMaxTiles, "every tile of a full call has the smallest size");
 
-// ~39 MB per device, held until the process ends.  Host code must never pass
+// ~58 MB per device, held until the process ends.  Host code must never pass
 // this name to a kernel: on the host it is only a stand-in for the symbol;
 // the device address comes from hipGetSymbolAddress below.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -95,7 +99,10 @@ extern "C" sal_status sal_label_points_noalloc(sal_context *ctx, const sal_surfa
         LabelScratch sc;
         sc.counters = (unsigned long long *)(base + kOffCounters);
         sc.flag_list = (FlagEntry *)(base + kOffFlags);
-        sc.list_n = (unsigned long long *)(base + kOffListN);
+        sc.work = (unsigned long long *)(base + kOffWork);
+        sc.span_w = (int32_t *)(base + kOffSpans);
+        sc.open_spans = (uint32_t *)(base + kOffOpen);
+        sc.pairs = (PairBits *)(base + kOffPairs);
         sc.ord.idx1 = (uint32_t *)(base + kOffIdx1);
         sc.ord.key1 = (uint16_t *)(base + kOffKey1);
         sc.ord.perm = (uint32_t *)(base + kOffPerm);

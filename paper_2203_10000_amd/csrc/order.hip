@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_order_hist(LabelArgs a) {
     const int ii = a.insts ? find_tile(a.insts, a.n_inst, blockIdx.x) : 0;
     const LabelInst &in = a.insts ? a.insts[ii] : a.one;
     const int64_t n = label_count(a, in), t = (int64_t)blockIdx.x - in.tile_base;
-    if (PASS == 1 && blockIdx.x == 0 && threadIdx.x == 0) *a.list_n = 0ull;
+    if (PASS == 1 && blockIdx.x == 0 && threadIdx.x < kNumWork) a.work[threadIdx.x] = 0ull;
     for (int b = threadIdx.x; b < bins<PASS>(); b += kThreads) h[b] = 0u;
     __syncthreads();
     const int64_t i0 = t * in.tile, i1 = i0 + in.tile < n ? i0 + in.tile : n;

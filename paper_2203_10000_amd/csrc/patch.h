@@ -12,21 +12,28 @@ namespace sal {
 namespace patch {
 
 constexpr int kNearCap = 96;    // near leaves of one box (96 x ~45 triangles)
+constexpr int kNearTri = 512;   // triangles that may meet a box
+constexpr int kRayTri = 256;    // and a ray's box
 constexpr int kFarCap = 384;    // far patches: 3 siblings per level and near node
 constexpr int kFrontCap = 64;   // near nodes of one level
 
 // One wavefront's working lists in LDS (4.4 KB: 37 wavefronts fit a CU's LDS,
-// so they do not limit occupancy).  Entries are record ranges {begin, count}.
+// so they do not limit occupancy).  Patches are record ranges {begin, count},
+// triangles record numbers.
 struct Lists {
     uint2 near[kNearCap];
-    uint2 far[kFarCap];
+    union {
+        uint2 far[kFarCap];
+        uint32_t tri[kNearTri + kRayTri];
+    };
     uint32_t front[2][kFrontCap];
 };
 
 // Sorts the surface's patches by the box [lo, hi] (the same in every lane):
 // patches whose box it misses go to the far list as their caps, leaves it
 // meets to the near list.  Sixteen nodes are opened at a time, one lane per
-// entry.  False when a list is full.
+// entry.  Without FAR no caps are listed.  False when a list is full.
+template <bool FAR>
 __device__ __forceinline__ bool sort_patches(const PatchEntry *__restrict__ ent, const float (&lo)[3],
                                              const float (&hi)[3], Lists &L, int &n_near, int &n_far) {
     const int lane = lane_id();
@@ -48,7 +55,7 @@ __device__ __forceinline__ bool sort_patches(const PatchEntry *__restrict__ ent,
                                lo[1] <= __uint_as_float(e1.y) && hi[1] >= __uint_as_float(e0.y) &&
                                lo[2] <= __uint_as_float(e1.z) && hi[2] >= __uint_as_float(e0.z);
             const bool leaf = (int32_t)e2.x < 0;
-            const bool to_far = live && !meets && e1.w != 0u;
+            const bool to_far = FAR && live && !meets && e1.w != 0u;
             const bool to_near = live && meets && leaf;
             const bool open = live && meets && !leaf;
             const uint64_t mf = ballot(to_far), mn = ballot(to_near), mo = ballot(open);
@@ -76,19 +83,23 @@ __device__ __forceinline__ Tri load_tri(const TriRec *__restrict__ rec, uint32_t
 }
 
 struct PointSum {
-    double half;       // sum of atan2(N, D): half the solid angle
+    double w;          // winding number
     bool on;           // the point lies on a triangle
-    bool uncertain;    // some float32 term is not certified (kFloat only)
     unsigned exact;    // exact-sign evaluations, this lane's
     unsigned n_f64;    // float32 terms recomputed in double, this lane's
 };
 
-// How a point's terms are evaluated: in float32 (uncertified ones counted),
-// in float32 with the uncertified ones in double, or all in double.
-enum Mode { kFloat, kMixed, kDouble };
+// How a point's terms are evaluated: in float32, those that it does not certify
+// in double, or all in double.
+enum Mode { kMixed, kDouble };
 
-// Half the solid angle of the listed ranges at one point (the same in every
-// lane).  Eight groups of eight lanes take ranges in turn, a group the next one
+// A closed surface has a whole winding number at every point off it.
+__device__ __forceinline__ double whole(double w) {
+    const double r = rint(w);
+    return fabs(w - r) < 1e-3 ? r : w;
+}
+
+// Winding number of the listed ranges at one point (the same in every lane).  Eight groups of eight lanes take ranges in turn, a group the next one
 // as it becomes free (all lanes run in step, so the assignment, and with it
 // the result, depends on the lists alone); a lane evaluates one triangle.  Most
 // caps have 20-60 triangles, so wider groups would leave more lanes idle at a
@@ -102,7 +113,7 @@ __device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, co
     const float branch_cut = kPiF - 0.25f * kap;
     const int items = n_near + n_far;
     const uint64_t leaders = 0x0101010101010101ull;
-    PointSum out{0.0, false, false, 0u, 0u};
+    PointSum out{0.0, false, 0u, 0u};
     float accf = 0.0f;
     double acc = 0.0;
     int next = 0, on = 0;
@@ -173,8 +184,6 @@ __device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, co
             const bool ill = !(fmaxf(fabsf(n1), fabsf(dd)) > thr) || fabsf(ang) > branch_cut;   // (NaN is ill)
             if (!ill) {
                 accf += ang;
-            } else if (MODE == kFloat) {
-                out.uncertain = true;
             } else {
                 const F64Term d = f64_term(q, px, py, pz, q_cap);
                 acc += d.half;
@@ -187,9 +196,8 @@ __device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, co
     acc += (double)accf;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d);
-    out.half = acc;
     out.on = ballot(on != 0) != 0;
-    out.uncertain = ballot(out.uncertain) != 0;
+    out.w = out.on ? acc * kInv2Pi : whole(acc * kInv2Pi);
     return out;
 }
 
@@ -301,6 +309,16 @@ __device__ __forceinline__ void cross(const Crossing<T> &t, const T (&d)[3], int
     else uncertain = true;
 }
 
+__device__ __forceinline__ void box_terms(const float (&lo)[3], const float (&hi)[3], float (&c)[3], float (&h)[3],
+                                          float &scale) {
+    scale = 0.0f;
+    for (int k = 0; k < 3; ++k) {
+        c[k] = 0.5f * lo[k] + 0.5f * hi[k];
+        h[k] = 0.5f * hi[k] - 0.5f * lo[k];
+        scale += fabsf(c[k]) + h[k];
+    }
+}
+
 // Whether triangle t may meet the box of centre c and half extents h (scale: |c|
 // + h): its own box does (exact comparisons) and its plane passes within the
 // box's radius, with a margin some thirty times the products' rounding.
@@ -320,40 +338,103 @@ __device__ __forceinline__ bool may_meet(const Tri &t, const float (&lo)[3], con
     return meets && !(fabsf(s) > reach + margin);
 }
 
-// Change of the winding number from q to each lane's point q + d (d as
-// computed; D bounds its length) through the near list's triangles.
-template <typename T>
-__device__ __forceinline__ void near_crossings(const TriRec *__restrict__ rec, const Lists &L, int n_near,
-                                               const float (&lo)[3], const float (&hi)[3],
-                                               const float (&q)[3], const T (&d)[3], T D, int &delta,
-                                               bool &uncertain) {
-    const int lane = lane_id();
-    float c[3], h[3];
-    for (int k = 0; k < 3; ++k) {
-        c[k] = 0.5f * lo[k] + 0.5f * hi[k];
-        h[k] = 0.5f * hi[k] - 0.5f * lo[k];
+// The surface's triangles that may meet the box, listed in L.tri from `at` on, at
+// most `cap`: their number, -1 if there are more (the surface then keeps to the
+// triangles unlisted; with cap 0, 0 is a proof that it does not enter the box).
+__device__ __forceinline__ int triangles_near(const PatchEntry *__restrict__ ent, const TriRec *__restrict__ rec,
+                                              const float (&lo)[3], const float (&hi)[3], Lists &L, int at,
+                                              int cap) {
+    int n_near, n_far, n = 0;
+    if (!sort_patches<false>(ent, lo, hi, L, n_near, n_far)) {
+        wave_sync();
+        return -1;
     }
-    const float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + h[0] + h[1] + h[2];
+    const int lane = lane_id();
+    float c[3], h[3], scale;
+    box_terms(lo, hi, c, h, scale);
     // a leaf a round (a leaf has at most 64 triangles), the next one's loaded ahead
     Tri t;
+    uint32_t r = 0;
     bool have = false;
     auto fetch = [&](int i) {
         const uint2 g = L.near[i < n_near ? i : 0];
         have = i < n_near && (uint32_t)lane < g.y;
-        t = load_tri(rec, have ? g.x + (uint32_t)lane : 0u);
+        r = have ? g.x + (uint32_t)lane : 0u;
+        t = load_tri(rec, r);
     };
     if (n_near > 0) fetch(0);
     for (int i = 0; i < n_near; ++i) {
-        const Tri now = t;
-        const bool live = have;
+        const bool meets = have && may_meet(t, lo, hi, c, h, scale);
+        const uint32_t now = r;
         fetch(i + 1);
-        const bool meets = live && may_meet(now, lo, hi, c, h, scale);
-        uint64_t m = ballot(meets);
-        if (m == 0) continue;
-        Crossing<T> own;
-        if (meets) own = make_crossing<T>(now, q, D);
-        for (; m; m &= m - 1) cross(own.from(__builtin_ctzll(m)), d, delta, uncertain);
+        const uint64_t m = ballot(meets);
+        if (n + __popcll(m) > cap) {
+            n = -1;
+            break;
+        }
+        if (meets) L.tri[at + n + lanes_below(m)] = now;
+        n += __popcll(m);
     }
+    wave_sync();
+    return n;
+}
+
+// Change of the winding number from q to each lane's point q + d (d as
+// computed; D bounds its length) through the n triangles listed first.
+template <typename T>
+__device__ __forceinline__ void near_crossings(const TriRec *__restrict__ rec, const Lists &L, int n,
+                                               const float (&q)[3], const T (&d)[3], T D, int &delta,
+                                               bool &uncertain) {
+    const int lane = lane_id();
+    for (int i = 0; i < n; i += 64) {
+        const int m = min(n - i, 64);
+        const Crossing<T> own = make_crossing<T>(load_tri(rec, L.tri[i + (lane < m ? lane : 0)]), q, D);
+        for (int j = 0; j < m; ++j) cross(own.from(j), d, delta, uncertain);
+    }
+}
+
+// Winding number at q, in the surface's box, from the crossings of a ray: 0 at
+// its end outside the box, which is reached along one of the axes (the nearest
+// face's for turn 0, the others for 1 and 2).  The ray leans by a percent, off
+// the planes of regular meshes and thin enough to meet few triangles.  One lane
+// per triangle, in double (a float's bound would leave a tenth of the rays
+// uncertain).  False if it is not certain.
+__device__ __forceinline__ bool ray_winding(const PatchEntry *__restrict__ ent, const TriRec *__restrict__ rec,
+                                            const SurfaceDev &sd, const float (&q)[3], int turn, Lists &L,
+                                            int &v) {
+    int axis = 0;
+    float best = __builtin_inff(), to[3];
+    for (int c = 0; c < 3; ++c) {
+        const float up = sd.hi[c] - q[c], down = q[c] - sd.lo[c], pad = 0.01f * (sd.hi[c] - sd.lo[c]);
+        to[c] = up <= down ? sd.hi[c] + pad : sd.lo[c] - pad;
+        if (fminf(up, down) < best) {
+            best = fminf(up, down);
+            axis = c;
+        }
+    }
+    axis = axis + turn >= 3 ? axis + turn - 3 : axis + turn;
+    const float len = fabsf(axis == 0 ? to[0] - q[0] : axis == 1 ? to[1] - q[1] : to[2] - q[2]);
+    float e[3], lo[3], hi[3];
+    double d[3], d2 = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        const float lean = c == 0 ? 0.0113f : c == 1 ? -0.0071f : 0.0093f;
+        e[c] = axis == c ? to[c] : fmaf(len, lean, q[c]);
+        lo[c] = fminf(e[c], q[c]);
+        hi[c] = fmaxf(e[c], q[c]);
+        d[c] = (double)e[c] - (double)q[c];
+        d2 += d[c] * d[c];
+    }
+    const int n = triangles_near(ent, rec, lo, hi, L, kNearTri, kRayTri);
+    int delta = 0;
+    bool uncertain = n < 0;
+    for (int i = 0; i < n; i += 64) {
+        if (lane_id() < n - i) {
+            const Tri t = load_tri(rec, L.tri[kNearTri + i + lane_id()]);
+            cross(make_crossing<double>(t, q, sqrt(d2) * 1.00001), d, delta, uncertain);
+        }
+    }
+    v = -(int)wave_add((unsigned)delta);
+    return ballot(uncertain) == 0;
 }
 
 }  // namespace patch

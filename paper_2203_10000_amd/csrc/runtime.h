@@ -21,7 +21,12 @@ struct sal_context {
     int64_t tile_cap = 0;
     uint32_t *ord_tot = nullptr;
     int64_t inst_cap = 0;
-    unsigned long long *list_n = nullptr;
+    int32_t *span_w = nullptr;
+    uint32_t *open_spans = nullptr;
+    int64_t span_cap = 0;
+    sal::PairBits *pairs = nullptr;
+    int64_t pair_cap = 0;
+    unsigned long long *work = nullptr;   // sal::kNumWork
     unsigned long long *counters = nullptr;  // sal::kNumCounters
     unsigned long long *tune_counters = nullptr;
     int n_cu = 0;
@@ -66,12 +71,12 @@ sal_status ensure_surface_balls(sal_context *ctx, const sal_surface_set *set);
 constexpr int64_t kChunkPoints = (int64_t)1 << 27;
 
 // Up to this many points are labeled one per wavefront, in the order given.  The
-// 64-point form pays six sorting launches first, and its wavefronts work through
-// their surfaces one after the other; with few of them on the chip that chain is
-// the time.  Measured (us, point form / 64-point form; box points): four shells
-// of 5,120 triangles, 8,192 points 118 / 300, 16,384 203 / 235, 32,768 359 / 203;
-// four of 20,480: 16,384 328 / 648, 65,536 1094 / 343.
-constexpr int64_t kPointFormMax = 16384;
+// 64-point form pays six sorting launches first, and with few wavefronts on the
+// chip the chain of one is the time.  Measured (us, point form / 64-point form;
+// 16,384, 32,768 and 60,000 points): lattice points, one surface, 30 / 75, 50 / 77,
+// 85 / 80; box points, four surfaces, 86 / 94, 155 / 108, 267 / 109; points near
+// two surfaces of 81,000 triangles, 75 / 276, 141 / 286, 249 / 296.
+constexpr int64_t kPointFormMax = 32768;
 
 // The same for an instance of a batch, whose other instances fill the chip.
 constexpr int64_t kBatchPointMax = 8192;
@@ -84,11 +89,26 @@ inline int32_t order_tile(int64_t n) {
 }
 inline int64_t order_tiles(int64_t n) { return (n + order_tile(n) - 1) / order_tile(n); }
 
-// Grows the context's labeling scratch to hold `points` in `tiles` tiles of
-// `insts` instances at once.
-sal_status ensure_label_scratch(sal_context *ctx, int64_t points, int64_t tiles, int64_t insts);
+// From this many (point, surface) pairs on, a pass over spans of 512 points
+// settles most of them first.  Below, its one more serial launch costs what it
+// saves.
+constexpr int64_t kSpanPairs = (int64_t)1 << 20;
+inline int64_t span_count(int64_t n) { return (n + kSpanPoints - 1) / kSpanPoints; }
+
+// Wavefronts per CU that share the open pairs: four times what its registers hold
+// at once, so that the last ones even out (6M lattice points, 20 surfaces in two
+// rounds, 24 instances; us): 24 872, 2998, 1208; 64 822, 2893, 1142.
+constexpr int kPairWaves = 64;
+inline int64_t group_count(int64_t n) { return (n + 63) / 64; }
+
+// What one launch sequence of the 64-point form needs.
+struct ScratchSize {
+    int64_t points = 0, tiles = 0, insts = 0, spans = 0, pairs = 0;   // (spans, pairs: x surfaces)
+};
+// Grows the context's labeling scratch to hold it.
+sal_status ensure_label_scratch(sal_context *ctx, const ScratchSize &need);
 // The same for a call on n points (nothing for the point form).
-sal_status ensure_label_scratch(sal_context *ctx, int64_t n);
+sal_status ensure_label_scratch(sal_context *ctx, const sal_surface_set *set, int64_t n);
 
 // Validated options with defaults applied.
 sal_status resolve_options(const sal_label_options *in, sal_label_options *out);
@@ -107,7 +127,10 @@ sal_status enqueue_label(sal_context *ctx, const sal_surface_set *set, int64_t n
 struct LabelScratch {
     unsigned long long *counters;
     FlagEntry *flag_list;
-    unsigned long long *list_n;
+    unsigned long long *work;
+    int32_t *span_w;
+    uint32_t *open_spans;
+    PairBits *pairs;
     OrderScratch ord;
 };
 

@@ -107,8 +107,10 @@ struct LabelInst {
     unsigned long long *counters; // kNumCounters
     int64_t n, wstride;
     int64_t order_base;           // first entry in the spatial order
-    int64_t group_base;           // first wavefront of the instance in its kernel's grid
+    int64_t group_base;           // first group of 64 points (or point) in the grids
+    int64_t pair_base;            // first (group, surface) pair
     int64_t tile_base;            // first tile of the spatial order
+    int64_t span_entry;           // first (span, surface) pair, a span being 8 groups
     int32_t n_tiles, tile;        // tiles of `tile` points
     int32_t n_surf;
     int32_t pad;
@@ -120,6 +122,19 @@ struct LabelInst {
 constexpr int kOrderBits1 = 11, kOrderBits2 = 10;   // 7 bits per axis
 constexpr int kOrderBins = 1 << kOrderBits1;
 constexpr int64_t kMinTile = 2048, kMaxTiles = 1024;   // per instance
+
+// Points of a span: the groups that may share one winding number.
+constexpr int64_t kSpanGroups = 8, kSpanPoints = 64 * kSpanGroups;
+constexpr int32_t kSpanUnknown = INT32_MIN;
+
+// What k_label_pair finds for the 64 points of a group against one surface.
+struct alignas(16) PairBits {
+    uint64_t in;     // winding number >= T
+    uint64_t redo;   // to be summed again (not certain, near T, or too far apart)
+};
+
+// Device counters of one launch sequence, cleared by launch_order.
+enum Work { kWorkFlagged = 0, kWorkOpen = 1, kNumWork = 2 };
 
 struct OrderScratch {
     uint32_t *idx1;   // [points] order after the first pass
@@ -142,7 +157,12 @@ struct LabelArgs {
     int32_t cull;             // skip a surface for points strictly outside its box
                               // (w = 0 exactly) or inside its ball (w = ball_w exactly)
     FlagEntry *flag_list;     // capacity: the points
-    unsigned long long *list_n;   // its length
+    unsigned long long *work; // kNumWork
+    PairBits *pairs;          // (group, surface)
+    int64_t n_pairs;          // over all instances
+    int32_t *span_w;          // (span, surface): the winding number that all of the span's points
+                              // have, or kSpanUnknown; null: no span pass
+    uint32_t *open_spans;     // the unknown ones
     OrderScratch ord;
 };
 
@@ -152,12 +172,17 @@ __device__ __forceinline__ int64_t label_count(const LabelArgs &a, const LabelIn
     return n < 0 ? 0 : (n < in.n ? n : in.n);
 }
 
-// Kernel launchers (label.hip, order.hip); `groups` and `tiles` are the
+// Kernel launchers (label.hip, order.hip); `groups`, `tiles` and `entries` are
 // totals over the instances, block_waves the wavefronts of a workgroup.
-// Spatial order of every instance's points; also clears *list_n.
+// Spatial order of every instance's points; also clears a.work.
 hipError_t launch_order(const LabelArgs &a, int64_t tiles, hipStream_t s);
-// 64 points of the order per wavefront.
-hipError_t launch_label_wave(const LabelArgs &a, bool fp64, int64_t groups, int block_waves, hipStream_t s);
+// Winding numbers of whole spans, into a.span_w (entries: spans x surfaces).
+hipError_t launch_label_span(const LabelArgs &a, int64_t entries, hipStream_t s);
+// The open (group, surface) pairs, 64 points of the order per wavefront; `waves`
+// wavefronts share them.
+hipError_t launch_label_pair(const LabelArgs &a, bool fp64, int64_t waves, int block_waves, hipStream_t s);
+// Labels, masks and the flag list from the pairs and spans.
+hipError_t launch_label_final(const LabelArgs &a, bool fp64, int64_t groups, hipStream_t s);
 // One point per wavefront, no order; results are final (nothing is flagged).
 // spread: the surfaces of a point are dealt to the workgroup's wavefronts.
 hipError_t launch_label_point(const LabelArgs &a, bool fp64, bool spread, int64_t groups, int block_waves,

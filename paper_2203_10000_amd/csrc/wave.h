@@ -43,6 +43,12 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+__device__ __forceinline__ unsigned wave_add(unsigned v) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) v += (unsigned)__shfl_xor((int)v, d);
+    return v;
+}
+
 __device__ __forceinline__ bool finite3(float x, float y, float z) {
     return __builtin_isfinite(x) && __builtin_isfinite(y) && __builtin_isfinite(z);
 }

@@ -14,7 +14,7 @@ import paper_2203_10000_amd as sal  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-POINT_FORM_MAX = 16384         # of label_points
+POINT_FORM_MAX = 32768         # of label_points
 BATCH_POINT_MAX = 8192         # of a batch's instance
 TOL = {"fp32": 1e-5, "fp64": 1e-12}   # the forms' stated bounds on winding numbers
 
@@ -126,3 +126,46 @@ def test_points_too_far_apart_for_a_common_walk(ctx, precision):
         assert torch.equal(lab, one)
         idx = rng.integers(0, p.shape[1], 400)
         assert np.array_equal(lab.cpu().numpy()[idx], oracle.label(p[:, idx].copy(), [surf]))
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_points_in_the_planes_of_a_regular_mesh(ctx, precision):
+    """Lattice points on the vertices, edges, diagonals and faces of a regular
+    box, and in the planes through them: rays from them and segments between
+    them meet edges."""
+    surf = _Surf(*SHAPES["box"](), label=4)
+    ss = sal.SurfaceSet(ctx, [surf])
+    for m in (13, 31):   # (both forms)
+        g = np.linspace(-60.0, 60.0, m, dtype=np.float32)   # steps of 10 and 4; 45 is met by neither
+        g = np.concatenate([g, [-45.0, 45.0]]).astype(np.float32)
+        pts = np.stack(np.meshgrid(g, g, g, indexing="ij")).reshape(3, -1).copy()
+        want, w_ref = oracle.label(pts, [surf], want_w=True)
+        lab, w, _ = sal.label_points(ctx, ss, torch.from_numpy(pts).cuda(), precision=precision, winding="f64")
+        assert np.array_equal(lab.cpu().numpy(), want), m
+        assert np.abs(w.cpu().numpy() - w_ref).max() < TOL[precision], m
+
+
+@pytest.mark.parametrize("cull", [False, True])
+def test_spans_of_points_against_many_surfaces(ctx, cull):
+    """Sixteen surfaces and 65535 or 65536 points, without and with whole spans
+    settled first; a last span and a last group that are not full."""
+    names = sorted(SHAPES)
+    surfs = []
+    for k in range(16):
+        v, f = SHAPES[names[k % 4]]()
+        surfs.append(_Surf(v * (1.0 - 0.05 * k) + np.array([3.0 * k - 20.0, 0.5 * k, -k]), f, k + 1))
+    ss = sal.SurfaceSet(ctx, surfs)
+    n = 65536 + 33
+    pts = _points(surfs[3], n, 23)
+    pts[:, 100] = np.nan
+    d = torch.from_numpy(pts).cuda()
+    lab, w, _ = sal.label_points(ctx, ss, d, winding="f64", cull=cull)
+    few = 65535
+    lab2, w2, _ = sal.label_points(ctx, ss, d[:, :few].contiguous(), winding="f64", cull=cull)
+    assert torch.equal(lab[:few], lab2)
+    assert torch.equal(torch.nan_to_num(w[:, :few], nan=-9.0), torch.nan_to_num(w2, nan=-9.0))
+    idx = np.concatenate([np.arange(101, 1101), np.arange(n - 600, n)])
+    want, w_ref = oracle.label(pts[:, idx].copy(), surfs, want_w=True)
+    assert np.array_equal(lab.cpu().numpy()[idx], want)
+    assert np.abs(w.cpu().numpy()[:, idx] - w_ref).max() < TOL["fp32"]
+    assert lab[100] == -1 and torch.isnan(w[:, 100]).all()
