@@ -295,6 +295,8 @@ sal_status sal_context_create(int device, void *stream, sal_context **out) {
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(counters)"); }
     e = dev_malloc((void **)&ctx->work, kNumWork * sizeof(unsigned long long));
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipMalloc(work counters)"); }
+    e = hipHostMalloc((void **)&ctx->host_words, 16 * sizeof(int64_t), hipHostMallocDefault);
+    if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipHostMalloc(host words)"); }
     e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
     if (e != hipSuccess) { sal_context_destroy(ctx); return hip_error(e, "hipStreamCreate"); }
     *out = ctx;
@@ -322,6 +324,7 @@ void sal_context_destroy(sal_context *ctx) {
                     ctx->batch_counters};
     for (void *p : bufs)
         if (p) (void)hipFree(p);
+    if (ctx->host_words) (void)hipHostFree(ctx->host_words);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
     pool_remove_context();
     delete ctx;

@@ -75,7 +75,7 @@ struct sal_tet_mesh {
     int64_t list_cap = 0;
     int64_t *blocks = nullptr;
     int64_t blocks_cap = 0;
-    int64_t *totals = nullptr;   // kMaxLevels + 1 counts
+    int64_t *totals = nullptr;   // kMaxLevels + 2 counts
     hipEvent_t ev[16] = {};
     // captured refine round
     int32_t *lab_scratch = nullptr;
@@ -189,6 +189,23 @@ sal_status compact(sal_tet_mesh *m, const CompactSrc &src, int64_t n, int32_t *o
     return SAL_OK;
 }
 
+// Lists the leaves (mask 0) or the entries with a flag bit of mask, level behind
+// level in `out`, and waits for the levels' counts and the extra word.
+sal_status compact_levels(sal_context *ctx, sal_tet_mesh *m, uint8_t mask, int32_t *out,
+                          int64_t (&count)[kMaxLevels + 1], const unsigned long long *extra = nullptr,
+                          int64_t *extra_out = nullptr) {
+    hipStream_t s = ctx->stream;
+    const LevelPtrs L = ptrs(m);
+    const int top = m->max_level;
+    const sal_status st = ensure_buf(m, &m->blocks, &m->blocks_cap, compact_level_blocks(L, top), s);
+    if (st != SAL_OK) return st;
+    SAL_HIP(launch_compact_levels(L, top, mask, m->blocks, m->totals, extra, ctx->host_words, out, s));
+    SAL_HIP(hipStreamSynchronize(s));
+    for (int l = 0; l <= kMaxLevels; ++l) count[l] = l <= top ? ctx->host_words[l] : 0;
+    if (extra_out) *extra_out = ctx->host_words[kMaxLevels + 1];
+    return SAL_OK;
+}
+
 // Labels n points whose centroids sit in the scratch into `labels`; records
 // ev_start after any launch-shape tuning and ev_mid after the pair loop
 // (before the recheck).
@@ -270,16 +287,10 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
     LevelPtrs L = ptrs(m);
     for (int l = 0; l <= top; ++l) SAL_HIP(launch_mark(L, m->g, m->T, l, s));
     SAL_HIP(hipEventRecord(m->ev[3], s));
-    int64_t off[kMaxLevels + 2] = {0};
-    for (int l = 0; l <= top; ++l) {
-        off[l + 1] = off[l] + m->n[l];
-        CompactSrc src{m->flag[l], nullptr};
-        if ((st = compact(m, src, m->n[l], m->list + off[l], m->totals + l, s)) != SAL_OK) return st;
-    }
+    int64_t count[kMaxLevels + 1], off[kMaxLevels + 2] = {0};
+    if ((st = compact_levels(ctx, m, 0xff, m->list, count)) != SAL_OK) return st;
     SAL_HIP(hipEventRecord(m->ev[4], s));
-    int64_t count[kMaxLevels + 1] = {0};
-    SAL_HIP(hipMemcpyAsync(count, m->totals, sizeof(int64_t) * (top + 1), hipMemcpyDeviceToHost, s));
-    SAL_HIP(hipStreamSynchronize(s));
+    for (int l = 0; l <= top; ++l) off[l + 1] = off[l] + count[l];
     for (int l = finest; l <= top; ++l) count[l] = 0;
     if (top == kMaxLevels && count[top] > 0)
         return set_error(SAL_ERR_CAPACITY, "refinement beyond level 3");
@@ -691,6 +702,11 @@ struct GrowBuf {
     explicit GrowBuf(uint64_t t) : token(t) {}
     GrowBuf(const GrowBuf &) = delete;
     ~GrowBuf() { pool_free(p, token); }
+    void drop() {
+        pool_free(p, token);
+        p = nullptr;
+        cap = 0;
+    }
     sal_status need(int64_t n) {
         if (n <= cap) return SAL_OK;
         pool_free(p, token);
@@ -765,7 +781,7 @@ sal_status sal_tet_mesh_create_lattice(sal_context *ctx, const double origin[3],
             if (hipEventCreate(&e) != hipSuccess) return fail(set_error(SAL_ERR_DEVICE, "hipEventCreate"));
         if ((st = ensure_level(m, 0, n0, ctx->stream)) != SAL_OK) return fail(st);
         m->n[0] = n0;
-        if (mesh_malloc(m, &m->totals, kMaxLevels + 1) != hipSuccess)
+        if (mesh_malloc(m, &m->totals, kMaxLevels + 2) != hipSuccess)
             return fail(set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(totals)"));
         if (hipError_t e = launch_fill_i32(m->child[0], -1, n0, ctx->stream); e != hipSuccess)
             return fail(hip_error(e, "fill child"));
@@ -959,16 +975,25 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         hipStream_t s = ctx->stream;
         sal_status st;
         DevScratch keep(m->token);                 // lives to the end of the call
-        unsigned long long *counters = nullptr;   // [0] keys added, [1] overflow
-        if ((st = keep.get(&counters, 2)) != SAL_OK) return st;
+        unsigned long long *counters = nullptr;   // [0] keys added, [1] overflow, [2..5] pieces, [6] keys listed
+        if ((st = keep.get(&counters, 7)) != SAL_OK) return st;
         // closure state: flags per entry (hanging bits, quarter point, red)
         // and the set of all vertices, built once and grown with the splits
         int64_t entries = 0;
         for (int l = 0; l <= m->max_level; ++l) entries += m->n[l];
         int64_t cap = 1 << 16, used = 0;
-        while (cap < 2 * entries) cap <<= 1;
+        while (cap < entries) cap <<= 1;   // (a vertex is shared by some 20 of them)
         DevScratch set_mem(m->token);
         unsigned long long *set = nullptr;
+        auto spans = [&](const int64_t *first) {
+            LevelSpans r{};
+            r.top = m->max_level;
+            for (int l = 0; l <= r.top; ++l) {
+                r.first[l] = first ? first[l] : 0;
+                r.n[l] = m->n[l];
+            }
+            return r;
+        };
         // (re)builds the set from every entry and the full patterns
         auto rebuild = [&]() -> sal_status {
             for (;;) {
@@ -977,10 +1002,8 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
                 if ((e = set_mem.get(&set, cap)) != SAL_OK) return e;
                 SAL_HIP(launch_fill_u64(set, ~0ull, cap, s));
                 SAL_HIP(launch_fill_u64(counters, 0ull, 2, s));
-                LevelPtrs L = ptrs(m);
-                for (int l = 0; l <= m->max_level; ++l)
-                    SAL_HIP(launch_insert_range(L, m->g, l, 0, m->n[l], set, cap, nullptr, 0,
-                                                nullptr, counters, counters + 1, s));
+                SAL_HIP(launch_insert_levels(ptrs(m), m->g, spans(nullptr), set, cap, nullptr, 0, nullptr,
+                                             counters, counters + 1, s));
                 unsigned long long c[2] = {0, 0};
                 SAL_HIP(hipMemcpyAsync(c, counters, sizeof(c), hipMemcpyDeviceToHost, s));
                 SAL_HIP(hipStreamSynchronize(s));
@@ -988,9 +1011,7 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
                 if (c[1] == 0 && 2 * used <= cap) break;
                 cap <<= 2;
             }
-            LevelPtrs L = ptrs(m);
-            for (int l = 0; l <= m->max_level; ++l)
-                SAL_HIP(launch_pattern_full(L, m->g, l, 0, m->n[l], set, cap, s));
+            SAL_HIP(launch_pattern_levels(ptrs(m), m->g, spans(nullptr), set, cap, nullptr, 0, nullptr, s));
             return SAL_OK;
         };
         if ((st = rebuild()) != SAL_OK) return st;
@@ -1000,21 +1021,21 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         GrowBuf<uint32_t> cells_buf(m->token);   // level-0 cells those vertices touch, one bit each
         const int64_t cell_words =
             ((int64_t)m->g.cells[0] * m->g.cells[1] * m->g.cells[2] + 31) / 32;
+        // Most rounds split a few leaves, so a round is bound by its launches and
+        // its one wait: eight launches over all levels at once (for each level
+        // with its own launches and three waits, the 19 rounds of 4.5M leaves
+        // took 6.6 ms of the call's 9.2; now 1.9 of 3.2).
         for (;;) {
-            int64_t off[kMaxLevels + 2] = {0};
-            for (int l = 0; l <= m->max_level; ++l) off[l + 1] = off[l] + m->n[l];
-            if ((st = red_buf.need(off[m->max_level + 1])) != SAL_OK) return st;
+            int64_t n_all = 0, off[kMaxLevels + 2] = {0};
+            for (int l = 0; l <= m->max_level; ++l) n_all += m->n[l];
+            if ((st = red_buf.need(n_all)) != SAL_OK) return st;
             int32_t *red_list = red_buf.p;
             int64_t red[kMaxLevels + 1] = {0}, total_red = 0;
+            if ((st = compact_levels(ctx, m, 0x80, red_list, red, counters, &used)) != SAL_OK) return st;
             for (int l = 0; l <= m->max_level; ++l) {
-                CompactSrc src{m->flag[l], nullptr, 0x80};
-                if ((st = compact(m, src, m->n[l], red_list + off[l], m->totals + l, s)) != SAL_OK)
-                    return st;
+                off[l + 1] = off[l] + red[l];
+                total_red += red[l];
             }
-            SAL_HIP(hipMemcpyAsync(red, m->totals, sizeof(int64_t) * (m->max_level + 1),
-                                   hipMemcpyDeviceToHost, s));
-            SAL_HIP(hipStreamSynchronize(s));
-            for (int l = 0; l <= m->max_level; ++l) total_red += red[l];
             if (total_red == 0) break;
             if (m->max_level == kMaxLevels && red[kMaxLevels] > 0)
                 return set_error(SAL_ERR_INTERNAL, "closure beyond level 3");
@@ -1036,53 +1057,40 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
                 m->n_leaves += 7 * red[l];
             }
             ++rounds;
-            // the new vertices are edge midpoints of the split leaves (6 each)
+            // the new vertices are edge midpoints of the split leaves (6 each): the
+            // tables get room for them before they can fill up
+            if (2 * (used + 6 * total_red) > cap) {
+                while (cap < 4 * (used + 6 * total_red)) cap <<= 1;
+                if ((st = rebuild()) != SAL_OK) return st;
+                continue;
+            }
             int64_t fcap = 1024;
             while (fcap < 12 * total_red) fcap <<= 1;
             if ((st = fresh_buf.need(fcap)) != SAL_OK) return st;
             unsigned long long *fresh = fresh_buf.p;
             if ((st = cells_buf.need(cell_words)) != SAL_OK) return st;
             uint32_t *cells_new = cells_buf.p;
-            SAL_HIP(launch_fill_u64(fresh, ~0ull, fcap, s));
-            SAL_HIP(launch_fill_i32((int32_t *)cells_new, 0, cell_words, s));
-            SAL_HIP(launch_fill_u64(counters, 0ull, 2, s));
-            LevelPtrs L = ptrs(m);
-            for (int l = 0; l <= m->max_level; ++l)
-                SAL_HIP(launch_insert_range(L, m->g, l, old_n[l], m->n[l] - old_n[l], set, cap, fresh,
-                                            fcap, cells_new, counters, counters + 1, s));
-            unsigned long long c[2] = {0, 0};
-            SAL_HIP(hipMemcpyAsync(c, counters, sizeof(c), hipMemcpyDeviceToHost, s));
-            SAL_HIP(hipStreamSynchronize(s));
-            used += (int64_t)c[0];
-            if (c[1] != 0 || 2 * used > cap) {
-                // a table filled up: a larger set and full patterns
-                while (cap < 4 * used) cap <<= 1;
-                if (c[1] != 0) cap <<= 1;
-                if ((st = rebuild()) != SAL_OK) return st;
-                SAL_HIP(hipStreamSynchronize(s));
-                continue;
-            }
-            // old entries: patterns plus what the new vertices hit; new
-            // children: full patterns
-            for (int l = 0; l <= m->max_level; ++l) {
-                SAL_HIP(launch_pattern_fresh(L, m->g, l, old_n[l], fresh, fcap, cells_new, s));
-                SAL_HIP(launch_pattern_full(L, m->g, l, old_n[l], m->n[l] - old_n[l], set, cap, s));
-            }
-            SAL_HIP(hipStreamSynchronize(s));
+            const LevelPtrs L = ptrs(m);
+            const LevelSpans r = spans(old_n);
+            SAL_HIP(launch_closure_clear(fresh, fcap, cells_new, cell_words, s));
+            SAL_HIP(launch_insert_levels(L, m->g, r, set, cap, fresh, fcap, cells_new, counters, counters + 1, s));
+            SAL_HIP(launch_pattern_levels(L, m->g, r, set, cap, fresh, fcap, cells_new, s));
         }
+        red_buf.drop();
+        fresh_buf.drop();
 
         // the leaves in index order per level
-        int64_t count[kMaxLevels + 1] = {0}, off[kMaxLevels + 2] = {0}, n_all = 0;
-        for (int l = 0; l <= m->max_level; ++l) off[l + 1] = off[l] + m->n[l];
-        if ((st = ensure_buf(m, &m->list, &m->list_cap, off[m->max_level + 1], s)) != SAL_OK) return st;
+        int64_t count[kMaxLevels + 1] = {0}, n_entries = 0, n_all = 0;
+        for (int l = 0; l <= m->max_level; ++l) n_entries += m->n[l];
+        if ((st = ensure_buf(m, &m->list, &m->list_cap, n_entries, s)) != SAL_OK) return st;
+        if ((st = compact_levels(ctx, m, 0, m->list, count)) != SAL_OK) return st;
+        LevelSpans leaves{};
+        leaves.top = m->max_level;
         for (int l = 0; l <= m->max_level; ++l) {
-            CompactSrc src{nullptr, m->child[l]};
-            if ((st = compact(m, src, m->n[l], m->list + off[l], m->totals + l, s)) != SAL_OK) return st;
+            leaves.first[l] = n_all;
+            leaves.n[l] = count[l];
+            n_all += count[l];
         }
-        SAL_HIP(hipMemcpyAsync(count, m->totals, sizeof(int64_t) * (m->max_level + 1),
-                               hipMemcpyDeviceToHost, s));
-        SAL_HIP(hipStreamSynchronize(s));
-        for (int l = 0; l <= m->max_level; ++l) n_all += count[l];
         if (n_all != m->n_leaves) return set_error(SAL_ERR_INTERNAL, "leaf count mismatch");
 
         // the tetrahedra of each leaf, at the exclusive sum of the counts
@@ -1090,64 +1098,53 @@ sal_status sal_tet_mesh_conform(sal_context *ctx, sal_tet_mesh *m, sal_conform_i
         int64_t *offsets = nullptr;
         if ((st = keep.get(&counts, n_all)) != SAL_OK || (st = keep.get(&offsets, n_all)) != SAL_OK)
             return st;
-        unsigned long long *hist = nullptr;   // leaves by number of pieces
-        if ((st = keep.get(&hist, 4)) != SAL_OK) return st;
-        SAL_HIP(launch_fill_u64(hist, 0ull, 4, s));
-        {
-            LevelPtrs L = ptrs(m);
-            int64_t coff = 0;
-            for (int l = 0; l <= m->max_level; coff += count[l], ++l)
-                SAL_HIP(launch_tet_counts(L, l, m->list + off[l], count[l], counts + coff, hist, s));
-        }
-        size_t tmp_bytes = 0;
-        SAL_HIP(exclusive_sum_i32(counts, offsets, n_all, nullptr, &tmp_bytes, s));
+        SAL_HIP(launch_fill_u64(counters + 2, 0ull, 5, s));
+        const LevelPtrs L = ptrs(m);
+        SAL_HIP(launch_tet_counts(L, leaves, m->list, counts, counters + 2, s));
+        size_t sum_bytes = 0, sort_bytes = 0;
+        SAL_HIP(exclusive_sum_i32(counts, offsets, n_all, nullptr, &sum_bytes, s));
+        // and the nodes: the vertex set's keys in ascending order
+        const int64_t n_nodes = used;
+        auto field_bits = [](int64_t cells) {
+            int b = 1;
+            while ((int64_t(1) << b) <= (cells << kMaxLevels)) ++b;
+            return b;
+        };
+        const NodeBits nb{field_bits(m->g.cells[1]), field_bits(m->g.cells[2])};
+        const int key_bits = field_bits(m->g.cells[0]) + nb.y + nb.z;
+        uint64_t *packed = nullptr, *sorted = nullptr;
+        if ((st = keep.get(&packed, n_nodes)) != SAL_OK || (st = keep.get(&sorted, n_nodes)) != SAL_OK) return st;
+        SAL_HIP(sort_packed(packed, sorted, n_nodes, key_bits, nullptr, &sort_bytes, s));
         char *tmp = nullptr;
+        size_t tmp_bytes = std::max(sum_bytes, sort_bytes);
         if ((st = keep.get(&tmp, (int64_t)tmp_bytes)) != SAL_OK) return st;
-        SAL_HIP(exclusive_sum_i32(counts, offsets, n_all, tmp, &tmp_bytes, s));
+        SAL_HIP(exclusive_sum_i32(counts, offsets, n_all, tmp, &sum_bytes, s));
+        SAL_HIP(launch_set_keys(set, cap, nb, packed, n_nodes, counters + 6, s));
         int64_t last_off = 0;
         int32_t last_cnt = 0;
+        unsigned long long hh[5] = {0, 0, 0, 0, 0};
         SAL_HIP(hipMemcpyAsync(&last_off, offsets + n_all - 1, sizeof(last_off), hipMemcpyDeviceToHost, s));
         SAL_HIP(hipMemcpyAsync(&last_cnt, counts + n_all - 1, sizeof(last_cnt), hipMemcpyDeviceToHost, s));
+        SAL_HIP(hipMemcpyAsync(hh, counters + 2, sizeof(hh), hipMemcpyDeviceToHost, s));
         SAL_HIP(hipStreamSynchronize(s));
+        if ((int64_t)hh[4] != n_nodes) return set_error(SAL_ERR_INTERNAL, "vertex count mismatch");
         const int64_t n_tets = last_off + last_cnt;
         const int64_t n_corner = 4 * n_tets;
         if (n_corner > INT32_MAX) return set_error(SAL_ERR_CAPACITY, "conforming mesh above 2^31 corners");
-        int64_t *tkeys = nullptr, *sorted = nullptr, *pos = nullptr, *nodes = nullptr;
-        int32_t *head = nullptr;
-        if ((st = keep.get(&tkeys, n_corner)) != SAL_OK || (st = keep.get(&sorted, n_corner)) != SAL_OK ||
-            (st = keep.get(&pos, n_corner)) != SAL_OK || (st = keep.get(&head, n_corner)) != SAL_OK ||
-            (st = keep.get(&nodes, n_corner)) != SAL_OK)
-            return st;
+        int64_t node_cap = 1024;
+        while (node_cap < 2 * n_nodes) node_cap <<= 1;
+        NodeEntry *table = nullptr;
+        if ((st = keep.get(&table, node_cap)) != SAL_OK) return st;
         if (mesh_malloc(m, &m->conf_labels, std::max<int64_t>(n_tets, 1)) != hipSuccess ||
             mesh_malloc(m, &m->conf_ids, std::max<int64_t>(n_corner, 1)) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(conforming mesh)");
-        LevelPtrs L = ptrs(m);
-        int64_t boff = 0;
-        for (int l = 0; l <= m->max_level; boff += count[l], ++l)
-            SAL_HIP(launch_emit(L, m->g, l, m->list + off[l], count[l], offsets + boff, tkeys,
-                                m->conf_labels, s));
-        // nodes: the distinct corner keys in ascending order; ids by search
-        size_t sort_bytes = 0, uniq_bytes = 0;
-        SAL_HIP(sort_keys_i64(tkeys, sorted, n_corner, nullptr, &sort_bytes, s));
-        SAL_HIP(launch_unique(sorted, n_corner, head, pos, nodes, nullptr, &uniq_bytes, s));
-        tmp_bytes = std::max(sort_bytes, uniq_bytes);
-        if ((st = keep.get(&tmp, (int64_t)tmp_bytes)) != SAL_OK) return st;
-        SAL_HIP(sort_keys_i64(tkeys, sorted, n_corner, tmp, &tmp_bytes, s));
-        SAL_HIP(launch_unique(sorted, n_corner, head, pos, nodes, tmp, &tmp_bytes, s));
-        int64_t last_pos = 0;
-        int32_t last_head = 0;
-        SAL_HIP(hipMemcpyAsync(&last_pos, pos + n_corner - 1, sizeof(last_pos), hipMemcpyDeviceToHost, s));
-        SAL_HIP(hipMemcpyAsync(&last_head, head + n_corner - 1, sizeof(last_head), hipMemcpyDeviceToHost, s));
-        SAL_HIP(hipStreamSynchronize(s));
-        const int64_t n_nodes = last_pos + last_head;
         if (mesh_malloc(m, &m->conf_keys, std::max<int64_t>(n_nodes, 1)) != hipSuccess ||
             mesh_malloc(m, &m->conf_xyz, std::max<int64_t>(3 * n_nodes, 1)) != hipSuccess)
             return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(conforming nodes)");
-        SAL_HIP(hipMemcpyAsync(m->conf_keys, nodes, (size_t)n_nodes * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
-        SAL_HIP(launch_node_ids(tkeys, n_corner, m->conf_keys, n_nodes, m->conf_ids, s));
-        SAL_HIP(launch_node_xyz(m->g, m->conf_keys, n_nodes, m->conf_xyz, s));
-        unsigned long long hh[4] = {0, 0, 0, 0};
-        SAL_HIP(hipMemcpyAsync(hh, hist, sizeof(hh), hipMemcpyDeviceToHost, s));
+        SAL_HIP(sort_packed(packed, sorted, n_nodes, key_bits, tmp, &sort_bytes, s));
+        SAL_HIP(launch_number_nodes(m->g, sorted, n_nodes, nb, table, node_cap, m->conf_keys, m->conf_xyz, s));
+        SAL_HIP(launch_emit(L, m->g, leaves, m->list, offsets, nb, table, node_cap, m->conf_ids, m->conf_labels,
+                            s));
         SAL_HIP(hipStreamSynchronize(s));
         m->conf_tets = n_tets;
         m->conf_nodes = n_nodes;
@@ -1290,21 +1287,12 @@ sal_status sal_tet_mesh_export(sal_context *ctx, const sal_tet_mesh *mc, uint64_
         for (int l = 0; l <= m->max_level; ++l) total_entries += m->n[l];
         sal_status st = ensure_buf(m, &m->list, &m->list_cap, total_entries, s);
         if (st != SAL_OK) return st;
-        int64_t off[kMaxLevels + 2] = {0};
-        for (int l = 0; l <= m->max_level; ++l) {
-            off[l + 1] = off[l] + m->n[l];
-            CompactSrc src{nullptr, m->child[l]};
-            if ((st = compact(m, src, m->n[l], m->list + off[l], m->totals + l, s)) != SAL_OK)
-                return st;
-        }
-        int64_t count[kMaxLevels + 1] = {0};
-        SAL_HIP(hipMemcpyAsync(count, m->totals, sizeof(int64_t) * (m->max_level + 1),
-                               hipMemcpyDeviceToHost, s));
-        SAL_HIP(hipStreamSynchronize(s));
+        int64_t count[kMaxLevels + 1];
+        if ((st = compact_levels(ctx, m, 0, m->list, count)) != SAL_OK) return st;
         int64_t out_base = 0;
         LevelPtrs L = ptrs(m);
         for (int l = 0; l <= m->max_level; ++l) {
-            SAL_HIP(launch_export(L, m->g, l, m->list + off[l], count[l], out_base, keys, labels, cx,
+            SAL_HIP(launch_export(L, m->g, l, m->list + out_base, count[l], out_base, keys, labels, cx,
                                   cy, cz, s));
             out_base += count[l];
         }

@@ -207,9 +207,8 @@ __global__ __launch_bounds__(kScanThreads) void k_count(CompactSrc s, int64_t n,
     if (threadIdx.x == 0) block_counts[blockIdx.x] = red[0];
 }
 
-// Exclusive scan of n_blocks counts in one workgroup; total -> *total.
-__global__ __launch_bounds__(1024) void k_scan_blocks(int64_t *__restrict__ counts, int64_t n_blocks,
-                                                     int64_t *__restrict__ total) {
+// Exclusive scan of n_blocks counts in one workgroup of 1024; returns the total.
+__device__ __forceinline__ int64_t scan_counts(int64_t *__restrict__ counts, int64_t n_blocks) {
     __shared__ int64_t part[1024];
     const int t = threadIdx.x;
     const int64_t per = (n_blocks + 1023) / 1024;
@@ -230,7 +229,63 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t *__restrict__ coun
         counts[b] = run;
         run += c;
     }
-    if (t == 1023) *total = part[1023];
+    return part[1023];
+}
+
+__global__ __launch_bounds__(1024) void k_scan_blocks(int64_t *__restrict__ counts, int64_t n_blocks,
+                                                     int64_t *__restrict__ total) {
+    const int64_t all = scan_counts(counts, n_blocks);
+    if (threadIdx.x == 0) *total = all;
+}
+
+// A compaction over several levels: tiles of level l from tile0[l] on.
+struct CompactLevels {
+    CompactSrc src[kMaxLevels + 1];
+    int64_t n[kMaxLevels + 1];
+    int64_t tile0[kMaxLevels + 2];
+    int top;
+
+    __device__ __forceinline__ int level(int64_t tile) const {
+        int l = 0;
+        while (l < top && tile >= tile0[l + 1]) ++l;
+        return l;
+    }
+};
+
+__global__ __launch_bounds__(kScanThreads) void k_count_levels(CompactLevels c,
+                                                               int64_t *__restrict__ block_counts) {
+    __shared__ int wave_total[kScanThreads / 64];
+    const int l = c.level(blockIdx.x);
+    const int64_t first = ((int64_t)blockIdx.x - c.tile0[l]) * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    int v = first < c.n[l] ? __popc(pred_bits(c.src[l], first, c.n[l])) : 0;
+    for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63u) == 0) wave_total[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+        for (int w = 0; w < kScanThreads / 64; ++w) sum += wave_total[w];
+        block_counts[blockIdx.x] = sum;
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_scan_levels(CompactLevels c, int64_t *__restrict__ counts,
+                                                      int64_t n_blocks, int64_t *__restrict__ totals,
+                                                      const unsigned long long *__restrict__ extra,
+                                                      int64_t *__restrict__ host_words) {
+    const int64_t all = scan_counts(counts, n_blocks);
+    __syncthreads();   // (the workgroup reads what it has written)
+    const int t = threadIdx.x;
+    int64_t v = 0;
+    if (t <= c.top) {
+        const int64_t b = c.tile0[t], e = c.tile0[t + 1];
+        v = b == e ? 0 : (e < n_blocks ? counts[e] : all) - counts[b];
+    }
+    if (t == kMaxLevels + 1 && extra) v = (int64_t)*extra;
+    if (t <= kMaxLevels + 1) {
+        totals[t] = v;
+        host_words[t] = v;
+        __threadfence_system();
+    }
 }
 
 // Ordered scatter of one tile: thread t owns the kScanItems consecutive
@@ -240,16 +295,13 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t *__restrict__ coun
 // out contiguously (coalesced writes).
 constexpr int kScanWaves = kScanThreads / 64;
 
-__global__ __launch_bounds__(kScanThreads) void k_scatter(CompactSrc s, int64_t n,
-                                                          const int64_t *__restrict__ n_dev,
-                                                          const int64_t *__restrict__ offsets,
-                                                          int32_t *__restrict__ out) {
+__device__ __forceinline__ void scatter_tile(const CompactSrc &s, int64_t n, int64_t tile, int64_t o,
+                                             int32_t *__restrict__ out) {
     __shared__ int32_t buf[kScanTile];
     __shared__ int wave_total[kScanWaves];
-    if (n_dev) n = *n_dev;
     const int lane = (int)(threadIdx.x & 63u);
     const int wv = (int)(threadIdx.x >> 6);
-    const int64_t first = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    const int64_t first = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
     uint32_t bits = first < n ? pred_bits(s, first, n) : 0u;
     const int cnt = __popc(bits);
     // inclusive scan of the counts over the wavefront's lanes
@@ -272,8 +324,21 @@ __global__ __launch_bounds__(kScanThreads) void k_scatter(CompactSrc s, int64_t 
         buf[pos++] = (int32_t)(first + j);
     }
     __syncthreads();
-    const int64_t o = offsets[blockIdx.x];
     for (int j = (int)threadIdx.x; j < total; j += kScanThreads) out[o + j] = buf[j];
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scatter(CompactSrc s, int64_t n,
+                                                          const int64_t *__restrict__ n_dev,
+                                                          const int64_t *__restrict__ offsets,
+                                                          int32_t *__restrict__ out) {
+    scatter_tile(s, n_dev ? *n_dev : n, blockIdx.x, offsets[blockIdx.x], out);
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scatter_levels(CompactLevels c,
+                                                                 const int64_t *__restrict__ offsets,
+                                                                 int32_t *__restrict__ out) {
+    const int l = c.level(blockIdx.x);
+    scatter_tile(c.src[l], c.n[l], (int64_t)blockIdx.x - c.tile0[l], offsets[blockIdx.x], out);
 }
 
 // Section 2.1.2: each listed leaf of level l becomes 8 level-(l+1) tetrahedra
@@ -750,6 +815,29 @@ hipError_t launch_compact(const CompactSrc &src, int64_t n, int64_t *block_scrat
     k_count<<<(unsigned)nb, kScanThreads, 0, s>>>(src, n, nullptr, block_scratch);
     k_scan_blocks<<<1, 1024, 0, s>>>(block_scratch, nb, total);
     k_scatter<<<(unsigned)nb, kScanThreads, 0, s>>>(src, n, nullptr, block_scratch, out);
+    return hipGetLastError();
+}
+
+int64_t compact_level_blocks(const LevelPtrs &L, int top) {
+    int64_t nb = 0;
+    for (int l = 0; l <= top; ++l) nb += compact_blocks(L.n[l]);
+    return nb;
+}
+
+hipError_t launch_compact_levels(const LevelPtrs &L, int top, uint8_t mask, int64_t *block_scratch,
+                                 int64_t *totals, const unsigned long long *extra, int64_t *host_words,
+                                 int32_t *out, hipStream_t s) {
+    CompactLevels c{};
+    c.top = top;
+    for (int l = 0; l <= kMaxLevels; ++l) {
+        c.n[l] = l <= top ? L.n[l] : 0;
+        c.src[l] = mask ? CompactSrc{L.flag[l], nullptr, mask} : CompactSrc{nullptr, L.child[l], 0};
+        c.tile0[l + 1] = c.tile0[l] + compact_blocks(c.n[l]);
+    }
+    const int64_t nb = c.tile0[top + 1];   // (> 0: level 0 has entries)
+    k_count_levels<<<(unsigned)nb, kScanThreads, 0, s>>>(c, block_scratch);
+    k_scan_levels<<<1, 1024, 0, s>>>(c, block_scratch, nb, totals, extra, host_words);
+    k_scatter_levels<<<(unsigned)nb, kScanThreads, 0, s>>>(c, block_scratch, out);
     return hipGetLastError();
 }
 

@@ -71,6 +71,14 @@ hipError_t launch_mark(const LevelPtrs &L, const LatticeGeom &g, const ChildTabl
 int64_t compact_blocks(int64_t n);
 hipError_t launch_compact(const CompactSrc &src, int64_t n, int64_t *block_scratch,
                           int64_t *total, int32_t *out, hipStream_t s);
+// One compaction over levels 0..top, a level's list behind the one before it in
+// `out`: the leaves, or (mask != 0) the entries with a flag bit of mask.  Writes
+// the levels' totals and the *extra word to totals[0..kMaxLevels + 1] and, once the
+// stream has got there, to the same places of host_words (pinned memory).
+int64_t compact_level_blocks(const LevelPtrs &L, int top);
+hipError_t launch_compact_levels(const LevelPtrs &L, int top, uint8_t mask, int64_t *block_scratch,
+                                 int64_t *totals, const unsigned long long *extra, int64_t *host_words,
+                                 int32_t *out, hipStream_t s);
 hipError_t launch_split(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
                         const int32_t *list, int64_t count, int64_t base_block, float *cx,
                         float *cy, float *cz, hipStream_t s);
@@ -128,37 +136,52 @@ hipError_t launch_child_masks(const LevelPtrs &L, const LatticeGeom &g, int l,
 // Flags of a leaf during the closure (in LevelPtrs::flag): bits 0-5 the
 // hanging edges, bit 6 a node at a quarter point, bit 7 split 1 -> 8.
 // cells_new: one bit per level-0 cell, set for the cells a vertex added to
-// `fresh` touches (unused when fresh is null).
-hipError_t launch_insert_range(const LevelPtrs &L, const LatticeGeom &g, int l, int64_t first,
-                               int64_t count, unsigned long long *set, int64_t cap,
-                               unsigned long long *fresh, int64_t fcap, uint32_t *cells_new,
-                               unsigned long long *n_new, unsigned long long *overflow,
-                               hipStream_t s);
-hipError_t launch_pattern_full(const LevelPtrs &L, const LatticeGeom &g, int l, int64_t first,
-                               int64_t count, const unsigned long long *set, int64_t cap,
-                               hipStream_t s);
-hipError_t launch_pattern_fresh(const LevelPtrs &L, const LatticeGeom &g, int l, int64_t count,
-                                const unsigned long long *fresh, int64_t fcap,
-                                const uint32_t *cells_new, hipStream_t s);
+// `fresh` touches (both null: the first pass).
+// Every launch covers levels 0..top: of level l the entries [first[l], n[l]).
+struct LevelSpans {
+    int top;
+    int64_t first[kMaxLevels + 1], n[kMaxLevels + 1];
+    uint32_t block0[kMaxLevels + 2];   // first workgroup (this and `turns` set by the launcher)
+    int turns;                         // items of a thread
+};
+hipError_t launch_closure_clear(unsigned long long *fresh, int64_t fcap, uint32_t *cells_new, int64_t cell_words,
+                                hipStream_t s);
+// n_new: accumulated, not cleared.  *overflow counts the keys that found no place.
+hipError_t launch_insert_levels(const LevelPtrs &L, const LatticeGeom &g, const LevelSpans &r,
+                                unsigned long long *set, int64_t cap, unsigned long long *fresh, int64_t fcap,
+                                uint32_t *cells_new, unsigned long long *n_new, unsigned long long *overflow,
+                                hipStream_t s);
+// New patterns after a closure round: entries [0, first) of a level from the
+// round's new vertices, entries [first, n) in full.
+hipError_t launch_pattern_levels(const LevelPtrs &L, const LatticeGeom &g, const LevelSpans &r,
+                                 const unsigned long long *set, int64_t cap, const unsigned long long *fresh,
+                                 int64_t fcap, const uint32_t *cells_new, hipStream_t s);
+// The conforming mesh: `list` holds the leaves level by level, n[l] of each.
 // hist: 4 counters (leaves cut into 1, 2, 3, 4 tetrahedra), accumulated.
-hipError_t launch_tet_counts(const LevelPtrs &L, int l, const int32_t *list, int64_t count,
-                             int32_t *counts, unsigned long long *hist, hipStream_t s);
+hipError_t launch_tet_counts(const LevelPtrs &L, const LevelSpans &r, const int32_t *list, int32_t *counts,
+                             unsigned long long *hist, hipStream_t s);
 // rocPRIM device-wide primitives: with tmp == nullptr they only set *tmp_bytes.
 hipError_t exclusive_sum_i32(const int32_t *in, int64_t *out, int64_t n, void *tmp,
                              size_t *tmp_bytes, hipStream_t s);
-hipError_t sort_keys_i64(const int64_t *in, int64_t *out, int64_t n, void *tmp, size_t *tmp_bytes,
-                         hipStream_t s);
-hipError_t launch_emit(const LevelPtrs &L, const LatticeGeom &g, int l, const int32_t *list,
-                       int64_t count, const int64_t *offsets, int64_t *tets, int32_t *labels,
+// Nodes: the vertex set's keys with their 21-bit fields packed (`bits` per axis), in
+// no order; sorted; numbered (keys, coordinates, and a table from packed key to
+// number, cap a power of two).
+struct NodeEntry {
+    unsigned long long key;   // ~0: empty
+    int32_t id, pad;
+};
+struct NodeBits {
+    int y, z;   // of the two lower fields
+};
+hipError_t launch_set_keys(const unsigned long long *set, int64_t cap, const NodeBits &nb, uint64_t *out,
+                           int64_t out_cap, unsigned long long *n_out, hipStream_t s);
+hipError_t sort_packed(const uint64_t *in, uint64_t *out, int64_t n, int bits, void *tmp, size_t *tmp_bytes,
                        hipStream_t s);
-// Distinct keys of a sorted array, in order; with tmp == nullptr it only sets
-// *tmp_bytes.
-hipError_t launch_unique(const int64_t *sorted, int64_t n, int32_t *head, int64_t *pos,
-                         int64_t *nodes, void *tmp, size_t *tmp_bytes, hipStream_t s);
-hipError_t launch_node_ids(const int64_t *tet_keys, int64_t n, const int64_t *nodes, int64_t n_nodes,
-                           int32_t *ids, hipStream_t s);
-hipError_t launch_node_xyz(const LatticeGeom &g, const int64_t *nodes, int64_t n, float *xyz,
-                           hipStream_t s);
+hipError_t launch_number_nodes(const LatticeGeom &g, const uint64_t *packed, int64_t n, const NodeBits &nb,
+                               NodeEntry *table, int64_t cap, int64_t *keys, float *xyz, hipStream_t s);
+hipError_t launch_emit(const LevelPtrs &L, const LatticeGeom &g, const LevelSpans &r, const int32_t *list,
+                       const int64_t *offsets, const NodeBits &nb, const NodeEntry *table, int64_t cap,
+                       int32_t *ids, int32_t *labels, hipStream_t s);
 
 // Checkpoint import (import.hip).
 struct ImportTables {

@@ -29,6 +29,7 @@ struct sal_context {
     unsigned long long *work = nullptr;   // sal::kNumWork
     unsigned long long *counters = nullptr;  // sal::kNumCounters
     unsigned long long *tune_counters = nullptr;
+    int64_t *host_words = nullptr;   // pinned: what a mesh call reads back
     int n_cu = 0;
     // batched form: the instance table on the device and its host copy
     sal::LabelInst *batch_insts = nullptr;

@@ -144,3 +144,29 @@ def test_conforming_mesh_cannot_be_refined_or_conformed_again(ctx):
         mesh.refine_relabel(ss, 1)
     with pytest.raises(sal.SalError):
         mesh.conform()
+
+
+@pytest.mark.parametrize("cells", [(9, 13, 5), (44, 50, 41)])
+def test_nodes_of_small_and_large_meshes(ctx, cells):
+    """The node numbers come from a table over the closure's vertex set: keys
+    ascending, every node used, the corners' keys those of their coordinates, and
+    the tetrahedra fill the lattice box without overlap.  The second mesh has
+    entries enough that a launch's threads take several each."""
+    surf = synth.config_small("head", cells=4, subdiv=2).surfaces
+    h = 180.0 / max(cells)
+    mesh = sal.TetMesh(ctx, tuple(-0.5 * h * c for c in cells), h, cells)
+    ss = sal.SurfaceSet(ctx, surf)
+    mesh.refine_relabel(ss, 2)
+    info = mesh.conform()
+    out = {k: v.cpu().numpy() for k, v in mesh.export_conforming().items()}
+    tets, keys, xyz = out["tets"].astype(np.int64), out["node_keys"], out["xyz"]
+    assert len(tets) == info["n_tets"] and len(keys) == info["n_nodes"]
+    assert (np.diff(keys) > 0).all()
+    assert np.array_equal(np.unique(tets), np.arange(len(keys)))
+    f = np.stack([keys >> 42, (keys >> 21) & 0x1FFFFF, keys & 0x1FFFFF], 1)
+    assert (f >= 0).all() and (f.max(0) == 8 * np.array(cells)).all()
+    want = np.array([-0.5 * h * c for c in cells]) + f * (h / 8.0)
+    assert np.abs(xyz - want).max() <= 180.0 * 2.0 ** -23   # float32 coordinates
+    p = f[tets]
+    vol6 = np.linalg.det((p[:, 1:] - p[:, :1]).astype(np.float64))
+    assert vol6.min() > 0.5 and round(vol6.sum()) == 6 * 8 ** 3 * int(np.prod(cells))
