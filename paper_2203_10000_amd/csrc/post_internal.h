@@ -67,25 +67,23 @@ constexpr int kTaubinUnroll = SAL_TAUBIN_UNROLL;   // entries per lane loaded to
 constexpr int kTaubinWindow = SAL_TAUBIN_WINDOW;   // positions a half-step block may stage in LDS
 
 // Edge graph construction.
-// *bad_labels counts tetrahedra with a label outside [-1, 254].
-hipError_t launch_edge_occurrences(const int32_t *ids, const int32_t *labels, int64_t n_tets,
-                                   uint64_t *keys, unsigned long long *bad_labels, hipStream_t s);
-hipError_t sort_keys_u64(const uint64_t *in, uint64_t *out, int64_t n, int end_bit, void *tmp,
-                         size_t *tmp_bytes, hipStream_t s);
-// Per sorted occurrence: 1 where its edge (key >> 8) starts.
-hipError_t launch_edge_heads(const uint64_t *keys, int64_t n, int32_t *head, hipStream_t s);
-hipError_t exclusive_sum_head(const int32_t *head, int64_t *pos, int64_t n, void *tmp,
-                              size_t *tmp_bytes, hipStream_t s);
-hipError_t launch_edge_directed(const uint64_t *keys, const int32_t *head, const int64_t *pos,
-                                int64_t n, int64_t n_edges, int64_t *start, const int32_t *rank,
-                                uint64_t *dkeys, unsigned long long *n_surf, hipStream_t s);
-// order[r]: the node of Morton rank r; rank[i]: the rank of node i.  With
-// tmp == nullptr it only sets *tmp_bytes.
+// The distinct edges in a table of n_nodes x per places (per a power of two), the
+// nodes' degrees (n_nodes + 1, the last 0) and cnt: [0] labels outside [-1, 254],
+// [1] edges that found no place, [2] edges, [3] interface edges.
+hipError_t launch_edge_table(const int32_t *ids, const int32_t *labels, int64_t n_tets, const int32_t *rank,
+                             int64_t n_nodes, unsigned long long *table, int per, uint32_t *mixed,
+                             int32_t *degree, unsigned long long *cnt, hipStream_t s);
+hipError_t exclusive_sum_degrees(const int32_t *degree, int64_t *rowptr, int64_t n, void *tmp,
+                                 size_t *tmp_bytes, hipStream_t s);
+// Both directions of every edge by row and ascending column; `degree` is used up.
+hipError_t launch_edge_rows(const unsigned long long *table, int64_t n_nodes, int per, const uint32_t *mixed,
+                            const int64_t *rowptr, int32_t *degree, uint32_t *rows, uint32_t *cols,
+                            hipStream_t s);
+// order[r]: the node of Morton rank r; rank[i]: the rank of node i; bits: of the
+// codes.  With tmp == nullptr it only sets *tmp_bytes.
 hipError_t launch_morton_order(const int64_t *keys, int64_t n, uint64_t *code, uint64_t *code_sorted,
-                               int32_t *ids, int32_t *order, int32_t *rank, void *tmp,
+                               int32_t *ids, int32_t *order, int32_t *rank, int bits, void *tmp,
                                size_t *tmp_bytes, hipStream_t s);
-hipError_t launch_csr(const uint64_t *dkeys, int64_t n2, int64_t n_nodes, int64_t *rowptr,
-                      uint32_t *cols, hipStream_t s);
 hipError_t launch_node_class(const int64_t *rowptr, const uint32_t *cols, const int64_t *keys,
                              const int32_t *order, int64_t n_nodes, const LatticeGeom &g, uint8_t *cls,
                              hipStream_t s);

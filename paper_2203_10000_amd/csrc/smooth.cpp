@@ -1,8 +1,6 @@
 // Taubin smoothing of the conforming mesh (paper section 2.2.1): host side.
-// The edge graph is built once per conforming mesh with radix sorts (edge
-// occurrences; the nodes by Morton code; both directions of each distinct
-// edge in Morton ranks); the phases then
-// run half steps until the stopping ratio is met, reading one double back
+// The edge graph is built once per conforming mesh (the nodes sorted by Morton
+// code, the edges from a table of places by node); the phases then run half steps until the stopping ratio is met, reading one double back
 // per iteration.
 #include <algorithm>
 #include <cmath>
@@ -60,43 +58,6 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
     if (6 * v.n_tets > INT32_MAX) return set_error(SAL_ERR_CAPACITY, "smoothing: too many tetrahedra");
     sal_status st;
     Temp t(v.token);
-    const int64_t n_occ = 6 * v.n_tets;
-    uint64_t *occ = nullptr, *occ_sorted = nullptr;
-    int32_t *head = nullptr;
-    int64_t *pos = nullptr;
-    if ((st = t.get(&occ, n_occ)) != SAL_OK || (st = t.get(&occ_sorted, n_occ)) != SAL_OK ||
-        (st = t.get(&head, n_occ)) != SAL_OK || (st = t.get(&pos, n_occ)) != SAL_OK)
-        return st;
-    unsigned long long *cnt = nullptr;   // [0] bad labels, [1] interface edges
-    if ((st = t.get(&cnt, 2)) != SAL_OK) return st;
-    SAL_HIP(launch_fill_u64(cnt, 0ull, 2, s));
-    SAL_HIP(launch_edge_occurrences(v.ids, v.labels, v.n_tets, occ, cnt, s));
-    const int nb = bits_for(v.n_nodes - 1);
-    size_t b1 = 0, b2 = 0;
-    SAL_HIP(sort_keys_u64(occ, occ_sorted, n_occ, 36 + nb, nullptr, &b1, s));
-    SAL_HIP(exclusive_sum_head(head, pos, n_occ, nullptr, &b2, s));
-    char *tmp = nullptr;
-    size_t tmp_bytes = std::max(b1, b2);
-    if ((st = t.get(&tmp, (int64_t)tmp_bytes)) != SAL_OK) return st;
-    SAL_HIP(sort_keys_u64(occ, occ_sorted, n_occ, 36 + nb, tmp, &tmp_bytes, s));
-    SAL_HIP(launch_edge_heads(occ_sorted, n_occ, head, s));
-    tmp_bytes = std::max(b1, b2);
-    SAL_HIP(exclusive_sum_head(head, pos, n_occ, tmp, &tmp_bytes, s));
-    int64_t last_pos = 0;
-    int32_t last_head = 0;
-    SAL_HIP(hipMemcpyAsync(&last_pos, pos + n_occ - 1, sizeof(last_pos), hipMemcpyDeviceToHost, s));
-    SAL_HIP(hipMemcpyAsync(&last_head, head + n_occ - 1, sizeof(last_head), hipMemcpyDeviceToHost, s));
-    SAL_HIP(hipStreamSynchronize(s));
-    unsigned long long bad = 0;
-    SAL_HIP(hipMemcpy(&bad, cnt, sizeof(bad), hipMemcpyDeviceToHost));
-    if (bad) return set_error(SAL_ERR_CAPACITY, "smoothing: labels outside [-1, 254]");
-    const int64_t n_edges = last_pos + last_head;
-    const int64_t n2 = 2 * n_edges;
-    int64_t *start = nullptr;
-    uint64_t *dkeys = nullptr, *dsorted = nullptr;
-    if ((st = t.get(&start, n_edges)) != SAL_OK || (st = t.get(&dkeys, n2)) != SAL_OK ||
-        (st = t.get(&dsorted, n2)) != SAL_OK)
-        return st;
     // Morton ranks of the nodes
     uint64_t *code = nullptr, *code_sorted = nullptr;
     int32_t *ids = nullptr, *rank = nullptr;
@@ -104,21 +65,36 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
         (st = t.get(&ids, v.n_nodes)) != SAL_OK || (st = t.get(&rank, v.n_nodes)) != SAL_OK ||
         (st = dev_alloc(&c->order, v.n_nodes, v.token)) != SAL_OK)
         return st;
-    size_t bm = 0;
-    SAL_HIP(launch_morton_order(v.keys, v.n_nodes, code, code_sorted, ids, c->order, rank, nullptr, &bm, s));
-    char *tmpm = nullptr;
-    if ((st = t.get(&tmpm, (int64_t)bm)) != SAL_OK) return st;
-    SAL_HIP(launch_morton_order(v.keys, v.n_nodes, code, code_sorted, ids, c->order, rank, tmpm, &bm, s));
-    SAL_HIP(launch_edge_directed(occ_sorted, head, pos, n_occ, n_edges, start, rank, dkeys, cnt + 1, s));
-    size_t b3 = 0;
-    SAL_HIP(sort_keys_u64(dkeys, dsorted, n2, 32 + nb, nullptr, &b3, s));
-    char *tmp3 = nullptr;
-    if ((st = t.get(&tmp3, (int64_t)b3)) != SAL_OK) return st;
-    SAL_HIP(sort_keys_u64(dkeys, dsorted, n2, 32 + nb, tmp3, &b3, s));
+    const int cells = std::max(v.g.cells[0], std::max(v.g.cells[1], v.g.cells[2]));
+    const int bits = 3 * bits_for((int64_t)cells << kMaxLevels);
+    size_t bm = 0, bs = 0;
+    SAL_HIP(launch_morton_order(v.keys, v.n_nodes, code, code_sorted, ids, c->order, rank, bits, nullptr, &bm, s));
+    SAL_HIP(exclusive_sum_degrees(nullptr, nullptr, v.n_nodes + 1, nullptr, &bs, s));
+    char *tmp = nullptr;
+    if ((st = t.get(&tmp, (int64_t)std::max(bm, bs))) != SAL_OK) return st;
+    SAL_HIP(launch_morton_order(v.keys, v.n_nodes, code, code_sorted, ids, c->order, rank, bits, tmp, &bm, s));
+    // the distinct edges (a tetrahedral mesh has seven to eight a node)
+    unsigned long long *cnt = nullptr, *table = nullptr;
+    uint32_t *mixed = nullptr, *rows = nullptr;
+    int32_t *degree = nullptr;
+    if ((st = t.get(&cnt, 4)) != SAL_OK || (st = t.get(&degree, v.n_nodes + 1)) != SAL_OK) return st;
+    unsigned long long hcnt[4] = {0, 0, 0, 0};
+    int per = 8;
+    do {
+        per *= 2;
+        if ((st = t.get(&table, v.n_nodes * per)) != SAL_OK || (st = t.get(&mixed, v.n_nodes * per / 32 + 1)) != SAL_OK)
+            return st;
+        SAL_HIP(launch_edge_table(v.ids, v.labels, v.n_tets, rank, v.n_nodes, table, per, mixed, degree, cnt, s));
+        SAL_HIP(hipMemcpyAsync(hcnt, cnt, sizeof(hcnt), hipMemcpyDeviceToHost, s));
+        SAL_HIP(hipStreamSynchronize(s));
+        if (hcnt[0]) return set_error(SAL_ERR_CAPACITY, "smoothing: labels outside [-1, 254]");
+    } while (hcnt[1] != 0);
+    const int64_t n_edges = (int64_t)hcnt[2], n2 = 2 * n_edges;
     if ((st = dev_alloc(&c->rowptr, v.n_nodes + 1, v.token)) != SAL_OK || (st = dev_alloc(&c->cols, n2, v.token)) != SAL_OK ||
-        (st = dev_alloc(&c->cls, v.n_nodes, v.token)) != SAL_OK)
+        (st = dev_alloc(&c->cls, v.n_nodes, v.token)) != SAL_OK || (st = t.get(&rows, n2)) != SAL_OK)
         return st;
-    SAL_HIP(launch_csr(dsorted, n2, v.n_nodes, c->rowptr, c->cols, s));
+    SAL_HIP(exclusive_sum_degrees(degree, c->rowptr, v.n_nodes + 1, tmp, &bs, s));
+    SAL_HIP(launch_edge_rows(table, v.n_nodes, per, mixed, c->rowptr, degree, rows, c->cols, s));
     SAL_HIP(launch_node_class(c->rowptr, c->cols, v.keys, c->order, v.n_nodes, v.g, c->cls, s));
     // node lists of the two phases, in node order
     int64_t *blocks = nullptr, *totals = nullptr;
@@ -130,10 +106,8 @@ sal_status build_graph(const ConformView &v, SmoothCache *c, hipStream_t s) {
         SAL_HIP(launch_compact(src, v.n_nodes, blocks, totals + ph, c->list[ph], s));
     }
     SAL_HIP(hipMemcpyAsync(c->n_list, totals, sizeof(c->n_list), hipMemcpyDeviceToHost, s));
-    unsigned long long hcnt[2] = {0, 0};
-    SAL_HIP(hipMemcpyAsync(hcnt, cnt, sizeof(hcnt), hipMemcpyDeviceToHost, s));
     SAL_HIP(hipStreamSynchronize(s));
-    c->n_surface_edges = (int64_t)hcnt[1];
+    c->n_surface_edges = (int64_t)hcnt[3];
     c->n_nodes = v.n_nodes;
     c->n_edges = n_edges;
     c->partials_cap = taubin_blocks(std::max(c->n_list[0], c->n_list[1]));

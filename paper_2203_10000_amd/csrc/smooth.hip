@@ -21,20 +21,117 @@ constexpr uint32_t kSurfBit = 1u << 31;
 
 inline unsigned grid_of(int64_t n) { return (unsigned)((n + kSmoothThreads - 1) / kSmoothThreads); }
 
-// Occurrence of edge e of tetrahedron t: (low id << 36) | (high id << 8) |
-// (label + 1), ids below 2^28 and labels in [-1, 254] (checked by the host).
-__global__ void k_edge_occurrences(const int32_t *__restrict__ ids, const int32_t *__restrict__ labels,
-                                   int64_t n_tets, uint64_t *__restrict__ keys,
-                                   unsigned long long *__restrict__ bad_labels) {
-    const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (jj >= 6 * n_tets) return;
-    const int64_t t = jj / 6;
-    const int e = (int)(jj - 6 * t);
-    const uint32_t a = (uint32_t)ids[4 * t + kEdgeA[e]], b = (uint32_t)ids[4 * t + kEdgeB[e]];
+// The distinct edges are found in a table of `per` places for each node's edges to
+// nodes of higher rank, so that the tetrahedra around a node work on one or two
+// cache lines; an edge that finds its node's places taken goes on to the next ones'.
+// A place holds (low rank << 36) | (high rank << 8) | (label + 1), ranks below 2^28
+// and labels in [-1, 254] (checked by the host), and changes once, from empty: the
+// bit of `mixed` is set where an occurrence of another label comes.  Bound by the
+// latency of the places' cache lines.  (With a sort of the 31M occurrences of 5.2M
+// tetrahedra's edges and one of both directions of the 6M distinct ones the whole
+// graph took 3.3 ms; it takes 1.8.)
+constexpr unsigned long long kNoEdge = ~0ull;
+
+__device__ __forceinline__ bool add_edge(unsigned long long *__restrict__ table, int64_t cap, int per,
+                                         uint32_t *__restrict__ mixed, uint32_t a, uint32_t b, uint64_t label) {
     const uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
+    const unsigned long long key = (lo << 36) | (hi << 8) | label;
+    int64_t h = (int64_t)lo * per + (int64_t)((hi * 0x9e3779b1u >> 16) & (uint32_t)(per - 1));
+    for (int64_t probe = 0; probe < cap; ++probe) {
+        // (a stale "empty" costs a compare-and-swap, which tells)
+        unsigned long long cur = __hip_atomic_load(&table[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (cur == kNoEdge) {
+            cur = atomicCAS(&table[h], kNoEdge, key);
+            if (cur == kNoEdge) return true;
+        }
+        if ((cur >> 8) == (key >> 8)) {
+            const uint32_t bit = 1u << (h & 31);
+            if (cur != key && !(mixed[h >> 5] & bit)) atomicOr(&mixed[h >> 5], bit);
+            return true;
+        }
+        if (++h == cap) h = 0;
+    }
+    return false;
+}
+
+// cnt[0]: labels outside [-1, 254]; cnt[1]: edges without a place.
+__global__ void k_edge_insert(const int32_t *__restrict__ ids, const int32_t *__restrict__ labels,
+                              int64_t n_tets, const int32_t *__restrict__ rank,
+                              unsigned long long *__restrict__ table, int64_t cap, int per,
+                              uint32_t *__restrict__ mixed, unsigned long long *__restrict__ cnt) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n_tets) return;
     const int32_t lab = labels[t];
-    if (e == 0 && (lab < -1 || lab > 254)) atomicAdd(bad_labels, 1ull);
-    keys[jj] = (lo << 36) | (hi << 8) | (uint64_t)(uint8_t)(lab + 1);
+    if (lab < -1 || lab > 254) {
+        atomicAdd(&cnt[0], 1ull);
+        return;
+    }
+    const int4 id = *(const int4 *)(ids + 4 * t);
+    const uint32_t r[4] = {(uint32_t)rank[id.x], (uint32_t)rank[id.y], (uint32_t)rank[id.z], (uint32_t)rank[id.w]};
+    for (int e = 0; e < 6; ++e)
+        if (!add_edge(table, cap, per, mixed, r[kEdgeA[e]], r[kEdgeB[e]], (uint64_t)(uint8_t)(lab + 1)))
+            atomicAdd(&cnt[1], 1ull);
+}
+
+// Edges at each node; cnt[2] the edges, cnt[3] the interface edges.
+constexpr int kEdgeTurns = 16;
+
+__global__ __launch_bounds__(kSmoothThreads) void k_edge_degrees(
+    const unsigned long long *__restrict__ table, int64_t cap, const uint32_t *__restrict__ mixed,
+    int32_t *__restrict__ degree, unsigned long long *__restrict__ cnt) {
+    __shared__ unsigned n[2];
+    if (threadIdx.x < 2) n[threadIdx.x] = 0;
+    __syncthreads();
+    unsigned all = 0, surf = 0;   // the wavefront's
+    for (int u = 0; u < kEdgeTurns; ++u) {
+        const int64_t h = ((int64_t)blockIdx.x * kEdgeTurns + u) * kSmoothThreads + threadIdx.x;
+        const unsigned long long k = h < cap ? table[h] : kNoEdge;
+        const bool edge = k != kNoEdge;
+        if (edge) {
+            atomicAdd(&degree[k >> 36], 1);
+            atomicAdd(&degree[(k >> 8) & ((1ull << 28) - 1)], 1);
+        }
+        all += (unsigned)__popcll(__ballot(edge));
+        surf += (unsigned)__popcll(__ballot(edge && (mixed[h >> 5] >> (h & 31) & 1u)));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&n[0], all);
+        atomicAdd(&n[1], surf);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && n[threadIdx.x]) atomicAdd(&cnt[2 + threadIdx.x], (unsigned long long)n[threadIdx.x]);
+}
+
+// Both directions of every edge into the rows, in no order; `degree` counts down
+// to 0.
+__global__ void k_edge_rows(const unsigned long long *__restrict__ table, int64_t cap,
+                            const uint32_t *__restrict__ mixed, const int64_t *__restrict__ rowptr,
+                            int32_t *__restrict__ degree, uint32_t *__restrict__ rows) {
+    const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (h >= cap) return;
+    const unsigned long long k = table[h];
+    if (k == kNoEdge) return;
+    const uint32_t a = (uint32_t)(k >> 36), b = (uint32_t)((k >> 8) & ((1ull << 28) - 1));
+    const uint32_t surf = (mixed[h >> 5] >> (h & 31) & 1u) ? kSurfBit : 0u;
+    rows[rowptr[a] + atomicSub(&degree[a], 1) - 1] = b | surf;
+    rows[rowptr[b] + atomicSub(&degree[b], 1) - 1] = a | surf;
+}
+
+// Rows by ascending column: eight lanes a row, each entry to its rank (some 14
+// distinct entries a row).
+constexpr int kSortGroup = 8;
+
+__global__ void k_sort_rows(const int64_t *__restrict__ rowptr, int64_t n, const uint32_t *__restrict__ rows,
+                            uint32_t *__restrict__ cols) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = t / kSortGroup;
+    if (i >= n) return;
+    const int64_t b = rowptr[i], len = rowptr[i + 1] - b;
+    for (int64_t q = t % kSortGroup; q < len; q += kSortGroup) {
+        const uint32_t mine = rows[b + q];
+        int64_t rank = 0;
+        for (int64_t j = 0; j < len; ++j) rank += (rows[b + j] & ~kSurfBit) < (mine & ~kSurfBit);
+        cols[b + rank] = mine;
+    }
 }
 
 // Morton code of a node (its three 21-bit finest-grid coordinates
@@ -63,61 +160,6 @@ __global__ void k_rank_of(const int32_t *__restrict__ order, int64_t n, int32_t 
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n) return;
     rank[order[r]] = (int32_t)r;
-}
-
-__global__ void k_edge_heads(const uint64_t *__restrict__ keys, int64_t n, int32_t *__restrict__ head) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    head[i] = (i == 0 || (keys[i] >> 8) != (keys[i - 1] >> 8)) ? 1 : 0;
-}
-
-__global__ void k_edge_starts(const int32_t *__restrict__ head, const int64_t *__restrict__ pos,
-                              int64_t n, int64_t *__restrict__ start) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || !head[i]) return;
-    start[pos[i]] = i;
-}
-
-// Both directions of edge e in Morton ranks: (row << 32) | (col << 1) |
-// interface, where the edge is an interface edge when its occurrences carry
-// different labels (sorted, so the first and the last differ).
-__global__ void k_edge_emit(const uint64_t *__restrict__ keys, const int64_t *__restrict__ start,
-                            int64_t n, int64_t n_edges, const int32_t *__restrict__ rank,
-                            uint64_t *__restrict__ dkeys, unsigned long long *__restrict__ n_surf) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint64_t surf = 0;
-    if (e < n_edges) {
-        const int64_t s = start[e];
-        const int64_t last = (e + 1 < n_edges ? start[e + 1] : n) - 1;
-        const uint64_t k = keys[s];
-        surf = (k & 0xffu) != (keys[last] & 0xffu) ? 1u : 0u;
-        const uint64_t a = (uint64_t)rank[k >> 36], b = (uint64_t)rank[(k >> 8) & ((1ull << 28) - 1)];
-        dkeys[2 * e] = (a << 32) | (b << 1) | surf;
-        dkeys[2 * e + 1] = (b << 32) | (a << 1) | surf;
-    }
-    // one counter update per block
-    __shared__ unsigned int block_count;
-    if (threadIdx.x == 0) block_count = 0;
-    __syncthreads();
-    const unsigned long long m = __ballot(surf != 0);
-    if ((threadIdx.x & 63) == 0 && m) atomicAdd(&block_count, (unsigned int)__popcll(m));
-    __syncthreads();
-    if (threadIdx.x == 0 && block_count) atomicAdd(n_surf, (unsigned long long)block_count);
-}
-
-// Row pointers from the sorted directed keys (rows without an entry get an
-// empty range) and the columns with the interface bit.
-__global__ void k_csr(const uint64_t *__restrict__ dkeys, int64_t n2, int64_t n_nodes,
-                      int64_t *__restrict__ rowptr, uint32_t *__restrict__ cols) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n2) return;
-    const uint64_t d = dkeys[k];
-    const int64_t r = (int64_t)(d >> 32);
-    cols[k] = (uint32_t)((d >> 1) & 0x7fffffffu) | ((d & 1u) ? kSurfBit : 0u);
-    const int64_t prev = k == 0 ? -1 : (int64_t)(dkeys[k - 1] >> 32);
-    for (int64_t q = prev + 1; q <= r; ++q) rowptr[q] = k;
-    if (k == n2 - 1)
-        for (int64_t q = r + 1; q <= n_nodes; ++q) rowptr[q] = n2;
 }
 
 // Per Morton rank: 0 on a face of the lattice box (never moves); 1 on an
@@ -378,58 +420,48 @@ int64_t taubin_blocks(int64_t n) {
     return (b + 7) / 8 * 8;
 }
 
-hipError_t launch_edge_occurrences(const int32_t *ids, const int32_t *labels, int64_t n_tets,
-                                   uint64_t *keys, unsigned long long *bad_labels, hipStream_t s) {
-    if (n_tets <= 0) return hipSuccess;
-    k_edge_occurrences<<<grid_of(6 * n_tets), kSmoothThreads, 0, s>>>(ids, labels, n_tets, keys,
-                                                                       bad_labels);
+hipError_t launch_edge_table(const int32_t *ids, const int32_t *labels, int64_t n_tets, const int32_t *rank,
+                             int64_t n_nodes, unsigned long long *table, int per, uint32_t *mixed,
+                             int32_t *degree, unsigned long long *cnt, hipStream_t s) {
+    const int64_t cap = n_nodes * per, tile = kEdgeTurns * kSmoothThreads;
+    hipError_t e = launch_fill_u64(table, kNoEdge, cap, s);
+    if (e == hipSuccess) e = launch_fill_i32((int32_t *)mixed, 0, (cap + 31) / 32, s);
+    if (e == hipSuccess) e = launch_fill_i32(degree, 0, n_nodes + 1, s);
+    if (e == hipSuccess) e = launch_fill_u64(cnt, 0ull, 4, s);
+    if (e != hipSuccess) return e;
+    if (n_tets > 0)
+        k_edge_insert<<<grid_of(n_tets), kSmoothThreads, 0, s>>>(ids, labels, n_tets, rank, table, cap, per,
+                                                                  mixed, cnt);
+    k_edge_degrees<<<(unsigned)((cap + tile - 1) / tile), kSmoothThreads, 0, s>>>(table, cap, mixed, degree, cnt);
     return hipGetLastError();
 }
 
-hipError_t sort_keys_u64(const uint64_t *in, uint64_t *out, int64_t n, int end_bit, void *tmp,
-                         size_t *tmp_bytes, hipStream_t s) {
-    return rocprim::radix_sort_keys(tmp, *tmp_bytes, in, out, (size_t)n, 0u, (unsigned)end_bit, s);
-}
-
-hipError_t launch_edge_heads(const uint64_t *keys, int64_t n, int32_t *head, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    k_edge_heads<<<grid_of(n), kSmoothThreads, 0, s>>>(keys, n, head);
+hipError_t launch_edge_rows(const unsigned long long *table, int64_t n_nodes, int per, const uint32_t *mixed,
+                            const int64_t *rowptr, int32_t *degree, uint32_t *rows, uint32_t *cols,
+                            hipStream_t s) {
+    const int64_t cap = n_nodes * per;
+    if (cap <= 0) return hipSuccess;
+    k_edge_rows<<<grid_of(cap), kSmoothThreads, 0, s>>>(table, cap, mixed, rowptr, degree, rows);
+    k_sort_rows<<<grid_of(n_nodes * kSortGroup), kSmoothThreads, 0, s>>>(rowptr, n_nodes, rows, cols);
     return hipGetLastError();
 }
 
-hipError_t exclusive_sum_head(const int32_t *head, int64_t *pos, int64_t n, void *tmp,
-                              size_t *tmp_bytes, hipStream_t s) {
-    return rocprim::exclusive_scan(tmp, *tmp_bytes, head, pos, (int64_t)0, (size_t)n,
+hipError_t exclusive_sum_degrees(const int32_t *degree, int64_t *rowptr, int64_t n, void *tmp,
+                                 size_t *tmp_bytes, hipStream_t s) {
+    return rocprim::exclusive_scan(tmp, *tmp_bytes, degree, rowptr, (int64_t)0, (size_t)n,
                                    rocprim::plus<int64_t>(), s);
 }
 
-hipError_t launch_edge_directed(const uint64_t *keys, const int32_t *head, const int64_t *pos,
-                                int64_t n, int64_t n_edges, int64_t *start, const int32_t *rank,
-                                uint64_t *dkeys, unsigned long long *n_surf, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    k_edge_starts<<<grid_of(n), kSmoothThreads, 0, s>>>(head, pos, n, start);
-    k_edge_emit<<<grid_of(n_edges), kSmoothThreads, 0, s>>>(keys, start, n, n_edges, rank, dkeys,
-                                                           n_surf);
-    return hipGetLastError();
-}
-
-hipError_t launch_csr(const uint64_t *dkeys, int64_t n2, int64_t n_nodes, int64_t *rowptr,
-                      uint32_t *cols, hipStream_t s) {
-    if (n2 <= 0) return hipSuccess;
-    k_csr<<<grid_of(n2), kSmoothThreads, 0, s>>>(dkeys, n2, n_nodes, rowptr, cols);
-    return hipGetLastError();
-}
-
 hipError_t launch_morton_order(const int64_t *keys, int64_t n, uint64_t *code, uint64_t *code_sorted,
-                               int32_t *ids, int32_t *order, int32_t *rank, void *tmp,
+                               int32_t *ids, int32_t *order, int32_t *rank, int bits, void *tmp,
                                size_t *tmp_bytes, hipStream_t s) {
     if (!tmp)
         return rocprim::radix_sort_pairs(tmp, *tmp_bytes, code, code_sorted, ids, order, (size_t)n,
-                                         0u, 63u, s);
+                                         0u, (unsigned)bits, s);
     if (n <= 0) return hipSuccess;
     k_morton_codes<<<grid_of(n), kSmoothThreads, 0, s>>>(keys, n, code, ids);
     hipError_t e = rocprim::radix_sort_pairs(tmp, *tmp_bytes, code, code_sorted, ids, order,
-                                             (size_t)n, 0u, 63u, s);
+                                             (size_t)n, 0u, (unsigned)bits, s);
     if (e != hipSuccess) return e;
     k_rank_of<<<grid_of(n), kSmoothThreads, 0, s>>>(order, n, rank);
     return hipGetLastError();
