@@ -99,15 +99,6 @@ __device__ __forceinline__ void mark_cells(uint32_t *__restrict__ bits, const La
             }
 }
 
-// Level and first item of this thread in a launch over LevelSpans; its others
-// follow in steps of the workgroup.
-__device__ __forceinline__ int span_level(const LevelSpans &r, int64_t &item) {
-    int l = 0;
-    while (l < r.top && blockIdx.x >= r.block0[l + 1]) ++l;
-    item = (int64_t)(blockIdx.x - r.block0[l]) * (256 * r.turns) + threadIdx.x;
-    return l;
-}
-
 // Empties the vertices new in a round and their cells' bits.
 __global__ void k_closure_clear(unsigned long long *__restrict__ fresh, int64_t fcap,
                                 uint32_t *__restrict__ cells_new, int64_t cell_words) {
@@ -449,22 +440,13 @@ inline unsigned grid_of(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-// Workgroups of 256 for per[l] items of level l, a level's first one its own.  In
-// a launch that counts, a large one gives a thread 16 items: a counter takes some
+// In a launch that counts, a large one gives a thread 16 items: a counter takes some
 // 5 ns for each workgroup's update (11M vertices inserted: 580 us with 45,000 of
 // them, 190 now).
-static LevelSpans with_blocks(LevelSpans r, const int64_t (&per)[kMaxLevels + 1], int64_t *blocks,
-                              bool counts = false) {
-    int64_t nb = 0, all = 0;
-    for (int l = 0; l <= r.top; ++l) all += per[l];
-    r.turns = counts && all >= (int64_t)1 << 21 ? 16 : 1;
-    for (int l = 0; l <= kMaxLevels; ++l) {
-        r.block0[l] = (uint32_t)nb;
-        if (l <= r.top) nb += (per[l] + 256 * r.turns - 1) / (256 * r.turns);
-    }
-    r.block0[kMaxLevels + 1] = (uint32_t)nb;
-    *blocks = nb;
-    return r;
+static int count_turns(const int64_t (&per)[kMaxLevels + 1]) {
+    int64_t all = 0;
+    for (const int64_t n : per) all += n;
+    return all >= (int64_t)1 << 21 ? 16 : 1;
 }
 
 hipError_t launch_closure_clear(unsigned long long *fresh, int64_t fcap, uint32_t *cells_new, int64_t cell_words,
@@ -479,7 +461,7 @@ hipError_t launch_insert_levels(const LevelPtrs &L, const LatticeGeom &g, const 
                                 hipStream_t s) {
     int64_t per[kMaxLevels + 1] = {}, nb;
     for (int l = 0; l <= r.top; ++l) per[l] = 4 * (r.n[l] - r.first[l]);
-    const LevelSpans q = with_blocks(r, per, &nb, true);
+    const LevelSpans q = with_blocks(r, per, count_turns(per), &nb);
     if (nb == 0) return hipSuccess;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     k_insert_levels<<<(unsigned)nb, 256, 0, s>>>(L, g, q, set, cap, fresh, fcap, cells_new, n_new, overflow);
@@ -491,7 +473,7 @@ hipError_t launch_pattern_levels(const LevelPtrs &L, const LatticeGeom &g, const
                                  int64_t fcap, const uint32_t *cells_new, hipStream_t s) {
     int64_t per[kMaxLevels + 1] = {}, nb;
     for (int l = 0; l <= r.top; ++l) per[l] = r.n[l];
-    const LevelSpans q = with_blocks(r, per, &nb);
+    const LevelSpans q = with_blocks(r, per, 1, &nb);
     if (nb == 0) return hipSuccess;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     k_pattern_levels<<<(unsigned)nb, 256, 0, s>>>(L, g, q, set, cap, fresh, fcap, cells_new);
@@ -502,7 +484,7 @@ hipError_t launch_tet_counts(const LevelPtrs &L, const LevelSpans &r, const int3
                              unsigned long long *hist, hipStream_t s) {
     int64_t per[kMaxLevels + 1] = {}, nb;
     for (int l = 0; l <= r.top; ++l) per[l] = r.n[l];
-    const LevelSpans q = with_blocks(r, per, &nb, true);
+    const LevelSpans q = with_blocks(r, per, count_turns(per), &nb);
     if (nb == 0) return hipSuccess;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     k_tet_counts<<<(unsigned)nb, 256, 0, s>>>(L, q, list, counts, hist);
@@ -540,7 +522,7 @@ hipError_t launch_emit(const LevelPtrs &L, const LatticeGeom &g, const LevelSpan
                        int32_t *ids, int32_t *labels, hipStream_t s) {
     int64_t per[kMaxLevels + 1] = {}, blocks;
     for (int l = 0; l <= r.top; ++l) per[l] = r.n[l];
-    const LevelSpans q = with_blocks(r, per, &blocks);
+    const LevelSpans q = with_blocks(r, per, 1, &blocks);
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     k_emit<<<(unsigned)blocks, 256, 0, s>>>(L, g, q, list, offsets, TetSink{table, cap, nb, ids}, labels);

@@ -72,4 +72,13 @@ __device__ __forceinline__ void kuhn_vertices(int q, const int64_t c[3], int64_t
     X[2][p1] += 1;
 }
 
+// Level and first item of this thread in a launch over LevelSpans; its others
+// follow in steps of the workgroup.
+__device__ __forceinline__ int span_level(const LevelSpans &r, int64_t &item) {
+    int l = 0;
+    while (l < r.top && blockIdx.x >= r.block0[l + 1]) ++l;
+    item = (int64_t)(blockIdx.x - r.block0[l]) * (256 * r.turns) + threadIdx.x;
+    return l;
+}
+
 }  // namespace sal

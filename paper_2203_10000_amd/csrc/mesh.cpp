@@ -76,7 +76,7 @@ struct sal_tet_mesh {
     int64_t *blocks = nullptr;
     int64_t blocks_cap = 0;
     int64_t *totals = nullptr;   // kMaxLevels + 2 counts
-    hipEvent_t ev[16] = {};
+    hipEvent_t ev[17] = {};
     // captured refine round
     int32_t *lab_scratch = nullptr;
     int64_t lab_cap = 0;
@@ -85,24 +85,18 @@ struct sal_tet_mesh {
     uint64_t round_key = 0;
     std::vector<uint64_t> round_fields;   // the fields hashed into round_key
     // four-node rule: level-0 node grid masks, per-leaf vertex masks of
-    // levels >= 1, masks of the labeled midpoints
+    // levels >= 1
     int rule = -1;   // element rule fixed by the first labeling
     unsigned long long *node0 = nullptr;
     unsigned long long *vmask[sal::kMaxLevels + 1] = {};
-    unsigned long long *mid_masks = nullptr;
-    int64_t mid_cap = 0;
     // midpoints of a split level and the node table (each node labeled once)
-    float *mid_xyz[3] = {};
-    int64_t mid_xyz_cap = 0;
-    uint64_t *mid_key = nullptr;
-    int64_t mid_key_cap = 0;
     int64_t *mid_slot = nullptr;
     int64_t mid_slot_cap = 0;
-    int32_t *new_list = nullptr;
-    int64_t new_list_cap = 0;
+    int64_t *new_slot = nullptr;
+    int64_t new_slot_cap = 0;
     unsigned long long *new_masks = nullptr;
     int64_t new_masks_cap = 0;
-    unsigned long long *n_new = nullptr;
+    unsigned long long *n_new = nullptr;   // of each split level
     unsigned long long *tkeys = nullptr, *tmasks = nullptr;
     int64_t tcap = 0, tused = 0;   // tused: upper bound of the entries
 };
@@ -193,13 +187,14 @@ sal_status compact(sal_tet_mesh *m, const CompactSrc &src, int64_t n, int32_t *o
 // level in `out`, and waits for the levels' counts and the extra word.
 sal_status compact_levels(sal_context *ctx, sal_tet_mesh *m, uint8_t mask, int32_t *out,
                           int64_t (&count)[kMaxLevels + 1], const unsigned long long *extra = nullptr,
-                          int64_t *extra_out = nullptr) {
+                          int64_t *extra_out = nullptr, hipEvent_t done = nullptr) {
     hipStream_t s = ctx->stream;
     const LevelPtrs L = ptrs(m);
     const int top = m->max_level;
-    const sal_status st = ensure_buf(m, &m->blocks, &m->blocks_cap, compact_level_blocks(L, top), s);
+    const sal_status st = ensure_buf(m, &m->blocks, &m->blocks_cap, compact_level_blocks(m->n, top), s);
     if (st != SAL_OK) return st;
-    SAL_HIP(launch_compact_levels(L, top, mask, m->blocks, m->totals, extra, ctx->host_words, out, s));
+    SAL_HIP(launch_compact_levels(L, top, m->n, mask, m->blocks, m->totals, extra, ctx->host_words, out, s));
+    if (done) SAL_HIP(hipEventRecord(done, s));
     SAL_HIP(hipStreamSynchronize(s));
     for (int l = 0; l <= kMaxLevels; ++l) count[l] = l <= top ? ctx->host_words[l] : 0;
     if (extra_out) *extra_out = ctx->host_words[kMaxLevels + 1];
@@ -230,7 +225,7 @@ sal_status label_scratch_dev(sal_context *ctx, sal_tet_mesh *m, const sal_surfac
     sal_label_options opt = opt_in;
     st = tune_launch(ctx, set, n_cap, m->cen[0], m->cen[1], m->cen[2], labels, &opt);
     if (st != SAL_OK) return st;
-    SAL_HIP(hipEventRecord(ev_start, ctx->stream));
+    if (ev_start) SAL_HIP(hipEventRecord(ev_start, ctx->stream));
     return enqueue_label_on(ctx, set, n_cap, (const int64_t *)n_dev, m->cen[0], m->cen[1],
                             m->cen[2], opt, labels, nullptr, ev_mid, ctx->stream, masks);
 }
@@ -271,40 +266,50 @@ float elapsed(hipEvent_t a, hipEvent_t b) {
 // level, deepest first, split the marked leaves and label their children.
 // Marked leaves at level `finest` or deeper are left as they are (the
 // converging recursion); without a limit a marked level-3 leaf is an error.
-// Synchronises once to size the new level (and once per level for timing).
+// Synchronises once to size the new levels, and with `out` once for its figures (a
+// round of a small mesh is bound by its launches and waits: with launches for each
+// level and a wait after each level's labels the 13 steps of a converging run on
+// 83,000 lattice tetrahedra took 7.0 ms, 5.2 now).
 sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set *set,
                        const sal_label_options &opt, sal_refine_stats *out,
                        int finest = kMaxLevels + 1, int64_t *n_split_out = nullptr) {
     hipStream_t s = ctx->stream;
     sal_status st;
     const int top = m->max_level;
+    const bool nodes = m->rule == SAL_RULE_FOUR_NODES;
+    // events 2 to 5 and 5 to 8 + 4 l: of the round and of the split of level l
+    auto record = [&](int k) -> sal_status {
+        if (!out) return SAL_OK;
+        SAL_HIP(hipEventRecord(m->ev[k], s));
+        return SAL_OK;
+    };
     int64_t total_entries = 0;
     for (int l = 0; l <= top; ++l) total_entries += m->n[l];
     if ((st = ensure_buf(m, &m->list, &m->list_cap, total_entries, s)) != SAL_OK) return st;
-    SAL_HIP(launch_fill_u64(ctx->counters, 0ull, kNumCounters, s));
-    SAL_HIP(hipEventRecord(m->ev[2], s));
-    for (int l = 0; l <= top; ++l) SAL_HIP(launch_fill_u8(m->flag[l], 0, m->n[l], s));
-    LevelPtrs L = ptrs(m);
-    for (int l = 0; l <= top; ++l) SAL_HIP(launch_mark(L, m->g, m->T, l, s));
-    SAL_HIP(hipEventRecord(m->ev[3], s));
+    if (nodes && !m->n_new && mesh_malloc(m, &m->n_new, kMaxLevels) != hipSuccess)
+        return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(node counter)");
+    if ((st = record(2)) != SAL_OK) return st;
+    {
+        const LevelPtrs L = ptrs(m);
+        SAL_HIP(launch_round_clear(L, top, m->n, ctx->counters, nodes ? m->n_new : nullptr, nullptr, s));
+        SAL_HIP(launch_mark(L, m->g, m->T, top, m->n, s));
+    }
+    if ((st = record(3)) != SAL_OK) return st;
     int64_t count[kMaxLevels + 1], off[kMaxLevels + 2] = {0};
-    if ((st = compact_levels(ctx, m, 0xff, m->list, count)) != SAL_OK) return st;
-    SAL_HIP(hipEventRecord(m->ev[4], s));
+    if ((st = compact_levels(ctx, m, 0xff, m->list, count, nullptr, nullptr, out ? m->ev[4] : nullptr)) != SAL_OK)
+        return st;
     for (int l = 0; l <= top; ++l) off[l + 1] = off[l] + count[l];
     for (int l = finest; l <= top; ++l) count[l] = 0;
     if (top == kMaxLevels && count[top] > 0)
         return set_error(SAL_ERR_CAPACITY, "refinement beyond level 3");
     int64_t n_split = 0, n_label = 0;
-    float ms_split = 0.0f, ms_label = 0.0f, ms_recheck = 0.0f;
     // Every buffer the round needs is allocated before the first split, so a
-    // round that runs out of device memory fails with the mesh unchanged
-    // (the in-loop ensure calls below then find the room already there).
+    // round that runs out of device memory fails with the mesh unchanged.
     {
-        const bool nodes = m->rule == SAL_RULE_FOUR_NODES;
         int64_t pts_max = 0, pts_sum = 0;
         for (int l = top; l >= 0; --l) {
             if (count[l] == 0) continue;
-            const int64_t n_pts = nodes ? 6 * count[l] : 8 * count[l];
+            const int64_t n_pts = nodes ? 6 * count[l] : 8 * count[l];   // midpoints or centroids
             pts_max = std::max(pts_max, n_pts);
             pts_sum += n_pts;
             if ((st = ensure_level(m, l + 1, m->n[l + 1] + 8 * count[l], s)) != SAL_OK) return st;
@@ -312,119 +317,74 @@ sal_status eager_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set 
         if (pts_max > 0) {
             if ((st = ensure_centroids(m, pts_max, s)) != SAL_OK) return st;
             if ((st = ensure_label_scratch(ctx, set, pts_max)) != SAL_OK) return st;
-            if (nodes) {
-                int64_t c3 = m->mid_xyz_cap;
-                for (int a = 0; a < 3; ++a) {
-                    c3 = m->mid_xyz_cap;
-                    if ((st = ensure_buf(m, &m->mid_xyz[a], &c3, pts_max, s)) != SAL_OK) return st;
-                }
-                m->mid_xyz_cap = c3;
-                if ((st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(m, &m->mid_masks, &m->mid_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(m, &m->mid_key, &m->mid_key_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(m, &m->mid_slot, &m->mid_slot_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(m, &m->new_list, &m->new_list_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_buf(m, &m->new_masks, &m->new_masks_cap, pts_max, s)) != SAL_OK ||
-                    (st = ensure_node_table(m, pts_sum, s)) != SAL_OK)
-                    return st;
-                if (!m->n_new && mesh_malloc(m, &m->n_new, 1) != hipSuccess)
-                    return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(node counter)");
-            }
+            if (nodes && ((st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, pts_max, s)) != SAL_OK ||
+                          (st = ensure_buf(m, &m->mid_slot, &m->mid_slot_cap, pts_max, s)) != SAL_OK ||
+                          (st = ensure_buf(m, &m->new_slot, &m->new_slot_cap, pts_max, s)) != SAL_OK ||
+                          (st = ensure_buf(m, &m->new_masks, &m->new_masks_cap, pts_max, s)) != SAL_OK ||
+                          (st = ensure_node_table(m, pts_sum, s)) != SAL_OK))
+                return st;
         }
     }
     // deepest level first: its children array never moves under a pending
     // split of a coarser level
     for (int l = top; l >= 0; --l) {
         if (count[l] == 0) continue;
-        const int64_t kids = 8 * count[l];
-        const bool nodes = m->rule == SAL_RULE_FOUR_NODES;
-        const int64_t n_pts = nodes ? 6 * count[l] : kids;   // midpoints or centroids
-        if ((st = ensure_level(m, l + 1, m->n[l + 1] + kids, s)) != SAL_OK) return st;
-        if ((st = ensure_centroids(m, n_pts, s)) != SAL_OK) return st;
-        if (nodes) {
-            int64_t c3 = m->mid_xyz_cap;
-            for (int a = 0; a < 3; ++a) {
-                c3 = m->mid_xyz_cap;
-                if ((st = ensure_buf(m, &m->mid_xyz[a], &c3, n_pts, s)) != SAL_OK) return st;
-            }
-            m->mid_xyz_cap = c3;
-            if ((st = ensure_buf(m, &m->lab_scratch, &m->lab_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(m, &m->mid_masks, &m->mid_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(m, &m->mid_key, &m->mid_key_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(m, &m->mid_slot, &m->mid_slot_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(m, &m->new_list, &m->new_list_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_buf(m, &m->new_masks, &m->new_masks_cap, n_pts, s)) != SAL_OK ||
-                (st = ensure_node_table(m, n_pts, s)) != SAL_OK)
-                return st;
-            if (!m->n_new && mesh_malloc(m, &m->n_new, 1) != hipSuccess)
-                return set_error(SAL_ERR_OUT_OF_MEMORY, "hipMalloc(node counter)");
-        }
+        const int64_t kids = 8 * count[l], n_pts = nodes ? 6 * count[l] : kids;
         const int64_t base_block = m->n[l + 1] / 8;
-        LevelPtrs L2 = ptrs(m);
-        SAL_HIP(hipEventRecord(m->ev[5], s));
-        SAL_HIP(launch_split(L2, m->g, m->T, l, m->list + off[l], count[l], base_block,
+        const int e = 5 + 4 * l;
+        const LevelPtrs L = ptrs(m);
+        if ((st = record(e)) != SAL_OK) return st;
+        SAL_HIP(launch_split(L, m->g, m->T, l, m->list + off[l], count[l], base_block,
                              nodes ? nullptr : m->cen[0], nodes ? nullptr : m->cen[1],
                              nodes ? nullptr : m->cen[2], s));
         if (nodes) {
             // midpoints -> node table -> only the nodes not labeled before
-            SAL_HIP(launch_midpoints(L2, m->g, l, m->list + off[l], count[l], m->mid_xyz[0],
-                                     m->mid_xyz[1], m->mid_xyz[2], m->mid_key, s));
-            SAL_HIP(launch_fill_u64(m->n_new, 0ull, 1, s));
-            SAL_HIP(launch_node_insert(m->mid_key, n_pts, m->tkeys, m->tcap, m->mid_slot,
-                                       m->new_list, m->n_new, s));
-            SAL_HIP(launch_node_gather(m->new_list, m->n_new, n_pts, m->mid_xyz[0], m->mid_xyz[1],
-                                       m->mid_xyz[2], m->cen[0], m->cen[1], m->cen[2], s));
+            SAL_HIP(launch_midpoints(L, m->g, l, m->list + off[l], count[l], m->tkeys, m->tcap, m->mid_slot,
+                                     m->new_slot, m->n_new + l, m->cen[0], m->cen[1], m->cen[2], s));
             m->tused += n_pts;
         }
-        SAL_HIP(hipEventRecord(m->ev[6], s));
         m->n[l + 1] += kids;
         m->n_leaves += 7 * count[l];
+        const hipEvent_t start = out ? m->ev[e + 1] : nullptr, mid = out ? m->ev[e + 2] : nullptr;
         if (nodes) {
-            if ((st = label_scratch_dev(ctx, m, set, n_pts, m->n_new, opt, m->lab_scratch,
-                                        m->ev[10], m->ev[9], m->new_masks)) != SAL_OK)
+            if ((st = label_scratch_dev(ctx, m, set, n_pts, m->n_new + l, opt, m->lab_scratch, start,
+                                        mid, m->new_masks)) != SAL_OK)
                 return st;
-            SAL_HIP(launch_node_store(m->new_list, m->n_new, n_pts, m->mid_slot, m->new_masks,
-                                      m->tmasks, s));
-            SAL_HIP(launch_node_fetch(m->mid_slot, n_pts, m->tmasks, m->mid_masks, s));
-            SAL_HIP(launch_child_masks(L2, m->g, l, m->list + off[l], count[l], base_block,
-                                       m->node0, m->vmask[l], m->mid_masks, m->vmask[l + 1],
+            SAL_HIP(launch_node_store(m->new_slot, m->n_new + l, n_pts, m->new_masks, m->tmasks, s));
+            SAL_HIP(launch_child_masks(L, m->g, l, m->list + off[l], count[l], base_block,
+                                       m->node0, m->vmask[l], m->mid_slot, m->tmasks, m->vmask[l + 1],
                                        set->surf, s));
         } else if ((st = label_scratch(ctx, m, set, kids, opt, m->label[l + 1] + 8 * base_block,
-                                       m->ev[10], m->ev[9])) != SAL_OK) {
+                                       start, mid)) != SAL_OK) {
             return st;
         }
-        SAL_HIP(hipEventRecord(m->ev[7], s));
-        SAL_HIP(hipEventSynchronize(m->ev[7]));
-        ms_split += elapsed(m->ev[5], m->ev[6]);
-        ms_label += elapsed(m->ev[10], m->ev[9]);
-        ms_recheck += elapsed(m->ev[9], m->ev[7]);
+        if ((st = record(e + 3)) != SAL_OK) return st;
         if (l + 1 > m->max_level) m->max_level = l + 1;
         n_split += count[l];
-        if (nodes) {
-            unsigned long long fresh = 0;
-            SAL_HIP(hipMemcpy(&fresh, m->n_new, sizeof(fresh), hipMemcpyDeviceToHost));
-            n_label += (int64_t)fresh;
-        } else {
-            n_label += n_pts;
-        }
+        if (!nodes) n_label += n_pts;
     }
     if (n_split_out) *n_split_out = n_split;
-    SAL_HIP(hipEventRecord(m->ev[8], s));
     if (out) {
-        unsigned long long cnt[kNumCounters];
-        SAL_HIP(hipEventSynchronize(m->ev[8]));
-        SAL_HIP(hipMemcpy(cnt, ctx->counters, sizeof(cnt), hipMemcpyDeviceToHost));
+        SAL_HIP(launch_report(ctx->counters, nodes ? m->n_new : nullptr, ctx->host_words, s));
+        if ((st = record(1)) != SAL_OK) return st;
+        SAL_HIP(hipStreamSynchronize(s));
+        for (int l = 0; l < kMaxLevels; ++l) n_label += ctx->host_words[1 + l];
         out->n_leaves = m->n_leaves;
         out->n_boundary = n_split;
         out->n_labeled = n_label;
         out->n_pairs = n_label * set->n_tri;
-        out->n_recheck_pairs = (int64_t)cnt[kCntRecheck];
+        out->n_recheck_pairs = ctx->host_words[0];
         out->ms_mark = elapsed(m->ev[2], m->ev[3]);
         out->ms_compact = elapsed(m->ev[3], m->ev[4]);
-        out->ms_split = ms_split;
-        out->ms_label = ms_label;
-        out->ms_recheck = ms_recheck;
-        out->ms_total = elapsed(m->ev[2], m->ev[8]);
+        out->ms_split = out->ms_label = out->ms_recheck = 0.0f;
+        for (int l = 0; l <= top; ++l) {
+            if (count[l] == 0) continue;
+            const int e = 5 + 4 * l;
+            out->ms_split += elapsed(m->ev[e], m->ev[e + 1]);
+            out->ms_label += elapsed(m->ev[e + 1], m->ev[e + 2]);
+            out->ms_recheck += elapsed(m->ev[e + 2], m->ev[e + 3]);
+        }
+        out->ms_total = elapsed(m->ev[2], m->ev[1]);
         out->graph = 0;
     }
     return SAL_OK;
@@ -460,33 +420,17 @@ sal_status enqueue_round(sal_context *ctx, sal_tet_mesh *m, const sal_surface_se
     int64_t *n_dev = rs_n(rs);
     LevelPtrs L = ptrs(m);
     L.n_dev = n_dev;
-    int64_t off[kMaxLevels + 2] = {0};
-    for (int l = 0; l <= kMaxLevels; ++l) off[l + 1] = off[l] + m->cap[l];
-    SAL_HIP(launch_round_begin(rs, ctx->counters, q));
-    for (int l = 0; l <= kMaxLevels; ++l)
-        if (m->cap[l] > 0) SAL_HIP(launch_clear_flags_dev(m->flag[l], n_dev + l, q));
-    for (int l = 0; l <= kMaxLevels; ++l)
-        if (m->cap[l] > 0) SAL_HIP(launch_mark(L, m->g, m->T, l, q));
-    for (int l = 0; l <= kMaxLevels; ++l) {
-        if (m->cap[l] > 0) {
-            CompactSrc src{m->flag[l], nullptr};
-            SAL_HIP(launch_compact_dev(src, n_dev + l, m->cap[l], m->blocks, m->totals + l,
-                                       m->list + off[l], q));
-        } else {
-            SAL_HIP(launch_fill_u64((unsigned long long *)(m->totals + l), 0ull, 1, q));
-        }
-    }
+    int top = 0;
+    while (top < kMaxLevels && m->cap[top + 1] > 0) ++top;
+    SAL_HIP(launch_round_clear(L, top, m->cap, ctx->counters, nullptr, rs, q));
+    SAL_HIP(launch_mark(L, m->g, m->T, top, m->cap, q));
+    SAL_HIP(launch_compact_levels(L, top, m->cap, 0xff, m->blocks, m->totals, nullptr, nullptr, m->list, q));
     SAL_HIP(launch_plan(rs, m->totals, q));
-    for (int l = kMaxLevels - 1; l >= 0; --l)
-        if (m->cap[l] > 0 && m->cap[l + 1] > 0)
-            SAL_HIP(launch_split_dev(L, m->g, m->T, l, m->list + off[l], m->totals, rs, m->cen[0],
-                                     m->cen[1], m->cen[2], q));
+    SAL_HIP(launch_split_dev(L, m->g, m->T, m->list, m->totals, rs, m->cen[0], m->cen[1], m->cen[2], q));
     sal_status st = enqueue_label_on(ctx, set, kid_cap, rs_n_kids(rs), m->cen[0], m->cen[1],
                                      m->cen[2], opt, m->lab_scratch, nullptr, nullptr, q);
     if (st != SAL_OK) return st;
-    for (int l = kMaxLevels - 1; l >= 0; --l)
-        if (m->cap[l] > 0 && m->cap[l + 1] > 0)
-            SAL_HIP(launch_commit(rs, m->totals, l, m->lab_scratch, m->label[l + 1], q));
+    SAL_HIP(launch_commit(L, rs, m->totals, m->lab_scratch, q));
     SAL_HIP(launch_round_end(rs, ctx->counters, q));
     return SAL_OK;
 }
@@ -512,11 +456,9 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
         return st;
     const int64_t kid_cap = std::min(m->cen_cap, m->lab_cap);
     if ((st = ensure_label_scratch(ctx, set, kid_cap)) != SAL_OK) return st;
-    int64_t list_need = 0, blocks_need = 1;
-    for (int l = 0; l <= kMaxLevels; ++l) {
-        list_need += m->cap[l];
-        blocks_need = std::max<int64_t>(blocks_need, compact_blocks(m->cap[l]) + 1);
-    }
+    int64_t list_need = 0;
+    for (int l = 0; l <= kMaxLevels; ++l) list_need += m->cap[l];
+    const int64_t blocks_need = compact_level_blocks(m->cap, kMaxLevels);
     if ((st = ensure_buf(m, &m->list, &m->list_cap, list_need, s)) != SAL_OK) return st;
     if ((st = ensure_buf(m, &m->blocks, &m->blocks_cap, blocks_need, s)) != SAL_OK) return st;
     if (!m->rs && mesh_malloc(m, &m->rs, 1) != hipSuccess)
@@ -739,11 +681,10 @@ void sal_tet_mesh_destroy(sal_tet_mesh *m) {
         drop(m->vmask[l]);
     }
     for (auto *c : m->cen) drop(c);
-    for (auto *p : m->mid_xyz) drop(p);
     sal::smooth_cache_free(m->smooth, 0);
     void *more[] = {m->list,      m->blocks,    m->totals,    m->lab_scratch, m->conf_ids, m->conf_labels,
-                    m->conf_keys, m->conf_xyz,  m->node0,     m->mid_masks,   m->mid_key,  m->mid_slot,
-                    m->new_list,  m->new_masks, m->n_new,     m->tkeys,       m->tmasks,   m->rs};
+                    m->conf_keys, m->conf_xyz,  m->node0,     m->mid_slot,
+                    m->new_slot,  m->new_masks, m->n_new,     m->tkeys,       m->tmasks,   m->rs};
     for (void *p : more) drop(p);
     if (m->round_graph) (void)hipGraphExecDestroy(m->round_graph);
     for (auto &e : m->ev)

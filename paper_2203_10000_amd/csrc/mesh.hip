@@ -51,44 +51,43 @@ __global__ void k_lattice_centroids(LatticeGeom g, int64_t n0, float *__restrict
     centroid(g, 0, q, c, cx[i], cy[i], cz[i]);
 }
 
-// The leaf containing the level-l tetrahedron (c, q): its (level, index), or
-// level -1 when (c, q) is itself refined (then its descendants are leaves).
+// The leaf containing the level-LV tetrahedron (c, q): its (level, index), or
+// level -1 when (c, q) is itself refined (then its descendants are leaves).  The
+// level is a template argument so that the chain of parents stays in registers.
+template <int LV>
 __device__ __forceinline__ void resolve(const LevelPtrs &L, const LatticeGeom &g,
-                                        const ChildTables &T, int l, int q, const int64_t c[3],
+                                        const ChildTables &T, int q, const int64_t c[3],
                                         int &lv_out, int64_t &idx_out) {
-    int qa[kMaxLevels + 1];
-    int64_t ca[kMaxLevels + 1][3];
-    int rank[kMaxLevels + 1];
-    qa[l] = q;
-    ca[l][0] = c[0]; ca[l][1] = c[1]; ca[l][2] = c[2];
-    for (int lv = l; lv > 0; --lv) {
+    int rank[LV + 1];
+    int qa = q;
+    int64_t x = c[0], y = c[1], z = c[2];
+#pragma unroll
+    for (int lv = LV; lv > 0; --lv) {
         int p0, p1, p2;
-        perm_of(qa[lv], p0, p1, p2);
-        int w[3];
-        w[p0] = 3; w[p1] = 2; w[p2] = 1;
-        int U[3];
-        int dcode = 0;
-        for (int a = 0; a < 3; ++a) {
-            const int d = (int)(ca[lv][a] & 1);
-            U[a] = 4 * d + w[a];
-            dcode |= d << a;
-            ca[lv - 1][a] = ca[lv][a] >> 1;
-        }
+        perm_of(qa, p0, p1, p2);
+        // U of each axis: 4 (c & 1) + 3, 2 or 1 by its place in the permutation
+        auto weight = [&](int a) { return p0 == a ? 3 : p1 == a ? 2 : 1; };
+        const int dx = (int)(x & 1), dy = (int)(y & 1), dz = (int)(z & 1);
+        const int ux = 4 * dx + weight(0), uy = 4 * dy + weight(1), uz = 4 * dz + weight(2);
         // axes in decreasing U
-        int s0 = 0, s1 = 1, s2 = 2, tmp;
-        if (U[s1] > U[s0]) { tmp = s0; s0 = s1; s1 = tmp; }
-        if (U[s2] > U[s1]) { tmp = s1; s1 = s2; s2 = tmp; }
-        if (U[s1] > U[s0]) { tmp = s0; s0 = s1; s1 = tmp; }
-        qa[lv - 1] = q_of(s0, s1, s2);
-        rank[lv] = T.rank[qa[lv - 1]][dcode][qa[lv]];
+        const int s0 = ux > uy ? (ux > uz ? 0 : 2) : (uy > uz ? 1 : 2);
+        const int s2 = ux < uy ? (ux < uz ? 0 : 2) : (uy < uz ? 1 : 2);
+        const int parent = q_of(s0, 3 - s0 - s2, s2);
+        rank[lv] = T.rank[parent][dx | dy << 1 | dz << 2][qa];
+        qa = parent;
+        x >>= 1;
+        y >>= 1;
+        z >>= 1;
     }
-    int64_t idx = ((ca[0][2] * g.cells[1] + ca[0][1]) * g.cells[0] + ca[0][0]) * 6 + qa[0];
-    for (int lv = 0;; ++lv) {
+    int64_t idx = ((z * g.cells[1] + y) * g.cells[0] + x) * 6 + qa;
+#pragma unroll
+    for (int lv = 0; lv <= LV; ++lv) {
         const int32_t ch = L.child[lv][idx];
         if (ch < 0) { lv_out = lv; idx_out = idx; return; }
-        if (lv == l) { lv_out = -1; idx_out = -1; return; }
-        idx = 8 * (int64_t)ch + rank[lv + 1];
+        if (lv < LV) idx = 8 * (int64_t)ch + rank[lv + 1];
     }
+    lv_out = -1;
+    idx_out = -1;
 }
 
 // Section 2.1.3 (Fig. 3): a leaf is on a tissue boundary when a leaf sharing a
@@ -96,49 +95,72 @@ __device__ __forceinline__ void resolve(const LevelPtrs &L, const LatticeGeom &g
 // its four faces at the same level; when the other side is a leaf (or lies in
 // a coarser leaf) with another label, both are flagged.  When the other side
 // is finer, its leaves find this one the same way, so every pair is seen.
-__device__ __forceinline__ int64_t level_n(const LevelPtrs &L, int l) {
-    return L.n_dev ? L.n_dev[l] : L.n[l];
-}
-
-__device__ void mark_one(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
-                         int64_t i) {
-    if (L.child[l][i] >= 0) return;
-    const int32_t lab = L.label[l][i];
+template <int LV>
+__device__ __forceinline__ void mark_one(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T,
+                                         int64_t i) {
+    if (L.child[LV][i] >= 0) return;
+    const int32_t lab = L.label[LV][i];
     int q, lk;
     int64_t c[3];
-    split_key(entry_key(L, g, l, i), lk, q, c);
+    split_key(entry_key(L, g, LV, i), lk, q, c);
     int p0, p1, p2;
     perm_of(q, p0, p1, p2);
-    const int64_t lim[3] = {(int64_t)g.cells[0] << l, (int64_t)g.cells[1] << l,
-                            (int64_t)g.cells[2] << l};
+    const int64_t lim[3] = {(int64_t)g.cells[0] << LV, (int64_t)g.cells[1] << LV, (int64_t)g.cells[2] << LV};
     bool mine = false;
+#pragma unroll
     for (int f = 0; f < 4; ++f) {
-        int64_t nc[3] = {c[0], c[1], c[2]};
-        int nq;
-        if (f == 0) { nc[p0] += 1; nq = q_of(p1, p2, p0); }
-        else if (f == 1) { nq = q_of(p1, p0, p2); }
-        else if (f == 2) { nq = q_of(p0, p2, p1); }
-        else { nc[p2] -= 1; nq = q_of(p2, p0, p1); }
+        int64_t nc[3];
+        for (int a = 0; a < 3; ++a)
+            nc[a] = c[a] + (f == 0 && a == p0 ? 1 : 0) - (f == 3 && a == p2 ? 1 : 0);
+        const int nq = f == 0 ? q_of(p1, p2, p0) : f == 1 ? q_of(p1, p0, p2)
+                     : f == 2 ? q_of(p0, p2, p1) : q_of(p2, p0, p1);
         if (nc[0] < 0 || nc[1] < 0 || nc[2] < 0 || nc[0] >= lim[0] || nc[1] >= lim[1] ||
             nc[2] >= lim[2])
             continue;   // domain boundary
         int lv;
         int64_t j;
-        resolve(L, g, T, l, nq, nc, lv, j);
+        resolve<LV>(L, g, T, nq, nc, lv, j);
         if (lv < 0) continue;
         if (L.label[lv][j] != lab) {
             mine = true;
             L.flag[lv][j] = 1;
         }
     }
-    if (mine) L.flag[l][i] = 1;
+    if (mine) L.flag[LV][i] = 1;
 }
 
-__global__ void k_mark(LevelPtrs L, LatticeGeom g, ChildTables T, int l) {
-    const int64_t n = level_n(L, l);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        mark_one(L, g, T, l, i);
+// Bound by the dependent loads of the neighbours' chains.  All levels in one launch.
+__global__ void k_mark(LevelPtrs L, LatticeGeom g, ChildTables T, LevelSpans r) {
+    int64_t i;
+    const int l = span_level(r, i);
+    if (i >= (L.n_dev ? L.n_dev[l] : r.n[l])) return;
+    static_assert(kMaxLevels == 3, "one instance a level");
+    if (l == 0) mark_one<0>(L, g, T, i);
+    else if (l == 1) mark_one<1>(L, g, T, i);
+    else if (l == 2) mark_one<2>(L, g, T, i);
+    else mark_one<3>(L, g, T, i);
+}
+
+constexpr int kClearFlags = 16;   // flags a thread clears
+
+__global__ void k_round_clear(LevelPtrs L, LevelSpans r, unsigned long long *__restrict__ counters,
+                              unsigned long long *__restrict__ n_new, RoundState *__restrict__ rs) {
+    const int t = threadIdx.x;
+    if (blockIdx.x == 0) {
+        if (t < kNumCounters) counters[t] = 0ull;
+        if (t < kMaxLevels && n_new) n_new[t] = 0ull;
+        if (t == 0 && rs) rs->n_kids = 0;
+    }
+    int64_t i;
+    const int l = span_level(r, i);
+    i *= kClearFlags;
+    const int64_t n = L.n_dev ? L.n_dev[l] : r.n[l];
+    uint8_t *f = L.flag[l] + i;
+    if (i + kClearFlags <= n && ((uintptr_t)f & 15u) == 0) {
+        *(uint4 *)f = make_uint4(0u, 0u, 0u, 0u);
+    } else {
+        for (int j = 0; j < kClearFlags && i + j < n; ++j) f[j] = 0;
+    }
 }
 
 // ------------------------------------------------------------- compaction
@@ -193,10 +215,8 @@ __device__ __forceinline__ uint32_t pred_bits(const CompactSrc &s, int64_t first
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_count(CompactSrc s, int64_t n,
-                                                        const int64_t *__restrict__ n_dev,
                                                         int64_t *__restrict__ block_counts) {
     __shared__ int red[kScanThreads];
-    if (n_dev) n = *n_dev;
     const int64_t first = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     red[threadIdx.x] = first < n ? __popc(pred_bits(s, first, n)) : 0;
     __syncthreads();
@@ -242,9 +262,11 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t *__restrict__ coun
 struct CompactLevels {
     CompactSrc src[kMaxLevels + 1];
     int64_t n[kMaxLevels + 1];
+    const int64_t *n_dev;   // when set, the sizes (n bounds them)
     int64_t tile0[kMaxLevels + 2];
     int top;
 
+    __device__ __forceinline__ int64_t size(int l) const { return n_dev ? n_dev[l] : n[l]; }
     __device__ __forceinline__ int level(int64_t tile) const {
         int l = 0;
         while (l < top && tile >= tile0[l + 1]) ++l;
@@ -257,7 +279,8 @@ __global__ __launch_bounds__(kScanThreads) void k_count_levels(CompactLevels c,
     __shared__ int wave_total[kScanThreads / 64];
     const int l = c.level(blockIdx.x);
     const int64_t first = ((int64_t)blockIdx.x - c.tile0[l]) * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int v = first < c.n[l] ? __popc(pred_bits(c.src[l], first, c.n[l])) : 0;
+    const int64_t n = c.size(l);
+    int v = first < n ? __popc(pred_bits(c.src[l], first, n)) : 0;
     for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
     if ((threadIdx.x & 63u) == 0) wave_total[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -283,8 +306,10 @@ __global__ __launch_bounds__(1024) void k_scan_levels(CompactLevels c, int64_t *
     if (t == kMaxLevels + 1 && extra) v = (int64_t)*extra;
     if (t <= kMaxLevels + 1) {
         totals[t] = v;
-        host_words[t] = v;
-        __threadfence_system();
+        if (host_words) {
+            host_words[t] = v;
+            __threadfence_system();
+        }
     }
 }
 
@@ -328,17 +353,16 @@ __device__ __forceinline__ void scatter_tile(const CompactSrc &s, int64_t n, int
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scatter(CompactSrc s, int64_t n,
-                                                          const int64_t *__restrict__ n_dev,
                                                           const int64_t *__restrict__ offsets,
                                                           int32_t *__restrict__ out) {
-    scatter_tile(s, n_dev ? *n_dev : n, blockIdx.x, offsets[blockIdx.x], out);
+    scatter_tile(s, n, blockIdx.x, offsets[blockIdx.x], out);
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scatter_levels(CompactLevels c,
                                                                  const int64_t *__restrict__ offsets,
                                                                  int32_t *__restrict__ out) {
     const int l = c.level(blockIdx.x);
-    scatter_tile(c.src[l], c.n[l], (int64_t)blockIdx.x - c.tile0[l], offsets[blockIdx.x], out);
+    scatter_tile(c.src[l], c.size(l), (int64_t)blockIdx.x - c.tile0[l], offsets[blockIdx.x], out);
 }
 
 // Section 2.1.2: each listed leaf of level l becomes 8 level-(l+1) tetrahedra
@@ -421,34 +445,6 @@ __global__ void k_elem_from_nodes0(LatticeGeom g, int64_t n0,
     label0[i] = mask_label(surf, m);
 }
 
-// The six edge midpoints of every listed level-l leaf (edges 01, 02, 03, 12,
-// 13, 23), in millimetres, into the labeling scratch: origin + h 2^-(l+1)
-// (X_a + X_b), products and sums rounded once in double, then to float.
-__global__ void k_midpoints(LevelPtrs L, LatticeGeom g, int l, const int32_t *__restrict__ list,
-                            int64_t count, float *__restrict__ mx, float *__restrict__ my,
-                            float *__restrict__ mz, uint64_t *__restrict__ mkey) {
-    const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (jj >= count * 6) return;
-    const int64_t j = jj / 6;
-    const int e = (int)(jj - j * 6);
-    int q, lk;
-    int64_t c[3];
-    split_key(entry_key(L, g, l, list[j]), lk, q, c);
-    int64_t X[4][3];
-    kuhn_vertices(q, c, X);
-    const int ea[6] = {0, 0, 0, 1, 1, 2}, eb[6] = {1, 2, 3, 2, 3, 3};
-    const double hl = ldexp(g.h, -(l + 1));
-    float *out[3] = {mx, my, mz};
-    for (int a = 0; a < 3; ++a)
-        out[a][jj] = lattice_coord(g.origin[a], hl, (double)(X[ea[e]][a] + X[eb[e]][a]));
-    // node key: coordinates on the level-kMaxLevels grid, 21 bits each
-    const int sh = kMaxLevels - (l + 1);
-    uint64_t key = 0;
-    for (int a = 0; a < 3; ++a)
-        key = (key << 21) | (uint64_t)((X[ea[e]][a] + X[eb[e]][a]) << sh);
-    mkey[jj] = key;
-}
-
 // ------------------------------------------------------------ node table
 // Open-addressing hash table of the nodes labeled after a split (keys on the
 // finest grid, linear probing), so a node shared by several split leaves, or
@@ -465,64 +461,78 @@ __device__ __forceinline__ uint64_t node_hash(uint64_t k) {
     return k;
 }
 
-// Inserts every midpoint key; the thread whose insert creates the entry lists
-// the midpoint as a new node.  slot[jj] = the key's table slot.
-__global__ void k_node_insert(const uint64_t *__restrict__ mkey, int64_t n,
-                              unsigned long long *__restrict__ tkeys, int64_t cap,
-                              int64_t *__restrict__ slot, int32_t *__restrict__ new_list,
-                              unsigned long long *__restrict__ n_new) {
+// The six edge midpoints of every listed level-l leaf (edges 01, 02, 03, 12, 13,
+// 23) into the table; those that were not in it are listed for labeling, with
+// their coordinates: origin + h 2^-(l+1) (X_a + X_b), products and sums rounded
+// once in double, then to float.  Most are there already (a node has some six
+// leaves around it), so an entry is read before it is claimed.
+__global__ void k_midpoints(LevelPtrs L, LatticeGeom g, int l, const int32_t *__restrict__ list,
+                            int64_t count, unsigned long long *__restrict__ tkeys, int64_t cap,
+                            int64_t *__restrict__ slot, int64_t *__restrict__ new_slot,
+                            unsigned long long *__restrict__ n_new, float *__restrict__ x,
+                            float *__restrict__ y, float *__restrict__ z) {
     const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (jj >= n) return;
-    const uint64_t key = mkey[jj];
+    const bool live = jj < count * 6;
+    const int64_t j = live ? jj / 6 : 0;
+    const int e = (int)(live ? jj - j * 6 : 0);
+    int q, lk;
+    int64_t c[3];
+    split_key(entry_key(L, g, l, list[j]), lk, q, c);
+    int64_t X[4][3];
+    kuhn_vertices(q, c, X);
+    int64_t m[3];   // X_a + X_b
+    for (int a = 0; a < 3; ++a) {
+        const int64_t va = e < 3 ? X[0][a] : e < 5 ? X[1][a] : X[2][a];
+        const int64_t vb = e == 0 ? X[1][a] : e == 1 || e == 3 ? X[2][a] : X[3][a];
+        m[a] = va + vb;
+    }
+    // key: coordinates on the level-kMaxLevels grid, 21 bits each
+    const int sh = kMaxLevels - (l + 1);
+    const uint64_t key = (uint64_t)(m[0] << sh) << 42 | (uint64_t)(m[1] << sh) << 21 | (uint64_t)(m[2] << sh);
+    int64_t at = -1;   // stays where the table is full (the host keeps it at most half full)
+    bool added = false;
     uint64_t h = node_hash(key) & (uint64_t)(cap - 1);
-    for (int64_t probe = 0; probe < cap; ++probe) {
-        const unsigned long long prev = atomicCAS(&tkeys[h], kEmptyKey, key);
-        if (prev == kEmptyKey) {
-            slot[jj] = (int64_t)h;
-            new_list[atomicAdd(n_new, 1ull)] = (int32_t)jj;
-            return;
-        }
-        if (prev == key) {
-            slot[jj] = (int64_t)h;
-            return;
+    for (int64_t probe = 0; live && probe < cap; ++probe) {
+        unsigned long long cur = __hip_atomic_load(&tkeys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (cur == kEmptyKey) cur = atomicCAS(&tkeys[h], kEmptyKey, key);
+        if (cur == kEmptyKey || cur == key) {
+            added = cur == kEmptyKey;
+            at = (int64_t)h;
+            break;
         }
         h = (h + 1) & (uint64_t)(cap - 1);
     }
-    slot[jj] = -1;   // table full (the host keeps it at most half full)
+    if (live) slot[jj] = at;
+    const unsigned long long mask = __ballot(added);
+    if (mask == 0) return;
+    const int lane = (int)(threadIdx.x & 63u), leader = __ffsll((unsigned long long)mask) - 1;
+    unsigned long long base = 0;
+    if (lane == leader) base = atomicAdd(n_new, (unsigned long long)__popcll(mask));
+    base = __shfl(base, leader, 64);
+    if (!added) return;
+    const int64_t t = (int64_t)base + __popcll(mask & ((1ull << lane) - 1ull));
+    const double hl = ldexp(g.h, -(l + 1));
+    new_slot[t] = at;
+    x[t] = lattice_coord(g.origin[0], hl, (double)m[0]);
+    y[t] = lattice_coord(g.origin[1], hl, (double)m[1]);
+    z[t] = lattice_coord(g.origin[2], hl, (double)m[2]);
 }
 
-// The new nodes' coordinates, compacted for labeling.
-__global__ void k_node_gather(const int32_t *__restrict__ new_list,
-                              const unsigned long long *__restrict__ n_new,
-                              const float *__restrict__ mx, const float *__restrict__ my,
-                              const float *__restrict__ mz, float *__restrict__ x,
-                              float *__restrict__ y, float *__restrict__ z) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)*n_new) return;
-    const int32_t jj = new_list[t];
-    x[t] = mx[jj];
-    y[t] = my[jj];
-    z[t] = mz[jj];
-}
-
-__global__ void k_node_store(const int32_t *__restrict__ new_list,
+__global__ void k_node_store(const int64_t *__restrict__ new_slot,
                              const unsigned long long *__restrict__ n_new,
-                             const int64_t *__restrict__ slot,
                              const unsigned long long *__restrict__ masks,
                              unsigned long long *__restrict__ tmasks) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)*n_new) return;
-    tmasks[slot[new_list[t]]] = masks[t];
+    tmasks[new_slot[t]] = masks[t];
 }
 
-// Midpoint masks from the table, in midpoint order.
-__global__ void k_node_fetch(const int64_t *__restrict__ slot, int64_t n,
-                             const unsigned long long *__restrict__ tmasks,
-                             unsigned long long *__restrict__ out) {
-    const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (jj >= n) return;
-    const int64_t sl = slot[jj];
-    out[jj] = sl >= 0 ? tmasks[sl] : 0ull;
+__global__ void k_report(const unsigned long long *__restrict__ counters,
+                         const unsigned long long *__restrict__ n_new, int64_t *__restrict__ host_words) {
+    const int t = threadIdx.x;
+    if (t == 0) host_words[0] = (int64_t)counters[kCntRecheck];
+    else if (t <= kMaxLevels) host_words[t] = n_new ? (int64_t)n_new[t - 1] : 0;
+    __threadfence_system();
 }
 
 // Re-inserts the entries of an old table into a larger one.
@@ -551,7 +561,8 @@ __global__ void k_child_masks(LevelPtrs L, LatticeGeom g, int l, const int32_t *
                               int64_t count, int64_t base_block,
                               const unsigned long long *__restrict__ node0,
                               const unsigned long long *__restrict__ vmask_parent,
-                              const unsigned long long *__restrict__ mid_masks,
+                              const int64_t *__restrict__ slot,
+                              const unsigned long long *__restrict__ tmasks,
                               unsigned long long *__restrict__ vmask_child,
                               const SurfaceDev *__restrict__ surf) {
     const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -573,7 +584,8 @@ __global__ void k_child_masks(LevelPtrs L, LatticeGeom g, int l, const int32_t *
     const int ea[6] = {0, 0, 0, 1, 1, 2}, eb[6] = {1, 2, 3, 2, 3, 3};
     for (int e = 0; e < 6; ++e) {
         for (int a = 0; a < 3; ++a) N[4 + e][a] = X[ea[e]][a] + X[eb[e]][a];
-        M[4 + e] = mid_masks[6 * j + e];
+        const int64_t sl = slot[6 * j + e];
+        M[4 + e] = sl >= 0 ? tmasks[sl] : 0ull;
     }
     const int64_t o = 8 * (base_block + j) + r;
     int cq, clk;
@@ -595,19 +607,7 @@ __global__ void k_child_masks(LevelPtrs L, LatticeGeom g, int l, const int32_t *
 // ------------------------------------------------- captured refine round
 // These kernels take every size from RoundState or the compaction totals, so
 // the same launch sequence serves every round; fixed grids stride over them.
-constexpr int kDevGrid = 2048;
-
-__global__ void k_round_begin(RoundState *rs, unsigned long long *counters) {
-    const int t = threadIdx.x;
-    if (t < kNumCounters) counters[t] = 0ull;
-    if (t == 0) rs->n_kids = 0;
-}
-
-__global__ void k_clear_flags_dev(uint8_t *__restrict__ flag, const int64_t *__restrict__ n_dev) {
-    const int64_t n = *n_dev;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) flag[i] = 0;
-}
+constexpr int kDevGrid = 1024;
 
 // One thread: sizes of this round's splits (levels deepest first, as the
 // host-driven round orders them), capacity checks, new level sizes.
@@ -642,27 +642,35 @@ __global__ void k_plan(RoundState *rs, const int64_t *__restrict__ totals) {
     st.n_labeled = run;
 }
 
-__global__ void k_split_dev(LevelPtrs L, LatticeGeom g, ChildTables T, int l,
-                            const int32_t *__restrict__ list, const int64_t *__restrict__ totals,
-                            const RoundState *__restrict__ rs, float *__restrict__ cx,
-                            float *__restrict__ cy, float *__restrict__ cz) {
+// The levels' lists lie one behind the other; a level has gridDim.y = its number.
+__device__ __forceinline__ int64_t list_offset(const int64_t *__restrict__ totals, int l) {
+    int64_t off = 0;
+    for (int k = 0; k < l; ++k) off += totals[k];
+    return off;
+}
+
+__global__ void k_split_dev(LevelPtrs L, LatticeGeom g, ChildTables T, const int32_t *__restrict__ list,
+                            const int64_t *__restrict__ totals, const RoundState *__restrict__ rs,
+                            float *__restrict__ cx, float *__restrict__ cy, float *__restrict__ cz) {
     if (rs->status) return;
+    const int l = (int)blockIdx.y;
     const int64_t n = 8 * totals[l];
     const int64_t base_block = rs->base_block[l];
     const int64_t off = rs->kid_off[l];
+    const int32_t *mine = list + list_offset(totals, l);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; jj < n; jj += stride)
-        split_one(L, g, T, l, list, jj, base_block, cx + off, cy + off, cz + off);
+        split_one(L, g, T, l, mine, jj, base_block, cx + off, cy + off, cz + off);
 }
 
-// Copies the children's labels from the labeling scratch into level l + 1.
-__global__ void k_commit(const RoundState *__restrict__ rs, const int64_t *__restrict__ totals,
-                         int l, const int32_t *__restrict__ scratch_labels,
-                         int32_t *__restrict__ level_labels) {
+// Copies the children's labels from the labeling scratch into their levels.
+__global__ void k_commit(LevelPtrs L, const RoundState *__restrict__ rs, const int64_t *__restrict__ totals,
+                         const int32_t *__restrict__ scratch_labels) {
     if (rs->status) return;
+    const int l = (int)blockIdx.y;
     const int64_t n = 8 * totals[l];
     const int32_t *src = scratch_labels + rs->kid_off[l];
-    int32_t *dst = level_labels + 8 * rs->base_block[l];
+    int32_t *dst = L.label[l + 1] + 8 * rs->base_block[l];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride)
         dst[j] = src[j];
@@ -728,41 +736,25 @@ hipError_t launch_elem_from_nodes0(const LatticeGeom &g, int64_t n0,
 }
 
 hipError_t launch_midpoints(const LevelPtrs &L, const LatticeGeom &g, int l, const int32_t *list,
-                            int64_t count, float *mx, float *my, float *mz, uint64_t *mkey,
+                            int64_t count, unsigned long long *tkeys, int64_t cap, int64_t *slot,
+                            int64_t *new_slot, unsigned long long *n_new, float *x, float *y, float *z,
                             hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    k_midpoints<<<grid_for(count * 6, 256), 256, 0, s>>>(L, g, l, list, count, mx, my, mz, mkey);
+    k_midpoints<<<grid_for(count * 6, 256), 256, 0, s>>>(L, g, l, list, count, tkeys, cap, slot, new_slot,
+                                                        n_new, x, y, z);
     return hipGetLastError();
 }
 
-hipError_t launch_node_insert(const uint64_t *mkey, int64_t n, unsigned long long *tkeys,
-                              int64_t cap, int64_t *slot, int32_t *new_list,
-                              unsigned long long *n_new, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    k_node_insert<<<grid_for(n, 256), 256, 0, s>>>(mkey, n, tkeys, cap, slot, new_list, n_new);
-    return hipGetLastError();
-}
-
-hipError_t launch_node_gather(const int32_t *new_list, const unsigned long long *n_new,
-                              int64_t n_cap, const float *mx, const float *my, const float *mz,
-                              float *x, float *y, float *z, hipStream_t s) {
+hipError_t launch_node_store(const int64_t *new_slot, const unsigned long long *n_new, int64_t n_cap,
+                             const unsigned long long *masks, unsigned long long *tmasks, hipStream_t s) {
     if (n_cap <= 0) return hipSuccess;
-    k_node_gather<<<grid_for(n_cap, 256), 256, 0, s>>>(new_list, n_new, mx, my, mz, x, y, z);
+    k_node_store<<<grid_for(n_cap, 256), 256, 0, s>>>(new_slot, n_new, masks, tmasks);
     return hipGetLastError();
 }
 
-hipError_t launch_node_store(const int32_t *new_list, const unsigned long long *n_new,
-                             int64_t n_cap, const int64_t *slot, const unsigned long long *masks,
-                             unsigned long long *tmasks, hipStream_t s) {
-    if (n_cap <= 0) return hipSuccess;
-    k_node_store<<<grid_for(n_cap, 256), 256, 0, s>>>(new_list, n_new, slot, masks, tmasks);
-    return hipGetLastError();
-}
-
-hipError_t launch_node_fetch(const int64_t *slot, int64_t n, const unsigned long long *tmasks,
-                             unsigned long long *out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    k_node_fetch<<<grid_for(n, 256), 256, 0, s>>>(slot, n, tmasks, out);
+hipError_t launch_report(const unsigned long long *counters, const unsigned long long *n_new,
+                         int64_t *host_words, hipStream_t s) {
+    k_report<<<1, 64, 0, s>>>(counters, n_new, host_words);
     return hipGetLastError();
 }
 
@@ -778,12 +770,12 @@ hipError_t launch_child_masks(const LevelPtrs &L, const LatticeGeom &g, int l,
                               const int32_t *list, int64_t count, int64_t base_block,
                               const unsigned long long *node0,
                               const unsigned long long *vmask_parent,
-                              const unsigned long long *mid_masks,
+                              const int64_t *slot, const unsigned long long *tmasks,
                               unsigned long long *vmask_child, const SurfaceDev *surf,
                               hipStream_t s) {
     if (count <= 0) return hipSuccess;
     k_child_masks<<<grid_for(count * 8, 256), 256, 0, s>>>(L, g, l, list, count, base_block, node0,
-                                                          vmask_parent, mid_masks, vmask_child,
+                                                          vmask_parent, slot, tmasks, vmask_child,
                                                           surf);
     return hipGetLastError();
 }
@@ -795,14 +787,28 @@ hipError_t launch_lattice_centroids(const LatticeGeom &g, int64_t n0, float *cx,
     return hipGetLastError();
 }
 
-hipError_t launch_mark(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
-                       hipStream_t s) {
-    if (L.n_dev) {
-        k_mark<<<kDevGrid, 256, 0, s>>>(L, g, T, l);
-        return hipGetLastError();
+hipError_t launch_round_clear(const LevelPtrs &L, int top, const int64_t *size, unsigned long long *counters,
+                              unsigned long long *n_new, RoundState *rs, hipStream_t s) {
+    LevelSpans r{};
+    r.top = top;
+    int64_t per[kMaxLevels + 1] = {}, nb;
+    for (int l = 0; l <= top; ++l) {
+        r.n[l] = size[l];
+        per[l] = (size[l] + kClearFlags - 1) / kClearFlags;
     }
-    if (L.n[l] <= 0) return hipSuccess;
-    k_mark<<<grid_for(L.n[l], 256), 256, 0, s>>>(L, g, T, l);
+    r = with_blocks(r, per, 1, &nb);
+    k_round_clear<<<(unsigned)nb, 256, 0, s>>>(L, r, counters, n_new, rs);
+    return hipGetLastError();
+}
+
+hipError_t launch_mark(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int top,
+                       const int64_t *size, hipStream_t s) {
+    LevelSpans r{};
+    r.top = top;
+    int64_t per[kMaxLevels + 1] = {}, nb;
+    for (int l = 0; l <= top; ++l) per[l] = r.n[l] = size[l];
+    r = with_blocks(r, per, 1, &nb);
+    k_mark<<<(unsigned)nb, 256, 0, s>>>(L, g, T, r);
     return hipGetLastError();
 }
 
@@ -812,25 +818,26 @@ hipError_t launch_compact(const CompactSrc &src, int64_t n, int64_t *block_scrat
                           int64_t *total, int32_t *out, hipStream_t s) {
     const int64_t nb = compact_blocks(n);
     if (nb <= 0) return launch_fill_u64((unsigned long long *)total, 0ull, 1, s);
-    k_count<<<(unsigned)nb, kScanThreads, 0, s>>>(src, n, nullptr, block_scratch);
+    k_count<<<(unsigned)nb, kScanThreads, 0, s>>>(src, n, block_scratch);
     k_scan_blocks<<<1, 1024, 0, s>>>(block_scratch, nb, total);
-    k_scatter<<<(unsigned)nb, kScanThreads, 0, s>>>(src, n, nullptr, block_scratch, out);
+    k_scatter<<<(unsigned)nb, kScanThreads, 0, s>>>(src, n, block_scratch, out);
     return hipGetLastError();
 }
 
-int64_t compact_level_blocks(const LevelPtrs &L, int top) {
+int64_t compact_level_blocks(const int64_t *size, int top) {
     int64_t nb = 0;
-    for (int l = 0; l <= top; ++l) nb += compact_blocks(L.n[l]);
+    for (int l = 0; l <= top; ++l) nb += compact_blocks(size[l]);
     return nb;
 }
 
-hipError_t launch_compact_levels(const LevelPtrs &L, int top, uint8_t mask, int64_t *block_scratch,
-                                 int64_t *totals, const unsigned long long *extra, int64_t *host_words,
-                                 int32_t *out, hipStream_t s) {
+hipError_t launch_compact_levels(const LevelPtrs &L, int top, const int64_t *size, uint8_t mask,
+                                 int64_t *block_scratch, int64_t *totals, const unsigned long long *extra,
+                                 int64_t *host_words, int32_t *out, hipStream_t s) {
     CompactLevels c{};
     c.top = top;
+    c.n_dev = L.n_dev;
     for (int l = 0; l <= kMaxLevels; ++l) {
-        c.n[l] = l <= top ? L.n[l] : 0;
+        c.n[l] = l <= top ? size[l] : 0;
         c.src[l] = mask ? CompactSrc{L.flag[l], nullptr, mask} : CompactSrc{nullptr, L.child[l], 0};
         c.tile0[l + 1] = c.tile0[l] + compact_blocks(c.n[l]);
     }
@@ -841,42 +848,21 @@ hipError_t launch_compact_levels(const LevelPtrs &L, int top, uint8_t mask, int6
     return hipGetLastError();
 }
 
-hipError_t launch_round_begin(RoundState *rs, unsigned long long *counters, hipStream_t s) {
-    k_round_begin<<<1, 64, 0, s>>>(rs, counters);
-    return hipGetLastError();
-}
-
-hipError_t launch_clear_flags_dev(uint8_t *flag, const int64_t *n_dev, hipStream_t s) {
-    k_clear_flags_dev<<<kDevGrid, 256, 0, s>>>(flag, n_dev);
-    return hipGetLastError();
-}
-
-// Tiles for `cap` entries; tiles past the device-side size count nothing.
-hipError_t launch_compact_dev(const CompactSrc &src, const int64_t *n_dev, int64_t cap,
-                              int64_t *block_scratch, int64_t *total, int32_t *out, hipStream_t s) {
-    const int64_t nb = compact_blocks(cap);
-    if (nb <= 0) return launch_fill_u64((unsigned long long *)total, 0ull, 1, s);
-    k_count<<<(unsigned)nb, kScanThreads, 0, s>>>(src, cap, n_dev, block_scratch);
-    k_scan_blocks<<<1, 1024, 0, s>>>(block_scratch, nb, total);
-    k_scatter<<<(unsigned)nb, kScanThreads, 0, s>>>(src, cap, n_dev, block_scratch, out);
-    return hipGetLastError();
-}
-
 hipError_t launch_plan(RoundState *rs, const int64_t *totals, hipStream_t s) {
     k_plan<<<1, 64, 0, s>>>(rs, totals);
     return hipGetLastError();
 }
 
-hipError_t launch_split_dev(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
-                            const int32_t *list, const int64_t *totals, const RoundState *rs,
-                            float *cx, float *cy, float *cz, hipStream_t s) {
-    k_split_dev<<<kDevGrid, 256, 0, s>>>(L, g, T, l, list, totals, rs, cx, cy, cz);
+hipError_t launch_split_dev(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, const int32_t *list,
+                            const int64_t *totals, const RoundState *rs, float *cx, float *cy, float *cz,
+                            hipStream_t s) {
+    k_split_dev<<<dim3(kDevGrid, kMaxLevels), 256, 0, s>>>(L, g, T, list, totals, rs, cx, cy, cz);
     return hipGetLastError();
 }
 
-hipError_t launch_commit(const RoundState *rs, const int64_t *totals, int l,
-                         const int32_t *scratch_labels, int32_t *level_labels, hipStream_t s) {
-    k_commit<<<kDevGrid, 256, 0, s>>>(rs, totals, l, scratch_labels, level_labels);
+hipError_t launch_commit(const LevelPtrs &L, const RoundState *rs, const int64_t *totals,
+                         const int32_t *scratch_labels, hipStream_t s) {
+    k_commit<<<dim3(kDevGrid, kMaxLevels), 256, 0, s>>>(L, rs, totals, scratch_labels);
     return hipGetLastError();
 }
 

@@ -44,6 +44,27 @@ struct RoundState {
     RoundStat stat[kMaxLevels + 1];
 };
 
+// A launch over levels 0..top, usually of the entries [first[l], n[l]) of level l.
+struct LevelSpans {
+    int top;
+    int64_t first[kMaxLevels + 1], n[kMaxLevels + 1];
+    uint32_t block0[kMaxLevels + 2];   // first workgroup (this and `turns` set by with_blocks)
+    int turns;                         // items of a thread
+};
+
+// Workgroups of 256 for per[l] items of level l, a level's first one its own.
+inline LevelSpans with_blocks(LevelSpans r, const int64_t (&per)[kMaxLevels + 1], int turns, int64_t *blocks) {
+    int64_t nb = 0;
+    r.turns = turns;
+    for (int l = 0; l <= kMaxLevels; ++l) {
+        r.block0[l] = (uint32_t)nb;
+        if (l <= r.top) nb += (per[l] + 256 * turns - 1) / (256 * turns);
+    }
+    r.block0[kMaxLevels + 1] = (uint32_t)nb;
+    *blocks = nb;
+    return r;
+}
+
 struct LatticeGeom {
     double origin[3];
     double h;
@@ -66,8 +87,13 @@ struct CompactSrc {
 
 hipError_t launch_lattice_centroids(const LatticeGeom &g, int64_t n0, float *cx, float *cy,
                                     float *cz, hipStream_t s);
-hipError_t launch_mark(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
-                       hipStream_t s);
+// Clears the flags of levels 0..top (size[l] entries, or L.n_dev[l] of them), the
+// label counters, the new nodes' counters (n_new, may be null) and the kids' count
+// (rs, may be null); then marks.
+hipError_t launch_round_clear(const LevelPtrs &L, int top, const int64_t *size, unsigned long long *counters,
+                              unsigned long long *n_new, RoundState *rs, hipStream_t s);
+hipError_t launch_mark(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int top,
+                       const int64_t *size, hipStream_t s);
 int64_t compact_blocks(int64_t n);
 hipError_t launch_compact(const CompactSrc &src, int64_t n, int64_t *block_scratch,
                           int64_t *total, int32_t *out, hipStream_t s);
@@ -75,8 +101,10 @@ hipError_t launch_compact(const CompactSrc &src, int64_t n, int64_t *block_scrat
 // `out`: the leaves, or (mask != 0) the entries with a flag bit of mask.  Writes
 // the levels' totals and the *extra word to totals[0..kMaxLevels + 1] and, once the
 // stream has got there, to the same places of host_words (pinned memory).
-int64_t compact_level_blocks(const LevelPtrs &L, int top);
-hipError_t launch_compact_levels(const LevelPtrs &L, int top, uint8_t mask, int64_t *block_scratch,
+// (Device-sized, with L.n_dev: size[l] bounds a level's entries, host_words is null.)
+int64_t compact_level_blocks(const int64_t *size, int top);
+hipError_t launch_compact_levels(const LevelPtrs &L, int top, const int64_t *size, uint8_t mask,
+                                 int64_t *block_scratch,
                                  int64_t *totals, const unsigned long long *extra, int64_t *host_words,
                                  int32_t *out, hipStream_t s);
 hipError_t launch_split(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
@@ -87,16 +115,12 @@ hipError_t launch_export(const LevelPtrs &L, const LatticeGeom &g, int l, const 
                          float *cx, float *cy, float *cz, hipStream_t s);
 // Device-sized forms for the captured refine round (sizes read from
 // RoundState / compaction totals; fixed grids stride over them).
-hipError_t launch_round_begin(RoundState *rs, unsigned long long *counters, hipStream_t s);
-hipError_t launch_clear_flags_dev(uint8_t *flag, const int64_t *n_dev, hipStream_t s);
-hipError_t launch_compact_dev(const CompactSrc &src, const int64_t *n_dev, int64_t cap,
-                              int64_t *block_scratch, int64_t *total, int32_t *out, hipStream_t s);
 hipError_t launch_plan(RoundState *rs, const int64_t *totals, hipStream_t s);
-hipError_t launch_split_dev(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, int l,
-                            const int32_t *list, const int64_t *totals, const RoundState *rs,
-                            float *cx, float *cy, float *cz, hipStream_t s);
-hipError_t launch_commit(const RoundState *rs, const int64_t *totals, int l,
-                         const int32_t *scratch_labels, int32_t *level_labels, hipStream_t s);
+hipError_t launch_split_dev(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, const int32_t *list,
+                            const int64_t *totals, const RoundState *rs, float *cx, float *cy, float *cz,
+                            hipStream_t s);
+hipError_t launch_commit(const LevelPtrs &L, const RoundState *rs, const int64_t *totals,
+                         const int32_t *scratch_labels, hipStream_t s);
 hipError_t launch_round_end(RoundState *rs, const unsigned long long *counters, hipStream_t s);
 
 // Four-node rule (node enclosure masks).
@@ -105,22 +129,16 @@ hipError_t launch_lattice_nodes(const LatticeGeom &g, int64_t n_nodes, float *x,
 hipError_t launch_elem_from_nodes0(const LatticeGeom &g, int64_t n0,
                                    const unsigned long long *node0, const SurfaceDev *surf,
                                    int32_t *label0, hipStream_t s);
+// Node table (open addressing; keys ~0 = empty; the host keeps it at most half
+// full).  The midpoints of the listed leaves' edges: slot[6 j + e] is the table's
+// place of leaf j's edge e; those not in it before are listed with their
+// coordinates (new_slot, x, y, z; *n_new of them).
 hipError_t launch_midpoints(const LevelPtrs &L, const LatticeGeom &g, int l, const int32_t *list,
-                            int64_t count, float *mx, float *my, float *mz, uint64_t *mkey,
+                            int64_t count, unsigned long long *tkeys, int64_t cap, int64_t *slot,
+                            int64_t *new_slot, unsigned long long *n_new, float *x, float *y, float *z,
                             hipStream_t s);
-// Node table (open addressing; keys ~0 = empty; the host keeps it at most
-// half full).
-hipError_t launch_node_insert(const uint64_t *mkey, int64_t n, unsigned long long *tkeys,
-                              int64_t cap, int64_t *slot, int32_t *new_list,
-                              unsigned long long *n_new, hipStream_t s);
-hipError_t launch_node_gather(const int32_t *new_list, const unsigned long long *n_new,
-                              int64_t n_cap, const float *mx, const float *my, const float *mz,
-                              float *x, float *y, float *z, hipStream_t s);
-hipError_t launch_node_store(const int32_t *new_list, const unsigned long long *n_new,
-                             int64_t n_cap, const int64_t *slot, const unsigned long long *masks,
-                             unsigned long long *tmasks, hipStream_t s);
-hipError_t launch_node_fetch(const int64_t *slot, int64_t n, const unsigned long long *tmasks,
-                             unsigned long long *out, hipStream_t s);
+hipError_t launch_node_store(const int64_t *new_slot, const unsigned long long *n_new, int64_t n_cap,
+                             const unsigned long long *masks, unsigned long long *tmasks, hipStream_t s);
 hipError_t launch_node_rehash(const unsigned long long *okeys, const unsigned long long *omasks,
                               int64_t ocap, unsigned long long *tkeys, unsigned long long *tmasks,
                               int64_t cap, hipStream_t s);
@@ -128,7 +146,7 @@ hipError_t launch_child_masks(const LevelPtrs &L, const LatticeGeom &g, int l,
                               const int32_t *list, int64_t count, int64_t base_block,
                               const unsigned long long *node0,
                               const unsigned long long *vmask_parent,
-                              const unsigned long long *mid_masks,
+                              const int64_t *slot, const unsigned long long *tmasks,
                               unsigned long long *vmask_child, const SurfaceDev *surf,
                               hipStream_t s);
 
@@ -137,13 +155,6 @@ hipError_t launch_child_masks(const LevelPtrs &L, const LatticeGeom &g, int l,
 // hanging edges, bit 6 a node at a quarter point, bit 7 split 1 -> 8.
 // cells_new: one bit per level-0 cell, set for the cells a vertex added to
 // `fresh` touches (both null: the first pass).
-// Every launch covers levels 0..top: of level l the entries [first[l], n[l]).
-struct LevelSpans {
-    int top;
-    int64_t first[kMaxLevels + 1], n[kMaxLevels + 1];
-    uint32_t block0[kMaxLevels + 2];   // first workgroup (this and `turns` set by the launcher)
-    int turns;                         // items of a thread
-};
 hipError_t launch_closure_clear(unsigned long long *fresh, int64_t fcap, uint32_t *cells_new, int64_t cell_words,
                                 hipStream_t s);
 // n_new: accumulated, not cleared.  *overflow counts the keys that found no place.
@@ -207,6 +218,9 @@ hipError_t launch_import_children(const LevelPtrs &L, const LatticeGeom &g, cons
                                   const int32_t *list, int64_t count, const ImportTables &t, ImportFaults *f,
                                   hipStream_t s);
 
+// counters[kCntRecheck] and n_new[0..kMaxLevels) into pinned host memory.
+hipError_t launch_report(const unsigned long long *counters, const unsigned long long *n_new,
+                         int64_t *host_words, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s);
 
