@@ -123,6 +123,7 @@ LabelInst make_inst(const sal_surface_set *set, int64_t n, const float *x, const
     in.rec = set->rec;
     in.surf = set->surf;
     in.ent = set->ent;
+    in.leaf = set->leaf;
     in.x = x;
     in.y = y;
     in.z = z;

@@ -84,12 +84,12 @@ __device__ __forceinline__ PointSum point_surface(const LabelInst &in, const Sur
         return PointSum{0.0, false, 0u, 0u};
     const float p[3] = {x, y, z};
     const TriRec *rec = in.rec + sd.rec_begin;
-    const PatchEntry *ent = in.ent + 4 * sd.node_begin;
+    const LeafBox *leaf = in.leaf + sd.leaf_begin;
     int v;
     for (int i = 0; i < 2; ++i)
-        if (patch::ray_winding(ent, rec, sd, p, i, L, v)) return PointSum{(double)v, false, 0u, 0u};
+        if (patch::ray_winding(leaf, rec, sd, p, i, L, v)) return PointSum{(double)v, false, 0u, 0u};
     int n_near, n_far;
-    if (!patch::sort_patches<true>(ent, p, p, L, n_near, n_far)) {
+    if (!patch::sort_patches(in.ent + 4 * sd.node_begin, p, p, L, n_near, n_far)) {
         // (a list is full only where hundreds of patches share the point)
         n_near = 1;
         n_far = 0;
@@ -285,12 +285,12 @@ __global__ __launch_bounds__(64) void k_label_span(LabelArgs a) {
         v = 0;
     } else {
         const TriRec *rec = in.rec + sd.rec_begin;
-        const PatchEntry *ent = in.ent + 4 * sd.node_begin;
-        if (patch::triangles_near(ent, rec, lo, hi, L, 0, 0) == 0) {
+        const LeafBox *leaf = in.leaf + sd.leaf_begin;
+        if (patch::triangles_near(leaf, sd.n_leaves, rec, lo, hi, L, 0, 0) == 0) {
             float q[3];
             for (int c = 0; c < 3; ++c) q[c] = 0.5f * lo[c] + 0.5f * hi[c];
             int r;
-            if (patch::ray_winding(ent, rec, sd, q, 0, L, r)) v = r;
+            if (patch::ray_winding(leaf, rec, sd, q, 0, L, r)) v = r;
         }
     }
     if (lane == 0) {
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(512) void k_label_pair(LabelArgs a) {
         }
         if (open) {
             const TriRec *rec = in.rec + sd.rec_begin;
-            const PatchEntry *ent = in.ent + 4 * sd.node_begin;
+            const LeafBox *leaf = in.leaf + sd.leaf_begin;
             // the whole wavefront, or aligned runs of lanes, halved while their box
             // meets more triangles than the lists hold
             for (int pos = first, len = 64 / RUNS; pos < end;) {
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(512) void k_label_pair(LabelArgs a) {
                     } else {
                         box_of(mine, px, py, pz, blo, bhi);
                     }
-                    n_cand = patch::triangles_near(ent, rec, blo, bhi, L, 0, patch::kNearTri);
+                    n_cand = patch::triangles_near(leaf, sd.n_leaves, rec, blo, bhi, L, 0, patch::kNearTri);
                     if (n_cand < 0 && len > kSplitMin) {
                         len >>= 1;
                         continue;
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(512) void k_label_pair(LabelArgs a) {
                         float q[3];
                         for (int c = 0; c < 3; ++c)
                             q[c] = fminf(fmaxf(fmaf(bhi[c] - blo[c], frac[i][c], blo[c]), blo[c]), bhi[c]);
-                        known = patch::ray_winding(ent, rec, sd, q, i, L, v);
+                        known = patch::ray_winding(leaf, rec, sd, q, i, L, v);
                         if (known && n_cand > 0) {
                             const T d[3] = {(T)px - (T)q[0], (T)py - (T)q[1], (T)pz - (T)q[2]};
                             T d2 = 0;

@@ -51,6 +51,7 @@ struct sal_surface_set {
     sal::TriRec *rec = nullptr;
     sal::SurfaceDev *surf = nullptr;        // n_surf entries
     sal::PatchEntry *ent = nullptr;         // patch trees of all surfaces
+    sal::LeafBox *leaf = nullptr;           // leaf boxes of all surfaces
     float lo[3] = {}, hi[3] = {};           // box of all surfaces
     std::vector<sal::SurfaceDev> host_table;
     bool balls_ready = false;              // ball_w of every surface known

@@ -60,13 +60,24 @@ constexpr int kLeafTri = 64;
 constexpr double kCapMargin = 0.02;
 
 // Per-surface table in device memory.
+// A leaf patch: its triangles' box and records [begin, begin + count); or a group of
+// kLeafGroup leaves that follow each other: their box (begin, count: the leaves).
+struct alignas(16) LeafBox {
+    float lo[3];
+    uint32_t begin;
+    float hi[3];
+    uint32_t count;
+};
+constexpr int kLeafGroup = 64;
+
 struct SurfaceDev {
     int64_t rec_begin, rec_end;      // the surface's triangles: records [begin, end)
                                      // (its caps follow)
     int64_t node_begin;              // root node of the patch tree
     int64_t n_tri;
+    int64_t leaf_begin;              // its leaves' boxes, then those of their groups
     int32_t label;
-    int32_t pad;
+    int32_t n_leaves;
     float lo[3], hi[3];              // bounding box of the vertices
     float ball[4];                   // centre and squared radius of a ball the surface does
                                      // not cross (radius shrunk for rounding)
@@ -100,6 +111,7 @@ struct LabelInst {
     const TriRec *rec;
     const SurfaceDev *surf;
     const PatchEntry *ent;
+    const LeafBox *leaf;
     const float *x, *y, *z;
     int32_t *labels;
     void *winding;                // [n_surf][wstride] float or double, or null

@@ -47,7 +47,8 @@ sal_status build_surface_set(sal_context *ctx, const sal_surface_desc *desc, int
     };
     if ((st = up((void **)&set->rec, rec.recs.data(), rec.recs.size() * sizeof(TriRec))) != SAL_OK ||
         (st = up((void **)&set->surf, table.data(), table.size() * sizeof(SurfaceDev))) != SAL_OK ||
-        (st = up((void **)&set->ent, rec.entries.data(), rec.entries.size() * sizeof(PatchEntry))) != SAL_OK) {
+        (st = up((void **)&set->ent, rec.entries.data(), rec.entries.size() * sizeof(PatchEntry))) != SAL_OK ||
+        (st = up((void **)&set->leaf, rec.leaves.data(), rec.leaves.size() * sizeof(LeafBox))) != SAL_OK) {
         destroy_surface_set(set);
         return st;
     }
@@ -105,6 +106,7 @@ void destroy_surface_set(sal_surface_set *set) {
     if (set->rec) (void)hipFree(set->rec);
     if (set->surf) (void)hipFree(set->surf);
     if (set->ent) (void)hipFree(set->ent);
+    if (set->leaf) (void)hipFree(set->leaf);
     delete set;
 }
 

@@ -158,7 +158,7 @@ public:
     std::vector<int32_t> order;       // triangles, leaf by leaf: their records
     std::vector<Corners> caps;        // the caps' triangles, patch by patch: the records after
     std::vector<PatchEntry> entries;  // 4 per node
-    int64_t n_leaves = 0;
+    std::vector<LeafBox> leaves;      // in record order, then their groups
 
     void build() {
         const int64_t nt = s_.nt;
@@ -179,7 +179,21 @@ public:
         std::vector<uint32_t> none;
         if (nt <= kLeafTri) leaf(0, 0, nt, &none);
         else split(0, 0, nt, &none);
+        const size_t n = leaves.size();
+        for (size_t b = 0; b < n; b += kLeafGroup) {
+            LeafBox g = leaves[b];
+            g.begin = (uint32_t)b;
+            g.count = (uint32_t)std::min<size_t>(kLeafGroup, n - b);
+            for (size_t i = b + 1; i < b + g.count; ++i)
+                for (int c = 0; c < 3; ++c) {
+                    g.lo[c] = std::min(g.lo[c], leaves[i].lo[c]);
+                    g.hi[c] = std::max(g.hi[c], leaves[i].hi[c]);
+                }
+            leaves.push_back(g);
+        }
+        n_leaves = (int64_t)n;
     }
+    int64_t n_leaves = 0;
 
 private:
     struct Box {
@@ -281,7 +295,14 @@ private:
                 const int64_t at = pos_[s_.twin[h] / 3];
                 if (at < b || at >= e) rim->push_back(h);
             }
-        ++n_leaves;
+        LeafBox lb;
+        for (int c = 0; c < 3; ++c) {
+            lb.lo[c] = box.lo[c];
+            lb.hi[c] = box.hi[c];
+        }
+        lb.begin = (uint32_t)b;
+        lb.count = (uint32_t)(e - b);
+        leaves.push_back(lb);
         cap(ent, *rim, b, e - b);
         set_box(ent, box);
         return box;
@@ -451,6 +472,7 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
     std::vector<PatchEntry> &entries = rec->entries;
     recs.clear();
     entries.clear();
+    rec->leaves.clear();
     rec->n_leaves = 0;
     table.assign((size_t)n, SurfaceDev{});
     int64_t &total_tri = rec->total_tri;
@@ -473,7 +495,9 @@ sal_status build_surface_records(const sal_surface_desc *desc, int32_t n, uint32
         sd.rec_begin = (int64_t)recs.size();
         sd.n_tri = hs.nt;
         sd.label = hs.label;
-        sd.pad = 0;
+        sd.leaf_begin = (int64_t)rec->leaves.size();
+        sd.n_leaves = (int32_t)patches.n_leaves;
+        rec->leaves.insert(rec->leaves.end(), patches.leaves.begin(), patches.leaves.end());
         for (int c = 0; c < 3; ++c) {
             sd.lo[c] = INFINITY;
             sd.hi[c] = -INFINITY;
@@ -535,7 +559,8 @@ extern "C" sal_status sal_surface_set_check(const sal_surface_desc *surfaces, in
             info->n_strips = rec.n_leaves;
             info->device_bytes = (int64_t)(rec.recs.size() * sizeof(sal::TriRec) +
                                            rec.table.size() * sizeof(sal::SurfaceDev) +
-                                           rec.entries.size() * sizeof(sal::PatchEntry));
+                                           rec.entries.size() * sizeof(sal::PatchEntry) +
+                                           rec.leaves.size() * sizeof(sal::LeafBox));
         }
         return SAL_OK;
     } catch (const std::bad_alloc &) {

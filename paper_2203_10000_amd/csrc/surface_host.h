@@ -14,6 +14,7 @@ struct SurfaceRecords {
     std::vector<TriRec> recs;
     std::vector<SurfaceDev> table;
     std::vector<PatchEntry> entries;   // four per node
+    std::vector<LeafBox> leaves;       // and their groups, surface by surface
     int64_t total_tri = 0, n_leaves = 0;
 };
 
