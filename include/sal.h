@@ -131,20 +131,22 @@ sal_status sal_surface_set_check(const sal_surface_desc *surfaces, int32_t n_sur
                                  uint32_t flags, sal_surface_set_info *info);
 
 /* ----------------------------------------------------------------- labeling
- * Precision forms of the pair loop:
- *   SAL_PREC_FP64          every solid angle in double, with an exact sign of
- *                          the triple product where double cannot certify it
- *                          ("plain FP64");
- *   SAL_PREC_FP32_RECHECK  solid angles in float32, summed per strip and
- *                          accumulated in double; a (point, surface) pair is
- *                          recomputed, in double where float32 does not certify
- *                          a term, when |w - T| < recheck_band or when any of
- *                          its triangles is ill-conditioned in float32 (see
- *                          kappa).  Labels are those of the FP64 form.
- * In both, a patch of triangles seen from outside its bounding box is summed
- * through a strip over its boundary (the two close to a surface that does not
- * enclose the point), and points that share a box no triangle enters share one
- * winding number.  Sums within 1e-3 of a whole number are that number: a closed
+ * Precision forms:
+ *   SAL_PREC_FP64          solid angles and crossings in double, with an exact
+ *                          sign of the triple product where double cannot
+ *                          certify it ("plain FP64");
+ *   SAL_PREC_FP32_RECHECK  the same in float32 where a bound on its rounding
+ *                          certifies the sign or term; a (point, surface) pair is
+ *                          recomputed, in double where float32 is not certain,
+ *                          when |w - T| < recheck_band or when a sign or term is
+ *                          ill-conditioned in float32 (see kappa).  Labels are
+ *                          those of the FP64 form.
+ * In both, the winding number of a point comes from the signed number of
+ * triangles that a segment from it crosses, to a point of known winding number
+ * or out of the surface's bounding box.  Where no crossing is certain the solid
+ * angles are summed, and a patch of triangles seen from outside its bounding box
+ * through another surface over its boundary (the two close to a surface that does
+ * not enclose the point).  Sums within 1e-3 of a whole number are that number: a closed
  * surface has no other winding number off the surface.  Points exactly on a
  * surface keep the sum of the triangles they do not lie on. */
 enum { SAL_PREC_FP64 = 0, SAL_PREC_FP32_RECHECK = 1 };
@@ -209,9 +211,9 @@ typedef struct sal_label_stats {
     int64_t n_exact_fallbacks; /* triangle evaluations that needed the exact sign */
     int64_t n_recheck_f64_terms; /* triangle terms of rechecked pairs evaluated in
                                     double (the others are certified float32) */
-    float ms_pairloop;         /* device time of the pair loop */
+    float ms_pairloop;         /* device time of the labeling up to the recheck */
     float ms_recheck;          /* device time of the FP64 recheck */
-    float ms_total;            /* device time from the pair loop's start to the
+    float ms_total;            /* device time from the labeling's start to the
                                   last kernel (launch-shape tuning excluded) */
     int32_t points_per_lane;   /* launch shape used (block_waves: the tuner's when 0 was asked) */
     int32_t block_waves;

@@ -2,11 +2,12 @@
 // decision, and the recomputation of what float32 cannot certify.  gfx950
 // (CDNA4), wave64.
 //
-// Two facts about closed surfaces replace most of the sum over triangles.  A
-// patch seen from outside its box has the solid angle of its cap (see
-// PatchEntry), so a point needs about 8 sqrt(T) terms instead of T.  And the
-// winding number is constant where the surface does not pass: a wavefront whose
-// 64 points lie in a box that meets no triangle needs it at one of them.
+// Three facts about closed surfaces replace the sum over triangles.  The winding
+// numbers of two points differ by the signed number of triangles that the segment
+// between them crosses.  They are 0 outside the surface's box, so one segment out
+// of it (a ray) gives a point's.  And where no ray is certain, a patch seen from
+// outside its box has the solid angle of its cap (see PatchEntry), so the sum takes
+// about 8 sqrt(T) terms instead of T.
 //   k_label_span   512 neighbouring points (order.hip) and one surface per
 //                  wavefront: the winding number they share, if the surface does
 //                  not enter their box.
@@ -15,7 +16,7 @@
 //                  the others differ from it by the signed number of near triangles
 //                  that the segment between them crosses.
 //   k_label_final  the labels from both.
-//   k_label_point  one point per wavefront, a lane per term: few points.
+//   k_label_point  one point per wavefront, a lane per triangle: few points.
 //   k_recheck      the same for flagged (point, surface) pairs.
 // No MFMA: a term has K = 3 products, square roots and a sign-sensitive sum.
 #include <hip/hip_runtime.h>

@@ -202,7 +202,7 @@ sal_status compact_levels(sal_context *ctx, sal_tet_mesh *m, uint8_t mask, int32
 }
 
 // Labels n points whose centroids sit in the scratch into `labels`; records
-// ev_start after any launch-shape tuning and ev_mid after the pair loop
+// ev_start after any launch-shape tuning and ev_mid after the labeling kernels
 // (before the recheck).
 sal_status label_scratch(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set *set, int64_t n,
                          const sal_label_options &opt, int32_t *labels, hipEvent_t ev_start,
