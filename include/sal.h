@@ -240,7 +240,7 @@ sal_status sal_label_points(sal_context *ctx, const sal_surface_set *set, int64_
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, kernels and results as sal_label_points, but the
  * call allocates nothing: its scratch (counters, flag list, spatial order of
- * the points, groups' results, about 58 MB) is one static device array per
+ * the points, groups' results, about 62 MB) is one static device array per
  * GPU, held until the process ends.  Limits and differences:
  *   n_points  at most 1048576 per call (SAL_ERR_CAPACITY beyond; label larger
  *             sets in chunks);

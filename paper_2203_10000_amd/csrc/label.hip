@@ -41,6 +41,12 @@ using patch::PointSum;
 // 137.
 constexpr int kSplitMin = 16;
 
+// Spans of an instance with fewer points are so large that most meet a surface:
+// they are left open unlooked at.  24 instances of up to 353,000 points, two
+// rounds under 20 surfaces (us): from 0 points on 1042 and 2616, from 2^16 944 and
+// 2597, from 2^18 997 and 2879, from 2^20 1051 and 3711.
+constexpr int64_t kSpanInstance = (int64_t)1 << 16;
+
 // Below this many (group, surface) pairs a wavefront takes a quarter of a group:
 // its chain is shorter, and the chip has places for all of them.  8,192 pairs or
 // fewer (us, whole groups / quarters): 60,001 points by two surfaces 398 / 295;
@@ -279,7 +285,9 @@ __global__ __launch_bounds__(64) void k_label_span(LabelArgs a) {
     const SurfaceDev &sd = in.surf[k];
     int32_t v = kSpanUnknown;
     unsigned long long culled = 0;
-    if (a.cull && (v = culled_span(in, a, sd, span, n)) != kSpanUnknown) {
+    if (n < kSpanInstance) {
+        // open
+    } else if (a.cull && (v = culled_span(in, a, sd, span, n)) != kSpanUnknown) {
         culled = n_good * (unsigned long long)sd.n_tri;
     } else if (!(lo[0] <= hi[0]) || lo[0] > sd.hi[0] || hi[0] < sd.lo[0] || lo[1] > sd.hi[1] || hi[1] < sd.lo[1] ||
         lo[2] > sd.hi[2] || hi[2] < sd.lo[2]) {

@@ -33,7 +33,7 @@ constexpr int64_t kScratchBytes =
     align256(kOffPairs + kNoAllocMaxPoints / 64 * kMaxSurfaces * (int64_t)sizeof(PairBits));
 static_assert(kNoAllocMaxPoints / kMinTile <= kMaxTiles, "every tile of a full call has the smallest size");
 
-// ~58 MB per device, held until the process ends.  Host code must never pass
+// ~62 MB per device, held until the process ends.  Host code must never pass
 // this name to a kernel: on the host it is only a stand-in for the symbol;
 // the device address comes from hipGetSymbolAddress below.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

@@ -83,9 +83,14 @@ constexpr int64_t kPointFormMax = 32768;
 // The same for an instance of a batch, whose other instances fill the chip.
 constexpr int64_t kBatchPointMax = 8192;
 
-// Tile size and count of the spatial order for n points.
+// Tile size and count of the spatial order for n points: up to kSmallOrder small
+// tiles, so that there is a workgroup for each CU (us, tiles of 2048 / 1024: 196,608
+// lattice points 88 / 83, 200,003 box points 142 / 135, 60,001 points near two
+// surfaces 280 / 267); above, the bins of more tiles cost more than that gives (two
+// rounds under 20 surfaces 2616 / 2647).
+constexpr int64_t kSmallOrder = (int64_t)1 << 18;
 inline int32_t order_tile(int64_t n) {
-    int64_t tile = kMinTile;
+    int64_t tile = n <= kSmallOrder ? kMinTile : 2 * kMinTile;
     while ((n + tile - 1) / tile > kMaxTiles) tile *= 2;
     return (int32_t)tile;
 }

@@ -133,7 +133,7 @@ struct LabelInst {
 // place on a Hilbert curve, kOrderBits1 low bits first.
 constexpr int kOrderBits1 = 11, kOrderBits2 = 10;   // 7 bits per axis
 constexpr int kOrderBins = 1 << kOrderBits1;
-constexpr int64_t kMinTile = 2048, kMaxTiles = 1024;   // per instance
+constexpr int64_t kMinTile = 1024, kMaxTiles = 1024;   // per instance
 
 // Points of a span: the groups that may share one winding number.
 constexpr int64_t kSpanGroups = 8, kSpanPoints = 64 * kSpanGroups;
