@@ -258,14 +258,13 @@ __device__ __forceinline__ int32_t culled_span(const LabelInst &in, const LabelA
     return ballot(!ball) == 0 ? sd.ball_w : kSpanUnknown;
 }
 
-__global__ __launch_bounds__(64) void k_label_span(LabelArgs a) {
-    __shared__ Lists L;
-    const int64_t g = blockIdx.x;
+// Entry g: settles it, or returns true where the groups are left to do it.
+__device__ __forceinline__ bool span_open(const LabelArgs &a, int64_t g, Lists &L) {
     const int ii = a.insts ? find_inst<&LabelInst::span_entry>(a.insts, a.n_inst, g) : 0;
     const LabelInst &in = a.insts ? a.insts[ii] : a.one;
     const int64_t n = label_count(a, in), span = (g - in.span_entry) / in.n_surf;
     const int k = (int)((g - in.span_entry) % in.n_surf), lane = lane_id();
-    if (span * kSpanPoints >= n) return;
+    if (span * kSpanPoints >= n) return false;
     const float inf = __builtin_inff();
     float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
     unsigned long long n_good = 0;
@@ -302,11 +301,34 @@ __global__ __launch_bounds__(64) void k_label_span(LabelArgs a) {
             if (patch::ray_winding(leaf, rec, sd, q, 0, L, r)) v = r;
         }
     }
-    if (lane == 0) {
-        a.span_w[g] = v;
-        if (v == kSpanUnknown) a.open_spans[atomicAdd(&a.work[kWorkOpen], 1ull)] = (uint32_t)g;
-    }
+    if (lane == 0) a.span_w[g] = v;
     count(in.counters, kCntCulled, culled);
+    return v == kSpanUnknown;
+}
+
+// The last wavefront of a workgroup lists what all of them left open: the list's
+// counter takes some 5 ns an update (us, an update a wavefront, a workgroup of 2, 4
+// and 8: 24 instances 944, 914, 909, 916; 6M lattice points 736, 725, 718, 730).
+constexpr int kSpanWaves = 4;
+
+__global__ __launch_bounds__(64 * kSpanWaves) void k_label_span(LabelArgs a, int64_t entries) {
+    __shared__ Lists lists[kSpanWaves];
+    __shared__ uint32_t s_open[kSpanWaves];
+    __shared__ unsigned s_n, s_done;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x == 0) { s_n = 0u; s_done = 0u; }
+    __syncthreads();
+    const int64_t g = (int64_t)blockIdx.x * kSpanWaves + wave;
+    const bool open = g < entries && span_open(a, g, lists[wave]);
+    if (lane_id() != 0) return;
+    if (open) s_open[atomicAdd(&s_n, 1u)] = (uint32_t)g;
+    __threadfence_block();
+    if (atomicAdd(&s_done, 1u) != kSpanWaves - 1) return;
+    __threadfence_block();
+    const unsigned n = s_n;
+    if (n == 0) return;
+    const unsigned long long base = atomicAdd(&a.work[kWorkOpen], (unsigned long long)n);
+    for (unsigned i = 0; i < n; ++i) a.open_spans[base + i] = s_open[i];
 }
 
 // ------------------------------------------------------------- open pairs
@@ -582,7 +604,8 @@ hipError_t launch_label_final(const LabelArgs &a, bool fp64, int64_t groups, hip
 hipError_t launch_label_span(const LabelArgs &a, int64_t entries, hipStream_t s) {
     if (entries <= 0) return hipSuccess;
     if (entries > 0x7fffffff) return hipErrorInvalidValue;
-    k_label_span<<<dim3((unsigned)entries), dim3(64), 0, s>>>(a);
+    k_label_span<<<dim3((unsigned)((entries + kSpanWaves - 1) / kSpanWaves)), dim3(64 * kSpanWaves), 0, s>>>(
+        a, entries);
     return hipGetLastError();
 }
 
