@@ -104,6 +104,10 @@ __global__ __launch_bounds__(kThreads) void k_order_hist(LabelArgs a) {
     const LabelInst &in = a.insts ? a.insts[ii] : a.one;
     const int64_t n = label_count(a, in), t = (int64_t)blockIdx.x - in.tile_base;
     if (PASS == 1 && blockIdx.x == 0 && threadIdx.x < kNumWork) a.work[threadIdx.x] = 0ull;
+    // The whole workgroup.  Grids of a device-side count are as large as its bound:
+    // with empty tiles counted and scanned, two captured rounds of a small head took
+    // 905 us instead of 805.
+    if (t * in.tile >= n) return;
     for (int b = threadIdx.x; b < bins<PASS>(); b += kThreads) h[b] = 0u;
     __syncthreads();
     const int64_t i0 = t * in.tile, i1 = i0 + in.tile < n ? i0 + in.tile : n;
@@ -116,23 +120,25 @@ __global__ __launch_bounds__(kThreads) void k_order_hist(LabelArgs a) {
     for (int b = threadIdx.x; b < bins<PASS>(); b += kThreads) out[(int64_t)b * in.n_tiles] = h[b];
 }
 
-// One wavefront per (bin, instance): exclusive scan over the tiles, in place.
+// One wavefront per (bin, instance): exclusive scan over the tiles that have
+// points, in place.
 template <int PASS>
 __global__ __launch_bounds__(64) void k_order_scan(LabelArgs a) {
     const int ii = (int)(blockIdx.x / bins<PASS>()), bin = (int)(blockIdx.x % bins<PASS>());
     const int lane = lane_id();
     const LabelInst &in = a.insts ? a.insts[ii] : a.one;
     uint32_t *h = a.ord.hist + kOrderBins * in.tile_base + (int64_t)bin * in.n_tiles;
+    const int used = (int)((label_count(a, in) + in.tile - 1) / in.tile);
     uint32_t run = 0;
-    for (int b = 0; b < in.n_tiles; b += 64) {
-        const uint32_t v = b + lane < in.n_tiles ? h[b + lane] : 0u;
+    for (int b = 0; b < used; b += 64) {
+        const uint32_t v = b + lane < used ? h[b + lane] : 0u;
         uint32_t s = v;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const uint32_t u = (uint32_t)__shfl_up((int)s, d);
             if (lane >= d) s += u;
         }
-        if (b + lane < in.n_tiles) h[b + lane] = run + s - v;
+        if (b + lane < used) h[b + lane] = run + s - v;
         run += (uint32_t)__shfl((int)s, 63);
     }
     if (lane == 0) a.ord.tot[(int64_t)ii * kOrderBins + bin] = run;
