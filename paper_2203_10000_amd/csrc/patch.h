@@ -98,9 +98,10 @@ __device__ __forceinline__ double whole(double w) {
     return fabs(w - r) < 1e-3 ? r : w;
 }
 
-// Winding number of the listed ranges at one point (the same in every lane).  Eight groups of eight lanes take ranges in turn, a group the next one
-// as it becomes free (all lanes run in step, so the assignment, and with it
-// the result, depends on the lists alone); a lane evaluates one triangle.  Most
+// Winding number of the listed ranges at one point (the same in every lane).
+// Eight groups of eight lanes take ranges in turn, a group the next one as it
+// becomes free (all lanes run in step, so the assignment, and with it the
+// result, depends on the lists alone); a lane evaluates one triangle.  Most
 // caps have 20-60 triangles, so wider groups would leave more lanes idle at a
 // range's end.  The next triangles are loaded before the present ones are
 // evaluated: a round waits for memory only as far as the arithmetic of the

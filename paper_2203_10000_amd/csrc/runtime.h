@@ -120,10 +120,11 @@ sal_status ensure_label_scratch(sal_context *ctx, const sal_surface_set *set, in
 // Validated options with defaults applied.
 sal_status resolve_options(const sal_label_options *in, sal_label_options *out);
 
-// Enqueues one labeling pass (winding numbers, and the recheck) of n points; counters must be cleared by the caller.  The launch shape is
-// resolved first (tune_launch); then ev_start (before the first kernel) and
-// ev_after_pairloop are recorded when non-null, so that timings bracketed by
-// them leave out any tuning.
+// Enqueues one labeling pass (winding numbers, and the recheck) of n points;
+// counters must be cleared by the caller.  The launch shape is resolved first
+// (tune_launch); then ev_start (before the first kernel) and ev_after_pairloop
+// are recorded when non-null, so that timings bracketed by them leave out any
+// tuning.
 sal_status enqueue_label(sal_context *ctx, const sal_surface_set *set, int64_t n, const float *x,
                          const float *y, const float *z, const sal_label_options &opt,
                          int32_t *labels, void *winding, hipEvent_t ev_start,

@@ -1,7 +1,8 @@
 // Taubin smoothing of the conforming mesh (paper section 2.2.1): host side.
 // The edge graph is built once per conforming mesh (the nodes sorted by Morton
-// code, the edges from a table of places by node); the phases then run half steps until the stopping ratio is met, reading one double back
-// per iteration.
+// code, the edges from a table of places by node); the phases then run half
+// steps until the stopping ratio is met, reading one double back per
+// iteration.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
