@@ -75,15 +75,7 @@ sal_status ensure_label_scratch(sal_context *ctx, const ScratchSize &need) {
 }
 
 sal_status ensure_label_scratch(sal_context *ctx, const sal_surface_set *set, int64_t n) {
-    if (n <= kPointFormMax) return SAL_OK;
-    const int64_t c = n < kChunkPoints ? n : kChunkPoints;
-    ScratchSize z;
-    z.points = c;
-    z.tiles = order_tiles(c);
-    z.insts = 1;
-    z.spans = span_count(c) * set->n_surf;
-    z.pairs = group_count(c) * set->n_surf;
-    return ensure_label_scratch(ctx, z);
+    return ensure_label_scratch(ctx, label_scratch_size(n, set->n_surf));
 }
 
 sal_status resolve_options(const sal_label_options *in, sal_label_options *out) {

@@ -1,6 +1,7 @@
 // Host-side objects behind the opaque handles of sal.h.
 #pragma once
 
+#include <algorithm>
 #include <vector>
 
 #include "sal_internal.h"
@@ -96,6 +97,15 @@ inline int32_t order_tile(int64_t n) {
 }
 inline int64_t order_tiles(int64_t n) { return (n + order_tile(n) - 1) / order_tile(n); }
 
+// The most tiles that any m <= n points have: where the tiles double their number
+// halves, so n itself may have fewer (262,144 points 256, 262,145 points 129).
+inline int64_t order_tiles_upto(int64_t n) {
+    int64_t most = order_tiles(n);
+    if (n > kSmallOrder) most = std::max(most, order_tiles(kSmallOrder));
+    if (n > 2 * kMinTile * kMaxTiles) most = kMaxTiles;
+    return most;
+}
+
 // From this many (point, surface) pairs on, a pass over spans of 512 points
 // settles most of them first.  Below, its one more serial launch costs what it
 // saves.
@@ -114,7 +124,22 @@ struct ScratchSize {
 };
 // Grows the context's labeling scratch to hold it.
 sal_status ensure_label_scratch(sal_context *ctx, const ScratchSize &need);
-// The same for a call on n points (nothing for the point form).
+
+// What a call on up to n points against n_surf surfaces needs (nothing for the
+// point form).  It never falls as n grows: a round sizes the scratch for its
+// largest level, the tuner's trials run on a part of the points.
+inline ScratchSize label_scratch_size(int64_t n, int n_surf) {
+    ScratchSize z;
+    if (n <= kPointFormMax) return z;
+    const int64_t c = std::min(n, kChunkPoints);
+    z.points = c;
+    z.tiles = order_tiles_upto(c);
+    z.insts = 1;
+    z.spans = span_count(c) * n_surf;
+    z.pairs = group_count(c) * n_surf;
+    return z;
+}
+// Grows the scratch for such a call.
 sal_status ensure_label_scratch(sal_context *ctx, const sal_surface_set *set, int64_t n);
 
 // Validated options with defaults applied.

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import synth
+from oracle import kuhn
 
 torch = pytest.importorskip("torch")
 import paper_2203_10000_amd as sal  # noqa: E402
@@ -82,4 +83,48 @@ def test_every_allocation_failure_is_reported_and_recoverable(case, rule):
             assert np.array_equal(a, b), k
     else:
         pytest.fail("the sequence kept failing")
+    assert failures >= 8
+
+
+def test_a_failed_round_over_levels_of_unlike_sizes_changes_nothing(case):
+    """A round that labels 373,248 points of one level, then 248,832 of the next
+    coarser one: the second needs more tiles of the spatial order than the first,
+    and every buffer has to be there before the first split."""
+    nx, ny = 19, 18
+    ctx = sal.Context(0)
+    cfg = case[0]
+    ss = sal.SurfaceSet(ctx, cfg.surfaces)
+    k0 = kuhn.level0_keys((nx, ny, ny))
+    deep = np.arange(len(k0)) // 6 % nx < 3          # three layers of cells along x, split once
+    keys = np.concatenate([k0[~deep], kuhn.children(k0[deep], (nx, ny, ny)).reshape(-1)])
+    labels = np.arange(len(keys)) % 5                # nearly every leaf has a neighbour of another label
+    d_keys = torch.from_numpy(keys.view(np.int64)).cuda()
+    d_labels = torch.from_numpy(labels.astype(np.int32)).cuda()
+    failures = 0
+    for k in range(1, 60):
+        mesh = sal.TetMesh(ctx, (-95.0, -90.0, -90.0), 10.0, (nx, ny, ny))
+        mesh.import_leaves(d_keys, d_labels)
+        ctx2 = sal.Context(0)                        # (its labeling scratch is not there yet)
+        mesh.ctx = ctx2
+        before = mesh.size()
+        sal.lib().sal_debug_fail_allocation(k)
+        try:
+            mesh.refine_relabel(ss, 1)
+            hit = False
+        except sal.SalError as e:
+            hit = True
+            assert e.status in (OOM, DEVICE), (k, e.status, str(e))
+        finally:
+            sal.lib().sal_debug_fail_allocation(0)
+        if hit:
+            assert mesh.size() == before, k
+            left = mesh.export(keys=True, labels=True, centroids=False)
+            assert int(left["labels"].min()) >= 0, k
+            failures += 1
+        mesh.close()
+        ctx2.close()
+        if not hit:
+            break
+    else:
+        pytest.fail("the round kept failing")
     assert failures >= 8
