@@ -1,5 +1,6 @@
-"""Host parts of libsal's runtime (scratch sizes), built with g++ under
-AddressSanitizer and UndefinedBehaviorSanitizer.  CPU only."""
+"""Host parts of libsal's runtime (scratch sizes, the kept device blocks on a
+stand-in for the card), built with g++ under AddressSanitizer and
+UndefinedBehaviorSanitizer.  CPU only."""
 import os
 import shutil
 import subprocess
@@ -18,7 +19,8 @@ def driver(tmp_path_factory):
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
                         "-fno-sanitize-recover=all", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                         "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                        os.path.join(ROOT, "tests", "sanitize", "runtime_driver.cpp"), "-o", out],
+                        os.path.join(ROOT, "tests", "sanitize", "runtime_driver.cpp"),
+                        os.path.join(CSRC, "devmem.cpp"), "-lpthread", "-o", out],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     return out
@@ -31,3 +33,7 @@ def _run(driver, check):
 
 def test_scratch_for_n_points_holds_every_smaller_call(driver):
     _run(driver, "scratch")
+
+
+def test_kept_blocks_are_a_reserve_of_every_allocation(driver):
+    _run(driver, "reserve")
