@@ -319,7 +319,7 @@ void sal_context_destroy(sal_context *ctx) {
         if (p) (void)hipFree(p);
     if (ctx->host_words) (void)hipHostFree(ctx->host_words);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
-    pool_remove_context();
+    pool_remove_context(ctx->stream_token);
     delete ctx;
 }
 

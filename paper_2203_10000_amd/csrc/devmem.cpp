@@ -29,15 +29,18 @@ constexpr size_t kKeepBytes = (size_t)2 << 30, kKeepBlock = (size_t)512 << 20;
 struct Block {
     void *ptr;
     size_t bytes;
-    uint64_t token;   // where its last work was enqueued; 0: none is pending
+    uint64_t token;    // where its last work was enqueued; 0: none is pending
+    uint64_t serial;   // of its release
 };
 
 // One device's blocks.  Held while a context lives on the device; with the last
-// one gone the kept blocks are freed and later ones are not kept.
+// one gone the kept blocks are freed and later ones are not kept.  The lock is
+// never held through a call that may wait for the device.
 struct Pool {
     std::mutex mu;
     int contexts = 0;
     size_t kept = 0;
+    uint64_t releases = 0;
     std::multimap<size_t, Block> idle;
     std::unordered_map<void *, size_t> live;   // blocks handed out
 };
@@ -58,10 +61,24 @@ size_t rounded(size_t bytes) {
     return (bytes + step - 1) / step * step;
 }
 
-void drop_idle(Pool &p) {
-    for (auto &b : p.idle) (void)hipFree(b.second.ptr);
-    p.idle.clear();
-    p.kept = 0;
+// Frees the idle blocks; false: there were none.
+bool drop_idle(Pool &p) {
+    std::multimap<size_t, Block> gone;
+    {
+        std::lock_guard<std::mutex> lk(p.mu);
+        gone.swap(p.idle);
+        p.kept = 0;
+    }
+    for (auto &b : gone) (void)hipFree(b.second.ptr);
+    return !gone.empty();
+}
+
+// hipMalloc with the idle blocks as a reserve.
+hipError_t card_malloc(Pool *p, void **ptr, size_t bytes) {
+    const hipError_t e = hipMalloc(ptr, bytes);
+    if (e != hipErrorOutOfMemory || !p || !drop_idle(*p)) return e;
+    (void)hipGetLastError();
+    return hipMalloc(ptr, bytes);
 }
 
 }  // namespace
@@ -73,14 +90,7 @@ hipError_t dev_malloc(void **ptr, size_t bytes) {
         if (ptr) *ptr = nullptr;
         return hipErrorOutOfMemory;
     }
-    const hipError_t e = hipMalloc(ptr, bytes);
-    Pool *p = e == hipErrorOutOfMemory ? current_pool() : nullptr;
-    if (!p) return e;
-    std::lock_guard<std::mutex> lk(p->mu);
-    if (p->idle.empty()) return e;
-    (void)hipGetLastError();
-    drop_idle(*p);
-    return hipMalloc(ptr, bytes);
+    return card_malloc(current_pool(), ptr, bytes);
 }
 
 uint64_t new_stream_token() {
@@ -95,11 +105,34 @@ void pool_add_context() {
     ++p->contexts;
 }
 
-void pool_remove_context() {
+// token: of the context that goes, whose stream is idle.
+void pool_remove_context(uint64_t token) {
     Pool *p = current_pool();
     if (!p) return;
-    std::lock_guard<std::mutex> lk(p->mu);
-    if (--p->contexts == 0) drop_idle(*p);
+    bool last;
+    {
+        std::lock_guard<std::mutex> lk(p->mu);
+        last = --p->contexts == 0;
+        for (auto &b : p->idle)
+            if (b.second.token == token) b.second.token = 0;
+    }
+    if (last) (void)drop_idle(*p);
+}
+
+hipError_t pool_device_synchronize() {
+    Pool *p = current_pool();
+    uint64_t before = 0;
+    if (p) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        before = p->releases;
+    }
+    const hipError_t e = hipDeviceSynchronize();
+    if (p && e == hipSuccess) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        for (auto &b : p->idle)
+            if (b.second.serial <= before) b.second.token = 0;
+    }
+    return e;
 }
 
 hipError_t pool_malloc(void **ptr, size_t bytes, uint64_t token) {
@@ -108,55 +141,43 @@ hipError_t pool_malloc(void **ptr, size_t bytes, uint64_t token) {
     Pool *p = current_pool();
     if (!p) return hipMalloc(ptr, bytes);
     const size_t size = rounded(bytes);
-    std::lock_guard<std::mutex> lk(p->mu);
-    // the smallest kept block that fits with at most a quarter to spare; of
-    // those of its size, one whose last work precedes the caller's in its stream
-    auto best = p->idle.end();
-    for (auto it = p->idle.lower_bound(size); it != p->idle.end() && it->first <= size + size / 4; ++it) {
-        if (best != p->idle.end() && it->first != best->first) break;
-        best = it;
-        if (it->second.token == token || it->second.token == 0) break;
-    }
-    if (best != p->idle.end()) {
-        const Block b = best->second;
-        if (b.token != token && b.token != 0) {
-            const hipError_t e = hipDeviceSynchronize();
-            if (e != hipSuccess) return e;
-            for (auto &i : p->idle) i.second.token = 0;
+    {
+        // the smallest kept block that fits with at most a quarter to spare and has
+        // no work pending in another stream (a fresh one costs less than waiting)
+        std::lock_guard<std::mutex> lk(p->mu);
+        for (auto it = p->idle.lower_bound(size); it != p->idle.end() && it->first <= size + size / 4; ++it) {
+            const Block b = it->second;
+            if (b.token != token && b.token != 0) continue;
+            p->idle.erase(it);
+            p->kept -= b.bytes;
+            p->live[b.ptr] = b.bytes;
+            *ptr = b.ptr;
+            return hipSuccess;
         }
-        p->idle.erase(best);
-        p->kept -= b.bytes;
-        p->live[b.ptr] = b.bytes;
-        *ptr = b.ptr;
-        return hipSuccess;
     }
-    hipError_t e = hipMalloc(ptr, size);
-    if (e == hipErrorOutOfMemory && !p->idle.empty()) {
-        (void)hipGetLastError();
-        drop_idle(*p);
-        e = hipMalloc(ptr, size);
+    const hipError_t e = card_malloc(p, ptr, size);
+    if (e == hipSuccess) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        p->live[*ptr] = size;
     }
-    if (e == hipSuccess) p->live[*ptr] = size;
     return e;
 }
 
 void pool_free(void *ptr, uint64_t token) {
     if (!ptr) return;
     Pool *p = current_pool();
-    if (!p) {
-        (void)hipFree(ptr);
-        return;
+    if (p) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        auto it = p->live.find(ptr);
+        const size_t bytes = it == p->live.end() ? 0 : it->second;
+        if (it != p->live.end()) p->live.erase(it);
+        if (bytes != 0 && bytes <= kKeepBlock && p->contexts > 0 && p->kept + bytes <= kKeepBytes) {
+            p->idle.insert({bytes, Block{ptr, bytes, token, ++p->releases}});
+            p->kept += bytes;
+            return;
+        }
     }
-    std::lock_guard<std::mutex> lk(p->mu);
-    auto it = p->live.find(ptr);
-    const size_t bytes = it == p->live.end() ? 0 : it->second;
-    if (it != p->live.end()) p->live.erase(it);
-    if (bytes == 0 || bytes > kKeepBlock || p->contexts == 0 || p->kept + bytes > kKeepBytes) {
-        (void)hipFree(ptr);
-        return;
-    }
-    p->idle.insert({bytes, Block{ptr, bytes, token}});
-    p->kept += bytes;
+    (void)hipFree(ptr);
 }
 
 }  // namespace sal

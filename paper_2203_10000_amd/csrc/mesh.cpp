@@ -670,7 +670,7 @@ extern "C" {
 void sal_tet_mesh_destroy(sal_tet_mesh *m) {
     if (!m) return;
     (void)hipSetDevice(m->device);
-    (void)hipDeviceSynchronize();
+    (void)pool_device_synchronize();
     // (the device is idle: whoever takes a block next need not wait)
     auto drop = [](void *p) { pool_free(p, 0); };
     for (int l = 0; l <= kMaxLevels; ++l) {

@@ -218,9 +218,11 @@ sal_status hip_error(hipError_t e, const char *what);
 // no work on it is pending.
 hipError_t pool_malloc(void **ptr, size_t bytes, uint64_t token);
 void pool_free(void *ptr, uint64_t token);
+// Waits for the device: what was freed before has no work pending then.
+hipError_t pool_device_synchronize();
 uint64_t new_stream_token();
 void pool_add_context();
-void pool_remove_context();
+void pool_remove_context(uint64_t token);
 
 }  // namespace sal
 

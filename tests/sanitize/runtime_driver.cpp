@@ -1,11 +1,15 @@
 // Runs host parts of libsal's runtime under AddressSanitizer and
 // UndefinedBehaviorSanitizer.  argv[1] names the check; exit status 0 when it
 // holds, a message and 1 when it does not.
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
+#include <future>
 #include <map>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 #include "runtime.h"
@@ -16,10 +20,18 @@ constexpr size_t kCard = (size_t)1 << 30;
 std::mutex card_mu;
 std::map<void *, size_t> card;
 size_t card_used = 0;
+constexpr size_t kSlow = 12288;          // an allocation of this size waits for `go`
+std::promise<void> slow_started, go;
+std::function<void()> during_sync;
+int syncs = 0;
 }  // namespace
 
 extern "C" {
 hipError_t hipMalloc(void **ptr, size_t bytes) {
+    if (bytes == kSlow) {
+        slow_started.set_value();
+        go.get_future().wait();
+    }
     std::lock_guard<std::mutex> lk(card_mu);
     *ptr = nullptr;
     if (card_used + bytes > kCard) return hipErrorOutOfMemory;
@@ -36,7 +48,11 @@ hipError_t hipFree(void *ptr) {
     return hipSuccess;
 }
 hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
-hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+    ++syncs;
+    if (during_sync) during_sync();
+    return hipSuccess;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 }
 
@@ -65,7 +81,63 @@ int reserve() {
     sal::pool_free(a, t);
     CHECK(sal::pool_malloc(&b, kCard * 3 / 4, t) == hipSuccess);
     sal::pool_free(b, t);
-    sal::pool_remove_context();
+    sal::pool_remove_context(t);
+    CHECK(card_used == 0);
+    return 0;
+}
+
+// A block with work pending in one stream is not waited for by another, and is that
+// stream's or anyone's again once the device or its own stream is idle.
+int streams() {
+    sal::pool_add_context();
+    sal::pool_add_context();
+    const uint64_t t = sal::new_stream_token(), u = sal::new_stream_token();
+    void *a = nullptr, *b = nullptr, *c = nullptr;
+    CHECK(sal::pool_malloc(&a, 4096, t) == hipSuccess && sal::pool_malloc(&c, 4096, t) == hipSuccess);
+    void *const a0 = a, *const c0 = c;
+    sal::pool_free(a, t);
+    CHECK(sal::pool_malloc(&b, 4096, u) == hipSuccess && b != a0 && syncs == 0);
+    CHECK(sal::pool_malloc(&a, 4096, t) == hipSuccess && a == a0);
+    sal::pool_free(a, t);
+    // freed while the device is waited for: work may have come after the wait began
+    during_sync = [&] { sal::pool_free(c0, t); };
+    CHECK(sal::pool_device_synchronize() == hipSuccess);
+    void *d = nullptr, *e = nullptr;
+    CHECK(sal::pool_malloc(&d, 4096, u) == hipSuccess && d == a0);
+    CHECK(sal::pool_malloc(&e, 4096, u) == hipSuccess && e != c0);
+    sal::pool_remove_context(t);
+    CHECK(sal::pool_malloc(&c, 4096, u) == hipSuccess && c == c0);
+    for (void *p : {b, c, d, e}) sal::pool_free(p, u);
+    sal::pool_remove_context(u);
+    CHECK(card_used == 0 && syncs == 1);
+    return 0;
+}
+
+// While one thread's allocation waits, another's goes on.
+int threads() {
+    sal::pool_add_context();
+    const uint64_t t = sal::new_stream_token(), u = sal::new_stream_token();
+    void *a = nullptr;
+    CHECK(sal::pool_malloc(&a, 4096, t) == hipSuccess);
+    sal::pool_free(a, t);
+    void *slow = nullptr;
+    std::thread waits([&] { (void)sal::pool_malloc(&slow, kSlow, u); });
+    slow_started.get_future().wait();
+    std::promise<void> done;
+    std::future<void> other = done.get_future();
+    std::thread goes([&] {
+        void *p = nullptr;
+        (void)sal::pool_malloc(&p, 4096, t);
+        sal::pool_free(p, t);
+        done.set_value();
+    });
+    const bool went = other.wait_for(std::chrono::seconds(5)) == std::future_status::ready;
+    go.set_value();
+    waits.join();
+    goes.join();
+    CHECK(went);
+    sal::pool_free(slow, u);
+    sal::pool_remove_context(u);
     CHECK(card_used == 0);
     return 0;
 }
@@ -100,5 +172,7 @@ int main(int argc, char **argv) {
     if (argc != 2) return 2;
     if (!std::strcmp(argv[1], "scratch")) return scratch();
     if (!std::strcmp(argv[1], "reserve")) return reserve();
+    if (!std::strcmp(argv[1], "streams")) return streams();
+    if (!std::strcmp(argv[1], "threads")) return threads();
     return 2;
 }

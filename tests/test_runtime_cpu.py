@@ -37,3 +37,8 @@ def test_scratch_for_n_points_holds_every_smaller_call(driver):
 
 def test_kept_blocks_are_a_reserve_of_every_allocation(driver):
     _run(driver, "reserve")
+
+
+@pytest.mark.parametrize("check", ["streams", "threads"])
+def test_kept_blocks_do_not_make_streams_or_threads_wait(driver, check):
+    _run(driver, check)
