@@ -169,11 +169,11 @@ typedef struct sal_label_options {
                                  per lane, whatever is asked */
     int32_t block_waves;      /* 0 = tuned; else 1, 2, 4 or 8 wavefronts per block
                                  (the results do not depend on it).  Tuned: the
-                                 first call for a (device, precision, log2
-                                 triangles, log2 points) times every size on up
-                                 to 2^19 of the points, synchronising the stream,
-                                 and caches the fastest for the process, and in
-                                 the file named by SAL_TUNE_CACHE if set;
+                                 first call for a (device, precision, kernels, log2
+                                 triangles, points and surfaces) times every size
+                                 on up to 2^19 of the points, synchronising the
+                                 stream, and caches the fastest for the process,
+                                 and in the file named by SAL_TUNE_CACHE if set;
                                  SAL_TUNE=0 disables tuning (4 waves). */
     int32_t use_graph;        /* sal_label_batch: 1 = capture the launch sequence in a
                                  hipGraph and replay it while the same instances (same

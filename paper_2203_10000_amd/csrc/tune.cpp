@@ -1,8 +1,6 @@
 // Launch-shape tuner of the labeling kernels: wavefronts per workgroup,
-// timed on the device the first time a (device, precision,
-// triangle-count bucket, point-count bucket) is seen, then cached for the
-// process (and in the file named by SAL_TUNE_CACHE, if set).  Point counts
-// at or above the trial size share one bucket.
+// timed on the device the first time a tune_key is seen, then cached for the
+// process (and in the file named by SAL_TUNE_CACHE, if set).
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -19,22 +17,9 @@
 namespace sal {
 namespace {
 
-using Key = TuneKey;
-
 std::mutex g_mu;
 TuneMap g_cache;
 bool g_loaded = false;
-
-constexpr int64_t kTrialPoints = (int64_t)1 << 19;   // enough workgroups to fill the device
-
-int bucket(int64_t v) {
-    int b = 0;
-    while (v > 1 && b < 62) {
-        v >>= 1;
-        ++b;
-    }
-    return b;
-}
 
 std::string arch_name(int device) {
     hipDeviceProp_t p;
@@ -58,7 +43,6 @@ void save_file() {
 // Fills opt->points_per_lane (1) and opt->block_waves when it is 0 (auto).
 sal_status tune_launch(sal_context *ctx, const sal_surface_set *set, int64_t n, const float *x,
                        const float *y, const float *z, int32_t *labels, sal_label_options *opt) {
-    const int asked_points = opt->points_per_lane;
     opt->points_per_lane = 1;   // the kernels hold one point per lane
     if (opt->block_waves != 0) return SAL_OK;
     const char *off = std::getenv("SAL_TUNE");
@@ -66,11 +50,7 @@ sal_status tune_launch(sal_context *ctx, const sal_surface_set *set, int64_t n, 
         opt->block_waves = 4;
         return SAL_OK;
     }
-    // The trials use at most kTrialPoints points, so every larger count runs
-    // the same trials: those counts share one entry.
-    const Key key(ctx->device, opt->precision, bucket(set->n_tri),
-                  bucket(n < kTrialPoints ? n : kTrialPoints), arch_name(ctx->device),
-                  asked_points, opt->block_waves);
+    const TuneKey key = tune_key(ctx->device, opt->precision, set->n_tri, n, set->n_surf, arch_name(ctx->device));
     {
         std::lock_guard<std::mutex> lk(g_mu);
         if (!g_loaded) load_file();

@@ -3,17 +3,37 @@
 
 #include <cstdio>
 
+#include "runtime.h"
+
 namespace sal {
+
+namespace {
+
+int bucket(int64_t v) {
+    int b = 0;
+    while (v > 1 && b < 62) {
+        v >>= 1;
+        ++b;
+    }
+    return b;
+}
+
+}  // namespace
+
+TuneKey tune_key(int device, int precision, int64_t n_tri, int64_t n, int n_surf, const std::string &arch) {
+    return TuneKey(device, precision, bucket(n_tri), bucket(n < kTrialPoints ? n : kTrialPoints), arch,
+                   n <= kPointFormMax ? kTunePoints : kTuneGroups, bucket(n_surf));
+}
 
 bool tune_cache_read(const char *path, TuneMap *out) {
     if (!path || !out) return false;
     FILE *f = std::fopen(path, "r");
     if (!f) return false;
     char arch[128];
-    int dev, prec, tb, nb, rp, rb, ppl, bw;
-    while (std::fscanf(f, "%127s %d %d %d %d %d %d %d %d", arch, &dev, &prec, &tb, &nb, &rp, &rb,
-                       &ppl, &bw) == 9)
-        (*out)[TuneKey(dev, prec, tb, nb, arch, rp, rb)] = {ppl, bw};
+    int dev, prec, tri, points, form, surfaces, ppl, bw;
+    while (std::fscanf(f, "%127s %d %d %d %d %d %d %d %d", arch, &dev, &prec, &tri, &points, &form,
+                       &surfaces, &ppl, &bw) == 9)
+        (*out)[TuneKey(dev, prec, tri, points, arch, form, surfaces)] = {ppl, bw};
     std::fclose(f);
     return true;
 }

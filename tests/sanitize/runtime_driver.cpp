@@ -1,5 +1,5 @@
 // Runs host parts of libsal's runtime under AddressSanitizer and
-// UndefinedBehaviorSanitizer.  argv[1] names the check; exit status 0 when it
+// UndefinedBehaviorSanitizer.  argv[1] names the check (argv[2]: a file to write); exit status 0 when it
 // holds, a message and 1 when it does not.
 #include <chrono>
 #include <cstdio>
@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "runtime.h"
+#include "tune_cache.h"
 
 // A card of kCard bytes in place of the device.
 namespace {
@@ -166,9 +167,37 @@ int scratch() {
     return 0;
 }
 
+// The tuner tells apart what runs other kernels or another number of surfaces, and
+// takes no entry of a file from before it did.
+int tuner(const char *file) {
+    const std::string arch = "gfx950";
+    const auto key = [&](int64_t n, int n_surf) { return sal::tune_key(0, 1, 5000, n, n_surf, arch); };
+    CHECK(key(sal::kPointFormMax, 1) != key(sal::kPointFormMax + 1, 1));
+    CHECK(key(sal::kPointFormMax - 1, 1) != key(sal::kPointFormMax + 1, 1));
+    CHECK(key(1000, 1) != key(1000, 20) && key(100000, 1) != key(100000, 20));
+    CHECK(key(100000, 5) == key(120000, 6));
+    CHECK(key((int64_t)1 << 19, 1) == key((int64_t)1 << 24, 1));
+    FILE *f = std::fopen(file, "w");
+    CHECK(f);
+    for (int points = 0; points <= 19; ++points)
+        for (const int rp : {0, 1, 2, 4})
+            for (const int rb : {0, 1, 2, 4, 8})
+                std::fprintf(f, "%s 0 1 12 %d %d %d 1 1\n", arch.c_str(), points, rp, rb);
+    std::fclose(f);
+    sal::TuneMap m;
+    CHECK(sal::tune_cache_read(file, &m) && m.size() == 400);
+    for (int64_t n = 1; n <= ((int64_t)1 << 20); n *= 2)
+        for (const int n_surf : {1, 2, 4, 16}) CHECK(m.count(key(n, n_surf)) == 0);
+    m = {{key(1000, 20), {1, 8}}};
+    CHECK(sal::tune_cache_write(file, m) && sal::tune_cache_read(file, &m) && m.size() == 1);
+    CHECK(m.at(key(1000, 20)) == std::make_pair(1, 8));
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
+    if (argc == 3 && !std::strcmp(argv[1], "tuner")) return tuner(argv[2]);
     if (argc != 2) return 2;
     if (!std::strcmp(argv[1], "scratch")) return scratch();
     if (!std::strcmp(argv[1], "reserve")) return reserve();

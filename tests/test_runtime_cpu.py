@@ -1,5 +1,5 @@
 """Host parts of libsal's runtime (scratch sizes, the kept device blocks on a
-stand-in for the card), built with g++ under AddressSanitizer and
+stand-in for the card, the tuner's keys), built with g++ under AddressSanitizer and
 UndefinedBehaviorSanitizer.  CPU only."""
 import os
 import shutil
@@ -20,14 +20,15 @@ def driver(tmp_path_factory):
                         "-fno-sanitize-recover=all", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                         "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                         os.path.join(ROOT, "tests", "sanitize", "runtime_driver.cpp"),
-                        os.path.join(CSRC, "devmem.cpp"), "-lpthread", "-o", out],
+                        os.path.join(CSRC, "devmem.cpp"), os.path.join(CSRC, "tune_cache.cpp"),
+                        "-lpthread", "-o", out],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     return out
 
 
-def _run(driver, check):
-    r = subprocess.run([driver, check], capture_output=True, text=True, timeout=120)
+def _run(driver, *check):
+    r = subprocess.run([driver, *check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr[-4000:]
 
 
@@ -42,3 +43,7 @@ def test_kept_blocks_are_a_reserve_of_every_allocation(driver):
 @pytest.mark.parametrize("check", ["streams", "threads"])
 def test_kept_blocks_do_not_make_streams_or_threads_wait(driver, check):
     _run(driver, check)
+
+
+def test_tuned_sizes_are_kept_by_form_and_surfaces(driver, tmp_path):
+    _run(driver, "tuner", str(tmp_path / "tune.txt"))
