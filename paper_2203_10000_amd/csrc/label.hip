@@ -430,13 +430,16 @@ __global__ __launch_bounds__(512) void k_label_pair(LabelArgs a) {
                         known = patch::ray_winding(leaf, rec, sd, q, i, L, v);
                         if (known && n_cand > 0) {
                             const T d[3] = {(T)px - (T)q[0], (T)py - (T)q[1], (T)pz - (T)q[2]};
-                            T d2 = 0;
+                            // (the longest side: where the squares underflow, within the
+                            // bounds' factor of two)
+                            T d2 = 0, side = 0;
                             for (int c = 0; c < 3; ++c) {
                                 const T r = fmax((T)bhi[c] - (T)q[c], (T)q[c] - (T)blo[c]);
                                 d2 += r * r;
+                                side = fmax(side, r);
                             }
-                            patch::near_crossings<T>(rec, L, n_cand, q, d, sqrt(d2) * (T)1.00001, delta,
-                                                     uncertain);
+                            patch::near_crossings<T>(rec, L, n_cand, q, d, fmax(sqrt(d2) * (T)1.00001, side),
+                                                     delta, uncertain);
                         }
                     }
                 }

@@ -81,6 +81,9 @@ __device__ __forceinline__ Tri load_tri(const TriRec *__restrict__ rec, uint32_t
     return Tri{{a.x, a.y, a.z}, {b.x, b.y, b.z}, {c.x, c.y, c.z}, {a.w, b.w, c.w}};
 }
 
+// Float32 takes no term whose products are smaller.
+constexpr float kLeast = 1e-36f;
+
 struct PointSum {
     double w;          // winding number
     bool on;           // the point lies on a triangle
@@ -172,16 +175,19 @@ __device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, co
         const float nn = fmaf(cx, q.n[0], fmaf(cy, q.n[1], cz * q.n[2]));   // 32 N
         const float mm = ar * br * cr;
         const float dd = fmaf(e12, ar, fmaf(e02, br, fmaf(e01, cr, mm)));
-        const float lim = fmaf(len * (kKnSmall / kNScale), cr, fmaf(kap, mm, fabsf(nn)));
-        if (__builtin_expect(live && dd > lim, 1)) {   // |N / D| < 1/32: the series
+        // (kLeast: products that underflow err by far less than 1e-8 of it; a product
+        // that overflows certifies nothing)
+        const bool finite = fmaxf(fabsf(nn), fabsf(dd)) < __builtin_inff();
+        const float lim = fmaf(len * (kKnSmall / kNScale), cr, fmaf(kap, mm, fabsf(nn) + kLeast));
+        if (__builtin_expect(live && finite && dd > lim, 1)) {   // |N / D| < 1/32: the series
             const float u = nn * __builtin_amdgcn_rcpf(dd);
             const float s2 = u * u;
             accf = fmaf(u, fmaf(fmaf(kA2, s2, kA1), s2, kA0), accf);
         } else if (live) {
             const float n1 = nn * (1.0f / kNScale);
             const float ang = atan2f(n1, dd);
-            const float thr = fmaf(cr, kap * (1.0f / kNScale) * len, kap * mm);
-            const bool ill = !(fmaxf(fabsf(n1), fabsf(dd)) > thr) || fabsf(ang) > branch_cut;   // (NaN is ill)
+            const float thr = fmaf(cr, kap * (1.0f / kNScale) * len, fmaf(kap, mm, kLeast));
+            const bool ill = !finite || !(fmaxf(fabsf(n1), fabsf(dd)) > thr) || fabsf(ang) > branch_cut;
             if (!ill) {
                 accf += ang;
             } else {
@@ -209,21 +215,22 @@ __device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, co
 // products relative to q, with bounds on their rounding (u the unit roundoff, L
 // the largest distance of a vertex from q, D that of a point): edge products
 // err by less than 12 u L^2 D, plane products by less than 10 u |n| (D + L) plus
-// the double rounding of n; twice that is taken.  A lane whose sign is within a
-// bound, and not settled by the others, is uncertain.
+// the double rounding of n; twice that is taken, and a few of the smallest numbers
+// for each product that underflows (`least`).  A lane whose sign is within a bound,
+// and not settled by the others, is uncertain.
 template <typename T>
 struct Bounds;
 template <>
 struct Bounds<float> {
     static constexpr float edge = 24.0f * 5.9604645e-8f, plane = 20.0f * 5.9604645e-8f;
     static constexpr float normal = 1.5e-13f;   // 32 (scaled normals) x 4.7e-15, per L^2
-    static constexpr float huge = 1e37f;
+    static constexpr float huge = 1e37f, least = 1e-44f;
 };
 template <>
 struct Bounds<double> {
     static constexpr double edge = 24.0 * 1.1102230246251565e-16, plane = 20.0 * 1.1102230246251565e-16;
     static constexpr double normal = 5e-15;
-    static constexpr double huge = 1e300;
+    static constexpr double huge = 1e300, least = 0.0;   // (products of float32 numbers)
 };
 
 // What 64 points need of one triangle, relative to q.
@@ -285,10 +292,11 @@ __device__ __forceinline__ Crossing<T> make_crossing(const Tri &t, const float (
     }
     const T len = fabs(n[0]) + fabs(n[1]) + fabs(n[2]), reach = D + sqrt(l2);
     const T s = dot_t(n, v[2]);
-    o.tol_e = B::edge * l2 * D;
-    o.tol_s = reach * (B::plane * len + B::normal * l2);
-    // far out of range: nothing is certain (also catches NaN)
-    if (!(l2 * reach < B::huge) || !(len * reach < B::huge)) o.tol_e = o.tol_s = B::huge;
+    o.tol_e = D * (B::edge * l2 + B::least) + B::least;
+    o.tol_s = reach * (B::plane * len + B::normal * l2 + B::least) + B::least;
+    // far out of range: nothing is certain, neither a product that overflows (also
+    // catches NaN)
+    if (!(l2 * reach < B::huge) || !(len * reach < B::huge)) o.tol_e = o.tol_s = (T)__builtin_inf();
     o.side = s < -o.tol_s ? 1 : (s > o.tol_s ? -1 : 0);
     for (int c = 0; c < 3; ++c) o.n[c] = (T)o.side * n[c];
     o.s = (T)o.side * s;
@@ -321,7 +329,9 @@ __device__ __forceinline__ void box_terms(const float (&lo)[3], const float (&hi
 
 // Whether triangle t may meet the box of centre c and half extents h (scale: |c|
 // + h): its own box does (exact comparisons) and its plane passes within the
-// box's radius, with a margin some thirty times the products' rounding.
+// box's radius, with a margin some thirty times the products' rounding.  A product
+// that overflows excludes nothing; the margin's least terms are for those that
+// underflow (in c and h too).
 __device__ __forceinline__ bool may_meet(const Tri &t, const float (&lo)[3], const float (&hi)[3],
                                          const float (&c)[3], const float (&h)[3], float scale) {
     bool meets = true;
@@ -334,8 +344,10 @@ __device__ __forceinline__ bool may_meet(const Tri &t, const float (&lo)[3], con
     const float s = fmaf(c[0] - t.C[0], t.n[0], fmaf(c[1] - t.C[1], t.n[1], (c[2] - t.C[2]) * t.n[2]));
     const float reach = fmaf(h[0], fabsf(t.n[0]), fmaf(h[1], fabsf(t.n[1]), h[2] * fabsf(t.n[2])));
     const float size = scale + fabsf(t.C[0]) + fabsf(t.C[1]) + fabsf(t.C[2]);
-    const float margin = size * (4e-6f * (fabsf(t.n[0]) + fabsf(t.n[1]) + fabsf(t.n[2])) + 1.5e-12f * ext * ext);
-    return meets && !(fabsf(s) > reach + margin);
+    const float margin =
+        (size + 1e-38f) * (4e-6f * (fabsf(t.n[0]) + fabsf(t.n[1]) + fabsf(t.n[2])) + 1.5e-12f * ext * ext + 1e-44f) +
+        1e-44f;
+    return meets && !(fabsf(s) > reach + margin && fabsf(s) < __builtin_inff());
 }
 
 // The surface's leaves that meet the box, listed as near: groups of 64 leaves by

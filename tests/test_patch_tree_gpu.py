@@ -169,3 +169,39 @@ def test_spans_of_points_against_many_surfaces(ctx, cull):
     assert np.array_equal(lab.cpu().numpy()[idx], want)
     assert np.abs(w.cpu().numpy()[:, idx] - w_ref).max() < TOL["fp32"]
     assert lab[100] == -1 and torch.isnan(w[:, 100]).all()
+
+
+def _grid(surf, n, seed):
+    """Surface and points on multiples of 2^-8 below 2^7: exact in float32 at every
+    scale of 2^-141 to 2^120."""
+    rng = np.random.default_rng(seed)
+    g = lambda a: (np.round(np.asarray(a, np.float64) * 256.0) / 256.0)  # noqa: E731
+    v = g(surf.v)
+    t = surf.f[rng.integers(0, len(surf.f), n // 2)]
+    w = rng.dirichlet((1.0, 1.0, 1.0), n // 2)
+    near = (w[:, :, None] * v[t]).sum(1) + rng.normal(0.0, 0.05, (n // 2, 3))
+    p = np.concatenate([v[:500], near, rng.uniform(-70.0, 70.0, (n - n // 2 - min(500, len(v)), 3))])
+    return v, g(p)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [POINT_FORM_MAX, 40000])
+@pytest.mark.parametrize("shape", ["torus", "box"])
+def test_scales_at_which_products_leave_the_range_of_float32(ctx, shape, n, precision):
+    """The same surface and points at powers of two from the smallest numbers to the
+    largest: same labels, same winding numbers off the surface."""
+    surf = _Surf(*SHAPES[shape](), label=5)
+    v, p = _grid(surf, n, 31)
+    want = w1 = None
+    for k in (0, -141, -130, -118, -100, -75, -62, -50, -49, -48, -47, -46, -45, -44, -40, 34, 35, 36, 37, 40, 55, 62, 63, 75, 100,
+              120):
+        s = _Surf(v * 2.0 ** k, surf.f, 5)
+        x = np.ascontiguousarray((p.T * 2.0 ** k).astype(np.float32))
+        assert np.array_equal(x.astype(np.float64), p.T * 2.0 ** k)
+        ss = sal.SurfaceSet(ctx, [s])
+        lab, w, _ = sal.label_points(ctx, ss, torch.from_numpy(x).cuda(), precision=precision, winding="f64")
+        lab, w = lab.cpu().numpy(), w.cpu().numpy()
+        if k == 0:
+            want, w1 = oracle.label(x, [s], want_w=True)
+        assert np.array_equal(lab, want), (k, int((lab != want).sum()))
+        assert np.abs(w - w1).max() < TOL[precision], k
