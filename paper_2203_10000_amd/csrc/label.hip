@@ -97,11 +97,17 @@ __device__ __forceinline__ PointSum point_surface(const LabelInst &in, const Sur
         if (patch::ray_winding(leaf, rec, sd, p, i, L, v)) return PointSum{(double)v, false, 0u, 0u};
     int n_near, n_far;
     if (!patch::sort_patches(in.ent + 4 * sd.node_begin, p, p, L, n_near, n_far)) {
-        // (a list is full only where hundreds of patches share the point)
-        n_near = 1;
+        // A list is full where hundreds of patches share the point: all triangles
+        // then, in as many ranges as the list holds, so that every group of lanes has
+        // some and a float32 sum stays short (64 points at a vertex of 65,536 triangles,
+        // as one range 52 ms, now 8.1).
+        const uint32_t all = (uint32_t)(sd.rec_end - sd.rec_begin);
+        const uint32_t per = ((all + patch::kNearCap - 1) / patch::kNearCap + 7u) & ~7u;
+        n_near = (int)((all + per - 1) / per);
         n_far = 0;
         wave_sync();
-        if (lane_id() == 0) L.near[0] = make_uint2(0u, (uint32_t)(sd.rec_end - sd.rec_begin));
+        for (uint32_t i = (uint32_t)lane_id(); i < (uint32_t)n_near; i += 64)
+            L.near[i] = make_uint2(i * per, all - i * per < per ? all - i * per : per);
         wave_sync();
     }
     const PointSum s = patch::point_sum<MODE>(rec, L, n_near, n_far, x, y, z, kap);
@@ -188,12 +194,14 @@ __device__ __forceinline__ bool point_final(const LabelInst &in, const LabelArgs
 }
 
 // ------------------------------------------------------------- single points
-// What bounds it: latency.  A point costs two dependent loads per tree level and
-// some ten leaves that its ray passes; with one wavefront per point (SPREAD: per
-// point and fourth of its surfaces) there is no other serial chain.  10,007 points
-// x 4 surfaces of 20,480 triangles: 58 us (as sums over the caps: 138).
+// What bounds it: latency.  A point costs two dependent loads, of the leaves'
+// groups and leaves, and some ten leaves that its ray passes; with one wavefront per
+// point (SPREAD: the surfaces dealt to the workgroup's) there is no other serial
+// chain.  10,007 points x 4 surfaces of 5,120 triangles: 44 us (as sums over the
+// caps 138, a tree level at a time 64).
+// Four wavefronts a SIMD (128 VGPRs): with three (133) they take 53 us.
 template <bool F64, bool SPREAD>
-__global__ __launch_bounds__(512) void k_label_point(LabelArgs a) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_label_point(LabelArgs a) {
     extern __shared__ __align__(16) unsigned char shared[];
     __shared__ unsigned long long s_enc;
     __shared__ unsigned s_flag;

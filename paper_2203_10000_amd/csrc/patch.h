@@ -132,6 +132,8 @@ __device__ __forceinline__ PointSum point_sum(const TriRec *__restrict__ rec, co
         if (m != 0) {
             const int it = next + __popcll(m & leaders & ((1ull << (lane & ~7)) - 1ull));
             if (need) {
+                acc += (double)accf;   // (float32 sums end with their range)
+                accf = 0.0f;
                 more = it < items;
                 cap = it >= n_near;
                 if (more) {

@@ -205,3 +205,22 @@ def test_scales_at_which_products_leave_the_range_of_float32(ctx, shape, n, prec
             want, w1 = oracle.label(x, [s], want_w=True)
         assert np.array_equal(lab, want), (k, int((lab != want).sum()))
         assert np.abs(w - w1).max() < TOL[precision], k
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_a_vertex_that_every_patch_shares(ctx, precision):
+    """Two cones of 2^20 triangles over one rim, seen from one's apex: all patches of
+    a cone meet there.  The apex sees the other cone under the angle of the rim."""
+    m = 1 << 20
+    a = 2 * np.pi * np.arange(m) / m
+    v = np.concatenate([[[0, 0, 50.0], [0, 0, -50.0]], np.stack([50 * np.cos(a), 50 * np.sin(a), 0 * a], 1)])
+    k = np.arange(m)
+    k1 = (k + 1) % m
+    f = np.concatenate([np.stack([0 * k, 2 + k, 2 + k1], 1), np.stack([0 * k + 1, 2 + k1, 2 + k], 1)])
+    ss = sal.SurfaceSet(ctx, [_Surf(v, f, 6)])
+    pts = np.array([[0, 0, 50.0], [0, 0, 49.99], [0, 0, 50.01]], np.float32).T.copy()
+    lab, w, _ = sal.label_points(ctx, ss, torch.from_numpy(pts).cuda(), precision=precision, winding="f64")
+    assert lab.tolist() == [6, 6, 0]
+    want = [0.5 * (1.0 - 0.5 ** 0.5), 1.0, 0.0]
+    # the rim's vertices are rounded to 2^-19 of 50: no more than 1e-9 of the angle
+    assert np.abs(w.cpu().numpy()[0] - want).max() < {"fp32": 1e-5, "fp64": 1e-9}[precision]
