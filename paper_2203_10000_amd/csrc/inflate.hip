@@ -46,8 +46,13 @@ __global__ void k_sorted_triangles(const TriRec *__restrict__ rec, int64_t first
         for (int c = 0; c < 3; ++c) o[3 * v + c] = (float)p[v][c];
 }
 
-__device__ __forceinline__ int bin_of(double x, double o, double inv_h, int n) {
-    const double f = floor((x - o) * inv_h);   // (the same for triangles and edges, and monotone)
+// floor((x - o) / h): a product with 1 / h errs by less than 1e-15 of itself, so the
+// division is made only where that may reach a whole number (a lattice of h = 49:
+// 49 / 49, but 49 * (1 / 49) < 1).
+__device__ __forceinline__ int bin_of(double x, double o, double h, double inv_h, int n) {
+    const double q = (x - o) * inv_h;
+    double f = floor(q);
+    if (!(fabs(q - rint(q)) > 1e-15 * fabs(q))) f = floor((x - o) / h);
     return f < 0.0 ? 0 : (f >= (double)n ? n - 1 : (int)f);
 }
 
@@ -59,8 +64,8 @@ __device__ __forceinline__ BinBox box_bins(const double lo[3], const double hi[3
     BinBox b;
     const double inv_h = 1.0 / g.h;
     for (int a = 0; a < 3; ++a) {
-        b.lo[a] = bin_of(lo[a], g.origin[a], inv_h, g.cells[a]);
-        b.hi[a] = bin_of(hi[a], g.origin[a], inv_h, g.cells[a]);
+        b.lo[a] = bin_of(lo[a], g.origin[a], g.h, inv_h, g.cells[a]);
+        b.hi[a] = bin_of(hi[a], g.origin[a], g.h, inv_h, g.cells[a]);
     }
     return b;
 }

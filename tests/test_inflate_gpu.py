@@ -160,3 +160,40 @@ def test_inflation_on_a_lattice_with_uneven_axes(ctx):
     got = out["xyz"].cpu().numpy()
     bad = np.nonzero(np.any(got != want.astype(np.float32), axis=1))[0]
     assert len(bad) == 0, (len(bad), bad[:5])
+
+
+def test_bins_of_triangles_on_lattice_planes(ctx):
+    """A box with its vertices on planes 1 to 5 of a lattice of 49 mm cells (the
+    multiples of 49 but the fifth, times the rounded 1/49, fall below whole): each triangle lies in the bins of floor((x - o) / h)
+    from its lowest to its highest corner."""
+    h, cells, o = 49.0, (7, 8, 9), np.array([-49.0, -49.0, -49.0])
+    ids, v, f = {}, [], []
+
+    def vid(p):
+        if p not in ids:
+            ids[p] = len(v)
+            v.append([h * c for c in p])
+        return ids[p]
+
+    for ax in range(3):
+        for side in (0, 4):
+            for i in range(4):
+                for j in range(4):
+                    q = []
+                    for a, b in ((i, j), (i + 1, j), (i + 1, j + 1), (i, j + 1)):
+                        p = [0, 0, 0]
+                        p[ax], p[(ax + 1) % 3], p[(ax + 2) % 3] = side, a, b
+                        q.append(vid(tuple(p)))
+                    t = [(q[0], q[1], q[2]), (q[0], q[2], q[3])]
+                    f += t if side else [(a, c, b) for a, b, c in t]
+    v, f = np.array(v, np.float32), np.array(f, np.int32)
+    ss = sal.SurfaceSet(ctx, [(v, f, 1)])
+    mesh = sal.TetMesh(ctx, tuple(o), h, cells)
+    mesh.refine_relabel(ss, 1)
+    mesh.conform()
+    info = mesh.inflate(ss, 0.05)
+    c = v.astype(np.float64)[f]
+    top = np.array(cells) - 1
+    lo = np.clip(np.floor((c.min(1) - o) / h), 0, top)
+    hi = np.clip(np.floor((c.max(1) - o) / h), 0, top)
+    assert info["n_bin_items"] == int(np.prod(hi - lo + 1, axis=1).sum())
