@@ -47,6 +47,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
         if (opt.winding_type != SAL_WINDING_NONE)
             return set_error(SAL_ERR_INVALID_ARG, "the batched form has no winding output");
         int64_t total = 0;
+        std::vector<int64_t> sizes;
         for (int i = 0; i < n_inst; ++i) {
             const sal_instance &in = inst[i];
             if (!in.surfaces) return set_error(SAL_ERR_INVALID_ARG, "instance without surfaces");
@@ -56,6 +57,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
             if (in.n_points > 0 && (!in.x || !in.y || !in.z || !in.labels))
                 return set_error(SAL_ERR_INVALID_ARG, "NULL point or label buffer");
             total += in.n_points;
+            sizes.push_back(in.n_points);
         }
         if (stats) std::memset(stats, 0, sizeof(sal_label_stats) * (size_t)n_inst);
         if (total == 0) return SAL_OK;
@@ -73,10 +75,11 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
         ScratchSize need;
         int64_t wave_groups = 0, point_groups = 0;
         size_t n_wave = 0;
+        const int64_t point_max = batch_point_max(sizes);
         for (const bool small : {false, true}) {
             for (int i = 0; i < n_inst; ++i) {
                 const sal_instance &in = inst[i];
-                if ((in.n_points <= kBatchPointMax) != small) continue;
+                if ((in.n_points <= point_max) != small) continue;
                 for (int64_t at = 0; at < in.n_points; at += kChunkPoints) {
                     const int64_t m = std::min(in.n_points - at, kChunkPoints);
                     LabelInst q = make_inst(in.surfaces, m, in.x + at, in.y + at, in.z + at, in.labels + at,
@@ -216,7 +219,7 @@ extern "C" sal_status sal_label_batch(sal_context *ctx, const sal_instance *inst
                 stats[i].n_recheck_f64_terms = (int64_t)ci[kCntRecheckF64];
                 stats[i].ms_total = ms;   // the whole batch (one launch sequence)
                 stats[i].ms_pairloop = ms;
-                stats[i].points_per_lane = 1;   // one point per lane, 4 wavefronts per workgroup
+                stats[i].points_per_lane = 1;
                 stats[i].block_waves = kBlockWaves;
             }
         }

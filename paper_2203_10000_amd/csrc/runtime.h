@@ -81,8 +81,22 @@ constexpr int64_t kChunkPoints = (int64_t)1 << 27;
 // two surfaces of 81,000 triangles, 75 / 276, 141 / 286, 249 / 296.
 constexpr int64_t kPointFormMax = 32768;
 
-// The same for an instance of a batch, whose other instances fill the chip.
-constexpr int64_t kBatchPointMax = 8192;
+// The same for an instance of a batch, whose other instances fill the chip.  Where
+// those between kBatchCrowdMin and this are many, their points together are past the
+// point form's range and the sort of each pays; below kBatchCrowdMin the sort's 2048
+// bins an instance cost more (us, point form / 64-point form; one surface of 320
+// triangles, four of 5,120): 8 instances of 8,000 points 116 / 108, 231 / 194; 32 of
+// 4,000 257 / 214, 474 / 402; 256 of 8,000 3356 / 1384, 6332 / 3013; but 8 of 4,000
+// 78 / 104, 135 / 171; 128 of 1,000 511 / 531, 728 / 1272.
+constexpr int64_t kBatchPointMax = 8192, kBatchCrowdMin = 2048, kBatchCrowd = 65536;
+
+// Instances of up to so many points take the point form; sizes: of all instances.
+inline int64_t batch_point_max(const std::vector<int64_t> &sizes) {
+    int64_t crowd = 0;
+    for (const int64_t n : sizes)
+        if (n > kBatchCrowdMin && n <= kBatchPointMax) crowd += n;
+    return crowd >= kBatchCrowd ? kBatchCrowdMin : kBatchPointMax;
+}
 
 // Tile size and count of the spatial order for n points: up to kSmallOrder small
 // tiles, so that there is a workgroup for each CU (us, tiles of 2048 / 1024: 196,608

@@ -167,6 +167,18 @@ int scratch() {
     return 0;
 }
 
+// Many instances of a batch between the bounds leave the point form together.
+int batch() {
+    using sal::batch_point_max;
+    CHECK(batch_point_max({}) == sal::kBatchPointMax);
+    CHECK(batch_point_max({8192, 8192, 400000}) == sal::kBatchPointMax);
+    CHECK(batch_point_max(std::vector<int64_t>(256, 8000)) == sal::kBatchCrowdMin);
+    CHECK(batch_point_max(std::vector<int64_t>(4096, 2048)) == sal::kBatchPointMax);
+    CHECK(batch_point_max(std::vector<int64_t>(8, 8192)) == sal::kBatchCrowdMin);
+    CHECK(batch_point_max({8192, 8192, 8192, 8192, 8192, 8192, 8192, 8191}) == sal::kBatchPointMax);
+    return 0;
+}
+
 // The tuner tells apart what runs other kernels or another number of surfaces, and
 // takes no entry of a file from before it did.
 int tuner(const char *file) {
@@ -200,6 +212,7 @@ int main(int argc, char **argv) {
     if (argc == 3 && !std::strcmp(argv[1], "tuner")) return tuner(argv[2]);
     if (argc != 2) return 2;
     if (!std::strcmp(argv[1], "scratch")) return scratch();
+    if (!std::strcmp(argv[1], "batch")) return batch();
     if (!std::strcmp(argv[1], "reserve")) return reserve();
     if (!std::strcmp(argv[1], "streams")) return streams();
     if (!std::strcmp(argv[1], "threads")) return threads();

@@ -224,3 +224,23 @@ def test_a_vertex_that_every_patch_shares(ctx, precision):
     want = [0.5 * (1.0 - 0.5 ** 0.5), 1.0, 0.0]
     # the rim's vertices are rounded to 2^-19 of 50: no more than 1e-9 of the angle
     assert np.abs(w.cpu().numpy()[0] - want).max() < {"fp32": 1e-5, "fp64": 1e-9}[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("last", [8191, 8192])
+def test_many_small_instances_change_form_together(ctx, last, graph, precision):
+    """Instances on both sides of 2,048 points whose larger ones have 65,535 or 65,536
+    points together: one by one, then as groups of 64."""
+    surfs = [_Surf(*SHAPES[s](), label=k + 1) for k, s in enumerate(("box", "torus"))]
+    sets = [sal.SurfaceSet(ctx, surfs[:k]) for k in (1, 2)]
+    inst = []
+    for k, n in enumerate((8192, 1, 8192, 2048, 2049, 8192, 8192, 63, 6143, 8192, 8192, 64, last)):
+        pts = torch.from_numpy(_points(surfs[k % 2], n + 4, 50 + k)[:, :n].copy()).cuda()
+        inst.append((sets[k % 2], pts, torch.full((n,), -7, dtype=torch.int32, device="cuda")))
+    for _ in range(2):
+        sal.label_batch(ctx, inst, precision=precision, use_graph=graph)
+        for ss, pts, lab in inst:
+            one, _, _ = sal.label_points(ctx, ss, pts, precision=precision)
+            assert torch.equal(lab, one)
+            lab.fill_(-7)

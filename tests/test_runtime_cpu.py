@@ -1,6 +1,6 @@
 """Host parts of libsal's runtime (scratch sizes, the kept device blocks on a
-stand-in for the card, the tuner's keys), built with g++ under AddressSanitizer and
-UndefinedBehaviorSanitizer.  CPU only."""
+stand-in for the card, the tuner's keys, the forms of a batch), built with g++
+under AddressSanitizer and UndefinedBehaviorSanitizer.  CPU only."""
 import os
 import shutil
 import subprocess
@@ -47,3 +47,7 @@ def test_kept_blocks_do_not_make_streams_or_threads_wait(driver, check):
 
 def test_tuned_sizes_are_kept_by_form_and_surfaces(driver, tmp_path):
     _run(driver, "tuner", str(tmp_path / "tune.txt"))
+
+
+def test_forms_of_a_batchs_instances(driver):
+    _run(driver, "batch")
