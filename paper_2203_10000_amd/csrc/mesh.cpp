@@ -529,7 +529,7 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
             m->round_graph = nullptr;
         }
         m->round_key = 0;
-        SAL_HIP(hipStreamSynchronize(s));
+        // (the capture has a stream of its own and waits for nothing enqueued on s)
         hipGraph_t g = nullptr;
         SAL_HIP(hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
         sal_status cst = enqueue_round(ctx, m, set, opt, kid_cap, ctx->capture_stream);
@@ -553,8 +553,7 @@ sal_status graph_rounds(sal_context *ctx, sal_tet_mesh *m, const sal_surface_set
     }
     h.kid_cap = kid_cap;
     h.n_leaves = m->n_leaves;
-    SAL_HIP(hipStreamSynchronize(s));
-    SAL_HIP(hipMemcpy(m->rs, &h, sizeof h, hipMemcpyHostToDevice));
+    SAL_HIP(launch_round_state(m->rs, h, s));
     SAL_HIP(hipEventRecord(m->ev[11], s));
     for (int r = 0; r < rounds; ++r) {
         SAL_HIP(hipGraphLaunch(m->round_graph, s));

@@ -609,6 +609,13 @@ __global__ void k_child_masks(LevelPtrs L, LatticeGeom g, int l, const int32_t *
 // the same launch sequence serves every round; fixed grids stride over them.
 constexpr int kDevGrid = 1024;
 
+// The state before the first round, as an argument: in the stream's order and with
+// nothing of the host's to outlive the call (a copy from the host had to wait for the
+// stream: two waits, some 50 us of 750 for a small head).
+__global__ void k_round_state(RoundState *rs, RoundState first) {
+    if (threadIdx.x == 0) *rs = first;
+}
+
 // One thread: sizes of this round's splits (levels deepest first, as the
 // host-driven round orders them), capacity checks, new level sizes.
 __global__ void k_plan(RoundState *rs, const int64_t *__restrict__ totals) {
@@ -845,6 +852,11 @@ hipError_t launch_compact_levels(const LevelPtrs &L, int top, const int64_t *siz
     k_count_levels<<<(unsigned)nb, kScanThreads, 0, s>>>(c, block_scratch);
     k_scan_levels<<<1, 1024, 0, s>>>(c, block_scratch, nb, totals, extra, host_words);
     k_scatter_levels<<<(unsigned)nb, kScanThreads, 0, s>>>(c, block_scratch, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_round_state(RoundState *rs, const RoundState &first, hipStream_t s) {
+    k_round_state<<<1, 64, 0, s>>>(rs, first);
     return hipGetLastError();
 }
 

@@ -115,6 +115,7 @@ hipError_t launch_export(const LevelPtrs &L, const LatticeGeom &g, int l, const 
                          float *cx, float *cy, float *cz, hipStream_t s);
 // Device-sized forms for the captured refine round (sizes read from
 // RoundState / compaction totals; fixed grids stride over them).
+hipError_t launch_round_state(RoundState *rs, const RoundState &first, hipStream_t s);
 hipError_t launch_plan(RoundState *rs, const int64_t *totals, hipStream_t s);
 hipError_t launch_split_dev(const LevelPtrs &L, const LatticeGeom &g, const ChildTables &T, const int32_t *list,
                             const int64_t *totals, const RoundState *rs, float *cx, float *cy, float *cz,
