@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 FLOPS_PER_PAIR = 75          # algorithmic FP32 flops of one VOS evaluation (FMA = 2)
 FP32_PEAK_TFLOPS = 157.3     # MI355X published FP32 vector peak
 FP64_PEAK_TFLOPS = 78.6      # MI355X published FP64 vector peak
-COUNTERS_FILE = os.path.join(ROOT, "profiles", "pairloop_f32_c2_hbm_counters.json")
+COUNTERS_FILE = os.path.join(ROOT, "profiles", "label_c2_hbm_counters.json")
 
 
 def parse():
@@ -108,8 +108,9 @@ def source_digest():
 
 
 def hbm_traffic(pairloop_launch_pairs):
-    """HBM bytes per launch from the committed rocprofv3 counter summary, if
-    it was taken on the current kernel source; else None."""
+    """HBM bytes of one labeling call of the default workload, from the committed
+    rocprofv3 counter summary, if it was taken on the current kernel source; else
+    None."""
     try:
         c = json.load(open(COUNTERS_FILE))
     except (OSError, ValueError):
@@ -443,10 +444,12 @@ def _c3_fp64_round0(ctx, ss, cfg, lat, rule):
 def label_rate(pairs, ms, kernel, fp64=False, traffic=None):
     """Device time of the labeling kernels over `pairs` = points x triangles.
     The pairs are answered, not evaluated one by one (a point's winding number
-    comes from the crossings of one segment), so the rate has no place under the
-    ALU peak: the fraction of it that the kernels issue is in the counter
-    summary."""
-    return {"bound": "alu", "kernel": kernel, "kernel_ms": round(ms, 3), "pairs": pairs,
+    comes from the crossings of one segment), so the rate is one of answers and has
+    no place under the ALU peak; ms_per_step is the measurement of the code.  What
+    bounds the kernels is the latency of their loads: the vector pipes issue a third
+    to six tenths of the time (the counter summary), and `traffic` over kernel_ms is
+    a quarter of the HBM peak."""
+    return {"bound": "latency", "kernel": kernel, "kernel_ms": round(ms, 3), "pairs": pairs,
             "pairs_counted": "points x triangles", "g_pairs_per_s": round(pairs / max(ms, 1e-9) / 1e6, 1),
             "peak": FP64_PEAK_TFLOPS if fp64 else FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
             "achieved": None, "frac": None, "traffic": traffic}

@@ -36,7 +36,7 @@ using patch::PointSum;
 
 // A run of lanes is halved while its box meets too many triangles for the lists,
 // down to kSplitMin lanes; below it a ray per point (k_recheck) is cheaper.
-// 60,001 points within 1 mm of two surfaces of 81,000 triangles, two shells of
+// 60,001 points within 1 mm of two surfaces of 162,000 triangles, two shells of
 // points of 2,048: 4 lanes 340 and 447 us, 16 lanes 295 and 128, 32 lanes 454 and
 // 137.
 constexpr int kSplitMin = 16;
@@ -340,9 +340,10 @@ __global__ __launch_bounds__(64 * kSpanWaves) void k_label_span(LabelArgs a, int
 }
 
 // ------------------------------------------------------------- open pairs
-// What bounds it: load latency in the tree, and the crossings, some 60
-// instructions for each triangle that meets the box.  One wavefront per pair: with
-// a group's surfaces one after the other the launch ended in a long tail.  The
+// What bounds it: the latency of the leaf boxes' and triangles' loads, the crossings,
+// some 60 instructions for each triangle that meets the box, and at the launch's end
+// the longest wavefronts, whose boxes overflow the lists and are halved.  One
+// wavefront per pair: with a group's surfaces one after the other the tail was longer.  The
 // point of known winding takes a ray; as a sum over the patches' caps it took 100
 // and more rounds of 130 instructions instead of some 10 of 40 (us, sum / ray: 6M
 // lattice points x 81,920 triangles 1190 / 820; 60,001 points near two surfaces

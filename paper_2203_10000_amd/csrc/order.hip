@@ -13,8 +13,9 @@
 // Per pass: a histogram per tile, a scan over the tiles of each bin, and a
 // scatter that ranks the keys of a tile in input order (wave by wave, 64 at a
 // time, equal digits found by one ballot per bit).  Up to some 200,000 points it is
-// bound by its six launches and the chains in them (61 us), at 6M by the ranking's
-// instructions (0.18 ms for 24 bytes a point read and 10 written).  One pass over
+// bound by its six launches and the chains in them (51 us), at 6M by the ranking's
+// instructions and the places on the curve, which three of the launches compute (276
+// us for 46 bytes a point read and 10 written).  One pass over
 // 2048 cells takes 20 us off below 2^18 points, but points along a surface fill few
 // cells: 60,001 of them near two surfaces 280 -> 490 us.  All instances of a batch are sorted by the same three
 // launches (their tiles are separate).  No memsets, no allocations: the

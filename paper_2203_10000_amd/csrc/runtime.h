@@ -78,7 +78,7 @@ constexpr int64_t kChunkPoints = (int64_t)1 << 27;
 // chip the chain of one is the time.  Measured (us, point form / 64-point form;
 // 16,384, 32,768 and 60,000 points): lattice points, one surface, 30 / 75, 50 / 77,
 // 85 / 80; box points, four surfaces, 86 / 94, 155 / 108, 267 / 109; points near
-// two surfaces of 81,000 triangles, 75 / 276, 141 / 286, 249 / 296.
+// two surfaces of 162,000 triangles, 75 / 276, 141 / 286, 249 / 296.
 constexpr int64_t kPointFormMax = 32768;
 
 // The same for an instance of a batch, whose other instances fill the chip.  Where

@@ -59,7 +59,6 @@ struct alignas(16) PatchEntry {
 constexpr int kLeafTri = 64;
 constexpr double kCapMargin = 0.02;
 
-// Per-surface table in device memory.
 // A leaf patch: its triangles' box and records [begin, begin + count); or a group of
 // kLeafGroup leaves that follow each other: their box (begin, count: the leaves).
 struct alignas(16) LeafBox {
@@ -70,6 +69,7 @@ struct alignas(16) LeafBox {
 };
 constexpr int kLeafGroup = 64;
 
+// Per-surface table in device memory.
 struct SurfaceDev {
     int64_t rec_begin, rec_end;      // the surface's triangles: records [begin, end)
                                      // (its caps follow)

@@ -1,5 +1,5 @@
-// Surface-set construction: validation of closed oriented manifolds, greedy
-// patch trees and triangle records on the device.
+// Surface-set construction: the records, patch trees and leaf boxes that
+// surface_host.cpp builds, on the device; the balls of cull_bounds.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
