@@ -75,10 +75,14 @@ bool drop_idle(Pool &p) {
 
 // hipMalloc with the idle blocks as a reserve.
 hipError_t card_malloc(Pool *p, void **ptr, size_t bytes) {
-    const hipError_t e = hipMalloc(ptr, bytes);
-    if (e != hipErrorOutOfMemory || !p || !drop_idle(*p)) return e;
-    (void)hipGetLastError();
-    return hipMalloc(ptr, bytes);
+    hipError_t e = hipMalloc(ptr, bytes);
+    if (e == hipErrorOutOfMemory && p && drop_idle(*p)) {
+        (void)hipGetLastError();
+        e = hipMalloc(ptr, bytes);
+    }
+    // (the caller reports it; the next launch is checked by the last error)
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
 }
 
 }  // namespace
@@ -105,7 +109,7 @@ void pool_add_context() {
     ++p->contexts;
 }
 
-// token: of the context that goes, whose stream is idle.
+// token: of the context that goes, whose stream is idle (0: that is not known).
 void pool_remove_context(uint64_t token) {
     Pool *p = current_pool();
     if (!p) return;

@@ -25,6 +25,7 @@ constexpr size_t kSlow = 12288;          // an allocation of this size waits for
 std::promise<void> slow_started, go;
 std::function<void()> during_sync;
 int syncs = 0;
+hipError_t last_error = hipSuccess;
 }  // namespace
 
 extern "C" {
@@ -35,7 +36,7 @@ hipError_t hipMalloc(void **ptr, size_t bytes) {
     }
     std::lock_guard<std::mutex> lk(card_mu);
     *ptr = nullptr;
-    if (card_used + bytes > kCard) return hipErrorOutOfMemory;
+    if (card_used + bytes > kCard) return last_error = hipErrorOutOfMemory;
     *ptr = std::malloc(1);
     card[*ptr] = bytes;
     card_used += bytes;
@@ -54,7 +55,11 @@ hipError_t hipDeviceSynchronize() {
     if (during_sync) during_sync();
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
 }
 
 namespace {
@@ -67,7 +72,8 @@ namespace {
         }                                                        \
     } while (0)
 
-// Idle blocks are given back when an allocation of either kind needs the memory.
+// Idle blocks are given back when an allocation of either kind needs the memory; one
+// that fails all the same leaves no error behind.
 int reserve() {
     sal::pool_add_context();
     const uint64_t t = sal::new_stream_token();
@@ -77,6 +83,8 @@ int reserve() {
     CHECK(card_used >= kCard * 3 / 8);   // kept
     CHECK(sal::dev_malloc(&b, kCard * 3 / 4) == hipSuccess);
     CHECK(sal::dev_malloc(&a, kCard / 2) == hipErrorOutOfMemory);   // nothing left to give
+    CHECK(sal::pool_malloc(&a, kCard / 2, t) == hipErrorOutOfMemory);
+    CHECK(last_error == hipSuccess);
     CHECK(hipFree(b) == hipSuccess);
     CHECK(sal::pool_malloc(&a, kCard * 3 / 8, t) == hipSuccess);
     sal::pool_free(a, t);
