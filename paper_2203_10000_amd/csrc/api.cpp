@@ -307,7 +307,7 @@ sal_status sal_context_set_stream(sal_context *ctx, void *stream) {
 void sal_context_destroy(sal_context *ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
-    (void)hipStreamSynchronize(ctx->stream);
+    const bool idle = hipStreamSynchronize(ctx->stream) == hipSuccess;
     for (auto &ev : ctx->ev)
         if (ev) (void)hipEventDestroy(ev);
     if (ctx->batch_graph) (void)hipGraphExecDestroy(ctx->batch_graph);
@@ -319,7 +319,7 @@ void sal_context_destroy(sal_context *ctx) {
         if (p) (void)hipFree(p);
     if (ctx->host_words) (void)hipHostFree(ctx->host_words);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
-    pool_remove_context(ctx->stream_token);
+    pool_remove_context(idle ? ctx->stream_token : 0);
     delete ctx;
 }
 

@@ -98,13 +98,13 @@ int reserve() {
 // A block with work pending in one stream is not waited for by another, and is that
 // stream's or anyone's again once the device or its own stream is idle.
 int streams() {
-    sal::pool_add_context();
-    sal::pool_add_context();
+    for (int k = 0; k < 3; ++k) sal::pool_add_context();
     const uint64_t t = sal::new_stream_token(), u = sal::new_stream_token();
     void *a = nullptr, *b = nullptr, *c = nullptr;
     CHECK(sal::pool_malloc(&a, 4096, t) == hipSuccess && sal::pool_malloc(&c, 4096, t) == hipSuccess);
     void *const a0 = a, *const c0 = c;
     sal::pool_free(a, t);
+    sal::pool_remove_context(0);   // a context goes whose stream may be at work
     CHECK(sal::pool_malloc(&b, 4096, u) == hipSuccess && b != a0 && syncs == 0);
     CHECK(sal::pool_malloc(&a, 4096, t) == hipSuccess && a == a0);
     sal::pool_free(a, t);
