@@ -244,3 +244,20 @@ def test_many_small_instances_change_form_together(ctx, last, graph, precision):
             one, _, _ = sal.label_points(ctx, ss, pts, precision=precision)
             assert torch.equal(lab, one)
             lab.fill_(-7)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [POINT_FORM_MAX, 40000])
+def test_far_from_the_origin(ctx, n, precision):
+    """Surface and points moved by some 3e4, still exact in float32: 24 bits, of which
+    the surface has 15.  Same labels and winding numbers."""
+    surf = _Surf(*SHAPES["torus"](), label=5)
+    v, p = _grid(surf, n, 37)
+    far = np.array([32000.0, -31000.0, 30000.0])
+    s, x = _Surf(v + far, surf.f, 5), np.ascontiguousarray((p + far).T.astype(np.float32))
+    assert np.array_equal(x.astype(np.float64), (p + far).T) and np.array_equal(s.v.astype(np.float64), v + far)
+    want, w_ref = oracle.label(np.ascontiguousarray(p.T.astype(np.float32)), [_Surf(v, surf.f, 5)], want_w=True)
+    lab, w, _ = sal.label_points(ctx, sal.SurfaceSet(ctx, [s]), torch.from_numpy(x).cuda(), precision=precision,
+                                 winding="f64")
+    assert np.array_equal(lab.cpu().numpy(), want)
+    assert np.abs(w.cpu().numpy() - w_ref).max() < TOL[precision]
